@@ -1,0 +1,58 @@
+"""Kernels at the sizes where their loops and splits change: edges of tiles, remainders, the smallest and the
+largest of a range.  Needs an MI355X (-m gpu)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import workload as W
+from oracle import cachecraft_oracle as O
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("hkv", [1, 3, 8])
+def test_scatter_runs_of_every_length_at_every_place(dtype, d, hkv):
+    # runs of 1..16 rows that start at every offset of a workgroup's four candidate rows, slots in any order
+    # inside a block, rows with a slot outside the pool between them
+    import paper_2502_15734_amd as P
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(hkv)
+    lengths = [1, 16, 2, 1, 15, 3, 5, 16, 7, 1, 1, 4, 16, 9, 2, 16, 16, 1]
+    blocks = rng.permutation(len(lengths) + 3)[: len(lengths)]
+    slots, n_blocks = [], len(lengths) + 3
+    for i, (b, m) in enumerate(zip(blocks, lengths)):
+        slots += [int(b) * 16 + int(s) for s in rng.permutation(16)[:m]]
+        if i % 5 == 3:
+            slots.append(-1 if i % 2 else n_blocks * 16)
+    n = len(slots)
+    pos = rng.integers(0, 30000, size=n).astype(np.int32)
+    ctx = P.Context(hkv, hkv, d, 5.0e5, P.CC_BF16 if dtype == "bf16" else P.CC_F32)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    k_new, v_new = (torch.randn(n, hkv, d, device="cuda", generator=g).to(dt) for _ in range(2))
+    k_pool = torch.randn(n_blocks, hkv, 16, d, device="cuda", generator=g).to(dt)
+    v_pool = torch.randn(n_blocks, hkv, d, 16, device="cuda", generator=g).to(dt)
+    want_k, want_v = k_pool.cpu().double().numpy(), v_pool.cpu().double().numpy()
+    ang = pos[:, None].astype(np.float64) * 5.0e5 ** (-2.0 * np.arange(d // 2) / d)
+    cs, sn = np.cos(ang)[:, None], np.sin(ang)[:, None]
+    kn = k_new.cpu().double().numpy()
+    x, y = kn[..., : d // 2], kn[..., d // 2:]
+    turned = np.concatenate([x * cs - y * sn, y * cs + x * sn], axis=-1)
+    for j, s in enumerate(slots):
+        if 0 <= s < n_blocks * 16:
+            want_k[s // 16, :, s % 16] = turned[j]
+            want_v[s // 16, :, :, s % 16] = v_new[j].cpu().double().numpy()
+    dev = lambda a: torch.from_numpy(np.asarray(a, dtype=np.int32)).cuda()
+    ctx.scatter_kv(k_new, v_new, dev(pos), dev(slots), k_pool, v_pool); torch.cuda.synchronize()
+    assert np.array_equal(v_pool.cpu().double().numpy(), want_v)
+    got_k = k_pool.cpu().double().numpy()
+    # half a unit in the last place of the stored value (bf16: 8 significant bits, so 2^-8 of it; fp32: 2^-24) and
+    # the fp32 rotation: a few 2^-24 of |x| + |y|, which stay below 8 here; the hardware sine / cosine of the
+    # bf16 form: 1e-6 of them
+    tol = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -24
+    slack = 8 * (1e-6 if dtype == "bf16" else 4 * 2.0 ** -24)
+    worst = float(np.max(np.abs(got_k - want_k) - tol * np.abs(want_k)))
+    assert worst <= slack
