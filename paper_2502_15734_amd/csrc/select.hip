@@ -87,54 +87,54 @@ void launch_score_scalar(const cc_ctx* ctx, const void* q, const void* k_pool, i
 
 // ---------------------------------------------------------------------------------------------
 // Top-N per chunk.  One workgroup per segment.  score = mean over heads of the mass; the N-th
-// largest score is found by building its bit pattern from the top bit down (32 counting rounds
-// with wavefront ballots), then tokens above it, and the lowest-index tokens equal to it, are
-// written in ascending index order through a workgroup-wide prefix count.  Equal scores go to
-// the lower index, so the result is unique.
+// largest score is found by building its bit pattern from the top down, two bits per round, then
+// the tokens above it, and the lowest-index tokens equal to it, are written in ascending index
+// order.  Equal scores go to the lower index, so the result is unique.
+// Bound by its chain of rounds, not by bytes: the bits all keys of a chunk share are skipped, a
+// round costs one barrier, the search ends as soon as exactly N keys lie above the threshold (about
+// log2(n) + a few bits instead of 32), and a thread keeps its keys in registers (wavefront w owns a
+// contiguous quarter of the chunk, so the final compaction needs one exchange of counts).
 // ---------------------------------------------------------------------------------------------
 constexpr int kTopnThreads = 256;
-constexpr int kTopnLds = 4096;              // chunk lengths up to this are ranked out of LDS
+constexpr int kTopnKeep = 16;               // keys a thread keeps in registers: chunks of up to 4096 tokens
 
 __device__ __forceinline__ uint32_t ordered_key(float v) {   // monotone float -> uint
   uint32_t u = __float_as_uint(v);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ int block_sum_i(int v, int* red) {  // sum over 256 threads, all get it
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// KEEP: the keys fit in registers (R <= kTopnKeep rounds of 64 tokens per wavefront); otherwise each
+// thread reads its own keys back from key_buf.
+template <bool KEEP>
+__device__ __forceinline__ void topn_segment(
+    const cc_segment& sg, const float* __restrict__ mass, int hq, bool given, const int32_t* __restrict__ block_tab,
+    int32_t* __restrict__ sel_idx, int32_t* __restrict__ q_row, int32_t* __restrict__ q_pos,
+    int32_t* __restrict__ slot_map, float* __restrict__ scores, uint32_t* key_buf) {
+  __shared__ uint32_t all_and[4], all_or[4];
+  __shared__ int counts[2][4][4];
+  const int n = sg.n_tokens, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rounds = (n + kTopnThreads - 1) / kTopnThreads;          // of 64 tokens per wavefront
+  const int first = w * rounds * 64 + lane;                          // token of round r: first + 64 r
+  uint32_t held[KEEP ? kTopnKeep : 1];
+  uint32_t* stored = key_buf + sg.tok_off;
+  // visits (token, key); a token past the chunk's end has key 0 (below every candidate threshold)
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+    if constexpr (KEEP) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  __syncthreads();
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
-}
-
-__global__ __launch_bounds__(kTopnThreads) void topn_kernel(
-    const float* __restrict__ mass, int hq, bool given, const int32_t* __restrict__ block_tab,
-    const cc_segment* __restrict__ segs, int32_t* __restrict__ sel_idx, int32_t* __restrict__ q_row,
-    int32_t* __restrict__ q_pos, int32_t* __restrict__ slot_map, float* __restrict__ scores,
-    uint32_t* __restrict__ key_buf) {
-  __shared__ uint32_t lds_keys[kTopnLds];
-  __shared__ int red[4];
-  __shared__ int wave_off[2][4];
-  const cc_segment sg = segs[blockIdx.x];
-  const int n = sg.n_tokens, tid = threadIdx.x;
-  auto emit = [&](int j, int idx) {
-    const int o = sg.sel_off + j;
-    sel_idx[o] = idx;
-    if (q_row) q_row[o] = sg.tok_off + idx;
-    if (q_pos) q_pos[o] = sg.logical_start + idx;
-    if (slot_map) slot_map[o] = block_tab[sg.tab_off + idx / kBlock] * kBlock + idx % kBlock;
+      for (int r = 0; r < kTopnKeep; ++r)
+        if (r < rounds) f(first + 64 * r, held[r]);
+    } else {
+      for (int r = 0; r < rounds; ++r) {
+        const int i = first + 64 * r;
+        f(i, i < n ? stored[i] : 0u);
+      }
+    }
   };
-  if (sg.kind != CC_SEG_CHUNK) {            // question: every token is a query
-    for (int i = tid; i < n; i += kTopnThreads) emit(i, i);
-    return;
-  }
-  const int n_sel = min(max(sg.n_select, 0), n);
-  uint32_t* keys = (n <= kTopnLds) ? lds_keys : key_buf + sg.tok_off;
+  // ---- scores and keys ----
   const float inv_h = 1.f / static_cast<float>(hq);
-  for (int i = tid; i < n; i += kTopnThreads) {
+  uint32_t k_and = 0xffffffffu, k_or = 0u;
+  auto make_key = [&](int i) __attribute__((always_inline)) {
+    if (i >= n) return 0u;
     float sc = 0.f;
     if (given) {                            // scores supplied by the caller, one per token
       sc = mass[static_cast<size_t>(sg.tok_off) + i];
@@ -155,56 +155,120 @@ __global__ __launch_bounds__(kTopnThreads) void topn_kernel(
       sc *= inv_h;
     }
     if (scores) scores[sg.tok_off + i] = sc;
-    keys[i] = ordered_key(sc);
-  }
-  __syncthreads();
-  if (n_sel == 0) return;
-  // N-th largest key, most significant bit first
-  // (a wavefront counts with ballots; the four wavefront counts meet in LDS, in two alternating
-  //  sets of cells so that one barrier per round is enough)
-  __shared__ int round_cnt[2][4];
-  uint32_t thr = 0;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = thr | (1u << bit);
-    int cnt = 0;
-    for (int i0 = 0; i0 < n; i0 += kTopnThreads) {
-      const int i = i0 + tid;
-      cnt += __popcll(__ballot(i < n && keys[i] >= cand));
+    const uint32_t k = ordered_key(sc);
+    k_and &= k;
+    k_or |= k;
+    return k;
+  };
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int r = 0; r < kTopnKeep; ++r)
+      if (r < rounds) held[r] = make_key(first + 64 * r);
+  } else {
+    for (int r = 0; r < rounds; ++r) {
+      const int i = first + 64 * r;
+      const uint32_t k = make_key(i);
+      if (i < n) stored[i] = k;
     }
-    int* cell = round_cnt[bit & 1];
-    if ((tid & 63) == 0) cell[tid >> 6] = cnt;
-    __syncthreads();
-    if (cell[0] + cell[1] + cell[2] + cell[3] >= n_sel) thr = cand;
   }
-  int cnt = 0;
-  for (int i = tid; i < n; i += kTopnThreads) cnt += keys[i] > thr;
-  const int n_gt = block_sum_i(cnt, red);
-  const int n_eq_take = n_sel - n_gt;       // how many of the ties (lowest indices) are kept
-  // ordered compaction, 256 tokens per round
-  int base_sel = 0, base_eq = 0;
-  const int lane = tid & 63, w = tid >> 6;
-  for (int i0 = 0; i0 < n; i0 += kTopnThreads) {
-    const int i = i0 + tid;
-    const uint32_t k = i < n ? keys[i] : 0u;
-    const bool gt = i < n && k > thr, eq = i < n && k == thr;
+  const int n_sel = min(max(sg.n_select, 0), n);
+  if (n_sel == 0) return;
+  // ---- threshold: bits shared by all keys first ----
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    k_and &= __shfl_xor(k_and, o, 64);
+    k_or |= __shfl_xor(k_or, o, 64);
+  }
+  if (lane == 0) { all_and[w] = k_and; all_or[w] = k_or; }
+  __syncthreads();
+  k_and = all_and[0] & all_and[1] & all_and[2] & all_and[3];
+  k_or = all_or[0] | all_or[1] | all_or[2] | all_or[3];
+  const uint32_t differ = k_and ^ k_or;
+  int bits = differ == 0 ? 0 : 32 - __builtin_clz(differ);           // low bits still open
+  uint32_t thr = bits == 32 ? 0u : (k_and >> bits) << bits;
+  int n_at = n;                                                      // keys >= thr
+  for (int round = 0; bits > 0 && n_at != n_sel; ++round) {
+    // two bits at a time: the largest of four candidates with at least n_sel keys at or above it
+    // (an odd last bit: the step of the candidates is one bit)
+    const int step = max(bits - 2, 0);
+    const int n_cand = bits >= 2 ? 3 : 1;
+    int cnt[3] = {0, 0, 0};
+    each([&](int, uint32_t k) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cnt[c] += __popcll(__ballot(k >= (thr | (static_cast<uint32_t>(c + 1) << step))));
+    });
+    int(*cell)[4] = counts[round & 1];
+    if (lane == 0) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cell[c][w] = cnt[c];
+    }
+    __syncthreads();
+    uint32_t take = 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int all = cell[c][0] + cell[c][1] + cell[c][2] + cell[c][3];
+      if (c < n_cand && all >= n_sel) { take = c + 1; n_at = all; }
+    }
+    thr |= take << step;
+    bits = step;
+  }
+  // exactly n_sel keys at or above thr: all of them; else thr is the N-th key itself and of its
+  // equals the first (lowest indices) are kept
+  const bool ties = n_at != n_sel;
+  int n_gt = 0, n_eq = 0;                                            // of this wavefront
+  each([&](int i, uint32_t k) __attribute__((always_inline)) {
+    n_gt += __popcll(__ballot(i < n && (ties ? k > thr : k >= thr)));
+    n_eq += __popcll(__ballot(i < n && ties && k == thr));
+  });
+  __shared__ int wave_gt[4], wave_eq[4];
+  if (lane == 0) { wave_gt[w] = n_gt; wave_eq[w] = n_eq; }
+  __syncthreads();
+  int gt_before = 0, eq_before = 0, gt_all = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (i < w) { gt_before += wave_gt[i]; eq_before += wave_eq[i]; }
+    gt_all += wave_gt[i];
+  }
+  const int n_eq_take = n_sel - gt_all;
+  int pos0 = gt_before + min(eq_before, n_eq_take), eq0 = eq_before;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  each([&](int i, uint32_t k) __attribute__((always_inline)) {
+    const bool eq = i < n && ties && k == thr;
     const unsigned long long b_eq = __ballot(eq);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    __syncthreads();
-    if (lane == 0) wave_off[0][w] = __popcll(b_eq);
-    __syncthreads();
-    int eq_rank = base_eq + __popcll(b_eq & below);
-    for (int ww = 0; ww < w; ++ww) eq_rank += wave_off[0][ww];
-    const int eq_round = wave_off[0][0] + wave_off[0][1] + wave_off[0][2] + wave_off[0][3];
-    const bool take = gt || (eq && eq_rank < n_eq_take);
+    const bool take = (i < n && (ties ? k > thr : k >= thr)) || (eq && eq0 + __popcll(b_eq & below) < n_eq_take);
     const unsigned long long b_tk = __ballot(take);
-    if (lane == 0) wave_off[1][w] = __popcll(b_tk);
-    __syncthreads();
-    int pos = base_sel + __popcll(b_tk & below);
-    for (int ww = 0; ww < w; ++ww) pos += wave_off[1][ww];
-    if (take) emit(pos, i);
-    base_sel += wave_off[1][0] + wave_off[1][1] + wave_off[1][2] + wave_off[1][3];
-    base_eq += eq_round;
+    if (take) {
+      const int o = sg.sel_off + pos0 + __popcll(b_tk & below);
+      sel_idx[o] = i;
+      if (q_row) q_row[o] = sg.tok_off + i;
+      if (q_pos) q_pos[o] = sg.logical_start + i;
+      if (slot_map) slot_map[o] = block_tab[sg.tab_off + i / kBlock] * kBlock + i % kBlock;
+    }
+    pos0 += __popcll(b_tk);
+    eq0 += __popcll(b_eq);
+  });
+}
+
+__global__ __launch_bounds__(kTopnThreads) void topn_kernel(
+    const float* __restrict__ mass, int hq, bool given, const int32_t* __restrict__ block_tab,
+    const cc_segment* __restrict__ segs, int32_t* __restrict__ sel_idx, int32_t* __restrict__ q_row,
+    int32_t* __restrict__ q_pos, int32_t* __restrict__ slot_map, float* __restrict__ scores,
+    uint32_t* key_buf) {
+  const cc_segment sg = segs[blockIdx.x];
+  if (sg.kind != CC_SEG_CHUNK) {            // question: every token is a query
+    for (int i = threadIdx.x; i < sg.n_tokens; i += kTopnThreads) {
+      const int o = sg.sel_off + i;
+      sel_idx[o] = i;
+      if (q_row) q_row[o] = sg.tok_off + i;
+      if (q_pos) q_pos[o] = sg.logical_start + i;
+      if (slot_map) slot_map[o] = block_tab[sg.tab_off + i / kBlock] * kBlock + i % kBlock;
+    }
+    return;
   }
+  if (sg.n_tokens <= kTopnKeep * kTopnThreads)
+    topn_segment<true>(sg, mass, hq, given, block_tab, sel_idx, q_row, q_pos, slot_map, scores, key_buf);
+  else
+    topn_segment<false>(sg, mass, hq, given, block_tab, sel_idx, q_row, q_pos, slot_map, scores, key_buf);
 }
 
 void launch_topn(const cc_ctx* ctx, const float* mass, const int32_t* block_tab,

@@ -13,6 +13,24 @@ from tests import helpers as H
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("lens", [[1, 2, 63, 64, 65], [255, 256, 257, 511], [1023, 4096], [4097]])
+@pytest.mark.parametrize("frac", [0.0, 0.01, 0.37, 1.0])
+def test_top_n_around_the_lengths_where_its_loops_change(lens, frac):
+    # (a wavefront owns 64-token rounds of a quarter of the chunk; up to 4096 tokens stay in registers)
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("topn", "f32", 2, 1, 64, 1.0e4, lens, [0] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [frac] * len(lens), 3)], 1.0, seed=13)
+    rng = np.random.default_rng(len(lens))
+    ties = rng.integers(0, 9, size=w.n_tok) / np.float32(8)                     # few distinct values
+    for given in (rng.standard_normal(w.n_tok), ties, np.zeros(w.n_tok), 0.75 + 1e-6 * rng.random(w.n_tok)):
+        given = given.astype(np.float32)
+        b = DeviceBatch(w)
+        b.select_from_scores(torch.from_numpy(given).cuda()); torch.cuda.synchronize()
+        for got, sg in zip(H.gpu_selection(w, b.sel_idx.cpu().numpy())[0], H.chunk_segments(w, 0)):
+            t0, n = int(sg[W.SEG_TOK]), int(sg[W.SEG_NTOK])
+            assert np.array_equal(got, O.top_n(given[t0:t0 + n].astype(np.float64), int(sg[W.SEG_NSEL])))
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("hkv", [1, 3, 8])
 def test_scatter_runs_of_every_length_at_every_place(dtype, d, hkv):
