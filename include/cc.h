@@ -118,7 +118,8 @@ const char* cc_status_string(int status);
 /* Message of the last failing call on this context (valid until the next call on it). */
 const char* cc_last_error(const cc_ctx* ctx);
 /* Kernel family used by cc_select / cc_sparse_prefill / cc_qkv_project: CC_IMPL_AUTO (default)
- * picks the fastest MFMA kernels built for the configuration (bf16, head_dim 128),
+ * picks the fastest MFMA kernels built for the configuration (bf16 arithmetic for bf16 tensors with
+ * head_dim 128 and head groups of 1, 2, 4 or 8, fp32 arithmetic for everything else),
  * CC_IMPL_SCALAR forces the plain ones, CC_IMPL_MFMA_NARROW the MFMA kernels that give a
  * wavefront 32 query rows (64 tokens in the score stage; the only MFMA form for head groups of
  * 1 or 2), CC_IMPL_MFMA_WIDE the ones that give it 64 (128) even where AUTO would find the

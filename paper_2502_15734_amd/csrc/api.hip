@@ -187,7 +187,7 @@ int cc_select(cc_ctx* ctx, const void* q, int32_t n_tok, const void* k_pool, int
     cc::launch_score_mfma(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off,
                           max_seg_tokens, mass, plan_ws, max_tiles_for(n_tok, n_segs), n_tok, st);
   else
-    cc::launch_score_scalar(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off,
+    cc::launch_score_plain(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off,
                             max_seg_tokens, mass, st);
   cc::launch_topn(ctx, mass, block_tab, segs, n_segs, sel_idx, q_row, q_pos, slot_map, scores, keys, false, st);
   return cc::check_launch(ctx, fn);
@@ -339,7 +339,7 @@ int cc_sparse_prefill(cc_ctx* ctx, const void* q, const void* k_new, const void*
                          block_tab, segs, n_segs, req_seg_off, n_requests, out, lse, workspace,
                          max_tiles_for(n_ctx_tokens, n_segs), src_rows, 0, st, nullptr, vs);
   else
-    cc::launch_attn_scalar(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks,
+    cc::launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks,
                            block_tab, segs, req_seg_off, n_requests, out, lse, src_rows, 0, st, vs);
   return cc::check_launch(ctx, fn);
 }
@@ -427,7 +427,7 @@ int cc_sparse_prefill_mass(cc_ctx* ctx, const void* q, const void* k_new, const 
                            segs, n_segs, req_seg_off, n_requests, out, lse, workspace,
                            max_tiles_for(n_ctx_tokens, n_segs), src_rows, 0, st, nullptr, vs);
     else
-      cc::launch_attn_scalar(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab,
+      cc::launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab,
                              segs, req_seg_off, n_requests, out, lse, src_rows, 0, st, vs);
     cc::launch_fill_zero(seg_mass, n_segs, st);
     return cc::check_launch(ctx, fn);

@@ -52,8 +52,17 @@ void launch_rope_shift(const cc_ctx* ctx, const void* k_src, const void* v_src, 
 void launch_gather_rows(const void* src, int n_src_rows, const int32_t* row_idx, int n_rows,
                         size_t row_bytes, void* dst, hipStream_t stream);
 
-// scores: per (token, query head) prior-chunk mass -> mass [n_tok][Hq] fp32
-void launch_score_scalar(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
+// fp32 arithmetic on the matrix cores (qk_f32.hip): what the bf16 MFMA kernels do not take
+void launch_score_f32(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks, const int32_t* block_tab,
+                      const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int max_seg_tokens, float* mass,
+                      hipStream_t stream);
+void launch_attn_f32(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q, int max_q_per_req,
+                     const void* k_pool, const void* v_pool, int n_blocks, const int32_t* block_tab,
+                     const cc_segment* segs, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
+                     const int32_t* q_map, int map_pos, hipStream_t stream, const ValueSource& vs);
+// scores: per (token, query head) prior-chunk mass -> mass [n_tok][Hq] fp32; the plain form runs the fp32
+// kernel, or the scalar one when CC_IMPL_SCALAR asks for it (attention below alike)
+void launch_score_plain(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
                          const int32_t* block_tab, const cc_segment* segs, int n_segs,
                          const int32_t* req_seg_off, int max_seg_tokens, float* mass,
                          hipStream_t stream);
@@ -78,7 +87,7 @@ void launch_rope_scatter(const cc_ctx* ctx, const void* k_new, const void* v_new
                          const ValueSource& vs = ValueSource());
 void launch_list_order_check(const int32_t* slot_map, int n_rows, int n_blocks, int32_t* mark,
                              int32_t* n_violations, hipStream_t stream);
-void launch_attn_scalar(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
+void launch_attn_plain(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
                         int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,
                         int n_blocks, const int32_t* block_tab, const cc_segment* segs,
                         const int32_t* req_seg_off, int n_requests, void* out, float* lse,

@@ -589,7 +589,7 @@ static void run_segment_list(const cc_ctx* ctx, const ListBuffers& b, const void
     launch_attn_mfma(ctx, q, pos, b.cu_v, cap, max_rows, k_pool, v_pool, n_blocks, block_tab, segs, n_segs,
                      b.seg_iota, n_segs, nullptr, b.lse_seg, b.plan_ws, max_tiles, map, map_pos, stream);
   else
-    launch_attn_scalar(ctx, q, pos, b.cu_v, cap, max_rows, k_pool, v_pool, n_blocks, block_tab, segs,
+    launch_attn_plain(ctx, q, pos, b.cu_v, cap, max_rows, k_pool, v_pool, n_blocks, block_tab, segs,
                        b.seg_iota, n_segs, nullptr, b.lse_seg, map, map_pos, stream);
 }
 
@@ -688,7 +688,7 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
     launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                      n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs);
   } else {
-    launch_attn_scalar(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
+    launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                        req_seg_off, n_requests, out, lse, src_rows, 0, stream, vs);
   }
   if (by.wide) {
@@ -750,7 +750,7 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
     launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                      n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs);
   } else {
-    launch_attn_scalar(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
+    launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                        req_seg_off, n_requests, out, lse, src_rows, 0, stream, vs);
   }
   const bool bf = ctx->cfg.dtype == CC_BF16;

@@ -236,7 +236,7 @@ void launch_rope_scatter(const cc_ctx* ctx, const void* k_new, const void* v_new
 #undef CC_LAUNCH
 }
 
-// Scalar attention: one wavefront per (query row, query head).  Lane i owns rotation pair
+// Scalar attention (CC_IMPL_SCALAR): one wavefront per (query row, query head).  Lane i owns rotation pair
 // (i, i + d/2) of q and the same two output dimensions.
 template <typename T, int D>
 __global__ __launch_bounds__(64) void attn_scalar_kernel(
@@ -299,13 +299,17 @@ __global__ __launch_bounds__(64) void attn_scalar_kernel(
   if (lse != nullptr && lane == 0) lse[static_cast<size_t>(j) * hq + h] = m + logf(z);
 }
 
-void launch_attn_scalar(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
+void launch_attn_plain(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
                         int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,
                         int n_blocks, const int32_t* block_tab, const cc_segment* segs,
                         const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                         const int32_t* q_map, int map_pos, hipStream_t stream, const ValueSource& vs) {
-  (void)max_q_per_req;
   if (n_q_tot <= 0) return;
+  if (ctx->impl != CC_IMPL_SCALAR) {
+    launch_attn_f32(ctx, q, q_pos, cu_q, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs, req_seg_off, n_requests,
+                    out, lse, q_map, map_pos, stream, vs);
+    return;
+  }
   const bool bf = ctx->cfg.dtype == CC_BF16;
   const int d = ctx->cfg.head_dim, hq = ctx->cfg.n_q_heads, hkv = ctx->cfg.n_kv_heads;
 #define CC_LAUNCH(T, D)                                                                         \

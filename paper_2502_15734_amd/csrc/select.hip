@@ -7,7 +7,7 @@ namespace cc {
 // ---------------------------------------------------------------------------------------------
 // Scalar score kernel: one wavefront per (chunk token, query head).  Lane i owns rotation pair
 // (i, i + d/2) of the query; keys of the request are visited in logical order, each logit is a
-// wavefront reduction.  Used for fp32 and as the fallback for shapes the MFMA kernel lacks.
+// wavefront reduction.  Runs when CC_IMPL_SCALAR asks for it.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int D>
 __global__ __launch_bounds__(64) void score_scalar_kernel(
@@ -71,14 +71,15 @@ static void launch_score_t(const cc_ctx* ctx, const void* q, const void* k_pool,
                      segs, req_seg_off, ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, ctx->inv_freq, mass);
 }
 
-void launch_score_scalar(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
+void launch_score_plain(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
                          const int32_t* block_tab, const cc_segment* segs, int n_segs,
                          const int32_t* req_seg_off, int max_seg_tokens, float* mass,
                          hipStream_t stream) {
   const bool bf = ctx->cfg.dtype == CC_BF16;
   const int d = ctx->cfg.head_dim;
 #define CC_ARGS ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off, max_seg_tokens, mass, stream
-  if (bf && d == 128) launch_score_t<bf16_t, 128>(CC_ARGS);
+  if (ctx->impl != CC_IMPL_SCALAR) launch_score_f32(CC_ARGS);
+  else if (bf && d == 128) launch_score_t<bf16_t, 128>(CC_ARGS);
   else if (bf && d == 64) launch_score_t<bf16_t, 64>(CC_ARGS);
   else if (!bf && d == 128) launch_score_t<float, 128>(CC_ARGS);
   else launch_score_t<float, 64>(CC_ARGS);

@@ -74,3 +74,32 @@ def test_scatter_runs_of_every_length_at_every_place(dtype, d, hkv):
     slack = 8 * (1e-6 if dtype == "bf16" else 4 * 2.0 ** -24)
     worst = float(np.max(np.abs(got_k - want_k) - tol * np.abs(want_k)))
     assert worst <= slack
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv", [("f32", 64, 4, 2), ("f32", 128, 3, 1), ("bf16", 64, 6, 2), ("bf16", 128, 3, 1)])
+@pytest.mark.parametrize("lens,question", [([15, 16, 17], 1), ([8209, 33], 18)])
+def test_fp32_arithmetic_kernels_against_the_scalar_ones(dtype, d, hq, hkv, lens, question):
+    # one row more or less than a 16-row tile and a 16-token block; more key blocks (515) than one list window (512)
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("f32k", dtype, hq, hkv, d, 1.0e4, lens, [3] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [0.003] * len(lens), question)], 1.0, seed=31)
+    got = {}
+    for impl in (P.CC_IMPL_AUTO, P.CC_IMPL_SCALAR):
+        b = DeviceBatch(w, impl=impl, poison=True)
+        b.rope_shift(); b.select()
+        if impl == P.CC_IMPL_SCALAR:
+            sel = got[P.CC_IMPL_AUTO][0]
+            b.set_selection(*sel)
+        else:
+            sel = tuple(t.cpu().numpy()[: w.n_q_tot] for t in (b.sel_idx, b.q_row, b.q_pos, b.slot_map))
+        b.sparse_prefill_fused(); torch.cuda.synchronize()
+        got[impl] = (sel, b.scores.cpu().double(), b.out.cpu().double(), b.lse.cpu().double())
+    a, s = got[P.CC_IMPL_AUTO], got[P.CC_IMPL_SCALAR]
+    # both sum n fp32 terms of one sign in different orders: n 2^-24 at the very worst, sqrt(n) 2^-24 in practice
+    n_ctx = sum(lens) + question
+    rel = lambda x, y: float((x - y).norm() / y.norm())
+    bound = 8 * math.sqrt(n_ctx) * 2.0 ** -24 + 1e-6                             # + the exponentials' own error
+    assert rel(a[1], s[1]) <= bound
+    assert rel(a[2], s[2]) <= bound + (2.0 ** -9 if dtype == "bf16" else 0.0)    # (bf16 output: a rounding may flip)
+    assert float((a[3] - s[3]).abs().max()) <= 8 * bound
