@@ -232,8 +232,8 @@ int cc_qkv_project(cc_ctx* ctx, const void* x, const void* w_qkv, int32_t n_rows
  *   cc_linear:       y [n_rows][n_out] = x [n_rows][n_in] W^T (+ residual [n_rows][n_out], or NULL;
  *                    residual may be y itself, x may not).
  *   cc_gated_linear: y [n_rows][n_ffn] = silu(x W_gate^T) * (x W_up^T), silu(t) = t / (1 + exp(-t)).
- * bf16 with n_out (2 n_ffn for the gated form) a multiple of 256 and n_in a multiple of 64, at
- * least 128: MFMA GEMM with 128 x 128 outputs per wavefront; otherwise a plain tiled kernel. */
+ * bf16 with n_out (2 n_ffn for the gated form) and n_in multiples of 64: MFMA GEMM; otherwise a plain
+ * tiled kernel. */
 int cc_rms_norm(cc_ctx* ctx, const void* x, const void* gain, float eps, int32_t n_rows, int32_t hidden,
                 void* y, void* stream);
 int cc_linear(cc_ctx* ctx, const void* x, const void* w, const void* residual, int32_t n_rows,

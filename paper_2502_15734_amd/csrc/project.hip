@@ -1,16 +1,11 @@
-// cc_qkv_project: [q | k | v] = x W^T for the chosen tokens only (Sec. 3.4.3).
+// cc_qkv_project: [q | k | v] = x W^T for the chosen tokens only (Sec. 3.4.3), and the other dense
+// products of a decoder layer for the recomputed rows (Sec. 2.1, Sec. 3.4.3): y = x W^T (+ residual)
+// and the feed-forward input silu(x W_gate^T) * (x W_up^T).
 //
-// x [n_rows][hidden], W [(Hq+2Hkv)d][hidden]: both operands have the contraction index contiguous.
-// bf16: MFMA GEMM.  A workgroup of 8 wavefronts owns a 256 (features) x 256 (tokens) tile of the
-// transposed product D^T = W x^T; wavefront (wn, wm) owns 64 features x 128 tokens = 2 x 4 blocks
-// of v_mfma_f32_32x32x16_bf16, so 6 operand reads from LDS feed 8 MFMAs per 16-wide k-step.
-// K-steps of 32 are double-buffered in LDS (2 x 32 KiB) with the next step's global loads held in
-// registers.  In the transposed product a lane holds 4 consecutive features of ONE token, so the
-// epilogue writes 8-byte pieces of an output row.  fp32 (and odd shapes): plain LDS-tiled kernel.
-//
-// The same GEMM kernels serve the other dense products of a decoder layer for the recomputed rows
-// (Sec. 2.1, Sec. 3.4.3): y = x W^T (+ residual) and the feed-forward input
-// silu(x W_gate^T) * (x W_up^T); only the epilogue and the rows of W a workgroup stages differ.
+// x [n_rows][hidden], W [features][hidden]: both operands have the contraction index contiguous.
+// bf16: MFMA GEMMs on the transposed product D^T = W x^T, in which a lane holds consecutive features of
+// ONE token and writes 16-byte pieces of an output row; the products differ in their epilogue and in
+// the rows of W a workgroup stages.  fp32 (and odd shapes): plain LDS-tiled kernels.
 #include <type_traits>
 
 #include "device_util.h"
@@ -123,236 +118,550 @@ __global__ __launch_bounds__(256) void linear_plain_kernel(
 // ---- MFMA kernel (bf16) -----------------------------------------------------------------------
 namespace {
 
-constexpr int kTN = 256, kTM = 256;                   // workgroup tile: features x tokens
-
-// ---- MFMA kernel, 128 x 128 outputs per wavefront -------------------------------------------------
-// Workgroup = 4 wavefronts (2 x 2), one per SIMD, 256 features x 256 tokens; a wavefront owns
-// 4 x 4 blocks of v_mfma_f32_32x32x16_bf16 (256 accumulation registers), so 8 operand reads from
-// LDS feed 16 MFMAs per 16-wide k-step.
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-__device__ __forceinline__ void gemm_load_to_lds(const void* src, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(lds_addr) : "memory", "m0");
+// 64 lanes x 16 bytes from global memory straight into LDS: lane L's 16 bytes land at lds_addr + 16 L,
+// read from base + voff(L)
+__device__ __forceinline__ void gemm_load_to_lds(const char* base, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
-__device__ __forceinline__ void gemm_mfma(f32x16& d, const u32x4& a, const u32x4& b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
-}
-
-// Epilogue of the 128 x 128-per-wavefront kernels.  D^T block (a, b): lane (nl, hh) holds token
-// m0 + 128 wm + 32 b + nl, features n0 + 128 wn + 32 a + 8 (i/4) + 4 hh + i%4.
-template <int MODE>
-__device__ __forceinline__ void gemm_store_tile(f32x16 (&acc)[4][4], const GemmOut& out, int n_rows, int n0, int m0,
-                                                int wn, int wm, int nl, int hh) {
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int row = m0 + wm * 128 + b * 32 + nl;
-    if (row >= n_rows) continue;
-    if (MODE == kOutGated) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        bf16_t* op = static_cast<bf16_t*>(out.o0) + static_cast<size_t>(row) * out.width + n0 / 2 + wn * 64 + a * 32 + 4 * hh;
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          bf16_t v4[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float gate = acc[a][b][4 * g4 + e], up = acc[a + 2][b][4 * g4 + e];
-            v4[e] = static_cast<bf16_t>(gate / (1.f + __expf(-gate)) * up);
-          }
-          *reinterpret_cast<uint2*>(op + 8 * g4) = *reinterpret_cast<uint2*>(v4);
-        }
-      }
-      continue;
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int col0 = n0 + wn * 128 + a * 32;        // a 32-feature block never straddles q | k | v
-      bf16_t* base;
-      int c_in, width;
-      if (MODE == kOutLinear) { base = static_cast<bf16_t*>(out.o0); c_in = col0; width = out.width; }
-      else if (col0 < out.nq) { base = static_cast<bf16_t*>(out.o0); c_in = col0; width = out.nq; }
-      else if (col0 < out.nq + out.nk) { base = static_cast<bf16_t*>(out.o1); c_in = col0 - out.nq; width = out.nk; }
-      else { base = static_cast<bf16_t*>(out.o2); c_in = col0 - out.nq - out.nk; width = out.nk; }
-      const size_t at = static_cast<size_t>(row) * width + c_in + 4 * hh;
-      bf16_t* op = base + at;
-      const bf16_t* rp = MODE == kOutLinear && out.residual != nullptr ? static_cast<const bf16_t*>(out.residual) + at : nullptr;
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        bf16_t v4[4];
-        if (rp != nullptr) {
-          bf16_t r4[4];
-          *reinterpret_cast<uint2*>(r4) = *reinterpret_cast<const uint2*>(rp + 8 * g4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v4[e] = static_cast<bf16_t>(acc[a][b][4 * g4 + e] + static_cast<float>(r4[e]));
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v4[e] = static_cast<bf16_t>(acc[a][b][4 * g4 + e]);
-        }
-        *reinterpret_cast<uint2*>(op + 8 * g4) = *reinterpret_cast<uint2*>(v4);
-      }
-    }
-  }
+__device__ __forceinline__ void gemm_mfma(f32x4& d, const u32x4& a, const u32x4& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
 
-// Operands go straight from global memory into LDS (global_load_lds: lane L of an instruction fills
-// piece base + L), whole cache lines per load.  A k-stage is 64 wide: 128 bytes = one cache line of
-// every row of W and x.  A load instruction brings 8 rows x 128 bytes (8 consecutive lanes share a
-// line; an image laid out in MFMA operand order instead - 32 rows x 32 bytes per instruction - was
-// measured: it touches 32 lines for the same kilobyte, needs every line in two stages, and ran the
-// gated product in 9.96 ms instead of 6.94), and the image in LDS is row-major, 128 bytes per row.  Operand reads walk down 32 rows at one 16-byte piece, so piece c of row r is kept at
-// c ^ swz(r), swz(r) = ((r >> 1) & 7) ^ ((r & 1) << 2): any 8 or 16 consecutive rows then spread
-// over all banks.  The permutation is applied on the global side (lane -> piece of the line),
-// because the load fixes where a lane's bytes land in LDS.  Two images of 64 KiB; per stage the
-// wavefronts meet once, at its end.
-constexpr int kTK3 = 64;
-constexpr int kStage3Bytes = (kTN + kTM) * kTK3 * 2;      // 64 KiB
-
-__device__ __forceinline__ int gemm_swz(int r) { return ((r >> 1) & 7) ^ ((r & 1) << 2); }
-
+// Both GEMM kernels below share the following.
 //
+// v_mfma_f32_16x16x32_bf16, not 32x32x16: under matrix load the chip is held by its power budget, and this
+// shape moves a quarter of the accumulator bytes per flop (MFMAs and barriers alone, everything else taken
+// out of the loop: 1.9 PFLOP/s against 1.48; the whole product 1.30 against 1.17 at 4096 x 4096 x 14336).
+//
+// Operands go straight from global memory into LDS (global_load_lds: lane L of an instruction fills
+// piece base + L), whole cache lines per load: a line of 128 bytes is 64 contraction indices of one row of W
+// or x, 8 consecutive lanes share it (8 rows per instruction), and the image in LDS is row-major, 128 bytes
+// per row.  Operand reads walk down 16 rows at one 16-byte piece, so piece c of row r is kept at
+// c ^ swizzle(r), which spreads any such walk over all banks (0 conflicts); the permutation is
+// applied on the global side (lane -> piece of the line), because the load fixes where a lane's bytes land.
+//
+// MFMA row m of the half i2 of a 32-feature block is feature 8 (m / 4) + 4 i2 + m % 4, so that the two halves give
+// a lane 8 consecutive features of a token: one 16-byte store.
+constexpr int kTK = 64;                               // contraction indices in a cache line
+__device__ __forceinline__ int gemm_swz_w(int r) { return ((r >> 1) & 1) | ((r >> 2) & 6); }   // (rows 8 (m / 4) + m % 4)
+__device__ __forceinline__ int gemm_swz_x(int r) { return (r >> 1) & 7; }                        // (rows m)
+
+// gated: of a wavefront's FB 32-feature blocks the first half are rows of W_gate and the second half the SAME
+// rows of W_up, so that a lane ends up holding both factors of an output
+
+// the residual's 8 values that belong to 8 consecutive features of one token (asking for a 256 x
+// 256 tile's residual ahead of its stores spills registers and gains nothing: all workgroups store at once, bound by bytes)
+template <int MODE>
+__device__ __forceinline__ uint4 gemm_residual8(const GemmOut& out, int row, int col) {
+  if (MODE != kOutLinear || out.residual == nullptr) return make_uint4(0u, 0u, 0u, 0u);
+  return *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(out.residual) + static_cast<size_t>(row) * out.width + col);
+}
+
+// stores 8 consecutive features of one token
+template <int MODE>
+__device__ __forceinline__ void gemm_store8(const f32x4& lo, const f32x4& hi, const f32x4& up_lo, const f32x4& up_hi,
+                                            const uint4& residual, const GemmOut& out, int row, int col) {
+  bf16_t* base;
+  int c_in = col, width;                              // (32 features never straddle q | k | v)
+  if (MODE != kOutQkv) { base = static_cast<bf16_t*>(out.o0); width = out.width; }
+  else if (col < out.nq) { base = static_cast<bf16_t*>(out.o0); width = out.nq; }
+  else if (col < out.nq + out.nk) { base = static_cast<bf16_t*>(out.o1); c_in = col - out.nq; width = out.nk; }
+  else { base = static_cast<bf16_t*>(out.o2); c_in = col - out.nq - out.nk; width = out.nk; }
+  const size_t at = static_cast<size_t>(row) * width + c_in;
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = e < 4 ? lo[e & 3] : hi[e & 3];
+  if (MODE == kOutGated) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = v[e] / (1.f + __expf(-v[e])) * (e < 4 ? up_lo[e & 3] : up_hi[e & 3]);
+  }
+  if (MODE == kOutLinear && out.residual != nullptr) {
+    const bf16x8 r = __builtin_bit_cast(bf16x8, residual);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += static_cast<float>(r[e]);
+  }
+  bf16x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = static_cast<bf16_t>(v[e]);
+  *reinterpret_cast<uint4*>(base + at) = __builtin_bit_cast(uint4, o);
+}
+
 // Which tile a workgroup takes: workgroups are handed to the 8 XCDs in turn, each XCD with an L2 of
 // its own.  Workgroup L therefore takes entry (L % 8) * per_xcd + L / 8 of a tile order in which 32
-// consecutive entries (what one XCD runs at a time) form a block of 4 feature tiles x 8 token tiles:
-// the block's 32 workgroups ask their L2 for 12 different operand panels instead of up to 34
-// (L2 hit rate 48 % -> 82 %, memory reads a third; 3 - 7 % faster for the plain products).  The
-// gated product keeps the plain order (feature tile fastest): every blocked order tried was 5 - 10 %
-// slower there although it, too, cut the reads that leave the L2s to a third - in the plain order
-// all XCDs walk the same rows of token tiles together, so the activations stream from HBM once,
-// and an XCD keeps to one fixed set of weight panels, which the memory-side cache can hold.
+// consecutive entries (what one XCD runs at a time) form a block of 4 feature tiles x 8 token tiles: the
+// block's 32 workgroups ask their L2 for 12 different operand panels instead of up to 34.  (The plain order
+// is 0 - 5 % slower, 8 x 4 and 2 x 16 blocks measure the same.)
 constexpr int kBlockN = 4, kBlockM = 8;
+__device__ __forceinline__ bool gemm_tile_of(int tiles_n, int tiles_m, int* tn, int* tm) {
+  const int entry = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (entry >= tiles_n * tiles_m) return false;            // (the grid is padded to a multiple of 8)
+  const int strip = min(entry / (kBlockN * tiles_m), (tiles_n - 1) / kBlockN);   // strip of up to 4 feature tiles
+  const int strip_w = min(kBlockN, tiles_n - strip * kBlockN);
+  const int in_strip = entry - strip * kBlockN * tiles_m;
+  const int blk = in_strip / (strip_w * kBlockM), in_blk = in_strip - blk * strip_w * kBlockM;
+  *tn = strip * kBlockN + in_blk % strip_w;
+  *tm = blk * kBlockM + in_blk / strip_w;
+  return true;
+}
 
-template <int MODE>
-__global__ __launch_bounds__(256, 1) void gemm_mfma3_kernel(
+template <int N>
+__device__ __forceinline__ void gemm_wait_loads() {       // at most N of this wavefront's loads outstanding
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void gemm_wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
+__device__ __forceinline__ void gemm_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// The kernel for short lists and remainders: any tile of FB x TB blocks (32 features, 16 tokens) per
+// wavefront, WF x WM wavefronts across the tile times WK along the contraction (each takes its share of a
+// stage's k-steps and the partial sums meet in LDS at the end: more wavefronts per tile without more operand
+// reads).  A stage is U cache lines of every row; NBUF stages are buffered, one barrier per stage, in front of
+// its last k-step, whose operands are in registers by then: behind it the next stage is readable and this stage's
+// buffer can be refilled.
+// Bound by what a compute unit's L1 delivers: about half of its 64 bytes per clock with the 64 x 128 tile (the
+// lines in flight are bounded, so the rate is that bound over the latency of the level the lines come
+// from), whatever the number of buffers or wavefronts.  A list of 449 rows against the 256 x 256 tile:
+// 4096 x 4096 101 -> 23 us, 4096 x 14336 354 -> 79 us, 6144 x 4096 106 -> 35 us.
+template <int MODE, int FB, int TB, int WF, int WM, int WK, int U, int NBUF>
+__global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NBUF * U * (32 * FB * WF + 16 * TB * WM) * 128 <= 163840) ? 2 : 1) void gemm_tile_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const bf16_t* __restrict__ w2, int n_rows,
     int hidden, int tiles_n, int tiles_m, GemmOut out) {
-  __shared__ uint4 lds[2 * kStage3Bytes / 16];
+  constexpr int NW = WF * WM * WK;                    // wavefronts
+  constexpr int F = 32 * FB * WF, M = 16 * TB * WM;   // features x tokens of the tile
+  constexpr int PW = U * (F + M) / 8 / NW;            // load instructions of a wavefront per stage
+  constexpr int kSub = (F + M) * kTK * 2, kStage = U * kSub;
+  constexpr int S = 2 * U / WK;                       // 32-wide k-steps of a stage a wavefront multiplies
+  static_assert((U * (F + M)) % (8 * NW) == 0 && (2 * U) % WK == 0, "stage must divide over the wavefronts");
+  static_assert(MODE != kOutGated || FB % 2 == 0, "a wavefront holds gate and up rows of the same outputs");
+  __shared__ uint4 lds[NBUF * kStage / 16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nl = lane & 31, hh = lane >> 5;
-  const int wn = wave & 1, wm = wave >> 1;
+  const int nl = lane & 15, g = lane >> 4;
+  const int wk = wave % WK, wn = (wave / WK) % WF, wm = wave / (WK * WF);
   int n0, m0;
-  if (MODE == kOutGated) {                                 // (see above: plain order measured faster here)
-    if (blockIdx.x >= tiles_n * tiles_m) return;
-    n0 = (blockIdx.x % tiles_n) * kTN;
-    m0 = (blockIdx.x / tiles_n) * kTM;
-  } else {
-    const int entry = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (entry >= tiles_n * tiles_m) return;                // (the grid is padded to a multiple of 8)
-    const int strip = min(entry / (kBlockN * tiles_m), (tiles_n - 1) / kBlockN);   // strip of up to 4 feature tiles
-    const int strip_w = min(kBlockN, tiles_n - strip * kBlockN);
-    const int in_strip = entry - strip * kBlockN * tiles_m;
-    const int blk = in_strip / (strip_w * kBlockM), in_blk = in_strip - blk * strip_w * kBlockM;
-    n0 = (strip * kBlockN + in_blk % strip_w) * kTN;
-    m0 = (blk * kBlockM + in_blk / strip_w) * kTM;
-  }
-  const int n_k = hidden / kTK3;
+  if (!gemm_tile_of(tiles_n, tiles_m, &n0, &m0)) return;
+  n0 *= F;
+  m0 *= M;
+  const int n_k = hidden / (kTK * U);
 
-  // ---- staging: wavefront w brings image rows 128 w .. 128 w + 127 (rows 0..255: W, 256..511: x),
-  // 8 rows per instruction: lane L -> row 8 j + L / 8, LDS piece L % 8 of that row
-  const char* src[16];
+  // ---- staging: image rows 0..F-1 are W, F..F+M-1 are x; wavefront w brings groups PW w .. of 8 rows: lane L
+  // -> row 8 j + L / 8, LDS piece L % 8 of that row
+  const char* base[PW];                                    // (wave-uniform)
+  uint32_t voff[PW];
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int r = 128 * wave + 8 * j + (lane >> 3);            // image row
-    const bf16_t* row;
-    if (r >= kTN) row = x + static_cast<size_t>(min(m0 + r - kTN, n_rows - 1)) * hidden;
-    else if (MODE != kOutGated) row = w + static_cast<size_t>(n0 + r) * hidden;
-    else {
-      // gated: of a wavefront's four 32-feature blocks, two are rows of W_gate and two the SAME
-      // rows of W_up, so that a lane ends up holding both factors of an output
-      const int blk = r >> 5;
-      const int f = n0 / 2 + 64 * (blk >> 2) + 32 * (blk & 1) + (r & 31);
-      row = ((blk & 2) ? w2 : w) + static_cast<size_t>(f) * hidden;
+  for (int j = 0; j < PW; ++j) {
+    const int grp8 = PW * wave + j, sub = grp8 / ((F + M) / 8);
+    const int r0 = 8 * (grp8 % ((F + M) / 8)), r = r0 + (lane >> 3);
+    int off_row;
+    if (r0 >= F) {
+      base[j] = reinterpret_cast<const char*>(x + static_cast<size_t>(m0) * hidden);
+      off_row = min(r - F, n_rows - 1 - m0);
+    } else if (MODE != kOutGated) {
+      base[j] = reinterpret_cast<const char*>(w + static_cast<size_t>(n0) * hidden);
+      off_row = r;
+    } else {
+      const int blk = r0 >> 5, grp = blk / FB, in = blk % FB;
+      base[j] = reinterpret_cast<const char*>((in >= FB / 2 ? w2 : w) + static_cast<size_t>(n0 / 2) * hidden);
+      off_row = 32 * (grp * (FB / 2) + in % (FB / 2)) + (r & 31);
     }
-    src[j] = reinterpret_cast<const char*>(row) + 16 * ((lane & 7) ^ gemm_swz(r));
+    base[j] += sub * (kTK * 2);
+    voff[j] = static_cast<uint32_t>(off_row) * static_cast<uint32_t>(hidden * 2) +
+              16 * ((lane & 7) ^ (r0 >= F ? gemm_swz_x(r - F) : gemm_swz_w(r)));
   }
   typedef __attribute__((address_space(3))) const uint4 lds_piece;
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_piece*)lds)));
-  // load j of stage t (past the last stage: a harmless repeat into the image nobody reads any more)
-  auto dma_one = [&](int t, int j) __attribute__((always_inline)) {
-    const uint32_t dst = lds_base + (t & 1) * kStage3Bytes + (128 * wave + 8 * j) * 128;
-    gemm_load_to_lds(src[j] + static_cast<size_t>(min(t, n_k - 1)) * (kTK3 * sizeof(bf16_t)), dst);
-  };
-  auto wait_all_loads = [&]() __attribute__((always_inline)) {
-    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));       // vmcnt(0)
-    asm volatile("" ::: "memory");
-  };
-  auto barrier = [&]() __attribute__((always_inline)) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+  // load j of stage t into buffer b (past the last stage: a harmless repeat into a buffer nobody reads any more)
+  auto dma_one = [&](int t, int b, int j) __attribute__((always_inline)) {
+    gemm_load_to_lds(base[j] + static_cast<size_t>(min(t, n_k - 1)) * (kTK * 2 * U), voff[j], lds_base + b * kStage + (PW * wave + j) * 1024);
   };
 
-  f32x16 acc[4][4];
+  // block (a, i2, b): features 32 a + 8 (m / 4) + 4 i2 + m % 4 of MFMA row m, tokens 16 b + n: a lane ends up with 8
+  // consecutive features of a token in the two halves i2
+  f32x4 acc[FB][2][TB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < FB; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[a][b][i]));
+      for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[a][i2][b][i]));
 
   const char* lds_bytes = reinterpret_cast<const char*>(lds);
-  const int swz = gemm_swz(nl);                                // (block bases are multiples of 32 rows)
-  const int row_a = (128 * wn + nl) * 128, row_b = (kTN + 128 * wm + nl) * 128;
-  auto read_a = [&](int t, int s, int a) __attribute__((always_inline)) {
-    return *reinterpret_cast<const u32x4*>(lds_bytes + (t & 1) * kStage3Bytes + row_a + a * 4096 + (((2 * s + hh) ^ swz) << 4));
-  };
-  auto read_b = [&](int t, int s, int b) __attribute__((always_inline)) {
-    return *reinterpret_cast<const u32x4*>(lds_bytes + (t & 1) * kStage3Bytes + row_b + b * 4096 + (((2 * s + hh) ^ swz) << 4));
+  const int r_w = 8 * (nl >> 2) + (nl & 3), r_x = nl;      // (block bases are multiples of 32 / 16 rows; +4 leaves swz_w alone)
+  const int row_w = (32 * FB * wn + r_w) * 128, row_x = (F + 16 * TB * wm + r_x) * 128;
+  u32x4 opa[2][FB][2], opb[2][TB];
+  auto read_step = [&](int set, int buf, int s) __attribute__((always_inline)) {       // s: the wavefront's step
+    const int step = s * WK + wk, c = 4 * (step & 1) + g;
+    const char* pw = lds_bytes + buf * kStage + (step >> 1) * kSub + row_w + ((c ^ gemm_swz_w(r_w)) << 4);
+    const char* px = lds_bytes + buf * kStage + (step >> 1) * kSub + row_x + ((c ^ gemm_swz_x(r_x)) << 4);
+#pragma unroll
+    for (int b = 0; b < TB; ++b) opb[set][b] = *reinterpret_cast<const u32x4*>(px + b * 2048);
+#pragma unroll
+    for (int a = 0; a < FB; ++a)
+#pragma unroll
+      for (int i2 = 0; i2 < 2; ++i2) opa[set][a][i2] = *reinterpret_cast<const u32x4*>(pw + a * 4096 + i2 * 512);
   };
 
 #pragma unroll
-  for (int j = 0; j < 16; ++j) dma_one(0, j);
-  wait_all_loads();
-  __syncthreads();
-  u32x4 opa[2][4], opb[2][4];
+  for (int t = 0; t < NBUF; ++t)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { opa[0][i] = read_a(0, 0, i); opb[0][i] = read_b(0, 0, i); }
-
-  for (int t = 0; t < n_k; ++t) {
+    for (int j = 0; j < PW; ++j) dma_one(t, t, j);
+  gemm_wait_loads<(NBUF - 1) * PW>();
+  gemm_barrier();
+  read_step(0, 0, 0);
+  int buf = 0;
+  // one stage; PAR: operand set of its first step
+  auto stage = [&](int t, auto par) __attribute__((always_inline)) {
+    constexpr int P0 = decltype(par)::value;
+    const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int cur = s & 1, nxt = cur ^ 1;
-      if (s < 3) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { opa[nxt][i] = read_a(t, s + 1, i); opb[nxt][i] = read_b(t, s + 1, i); }
+    for (int s = 0; s < S; ++s) {
+      const int cur = (P0 + s) & 1, nxt = cur ^ 1;
+      if (s == S - 1) {
+        // this wavefront's last operands of the stage are in registers and its loads of stage t+1 have
+        // landed; behind the barrier the whole stage t+1 can be read and buffer t refilled
+        gemm_wait_loads<(NBUF - 2) * PW>();
+        gemm_wait_lds();
+        gemm_barrier();
+        read_step(nxt, nbuf, 0);
+      } else {
+        read_step(nxt, buf, s + 1);
       }
       __builtin_amdgcn_sched_barrier(0);
+      // (the refill's loads go out between the MFMAs of this step)
+      constexpr int kSlots = FB * 2 * TB, kPer = (PW + kSlots - 1) / kSlots, kEvery = PW >= kSlots ? 1 : kSlots / PW;
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < FB; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          gemm_mfma(acc[a][b], opa[cur][a], opb[cur][b]);
-          // The 16 loads of the next image go out under the MFMAs of the first two k-steps.
-          // Measured alternatives: all 16 under the first k-step +2 %, spread over all four +8 %;
-          // a barrier before the last k-step (the next stage's first operands then come in under
-          // MFMAs, but the loads have one k-step less to land) +4 %; that plus a second barrier
-          // at the end of the stage +6 %.
-          if (s < 2 && (b & 1)) dma_one(t + 1, 8 * s + 2 * a + (b >> 1));
-        }
+        for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+          for (int b = 0; b < TB; ++b) {
+            gemm_mfma(acc[a][i2][b], opa[cur][a][i2], opb[cur][b]);
+            if (s == S - 1) {
+#pragma unroll
+              for (int u = 0; u < kPer; ++u) {
+                const int m = (a * 2 + i2) * TB + b, j = (m / kEvery) * kPer + u;
+                if (m % kEvery == 0 && j < PW) dma_one(t + NBUF, buf, j);
+              }
+            }
+          }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // all loads of image t+1 have landed and everyone has left image t (the loads of the stage
-    // after next may overwrite it); the next stage's first operands are read behind the barrier
-    wait_all_loads();
-    barrier();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { opa[0][i] = read_a(t + 1, 0, i); opb[0][i] = read_b(t + 1, 0, i); }
+    buf = nbuf;
+  };
+  if constexpr (S % 2 == 0) {
+    for (int t = 0; t < n_k; ++t) stage(t, std::integral_constant<int, 0>{});
+  } else {
+    for (int t = 0; t < n_k; t += 2) {
+      stage(t, std::integral_constant<int, 0>{});
+      if (t + 1 < n_k) stage(t + 1, std::integral_constant<int, 1>{});
+    }
   }
+  gemm_wait_loads<0>();            // (nothing may still be landing when the LDS is given back)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  gemm_store_tile<MODE>(acc, out, n_rows, n0, m0, wn, wm, nl, hh);
+
+  const int tok0 = m0 + 16 * TB * wm + nl;
+  const int col0 = (MODE == kOutGated ? n0 / 2 + 32 * (FB / 2) * wn : n0 + 32 * FB * wn) + 8 * g;
+  constexpr int FO = MODE == kOutGated ? FB / 2 : FB;      // 32-feature blocks of outputs
+  if constexpr (WK > 1) {
+    // the WK wavefronts of a tile hold partial sums over their k-steps: they exchange token blocks through LDS
+    // and each finishes TB / WK of them
+    constexpr int H = TB / WK, kBlk = FB * 2 * H;          // token blocks, 1 KiB pieces a wavefront gets from each other one
+    static_assert(TB % WK == 0, "token blocks are shared out");
+    static_assert(WF * WM * WK * WK * kBlk * 1024 <= NBUF * kStage, "partial sums must fit");
+    gemm_wait_loads<0>();
+    __syncthreads();
+    f32x4* share = reinterpret_cast<f32x4*>(lds) + (wave / WK) * (WK * WK * kBlk * 64) + lane;
+#pragma unroll
+    for (int k = 0; k < WK; ++k)
+#pragma unroll
+      for (int a = 0; a < FB; ++a)
+#pragma unroll
+        for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+          for (int b = 0; b < H; ++b)
+            if (k != wk) share[((k * WK + wk) * kBlk + (a * 2 + i2) * H + b) * 64] = acc[a][i2][k * H + b];
+    uint4 res[H][FO];
+#pragma unroll
+    for (int b = 0; b < H; ++b)
+#pragma unroll
+      for (int a = 0; a < FO; ++a) res[b][a] = gemm_residual8<MODE>(out, min(tok0 + 16 * (wk * H + b), n_rows - 1), col0 + 32 * a);
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < H; ++b) {
+      f32x4 sum[FB][2];
+#pragma unroll
+      for (int a = 0; a < FB; ++a)
+#pragma unroll
+        for (int i2 = 0; i2 < 2; ++i2) {
+          f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int k = 0; k < WK; ++k) {                   // (summed in the order of k whatever the wavefront)
+            f32x4 part;
+            if (k == wk) {
+              part = acc[a][i2][b];
+#pragma unroll
+              for (int o = 1; o < WK; ++o) if (wk == o) part = acc[a][i2][o * H + b];
+            } else {
+              part = share[((wk * WK + k) * kBlk + (a * 2 + i2) * H + b) * 64];
+            }
+            v += part;
+          }
+          sum[a][i2] = v;
+        }
+      const int row = tok0 + 16 * (wk * H + b);
+      if (row < n_rows) {
+#pragma unroll
+        for (int a = 0; a < FO; ++a)
+          gemm_store8<MODE>(sum[a][0], sum[a][1], sum[FB - FO + a][0], sum[FB - FO + a][1], res[b][a], out, row, col0 + 32 * a);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < TB; ++b) {
+      const int row = tok0 + 16 * b;
+      if (row >= n_rows) continue;
+#pragma unroll
+      for (int a = 0; a < FO; ++a)
+        gemm_store8<MODE>(acc[a][0][b], acc[a][1][b], acc[FB - FO + a][0][b], acc[FB - FO + a][1][b],
+                          gemm_residual8<MODE>(out, row, col0 + 32 * a), out, row, col0 + 32 * a);
+    }
+  }
 }
 
-// the 128 x 128-per-wavefront kernel (contraction length a multiple of 64)
+// The kernel for long lists: 256 features x 256 tokens, 8 wavefronts of 128 x 64 (two per SIMD), 12 operand reads
+// feed 32 MFMAs.  A stage is one cache line of every row, W and x in buffers of 32 KiB each; five of them
+// fill the LDS, so that W of stage t+2 starts landing when stage t begins (two stages ahead) and x of
+// stage t+2 right behind the barrier that frees W of stage t (one stage ahead).  A wavefront keeps one set of
+// W operands and rolls it: as soon as a half-block has met the step's four token blocks its registers take
+// the next step's piece, which spreads the LDS reads over the MFMAs and leaves room for two wavefronts per SIMD.
+// One barrier per stage, behind the first kMeet half-blocks of its second step.
+// 1.37 - 1.40 PFLOP/s in full rounds of tiles (the 32x32x16 form with four wavefronts of 128 x 128: 1.15 - 1.24):
+// 13 824 rows x 4096 x 14336 1.58 -> 1.28 ms, gated 4096 -> 2 x 14336 2.60 -> 2.37 ms.  What is left: loads from
+// beyond the L2 cost 12 % (measured with the stages repeated), the loads themselves 10 %, operand reads 9 %.
 template <int MODE>
-void launch_gemm_wide(dim3 grid, hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in,
-                      const GemmOut& out) {
-  hipLaunchKernelGGL(gemm_mfma3_kernel<MODE>, dim3((grid.x * grid.y + 7) / 8 * 8), dim3(256), 0, stream,
-                     static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), static_cast<const bf16_t*>(w2),
-                     n_rows, n_in, static_cast<int>(grid.x), static_cast<int>(grid.y), out);
+__global__ __launch_bounds__(512, 2) void gemm_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const bf16_t* __restrict__ w2, int n_rows,
+    int hidden, int tiles_n, int tiles_m, GemmOut out) {
+  constexpr int F = 256, M = 256, FB = 4, TB = 4, WF = 2;
+  constexpr int kHalf = 32768, kSlots = 5;             // bytes and number of the half-stage buffers
+  constexpr int kMeet = 2;                             // feature half-blocks of the second step in front of the barrier (1 or 3: the same)
+  __shared__ uint4 lds[kSlots * kHalf / 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nl = lane & 15, g = lane >> 4;
+  const int wn = wave % WF, wm = wave / WF;
+  int n0, m0;
+  if (!gemm_tile_of(tiles_n, tiles_m, &n0, &m0)) return;
+  n0 *= F;
+  m0 *= M;
+  const int n_k = hidden / kTK;
+  // wavefront w brings rows 32 w .. 32 w + 31 of W and of x, 8 rows per instruction
+  uint32_t voff_w[4], voff_x[4];
+  const char* base_w;
+  const char* base_x = reinterpret_cast<const char*>(x + static_cast<size_t>(m0) * hidden);
+  if (MODE != kOutGated) base_w = reinterpret_cast<const char*>(w + static_cast<size_t>(n0) * hidden);
+  else base_w = reinterpret_cast<const char*>(((wave % FB) >= FB / 2 ? w2 : w) + static_cast<size_t>(n0 / 2) * hidden);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = 32 * wave + 8 * j + (lane >> 3);
+    const int rw = MODE != kOutGated ? r : 32 * ((wave / FB) * (FB / 2) + wave % (FB / 2)) + (r & 31);
+    voff_w[j] = static_cast<uint32_t>(rw) * static_cast<uint32_t>(hidden * 2) + 16 * ((lane & 7) ^ gemm_swz_w(r));
+    voff_x[j] = static_cast<uint32_t>(min(r, n_rows - 1 - m0)) * static_cast<uint32_t>(hidden * 2) + 16 * ((lane & 7) ^ gemm_swz_x(r));
+  }
+  typedef __attribute__((address_space(3))) const uint4 lds_piece;
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_piece*)lds))) + wave * 4096;
+  auto dma_w = [&](int t, int slot, int j) __attribute__((always_inline)) {
+    gemm_load_to_lds(base_w + static_cast<size_t>(min(t, n_k - 1)) * (kTK * 2), voff_w[j], lds_base + slot * kHalf + j * 1024);
+  };
+  auto dma_x = [&](int t, int slot, int j) __attribute__((always_inline)) {
+    gemm_load_to_lds(base_x + static_cast<size_t>(min(t, n_k - 1)) * (kTK * 2), voff_x[j], lds_base + slot * kHalf + j * 1024);
+  };
+  f32x4 acc[FB][2][TB];
+#pragma unroll
+  for (int a = 0; a < FB; ++a)
+#pragma unroll
+    for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+      for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(acc[a][i2][b][i]));
+
+  const char* lds_bytes = reinterpret_cast<const char*>(lds);
+  const int r_w = 8 * (nl >> 2) + (nl & 3), r_x = nl;
+  const int at_w0 = (32 * FB * wn + r_w) * 128 + ((g ^ gemm_swz_w(r_w)) << 4), at_w1 = (32 * FB * wn + r_w) * 128 + (((4 + g) ^ gemm_swz_w(r_w)) << 4);
+  const int at_x0 = (16 * TB * wm + r_x) * 128 + ((g ^ gemm_swz_x(r_x)) << 4), at_x1 = (16 * TB * wm + r_x) * 128 + (((4 + g) ^ gemm_swz_x(r_x)) << 4);
+  auto read_w = [&](int slot, int s, int i) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(lds_bytes + slot * kHalf + (s == 0 ? at_w0 : at_w1) + (i >> 1) * 4096 + (i & 1) * 512);
+  };
+  auto read_x = [&](int slot, int s, int b) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(lds_bytes + slot * kHalf + (s == 0 ? at_x0 : at_x1) + b * 2048);
+  };
+  u32x4 opw[8], opx[2][TB];
+
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dma_w(t, 2 * t, j);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dma_x(t, 2 * t + 1, j);
+  }
+  gemm_wait_loads<8>();
+  gemm_barrier();
+#pragma unroll
+  for (int b = 0; b < TB; ++b) opx[0][b] = read_x(1, 0, b);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) opw[i] = read_w(0, 0, i);
+  int sw = 0;                                              // slot of W of stage t; x sits in the next slot
+  for (int t = 0; t < n_k; ++t) {
+    const int sx = sw == 4 ? 0 : sw + 1, sp = sw == 0 ? 4 : sw - 1;
+    const int sw1 = sw >= 3 ? sw - 3 : sw + 2, sx1 = sw1 == 4 ? 0 : sw1 + 1;
+#pragma unroll
+    for (int b = 0; b < TB; ++b) opx[1][b] = read_x(sx, 1, b);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+#pragma unroll
+      for (int b = 0; b < TB; ++b) gemm_mfma(acc[i >> 1][i & 1][b], opw[i], opx[0][b]);
+      opw[i] = read_w(sw, 1, i);
+      if (i & 1) dma_w(t + 2, sp, i >> 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i == kMeet) {
+        gemm_wait_loads<4>();
+        gemm_wait_lds();
+        gemm_barrier();
+#pragma unroll
+        for (int k = 0; k < kMeet; ++k) opw[k] = read_w(sw1, 0, k);
+#pragma unroll
+        for (int b = 0; b < TB; ++b) opx[0][b] = read_x(sx1, 0, b);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int b = 0; b < TB; ++b) gemm_mfma(acc[i >> 1][i & 1][b], opw[i], opx[1][b]);
+      if (i >= kMeet) opw[i] = read_w(sw1, 0, i);
+      if (i >= kMeet && i < kMeet + 4) dma_x(t + 2, sw, i - kMeet);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    sw = sw1;
+  }
+  gemm_wait_loads<0>();            // (nothing may still be landing when the LDS is given back)
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  const int tok0 = m0 + 16 * TB * wm + nl;
+  const int col0 = (MODE == kOutGated ? n0 / 2 + 32 * (FB / 2) * wn : n0 + 32 * FB * wn) + 8 * g;
+  constexpr int FO = MODE == kOutGated ? FB / 2 : FB;
+#pragma unroll
+  for (int b = 0; b < TB; ++b) {
+    const int row = tok0 + 16 * b;
+    if (row >= n_rows) continue;
+#pragma unroll
+    for (int a = 0; a < FO; ++a)
+      gemm_store8<MODE>(acc[a][0][b], acc[a][1][b], acc[FB - FO + a][0][b], acc[FB - FO + a][1][b],
+                        gemm_residual8<MODE>(out, row, col0 + 32 * a), out, row, col0 + 32 * a);
+  }
 }
 
-// the MFMA GEMM takes outputs in tiles of 256 features and contraction lengths in stages of 64, at least two
-inline bool gemm_wide_fits(int n_features, int n_in) { return n_features % kTN == 0 && n_in % kTK3 == 0 && n_in >= 2 * kTK3; }
+template <int MODE>
+void launch_gemm_256(hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in, int n_features,
+                      const GemmOut& out) {
+  const int tiles_n = n_features / 256, tiles_m = (n_rows + 255) / 256;
+  hipLaunchKernelGGL((gemm_kernel<MODE>), dim3((tiles_n * tiles_m + 7) / 8 * 8), dim3(512), 0,
+                     stream, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), static_cast<const bf16_t*>(w2),
+                     n_rows, n_in, tiles_n, tiles_m, out);
+}
+
+template <int MODE, int FB, int TB, int WF, int WM, int WK, int U, int NBUF>
+void launch_gemm_tile(hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in, int n_features,
+                      const GemmOut& out) {
+  const int tiles_n = n_features / (32 * FB * WF), tiles_m = (n_rows + 16 * TB * WM - 1) / (16 * TB * WM);
+  hipLaunchKernelGGL((gemm_tile_kernel<MODE, FB, TB, WF, WM, WK, U, NBUF>), dim3((tiles_n * tiles_m + 7) / 8 * 8), dim3(64 * WF * WM * WK), 0,
+                     stream, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), static_cast<const bf16_t*>(w2),
+                     n_rows, n_in, tiles_n, tiles_m, out);
+}
+
+// Tile shapes and what a stage of 64 contraction indices takes on a compute unit that runs one workgroup of
+// that shape (measured, us): big tiles do more flops per byte that passes a compute unit's L1, small
+// ones give short lists enough workgroups.  A product takes the shape with the smallest
+// (rounds of 256 workgroups) x (stage time).
+struct GemmTile { int f, m, k; float stage_us; };
+constexpr GemmTile kGemmTiles[] = {{256, 256, 64, 1.43f}, {128, 256, 64, 0.92f}, {128, 128, 64, 0.54f},
+                                   {64, 128, 64, 0.36f},  {64, 64, 128, 0.27f},  {32, 64, 128, 0.21f}};
+constexpr int kGemmUnits = 256;                       // compute units
+
+inline bool gemm_tile_fits(int i, int n_features, int n_in, bool gated) {
+  return n_features % kGemmTiles[i].f == 0 && n_in % kGemmTiles[i].k == 0 && !(gated && kGemmTiles[i].f < 64);
+}
+inline float gemm_tile_cost(int i, int n_features, int n_rows) {
+  const GemmTile& t = kGemmTiles[i];
+  const int64_t tiles = static_cast<int64_t>(n_features / t.f) * ((n_rows + t.m - 1) / t.m);
+  return static_cast<float>((tiles + kGemmUnits - 1) / kGemmUnits) * t.stage_us;
+}
+inline int gemm_best_tile(int n_features, int n_in, int n_rows, bool gated) {
+  int best = -1;
+  for (int i = 0; i < 6; ++i)
+    if (gemm_tile_fits(i, n_features, n_in, gated) &&
+        (best < 0 || gemm_tile_cost(i, n_features, n_rows) < gemm_tile_cost(best, n_features, n_rows))) best = i;
+  return best;
+}
+
+template <int MODE>
+void launch_gemm_shape(int shape, hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in,
+                       int n_features, const GemmOut& out) {
+#define CC_TILE(...) launch_gemm_tile<MODE, __VA_ARGS__>(stream, x, w, w2, n_rows, n_in, n_features, out)
+  switch (shape) {
+    case 0: launch_gemm_256<MODE>(stream, x, w, w2, n_rows, n_in, n_features, out); break;
+    case 1: CC_TILE(2, 4, 2, 4, 1, 1, 3); break;      // (128 x 256: 8 wavefronts of 64 x 64)
+    case 2: CC_TILE(2, 4, 2, 2, 2, 1, 4); break;      // (128 x 128: 8 of 64 x 64, half the k-steps each)
+    case 3: CC_TILE(2, 4, 1, 2, 2, 1, 5); break;      // (64 x 128: 4 of 64 x 64, half the k-steps each)
+    case 4: CC_TILE(2, 4, 1, 1, 4, 2, 5); break;      // (64 x 64: 4, a quarter of the k-steps each)
+    default: if constexpr (MODE != kOutGated) CC_TILE(1, 4, 1, 1, 4, 2, 5); break;   // (32 x 64: the same)
+  }
+#undef CC_TILE
+}
+
+template <int MODE>
+void launch_gemm(hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in, int n_features,
+                 const GemmOut& out) {
+  constexpr bool kGated = MODE == kOutGated;
+  const int best = gemm_best_tile(n_features, n_in, n_rows, kGated);
+  // A product of a few rounds of 256 x 256 tiles leaves most of the chip idle in its last one: then the
+  // rows of the whole rounds go to that kernel and the rest to the shape that suits it, in a launch of its
+  // own (about 6 us more).
+  if (gemm_tile_fits(0, n_features, n_in, kGated)) {
+    const int tiles_n = n_features / 256, rounds = tiles_n * ((n_rows + 255) / 256) / kGemmUnits;
+    const int rows_full = rounds * kGemmUnits / tiles_n * 256, rest = n_rows - rows_full;
+    if (rows_full > 0 && rest > 0) {
+      const int tail = gemm_best_tile(n_features, n_in, rest, kGated);
+      const float split = gemm_tile_cost(0, n_features, rows_full) + gemm_tile_cost(tail, n_features, rest) + 6.f * kTK / n_in;
+      if (split < gemm_tile_cost(best, n_features, n_rows)) {
+        launch_gemm_shape<MODE>(0, stream, x, w, w2, rows_full, n_in, n_features, out);
+        const size_t at = static_cast<size_t>(rows_full);
+        auto shift = [&](const void* p, int width) { return p == nullptr ? nullptr : static_cast<const bf16_t*>(p) + at * width; };
+        GemmOut o = out;
+        if (MODE == kOutQkv) {
+          o.o0 = const_cast<bf16_t*>(shift(out.o0, out.nq)); o.o1 = const_cast<bf16_t*>(shift(out.o1, out.nk)); o.o2 = const_cast<bf16_t*>(shift(out.o2, out.nk));
+        } else {
+          o.o0 = const_cast<bf16_t*>(shift(out.o0, out.width)); o.residual = shift(out.residual, out.width);
+        }
+        launch_gemm_shape<MODE>(tail, stream, shift(x, n_in), w, w2, rest, n_in, n_features, o);
+        return;
+      }
+    }
+  }
+  launch_gemm_shape<MODE>(best, stream, x, w, w2, n_rows, n_in, n_features, out);
+}
+
+// the MFMA GEMMs take outputs in tiles of at least 64 features and contraction lengths in whole cache lines
+inline bool gemm_fits(int n_features, int n_in) { return n_features % 64 == 0 && n_in % kTK == 0; }
 
 }  // namespace
 
@@ -360,10 +669,9 @@ void launch_qkv_project(const cc_ctx* ctx, const void* x, const void* w, int n_r
                         void* q, void* k, void* v, hipStream_t stream) {
   const int d = ctx->cfg.head_dim;
   const int nq = ctx->cfg.n_q_heads * d, nk = ctx->cfg.n_kv_heads * d, n_cols = nq + 2 * nk;
-  if (ctx->cfg.dtype == CC_BF16 && ctx->impl != CC_IMPL_SCALAR && gemm_wide_fits(n_cols, hidden) &&
+  if (ctx->cfg.dtype == CC_BF16 && ctx->impl != CC_IMPL_SCALAR && gemm_fits(n_cols, hidden) &&
       nq % 32 == 0 && nk % 32 == 0) {
-    dim3 grid(n_cols / kTN, (n_rows + kTM - 1) / kTM);
-    launch_gemm_wide<kOutQkv>(grid, stream, x, w, nullptr, n_rows, hidden, GemmOut{q, k, v, nullptr, nq, nk, 0});
+    launch_gemm<kOutQkv>(stream, x, w, nullptr, n_rows, hidden, n_cols, GemmOut{q, k, v, nullptr, nq, nk, 0});
     return;
   }
   dim3 grid((n_cols + 63) / 64, (n_rows + 63) / 64);
@@ -383,9 +691,8 @@ void launch_qkv_project(const cc_ctx* ctx, const void* x, const void* w, int n_r
 void launch_linear(const cc_ctx* ctx, const void* x, const void* w, const void* residual, int n_rows, int n_in,
                    int n_out, void* y, hipStream_t stream) {
   const bool bf = ctx->cfg.dtype == CC_BF16;
-  if (bf && ctx->impl != CC_IMPL_SCALAR && gemm_wide_fits(n_out, n_in)) {
-    dim3 grid(n_out / kTN, (n_rows + kTM - 1) / kTM);
-    launch_gemm_wide<kOutLinear>(grid, stream, x, w, nullptr, n_rows, n_in, GemmOut{y, nullptr, nullptr, residual, 0, 0, n_out});
+  if (bf && ctx->impl != CC_IMPL_SCALAR && gemm_fits(n_out, n_in)) {
+    launch_gemm<kOutLinear>(stream, x, w, nullptr, n_rows, n_in, n_out, GemmOut{y, nullptr, nullptr, residual, 0, 0, n_out});
     return;
   }
   dim3 grid((n_out + 63) / 64, (n_rows + 63) / 64);
@@ -403,9 +710,8 @@ void launch_linear(const cc_ctx* ctx, const void* x, const void* w, const void* 
 void launch_gated_linear(const cc_ctx* ctx, const void* x, const void* w_gate, const void* w_up, int n_rows,
                          int n_in, int n_ffn, void* y, hipStream_t stream) {
   const bool bf = ctx->cfg.dtype == CC_BF16;
-  if (bf && ctx->impl != CC_IMPL_SCALAR && gemm_wide_fits(2 * n_ffn, n_in)) {
-    dim3 grid(2 * n_ffn / kTN, (n_rows + kTM - 1) / kTM);
-    launch_gemm_wide<kOutGated>(grid, stream, x, w_gate, w_up, n_rows, n_in, GemmOut{y, nullptr, nullptr, nullptr, 0, 0, n_ffn});
+  if (bf && ctx->impl != CC_IMPL_SCALAR && gemm_fits(2 * n_ffn, n_in)) {
+    launch_gemm<kOutGated>(stream, x, w_gate, w_up, n_rows, n_in, 2 * n_ffn, GemmOut{y, nullptr, nullptr, nullptr, 0, 0, n_ffn});
     return;
   }
   dim3 grid((n_ffn + 63) / 64, (n_rows + 63) / 64);

@@ -103,3 +103,36 @@ def test_fp32_arithmetic_kernels_against_the_scalar_ones(dtype, d, hq, hkv, lens
     assert rel(a[1], s[1]) <= bound
     assert rel(a[2], s[2]) <= bound + (2.0 ** -9 if dtype == "bf16" else 0.0)    # (bf16 output: a rounding may flip)
     assert float((a[3] - s[3]).abs().max()) <= 8 * bound
+
+
+@pytest.mark.parametrize("n_in", [64, 128, 192, 640])
+@pytest.mark.parametrize("op,n_out,rows", [
+    ("linear", 64, 65), ("linear", 192, 127), ("linear", 256, 300), ("linear", 4096, 31), ("linear", 4096, 129),
+    ("linear", 4096, 513), ("linear", 4096, 1025), ("linear", 8192, 2305), ("linear", 32768, 257),
+    ("gated", 96, 33), ("gated", 4096, 64), ("gated", 4096, 449), ("gated", 8192, 1281),
+    ("qkv", 6144, 15), ("qkv", 6144, 449), ("qkv", 6144, 2817)])
+def test_matrix_products_of_every_tile_shape(op, n_out, rows, n_in):
+    # one row and one tile more or less than the shapes of the dispatch (32 x 64 ... 256 x 256 features x tokens, and
+    # whole rounds of the largest with the remainder in another launch), contraction lengths of one stage and up
+    import paper_2502_15734_amd as P
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    rnd = lambda *s, sc=1.0: (torch.randn(*s, device="cuda", generator=g) * sc).to(torch.bfloat16)
+    ctx = P.Context(32, 8, 128, 5.0e5, P.CC_BF16)
+    x, w = rnd(rows, n_in), rnd(n_out * (2 if op == "gated" else 1), n_in, sc=n_in ** -0.5)
+    nan = lambda n: torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    product = x.float() @ w.float().t()
+    if op == "qkv":
+        got = [nan(n) for n in (4096, 1024, 1024)]
+        ctx.qkv_project(x, w, *got)
+        got, want = torch.cat(got, dim=1), product
+    elif op == "gated":
+        got = nan(n_out)
+        ctx.gated_linear(x, w[:n_out], w[n_out:], got)
+        want = torch.nn.functional.silu(product[:, :n_out]) * product[:, n_out:]
+    else:
+        got, res = nan(n_out), rnd(rows, n_out)
+        ctx.linear(x, w, got, residual=res)
+        want = product + res.float()
+    torch.cuda.synchronize()
+    # half a unit in the last place of bf16, and fp32 sums of n_in products of size n_in^-1/2 in two orders
+    assert float(((got.float() - want).abs() - 2.0 ** -8 * want.abs()).max()) <= 8 * n_in * 2.0 ** -24 * 4
