@@ -1,22 +1,23 @@
 // cc_sparse_prefill's attention for head groups that are a multiple of 4 (bf16, head_dim 128):
 // per-token form of Eq. (1); Sec. 4 "Selective Token Recomputation".
 //
-// One workgroup = 4 wavefronts = 4 query heads of one KV head x 64 query rows of the compact list;
-// a wavefront owns one head and all 64 rows (two 32-row MFMA column blocks), so every K / V operand
-// it reads from LDS feeds two MFMAs.  One wavefront per SIMD (up to 512 registers): the running
-// output (128 registers) and the rotated queries (64) sit in accumulation registers, two 32-key
-// score blocks (64), the packed probabilities (32) and the operand ring (32) in vector registers.
+// One workgroup = 8 wavefronts, two per SIMD (up to 256 registers each), in one of two forms:
+//   KS = 1: 4 query heads of one KV head x 64 query rows of the compact list; wavefront w owns head w % 4 and
+//           rows 32 (w / 4) .. + 31, and all walk the same key tiles;
+//   KS = 2: 4 query heads x 32 rows; wavefronts 0-3 walk the even key tiles, 4-7 the odd ones, and the two
+//           halves of a (head, row) meet in LDS at the end.  Twice the workgroups with half the tiles each,
+//           for grids that leave compute units idle.
+// The running output (64 registers) and the rotated queries (32) sit in accumulation registers, two 32-key
+// score blocks (32), the packed probabilities (16) and the operand ring (32) in vector registers.
+// While one wavefront of a SIMD waits (for LDS, for its exponentials - a transcendental does not run beside a
+// matrix instruction of its own wavefront) the other one keeps the matrix pipe busy.
 //
 // Orientation and key permutation are those of mfma_tile.h: S^T = K Q^T, O^T = V^T P^T with
 // v_mfma_f32_32x32x16_bf16, a lane holds one query column, P^T goes from the accumulators to
 // the second product without leaving the lane.
 //
-// A SIMD with a single wavefront issues at most one instruction of any kind every four clocks, and
-// a 32x32x16 MFMA occupies the matrix pipe for 32: the loop can keep the pipe full only if it
-// spends at most seven other instructions per MFMA.  Everything below serves that count.
-//
-// Schedule.  Keys advance in 32-key blocks b = 0, 1, 2, ... (two per 64-key tile).  The matrix pipe
-// sees   S(b+1), PV(b), S(b+2), PV(b+1), ...   16 MFMAs each, and under every MFMA one exponential
+// Schedule.  A wavefront's keys advance in 32-key blocks b = 0, 1, 2, ... (two per 64-key tile).  Its matrix
+// instructions are   S(b+1), PV(b), S(b+2), PV(b+1), ...   8 MFMAs each, and under every MFMA one exponential
 // of a block whose S is already complete: the first half of exp(b) under PV(b-1), the second half
 // under S(b+1).  Per element that is one v_exp_f32 and one add into the row sum: the reference is
 // already subtracted (it enters through the C operand of the block's first MFMA).  The row sum
@@ -26,15 +27,16 @@
 // late, in front of the next exponential, so that no instruction reads a transcendental result
 // right behind its issue.
 //
-// Softmax reference: m_ref = maximum of the row's first 32-key block, for the whole row (fp32 and
+// Softmax reference: m_ref = maximum of the row's first 32-key block (of its key stream), for the whole row (fp32 and
 // bf16 share the exponent range, so p = exp2(S - m_ref) may grow to 1e30 without loss).  Rows whose
 // sum leaves the safe range are flagged and redone by the kernel that can move its reference
 // (see the launcher).
 //
 // Staging: four tile images in LDS, filled by loads that write LDS directly (global_load_lds, 16
 // bytes per lane: lane L of an instruction fills piece base + L, so the image layout is chosen by
-// the global address each lane is given).  Wavefront w brings page w (16 tokens) of the tile, K and
-// V, each with four instructions whose addresses are one scalar base + one per-lane constant + an
+// the global address each lane is given).  KS = 1: wavefronts 0-3 bring the four K pages (16 tokens) of a tile,
+// 4-7 the four V pages; KS = 2: the four wavefronts of a key stream bring a K and a V page each of their own
+// tiles.  A page is four instructions whose addresses are one scalar base + one per-lane constant + an
 // immediate: no vector arithmetic per tile.  Image of a tile (16-byte pieces):
 //   K piece (MFMA row m of 32-key block b, k-step kk, half hh):
 //       ((b*2 + kk/4)*4 + m/8)*64 + ((kk%4)*2 + (hh ^ (m/8)%2))*8 + m%8
@@ -42,12 +44,23 @@
 //     K loads cost three times what the V loads cost for the same bytes)
 //   V piece (page pg, 32-dim group db, half hh, dim n):  1024 + (pg*4+db)*64 + hh*32 + n
 // An MFMA operand read takes contiguous runs of 128 bytes that alternate between the two halves
-// of the 256-byte bank sweep (K) or one contiguous KiB (V): no bank conflicts.  In iteration t the wavefronts read image t and (for S of
-// the next tile's first block) image t+1 and start the loads of image t+3; before the iteration's
-// barrier each wavefront waits until its loads of image t+2 have landed.  One s_barrier per tile.
+// of the 256-byte bank sweep (K) or one contiguous KiB (V): no bank conflicts.  In iteration t the wavefronts
+// read image t and (for S of the next tile's first block) image t+1.  KS = 1: they start the loads of image t+3
+// and, before the iteration's barrier, wait for their loads of image t+2; KS = 2 (two images per stream): they
+// start the loads of image t+1's successor into the image they left in the last iteration, and wait for
+// them at the iteration's end.  One s_barrier per tile.
 // Block padding: K padding never reaches a product (its S entries are masked by selection); V
 // padding would, as 0 x garbage, so the wavefront that loaded a V page blanks the page's padding
 // slots in LDS before the barrier, in a branch only a segment's last tile takes.
+//
+// What bounds it: long prompts, the two wavefronts' MFMAs and exponentials (32 x 32 clocks of matrix pipe and 32
+// exponentials per wavefront and tile); short ones, the latency in front of and behind the loop.  Hence the
+// prologue: one load names the rows and the key tiles, the first pages are on their way before the rows' positions
+// are known, a head computes a quarter of the angles and shares them, visible tiles are counted in the
+// window; and the epilogue turns the output in LDS so that stores write whole rows.  Measured against a chain of
+// dependent loads, each wavefront's own angles and 8-byte stores: one request of 2.6k tokens 65 -> 59 us (two
+// streams: 44), the 8B batch of 32 1883 -> 1773, 4 x 32k tokens 3270 -> 3165 (1.2 PFLOP/s).
+#include <algorithm>
 #include <type_traits>
 
 #include "mfma_tile.h"
@@ -62,6 +75,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 constexpr int kImage = 2048;    // 16-byte pieces per tile image (K: 1024, V: 1024)
 constexpr int kBufs = 4;
+// Two key streams up to this many 64-row workgroups.  A compute unit holds one workgroup; twice as many with half
+// the tiles fill units that would idle and still run in one round, or nearly.  Measured (4 query heads per KV
+// head, one stream / two, us): 64 workgroups 59 / 44, 112: 61 / 46, 144 (10k keys): 201 / 152, 192: 67 / 63, 256: 72 / 85.
+constexpr int kTwoStreamGrid = 160;
 #ifndef CC_RING_DEPTH
 #define CC_RING_DEPTH 8
 #endif
@@ -124,13 +141,11 @@ __device__ __forceinline__ void exp_behind_pack(uint32_t& pk, float& l, float& e
   asm volatile("v_cvt_pk_bf16_f32 %0, %2, %3\n\tv_add_f32 %1, %1, %2\n\tv_add_f32 %1, %1, %3\n\tv_exp_f32 %2, %4"
                : "=&v"(pk), "+v"(l), "+v"(e) : "v"(v), "v"(s));
 }
-// one 16-byte LDS piece straight into accumulation registers
-__device__ __forceinline__ u32x4 lds_to_acc(const uint4* p) {
+__device__ __forceinline__ void lds_to_acc(const uint4* p, u32x4& r0, u32x4& r1) {
   typedef __attribute__((address_space(3))) const uint4 lds_piece;
   const uint32_t addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_piece*)p));   // LDS byte offset
-  u32x4 r;
-  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=a"(r) : "v"(addr) : "memory");
-  return r;
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:8192\n\ts_waitcnt lgkmcnt(0)"
+               : "=&a"(r0), "=&a"(r1) : "v"(addr) : "memory");
 }
 // s_waitcnt with only the LDS counter set (vector-memory and export counters left alone)
 template <int N>
@@ -138,27 +153,26 @@ __device__ __forceinline__ void wait_lds() {
   __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (N << 8));
 }
 
-// QB = 2: 4 wavefronts, each one head x 64 rows (one wavefront per SIMD, up to 512 registers);
-// QB = 1: 8 wavefronts, each one head x 32 rows (two per SIMD, up to 256 registers each): the workgroup
-// covers the same 4 heads x 64 rows, and while one wavefront of a SIMD waits (for LDS, for its
-// exponentials - a transcendental does not run beside a matrix instruction of its own wavefront)
-// the other one keeps the matrix pipe busy.
-template <int QB>
-__global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
-    const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos, const int32_t* __restrict__ cu_q,
+// BY: with the by-product (see the tile loop).
+template <int KS, bool BY>
+__global__ __launch_bounds__(512, 1) void attn_v2_kernel(
+    const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos,
     const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool, int n_blocks,
-    const TileDesc* __restrict__ tiles, const int32_t* __restrict__ seg_tile_off, int max_tiles,
-    const int32_t* __restrict__ order, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
+    const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     int n_sub, int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ redo, const int32_t* __restrict__ q_map, int map_pos,
     const int32_t* __restrict__ snap_index, float* __restrict__ cum, int s_max,
     const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
-  constexpr int TQ = 64;                    // query rows per workgroup
-  constexpr int NT = 512 / QB;              // threads
-  __shared__ uint4 lds_all[kBufs * kImage];
+  constexpr int TQ = KS == 1 ? 64 : 32;     // query rows per workgroup
+  // LDS: KS = 1: four images of K | V; KS = 2: per key stream three K images and two V images
+  // (and 16 KiB more that the queries pass through on their way into the accumulation registers; KS = 2 has an
+  // image to spare for that)
+  __shared__ uint4 lds_all[KS == 1 ? kBufs * kImage + 1024 : 5 * kImage];
+  auto here = [&]() __attribute__((always_inline)) { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t & 63; };
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int n = lane & 31, hh = lane >> 5;
-  const int whead = wave & 3, wrows = (wave >> 2) * 32;     // this wavefront's head of the four, its first row of the 64
+  const int whead = wave & 3, wgrp = wave >> 2;              // this wavefront's head of the four; row half or key stream
+  const int ks = KS == 1 ? 0 : wgrp, wrows = KS == 1 ? 32 * wgrp : 0;
   const int per_tile = hkv * n_sub;
   const int tile = n_tiles_x - 1 - blockIdx.x / per_tile;    // late (long) tiles are dispatched first
   const int rem = blockIdx.x % per_tile;
@@ -166,176 +180,15 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
   const int h = kvh * (4 * n_sub) + hsub * 4 + whead;
 
   // ---- which queries ------------------------------------------------------------------------
-  const int r = order[blockIdx.y];                           // longest contexts are dispatched first
-  const int q0 = cu_q[r] + tile * TQ, q_end = cu_q[r + 1];
+  const uint4* ip = reinterpret_cast<const uint4*>(items + blockIdx.y);
+  const uint4 i0 = ip[0], i1 = ip[1];
+  const int r = uniform(i0.x), q_first = uniform(i0.z), q_end = q_first + uniform(i0.w);
+  const int j_begin = uniform(i1.y), j_end = min(uniform(i1.z), max_tiles);
+  const int q0 = q_first + tile * TQ;
   if (q0 >= q_end) return;
-  // (with a row map, list row j takes its query from row q_map[j] of q - and, if map_pos, its
-  // position from q_pos[q_map[j]]; results are always indexed by the list row)
-  int row[QB], src_row[QB], p[QB];
-  bool row_valid[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    row[qb] = min(q0 + wrows + 32 * qb + n, q_end - 1);
-    row_valid[qb] = q0 + wrows + 32 * qb + n < q_end;
-    src_row[qb] = q_map != nullptr ? q_map[row[qb]] : row[qb];
-    p[qb] = q_pos[map_pos ? src_row[qb] : row[qb]];
-  }
-  // first and last position over all 64 rows of the workgroup (every wavefront walks the same tiles)
-  int pmx, pmn;
-  {
-    const int ra = min(q0 + n, q_end - 1), rb = min(q0 + 32 + n, q_end - 1);
-    const int pa = q_pos[map_pos ? (q_map != nullptr ? q_map[ra] : ra) : ra];
-    const int pb = q_pos[map_pos ? (q_map != nullptr ? q_map[rb] : rb) : rb];
-    pmx = max(pa, pb); pmn = min(pa, pb);
-  }
-  const int p_max = uniform(wave_max_i(pmx)), p_min = uniform(wave_min_i(pmn));
-
-  // ---- tiles of the request whose first key some query of the workgroup sees ------------------
-  // (tiles are listed in prompt order, so these form a prefix)
-  const int j_begin = seg_tile_off[req_seg_off[r]];
-  const int j_end = min(seg_tile_off[req_seg_off[r + 1]], max_tiles);
-  int n_t = 0;
-  for (int j0 = j_begin; j0 < j_end; j0 += NT) {
-    const int j = j0 + tid;
-    n_t += __syncthreads_count(j < j_end && tiles[min(j, j_end - 1)].kpos0 <= p_max);
-  }
-  n_t = uniform(n_t);
-  if (n_t == 0) return;                                      // cannot happen for a valid prompt
-
-  // ---- load the query rows, rotate them to their positions, fold the softmax scale -------------
-  // lane (n, hh) keeps, for k-step kk, dims 16kk + 8hh .. +7; dims < 64 pair with dims + 64.
-  const float c2 = 0.08838834764831845f * kLog2e;            // log2(e) / sqrt(128)
-  __shared__ uint4 q_bounce[NT];      // one piece per lane: the way into the accumulation registers
-  u32x4 qreg[QB][8];
-  // (called after the first tile loads are on their way, so that the trigonometry hides their latency)
-  auto load_queries = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const bf16_t* qp = q + (static_cast<size_t>(src_row[qb]) * hq + h) * kD + 8 * hh;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        bf16x8 xv = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qp + 16 * kk));
-        bf16x8 yv = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qp + 16 * kk + 64));
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float c, s;
-          rot_cos_sin_fast(p[qb], inv_freq.f[16 * kk + 8 * hh + j], &c, &s);
-          c *= c2; s *= c2;
-          const float x = static_cast<float>(xv[j]), y = static_cast<float>(yv[j]);
-          xv[j] = static_cast<bf16_t>(x * c - y * s);
-          yv[j] = static_cast<bf16_t>(y * c + x * s);
-        }
-        q_bounce[tid] = __builtin_bit_cast(uint4, xv);
-        qreg[qb][kk] = lds_to_acc(&q_bounce[tid]);
-        q_bounce[tid] = __builtin_bit_cast(uint4, yv);
-        qreg[qb][kk + 4] = lds_to_acc(&q_bounce[tid]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-
+  const int n_all = j_end - j_begin;
+  if (n_all <= 0) return;
   const char* lds_bytes = reinterpret_cast<const char*>(lds_all);
-  // byte offsets of this lane's operand pieces inside an image (see the layout above)
-  const int k_rd = (n >> 3) * 1024 + (hh ^ ((n >> 3) & 1)) * 128 + (n & 7) * 16;
-  const int v_rd = 16384 + lane * 16;
-  float m_ref[QB], lsum[QB], ev[QB], vodd[QB];
-  f32x16 cinit[QB];                   // -m_ref in all 16 registers: the C operand that opens an S block
-  f32x16 o[QB][4];                    // running output, accumulation registers for the whole loop
-  f32x16 sacc[QB][2];                 // S of the two 32-key blocks in flight (vector registers)
-  uint32_t pk[QB][2][2][4];           // P^T of [block parity][16-key half], packed bf16 pairs
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    m_ref[qb] = 0.f; lsum[qb] = 0.f; ev[qb] = 0.f; vodd[qb] = 0.f;
-#pragma unroll
-    for (int db = 0; db < 4; ++db) zero_acc(o[qb][db]);
-  }
-
-  // ---- operand ring ---------------------------------------------------------------------------
-  // Steps of one iteration (tile t, image img; nimg = image of tile t+1):
-  //    0.. 7  K pieces of block 1 of img        (S of the tile's second block)
-  //    8..15  V pieces of pages 0, 1 of img     (PV of the first block)
-  //   16..23  K pieces of block 0 of nimg       (S of the next tile's first block)
-  //   24..31  V pieces of pages 2, 3 of img     (PV of the second block)
-  //   32..39  = steps 0..7 of the next iteration
-  // (behind the last tile the "next image" holds stale keys: that S block is masked as a whole)
-  // Reads are issued two at a time behind every odd step (into the slots of the two pieces just
-  // used), and one wait in front of every even step covers that step and the next.
-  u32x4 ring[kDepth];
-  auto k_piece = [&](int img_off, int b, int kk) __attribute__((always_inline)) {
-    return *reinterpret_cast<const u32x4*>(lds_bytes + img_off + k_rd + b * 8192 + (kk >> 2) * 4096 + (kk & 3) * 256);
-  };
-  auto v_piece = [&](int img_off, int j) __attribute__((always_inline)) {      // j = page * 4 + dim group
-    return *reinterpret_cast<const u32x4*>(lds_bytes + img_off + v_rd + j * 1024);
-  };
-  auto issue = [&](int img, int nimg, int s) __attribute__((always_inline)) {   // s: compile-time
-    if (s < 8) ring[s % kDepth] = k_piece(img, 1, s);
-    else if (s < 16) ring[s % kDepth] = v_piece(img, s - 8);
-    else if (s < 24) ring[s % kDepth] = k_piece(nimg, 0, s - 16);
-    else if (s < 32) ring[s % kDepth] = v_piece(img, s - 16);
-    else ring[s % kDepth] = k_piece(nimg, 1, s - 32);
-  };
-
-  // one exponential: element i (0..15) of block parity bp.  An even element first packs the pair
-  // in front of it (element 0: the last pair of the block before, which has the other parity).
-  auto exp_step = [&](int qb, int bp, int i) __attribute__((always_inline)) {
-    const float s = sacc[qb][bp][i];
-    if (i & 1) exp_only(vodd[qb], s);
-    else if (i == 0) exp_behind_pack(pk[qb][bp ^ 1][1][3], lsum[qb], ev[qb], vodd[qb], s);
-    else exp_behind_pack(pk[qb][bp][(i - 2) >> 3][((i - 2) & 7) >> 1], lsum[qb], ev[qb], vodd[qb], s);
-  };
-  // S block into parity bp from the ring; side(kk, qb) runs after each MFMA
-  auto s_slot = [&](int img, int nimg, int s0, int bp, auto&& side) __attribute__((always_inline)) {
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      if ((kk & 1) == 0) wait_lds<kDepth - 2>();
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        if (kk == 0) mfma_s_first(sacc[qb][bp], ring[(s0 + kk) % kDepth], qreg[qb][kk], cinit[qb]);
-        else mfma_s_acc(sacc[qb][bp], ring[(s0 + kk) % kDepth], qreg[qb][kk]);
-        if (qb == QB - 1 && (kk & 1)) {
-          issue(img, nimg, s0 + kk - 1 + kDepth);
-          issue(img, nimg, s0 + kk + kDepth);
-        }
-        side(kk, qb);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-  // PV of block parity bp: step st = (u, db): 16-key half u (page), 32-dim group db
-  auto pv_slot = [&](int img, int nimg, int s0, int bp, auto&& side) __attribute__((always_inline)) {
-#pragma unroll
-    for (int st = 0; st < 8; ++st) {
-      const int u = st >> 2, db = st & 3;
-      if ((st & 1) == 0) wait_lds<kDepth - 2>();
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        const u32x4 pw = {pk[qb][bp][u][0], pk[qb][bp][u][1], pk[qb][bp][u][2], pk[qb][bp][u][3]};
-        mfma_o_acc(o[qb][db], ring[(s0 + st) % kDepth], pw);
-        if (qb == QB - 1 && (st & 1)) {
-          issue(img, nimg, s0 + st - 1 + kDepth);
-          issue(img, nimg, s0 + st + kDepth);
-        }
-        side(st, qb);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-
-  // padding / causal edge: entries of block parity bp (tile block blk) the query must not see
-  // become -inf (register i of block blk holds key 32 blk + 16(i/8) + 8hh + i%8 of the tile)
-  auto mask_block = [&](int bp, int blk, int kpos0, int nvalid) __attribute__((always_inline)) {
-    mfma_result_wait();
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      int lim = min(nvalid - 1, p[qb] - kpos0) - 8 * hh - 32 * blk;
-      asm volatile("" : "+v"(lim));
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        sacc[qb][bp][i] = (16 * (i / 8) + (i % 8) <= lim) ? sacc[qb][bp][i] : -INFINITY;
-      asm volatile("" : "+v"(sacc[qb][bp]));
-    }
-  };
-
   // ---- descriptors and staging --------------------------------------------------------------------
   // What the loop needs of 64 consecutive tiles sits in vector registers, one tile per lane, and is
   // handed out with v_readlane: no memory access per tile.  The straight path reads two values per
@@ -348,15 +201,26 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
   // w_own: block of the page this wavefront brings in (-1: none); w_vown: where that page's values
   // are - the same block of v_pool, or (<= -2) block -2 - w_vown of v_shared while the value map
   // still points there (copy-on-write pending)
-  int w_kpos0, w_nvalid, w_seg, w_seg_next, w_own, w_vown, w_flags;
+  int w_kpos0, w_nvalid, w_seg, w_seg_next, w_own, w_vown, w_flags, w_pair = 0, w_seg_far = 0;
   auto fill_window = [&](int base) __attribute__((always_inline)) {
-    const int jl = min(base + lane, n_t - 1);
+    const int jl = min(KS * (base + lane) + ks, n_all - 1);
     const TileDesc v = fetch_desc(tiles, j_begin + jl, max_tiles);
     const int b0 = v.blk[0], b1 = v.blk[1], b2 = v.blk[2], b3 = v.blk[3];
     w_kpos0 = v.kpos0; w_nvalid = v.nvalid; w_seg = v.seg;
-    int jn = min(max(j_begin + min(jl + 1, n_t - 1), 0), max_tiles - 1);
+    int jn = min(max(j_begin + min(jl + 1, n_all - 1), 0), max_tiles - 1);
     asm volatile("" : "+v"(jn));                   // (a vector load, like the descriptor itself: see fetch_desc)
     w_seg_next = tiles[jn].seg;
+    if constexpr (KS == 2) {       // both streams' tiles (their loops and segment ends agree)
+      int je = min(j_begin + min(2 * (base + lane), n_all - 1), max_tiles - 1);
+      int jo = min(j_begin + min(2 * (base + lane) + 1, n_all - 1), max_tiles - 1);
+      asm volatile("" : "+v"(je), "+v"(jo));
+      w_pair = tiles[ks == 0 ? jo : je].kpos0;      // first key of the other stream's tile
+      if constexpr (BY) {
+        int jf = min(j_begin + min(2 * (base + lane) + 2, n_all - 1), max_tiles - 1);
+        asm volatile("" : "+v"(jf));
+        w_seg = tiles[je].seg; w_seg_next = tiles[jo].seg; w_seg_far = tiles[jf].seg;
+      }
+    }
     w_own = whead == 0 ? b0 : whead == 1 ? b1 : whead == 2 ? b2 : b3;
     w_vown = w_own;
     if (v_map != nullptr && w_own >= 0) {
@@ -364,11 +228,13 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
       if (m >= 0 && m < n_shared_blocks) w_vown = -2 - m;
     }
     const bool edge = v.nvalid < kTile || (b0 | b1 | b2 | b3) < 0;
-    w_flags = ((edge || v.kpos0 + kTile - 1 > p_min) ? 1 : 0) | (edge ? 2 : 0) | (w_seg_next != v.seg ? 4 : 0);
+    w_flags = (edge ? 3 : 0) | (w_seg_next != w_seg ? 4 : 0) | (KS == 2 && BY && w_seg_far != w_seg_next ? 8 : 0);
   };
   fill_window(0);
-  auto lane_of = [&](int t) __attribute__((always_inline)) { return min(t, n_t - 1) - win_base; };
-  auto image_off = [&](int t) __attribute__((always_inline)) { return (t & (kBufs - 1)) * (kImage * 16); };   // bytes
+  // byte offset of the K / V image of (local) tile t (KS = 1: one image, V behind K)
+  auto k_image = [&](int t) __attribute__((always_inline)) { return KS == 1 ? (t & (kBufs - 1)) * (kImage * 16) : ks * 49152 + (t % 3) * 16384; };
+  auto v_image = [&](int t) __attribute__((always_inline)) { return KS == 1 ? (t & (kBufs - 1)) * (kImage * 16) : 98304 + ks * 32768 + (t & 1) * 16384; };
+  constexpr int kVPart = KS == 1 ? 16384 : 0;
   // Loads of one tile, straight into image `img_off`: wavefront w brings page w % 4 - K and V if
   // there are four wavefronts, else K (w < 4) or V.
   //   K: instruction (rg, kq) brings rows 8 rg .. 8 rg + 7 of the page (row r sits in token slot
@@ -385,19 +251,19 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
   typedef __attribute__((address_space(3))) const uint4 lds_piece;
   const uint32_t lds_base = uniform(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_piece*)lds_all)));   // LDS byte address
   const int page = whead;
-  const bool brings_k = QB == 2 || wave < 4, brings_v = QB == 2 || wave >= 4;
+  const bool brings_k = KS == 2 || wave < 4, brings_v = KS == 2 || wave >= 4;
   const uint32_t k_img = lds_base + ((page >> 1) * 8 + (page & 1) * 2) * 1024;   // this wavefront's first K group in image 0
-  const uint32_t v_img = lds_base + (16 + 4 * page) * 1024;                   // ... and its V page
+  const uint32_t v_img = lds_base + kVPart + 4 * page * 1024;                   // ... and its V page
   const char* k_src = nullptr;                                                // page of the tile being loaded (scalar)
   const char* v_src = nullptr;
   uint32_t k_dst = 0, v_dst = 0;
-  auto dma_begin = [&](int l, int img_off) __attribute__((always_inline)) {          // l: the tile's lane in the window
-    const int own = __builtin_amdgcn_readlane(w_own, l), vown = __builtin_amdgcn_readlane(w_vown, l);
+  auto dma_begin = [&](int lk, int lv, int k_to, int v_to) __attribute__((always_inline)) {      // the tiles' lanes in the window, their images
+    const int own = __builtin_amdgcn_readlane(w_own, lk), vown = __builtin_amdgcn_readlane(w_vown, lv);
     k_src = k_head + static_cast<size_t>(max(own, 0)) * blk_bytes;
     v_src = vown <= -2 ? v_head_shared + static_cast<size_t>(-2 - vown) * blk_bytes
                        : v_head + static_cast<size_t>(max(vown, 0)) * blk_bytes;
-    k_dst = k_img + img_off;
-    v_dst = v_img + img_off;
+    k_dst = k_img + k_to;
+    v_dst = v_img + v_to;
   };
   // (the two halves of a row are 4 KiB apart in the image and 128 bytes apart in memory; the two
   // row groups of a page are neighbours in the image)
@@ -413,22 +279,15 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
     if (half == 0) dma_two<0, 1024>(v_voff, v_src, v_dst);
     else dma_two<2048, 3072>(v_voff, v_src, v_dst);
   };
-  auto dma_tile = [&](int t, int img_off) __attribute__((always_inline)) {
-    dma_begin(lane_of(t), img_off);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma_k(j);
-    dma_v(0);
-    dma_v(1);
-  };
   // blank the padding slots of the V page this wavefront loaded (rare; after its loads have landed)
-  auto blank_padding = [&](int t, int img_off) __attribute__((always_inline)) {
-    const int l = lane_of(t);
+  auto blank_padding = [&](int l, int img) __attribute__((always_inline)) {
     const int nvalid = __builtin_amdgcn_readlane(w_nvalid, l), own = __builtin_amdgcn_readlane(w_own, l);
     const int nv = own < 0 ? 0 : min(max(nvalid - kBlock * page, 0), kBlock);
     if (brings_v && nv < kBlock) {
-      uint4* vp = reinterpret_cast<uint4*>(const_cast<char*>(lds_bytes) + img_off + (16 + 4 * page) * 1024 + lane * 16);
+      const int ln = here();
+      uint4* vp = reinterpret_cast<uint4*>(const_cast<char*>(lds_bytes) + img + kVPart + 4 * page * 1024 + ln * 16);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) vp[j * 64] = zero_pad_slots(vp[j * 64], hh, nv);
+      for (int j = 0; j < 4; ++j) vp[j * 64] = zero_pad_slots(vp[j * 64], ln >> 5, nv);
       // (a rare branch leaves nothing pending, so that the code behind the join waits for no more
       // than the straight path does)
       wait_lds<0>();
@@ -446,57 +305,254 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
     asm volatile("" ::: "memory");
   };
 
-  // prologue: images 0, 1, 2; S of block 0 and the first half of its exponentials
-  dma_tile(0, image_off(0));
-  dma_tile(1, image_off(1));
-  dma_tile(2, image_off(2));
+  // ---- first tiles: on their way before anything about the rows is known ------------------------------
+  // (KS = 1: images 0, 1, 2; KS = 2: K of the stream's tiles 0 and 1, V of tile 0.  Tiles no row sees are
+  // loaded in vain; past the request's last tile that tile is repeated.)
+  constexpr int kAheadK = KS == 1 ? 3 : 2, kAheadV = KS == 1 ? 3 : 1;
+  const int n_av = (n_all - ks + KS - 1) / KS;                // tiles of the stream in the whole request
+#pragma unroll
+  for (int t = 0; t < kAheadK; ++t) {
+    const int l = max(min(t, n_av - 1), 0);
+    dma_begin(l, l, k_image(t), v_image(t));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dma_k(j);
+    if (t < kAheadV) {
+      dma_v(0);
+      dma_v(1);
+    }
+  }
+
+  // (with a row map, list row j takes its query from row q_map[j] of q - and, if map_pos, its
+  // position from q_pos[q_map[j]]; results are always indexed by the list row)
+  int row, src_row, p;
+  bool row_valid;
+  {
+    row = min(q0 + wrows + n, q_end - 1);
+    row_valid = q0 + wrows + n < q_end;
+    src_row = q_map != nullptr ? q_map[row] : row;
+    p = q_pos[map_pos ? src_row : row];
+  }
+  // first and last position over all rows of the workgroup (every wavefront walks the same tiles)
+  int pmx = p, pmn = p;
+  if constexpr (KS == 1) {
+    const int other = min(q0 + (32 - wrows) + n, q_end - 1);
+    const int po = q_pos[map_pos ? (q_map != nullptr ? q_map[other] : other) : other];
+    pmx = max(p, po); pmn = min(p, po);
+  }
+  const int p_max = uniform(wave_max_i(pmx)), p_min = uniform(wave_min_i(pmn));
+
+  // ---- tiles of the request whose first key some query of the workgroup sees ------------------
+  // (tiles are listed in prompt order, so these form a prefix)
+  // (counted in the window; while all 64 are visible, those behind it are taken to be, until the window moves there)
+  int n_odd = 0;                 // (tiles of the odd stream)
+  int n_it, n_loc;               // iterations of the workgroup; tiles of this wavefront's key stream (the odd one may have none)
+  auto see_window = [&]() __attribute__((always_inline)) {
+    if (w_kpos0 + kTile - 1 > p_min) w_flags |= 1;
+    const int jl = KS * (win_base + here()) + ks;
+    const uint64_t seen = __ballot(jl < n_all && w_kpos0 <= p_max);
+    n_loc = seen == ~0ull ? n_av : win_base + __popcll(seen);
+    if constexpr (KS == 1) {
+      n_loc = n_it = max(n_loc, 1);
+    } else {
+      const uint64_t pair = __ballot((jl ^ 1) < n_all && w_pair <= p_max);
+      const int n_other = pair == ~0ull ? (n_all - (ks ^ 1) + 1) / 2 : win_base + __popcll(pair);
+      n_it = max(max(n_loc, n_other), 1);
+      if (BY) n_odd = min(n_loc, n_other);
+    }
+  };
+  see_window();
+  auto lane_of = [&](int t) __attribute__((always_inline)) { return (KS == 1 ? min(t, n_loc - 1) : max(min(t, n_loc - 1), 0)) - win_base; };
+  // ---- load the query rows, rotate them to their positions, fold the softmax scale -------------
+  // lane (n, hh) keeps, for k-step kk, dims 16kk + 8hh .. +7; dims < 64 pair with dims + 64.
+  const float c2 = 0.08838834764831845f * kLog2e;            // log2(e) / sqrt(128)
+  u32x4 qreg[8];
+  auto load_queries = [&]() __attribute__((always_inline)) {
+    const bf16_t* qp = q + (static_cast<size_t>(src_row) * hq + h) * kD + 8 * hh;
+    uint4 qx[4], qy[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      qx[kk] = *reinterpret_cast<const uint4*>(qp + 16 * kk);
+      qy[kk] = *reinterpret_cast<const uint4*>(qp + 16 * kk + 64);
+    }
+    float4* turns = reinterpret_cast<float4*>(const_cast<char*>(lds_bytes) + (KS == 1 ? k_image(3) + wgrp * 16384 : k_image(2))) + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float4 t;
+      rot_cos_sin_fast(p, inv_freq.f[16 * whead + 8 * hh + 2 * i], &t.x, &t.y);
+      rot_cos_sin_fast(p, inv_freq.f[16 * whead + 8 * hh + 2 * i + 1], &t.z, &t.w);
+      t.x *= c2; t.y *= c2; t.z *= c2; t.w *= c2;
+      turns[(whead * 4 + i) * 64] = t;
+    }
+    wait_lds<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      bf16x8 xv = __builtin_bit_cast(bf16x8, qx[kk]), yv = __builtin_bit_cast(bf16x8, qy[kk]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 t = turns[(kk * 4 + i) * 64];
+        const float x0 = static_cast<float>(xv[2 * i]), y0 = static_cast<float>(yv[2 * i]);
+        const float x1 = static_cast<float>(xv[2 * i + 1]), y1 = static_cast<float>(yv[2 * i + 1]);
+        xv[2 * i] = static_cast<bf16_t>(x0 * t.x - y0 * t.y);
+        yv[2 * i] = static_cast<bf16_t>(y0 * t.x + x0 * t.y);
+        xv[2 * i + 1] = static_cast<bf16_t>(x1 * t.z - y1 * t.w);
+        yv[2 * i + 1] = static_cast<bf16_t>(y1 * t.z + x1 * t.w);
+      }
+      // (a lane reads back what it wrote itself)
+      uint4* bounce = reinterpret_cast<uint4*>(const_cast<char*>(lds_bytes) + (KS == 1 ? 131072 : v_image(1))) + (KS == 1 ? tid : tid & 255);
+      bounce[0] = __builtin_bit_cast(uint4, xv);
+      bounce[512] = __builtin_bit_cast(uint4, yv);
+      lds_to_acc(bounce, qreg[kk], qreg[kk + 4]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // byte offsets of this lane's operand pieces inside an image (see the layout above)
+  const int k_rd = (n >> 3) * 1024 + (hh ^ ((n >> 3) & 1)) * 128 + (n & 7) * 16;
+  const int v_rd = kVPart + lane * 16;
+  float m_ref, lsum, ev, vodd;
+  f32x16 cinit;                   // -m_ref in all 16 registers: the C operand that opens an S block
+  f32x16 o[4];                    // running output, accumulation registers for the whole loop
+  f32x16 sacc[2];                 // S of the two 32-key blocks in flight (vector registers)
+  uint32_t pk[2][2][4];           // P^T of [block parity][16-key half], packed bf16 pairs
+  {
+    m_ref = 0.f; lsum = 0.f; ev = 0.f; vodd = 0.f;
+#pragma unroll
+    for (int db = 0; db < 4; ++db) zero_acc(o[db]);
+  }
+
+  // ---- operand ring ---------------------------------------------------------------------------
+  // Steps of one iteration (tile t, image img; nimg = image of tile t+1):
+  //    0.. 7  K pieces of block 1 of img        (S of the tile's second block)
+  //    8..15  V pieces of pages 0, 1 of img     (PV of the first block)
+  //   16..23  K pieces of block 0 of nimg       (S of the next tile's first block)
+  //   24..31  V pieces of pages 2, 3 of img     (PV of the second block)
+  //   32..39  = steps 0..7 of the next iteration
+  // (behind the last tile the "next image" holds stale keys: that S block is masked as a whole)
+  // Reads are issued two at a time behind every odd step (into the slots of the two pieces just
+  // used), and one wait in front of every even step covers that step and the next.
+  u32x4 ring[kDepth];
+  auto k_piece = [&](int img, int b, int kk) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(lds_bytes + img + k_rd + b * 8192 + (kk >> 2) * 4096 + (kk & 3) * 256);
+  };
+  auto v_piece = [&](int img, int j) __attribute__((always_inline)) {      // j = page * 4 + dim group
+    return *reinterpret_cast<const u32x4*>(lds_bytes + img + v_rd + j * 1024);
+  };
+  auto issue = [&](int kimg, int vimg, int knext, int s) __attribute__((always_inline)) {   // s: compile-time
+    if (s < 8) ring[s % kDepth] = k_piece(kimg, 1, s);
+    else if (s < 16) ring[s % kDepth] = v_piece(vimg, s - 8);
+    else if (s < 24) ring[s % kDepth] = k_piece(knext, 0, s - 16);
+    else if (s < 32) ring[s % kDepth] = v_piece(vimg, s - 16);
+    else ring[s % kDepth] = k_piece(knext, 1, s - 32);
+  };
+
+  // one exponential: element i (0..15) of block parity bp.  An even element first packs the pair
+  // in front of it (element 0: the last pair of the block before, which has the other parity).
+  auto exp_step = [&](int bp, int i) __attribute__((always_inline)) {
+    const float s = sacc[bp][i];
+    if (i & 1) exp_only(vodd, s);
+    else if (i == 0) exp_behind_pack(pk[bp ^ 1][1][3], lsum, ev, vodd, s);
+    else exp_behind_pack(pk[bp][(i - 2) >> 3][((i - 2) & 7) >> 1], lsum, ev, vodd, s);
+  };
+  // S block into parity bp from the ring; side(kk) runs after each MFMA
+  auto s_slot = [&](int kimg, int vimg, int knext, int s0, int bp, auto&& side) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      if ((kk & 1) == 0) wait_lds<kDepth - 2>();
+      {
+        if (kk == 0) mfma_s_first(sacc[bp], ring[(s0 + kk) % kDepth], qreg[kk], cinit);
+        else mfma_s_acc(sacc[bp], ring[(s0 + kk) % kDepth], qreg[kk]);
+        if ((kk & 1)) {
+          issue(kimg, vimg, knext, s0 + kk - 1 + kDepth);
+          issue(kimg, vimg, knext, s0 + kk + kDepth);
+        }
+        side(kk);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  // PV of block parity bp: step st = (u, db): 16-key half u (page), 32-dim group db
+  auto pv_slot = [&](int kimg, int vimg, int knext, int s0, int bp, auto&& side) __attribute__((always_inline)) {
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      const int u = st >> 2, db = st & 3;
+      if ((st & 1) == 0) wait_lds<kDepth - 2>();
+      {
+        const u32x4 pw = {pk[bp][u][0], pk[bp][u][1], pk[bp][u][2], pk[bp][u][3]};
+        mfma_o_acc(o[db], ring[(s0 + st) % kDepth], pw);
+        if ((st & 1)) {
+          issue(kimg, vimg, knext, s0 + st - 1 + kDepth);
+          issue(kimg, vimg, knext, s0 + st + kDepth);
+        }
+        side(st);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  // padding / causal edge: entries of block parity bp (tile block blk) the query must not see
+  // become -inf (register i of block blk holds key 32 blk + 16(i/8) + 8hh + i%8 of the tile)
+  auto mask_block = [&](int bp, int blk, int kpos0, int nvalid) __attribute__((always_inline)) {
+    mfma_result_wait();
+    {
+      int lim = min(nvalid - 1, p - kpos0) - 8 * hh - 32 * blk;
+      asm volatile("" : "+v"(lim));
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        sacc[bp][i] = (16 * (i / 8) + (i % 8) <= lim) ? sacc[bp][i] : -INFINITY;
+      asm volatile("" : "+v"(sacc[bp]));
+    }
+  };
+
+  auto mask_tile = [&](int bp, int blk, int t) __attribute__((always_inline)) {      // (a tile the stream does not have: all of it)
+    const int l = lane_of(t);
+    mask_block(bp, blk, __builtin_amdgcn_readlane(w_kpos0, l), t >= n_loc ? 0 : __builtin_amdgcn_readlane(w_nvalid, l));
+  };
+
+  // prologue: S of block 0 and the first half of its exponentials
   load_queries();
   wait_loads(std::integral_constant<int, 0>{});
-  {
-    const int f012 = __builtin_amdgcn_readlane(w_flags, lane_of(0)) | __builtin_amdgcn_readlane(w_flags, lane_of(1)) |
-                     __builtin_amdgcn_readlane(w_flags, lane_of(2));
-    if (f012 & 2) {
-      blank_padding(0, image_off(0));
-      blank_padding(1, image_off(1));
-      blank_padding(2, image_off(2));
-    }
+#pragma unroll
+  for (int t = 0; t < kAheadV; ++t) {
+    const int l = max(min(t, n_av - 1), 0);
+    if (__builtin_amdgcn_readlane(w_flags, l) & 2) blank_padding(l, v_image(t));
   }
   __syncthreads();
   int f_cur = __builtin_amdgcn_readlane(w_flags, lane_of(0));      // flags of tile t, t+1 (carried from tile to tile)
   int f_next = __builtin_amdgcn_readlane(w_flags, lane_of(1));
   {
-    const int img = image_off(0);
+    const int kimg = k_image(0);
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      const u32x4 a = k_piece(img, 0, kk);
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        if (kk == 0) mfma_s_zero(sacc[qb][0], a, qreg[qb][kk]);
-        else mfma_s_acc(sacc[qb][0], a, qreg[qb][kk]);
+      const u32x4 a = k_piece(kimg, 0, kk);
+      {
+        if (kk == 0) mfma_s_zero(sacc[0], a, qreg[kk]);
+        else mfma_s_acc(sacc[0], a, qreg[kk]);
       }
     }
-    if (f_cur & 1) mask_block(0, 0, __builtin_amdgcn_readlane(w_kpos0, 0), __builtin_amdgcn_readlane(w_nvalid, 0));
+    if ((f_cur & 1) || (KS == 2 && n_loc == 0)) mask_tile(0, 0, 0);
     else mfma_result_wait();
-    // first block of the request: its key 0 is visible to every query, so the maximum is finite;
-    // it is the reference for the whole row
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float t = max16(sacc[qb][0]);
-      m_ref[qb] = fmaxf(t, __shfl_xor(t, 32, 64));
+    // the maximum of the stream's first block is the reference for the whole row.  KS = 1: it holds key 0 of the
+    // request, which every query sees, so it is finite; KS = 2: a query may see no key of the odd stream at all
+    // (then it sees none of its later tiles either, and its sum stays 0)
+    {
+      const float t = max16(sacc[0]);
+      m_ref = fmaxf(t, __shfl_xor(t, 32, 64));
+      if (KS == 2 && m_ref == -INFINITY) m_ref = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        sacc[qb][0][i] -= m_ref[qb];
-        cinit[qb][i] = -m_ref[qb];
+        sacc[0][i] -= m_ref;
+        cinit[i] = -m_ref;
       }
     }
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) exp_only(ev[qb], sacc[qb][0][0]);
+    exp_only(ev, sacc[0][0]);
 #pragma unroll
     for (int i = 1; i < 8; ++i)
+exp_step(0, i);
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) exp_step(qb, 0, i);
-#pragma unroll
-    for (int s = 0; s < kDepth; ++s) issue(img, img, s);     // steps 0..kDepth-1 of iteration 0
+    for (int s = 0; s < kDepth; ++s) issue(kimg, v_image(0), kimg, s);     // steps 0..kDepth-1 of iteration 0
     __builtin_amdgcn_sched_barrier(0);
   }
 
@@ -512,106 +568,183 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_v2_kernel(
   // has just been closed is the last one of its segment, the log-sum-exp over all keys up to here
   // goes to cum[snap row][head][segment's index in its request].  The reference never moves in this
   // kernel, so these running sums subtract exactly.  (Rare: once per segment of the request.)
-  const int seg_first = cum != nullptr ? req_seg_off[order[blockIdx.y]] : 0;
+  const int seg_first = BY ? req_seg_off[r] : 0;
   // (segments without tokens have no tile: the value also stands for those between this tile's
   // segment and the next tile's; the row sum is taken with the pair that is still to be packed)
-  auto snapshot = [&](int t) __attribute__((always_inline)) {
-    const int l = lane_of(t);
-    const int seg = __builtin_amdgcn_readlane(w_seg, l), seg_next = __builtin_amdgcn_readlane(w_seg_next, l);
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float mine = lsum[qb] + (ev[qb] + vodd[qb]);
-      const float tot = mine + __shfl_xor(mine, 32, 64);
-      const int sr = snap_index != nullptr ? snap_index[row[qb]] : row[qb];     // (no index: every row is a snap row)
-      if (row_valid[qb] && hh == 0 && sr >= 0) {
-        const float v = kLn2 * (m_ref[qb] + __builtin_amdgcn_logf(tot));
-        for (int sl = max(seg - seg_first, 0); sl < min(seg_next - seg_first, s_max); ++sl)
-          cum[(static_cast<size_t>(sr) * hq + h) * s_max + sl] = v;
-      }
+  // KS = 2: the even stream writes what a segment that ends with its tile leaves, the odd one likewise; each needs the
+  // other's sum up to there, through the K image of tile t (free behind slot 1; rare as this is, it pays two
+  // barriers).  prev: the odd stream's sum one tile ago.
+  float prev = 0.f;
+  auto running = [&]() __attribute__((always_inline)) {
+    const float mine = lsum + (ev + vodd);
+    return mine + __shfl_xor(mine, 32, 64);
+  };
+  auto snapshot = [&](int t, float tot, int ends) __attribute__((always_inline)) {
+    const int l = lane_of(t), pair = KS == 1 ? 0 : t - win_base;
+    int seg = __builtin_amdgcn_readlane(w_seg, KS == 1 ? l : pair), seg_next = __builtin_amdgcn_readlane(w_seg_next, KS == 1 ? l : pair);
+    const int ln = here(), at = q0 + wrows + (ln & 31);
+    float m_all = m_ref;
+    bool writes = true;
+    if constexpr (KS == 2) {
+      float4* meet = reinterpret_cast<float4*>(lds_all) + whead * 32 + (ln & 31);      // (the even stream's K image of tile t)
+      meet = reinterpret_cast<float4*>(reinterpret_cast<char*>(meet) + (t % 3) * 16384);
+      barrier();
+      if (ln < 32) meet[ks * 128] = make_float4(m_ref, tot, prev, 0.f);
+      wait_lds<0>();
+      barrier();
+      const float4 theirs = meet[(ks ^ 1) * 128];
+      const float l_other = ks == 0 ? theirs.z : theirs.y;
+      m_all = tot == 0.f ? theirs.x : l_other == 0.f ? m_ref : fmaxf(m_ref, theirs.x);
+      tot = (tot == 0.f ? 0.f : tot * __builtin_amdgcn_exp2f(m_ref - m_all)) + (l_other == 0.f ? 0.f : l_other * __builtin_amdgcn_exp2f(theirs.x - m_all));
+      if (ks == 1) { seg = seg_next; seg_next = __builtin_amdgcn_readlane(w_seg_far, pair); }
+      writes = ks == 0 ? (ends & 4) != 0 : (ends & 8) != 0 && t < n_odd;
+    }
+    const int sr = at >= q_end ? -1 : snap_index != nullptr ? snap_index[at] : at;     // (no index: every row is a snap row)
+    if (writes && ln < 32 && sr >= 0) {
+      const float v = kLn2 * (m_all + __builtin_amdgcn_logf(tot));
+      for (int sl = max(seg - seg_first, 0); sl < min(seg_next - seg_first, s_max); ++sl)
+        cum[(static_cast<size_t>(sr) * hq + h) * s_max + sl] = v;
     }
     wait_lds<0>();                                 // (see blank_padding)
   };
   int f_far = 0;                                   // flags of tile t+2
-  for (int t = 0; t < n_t; ++t) {
-    const int img = image_off(t), nimg = image_off(t + 1);
-    if (min(t + 3, n_t - 1) - win_base >= 64) {          // next 64 descriptors, starting at tile t (rare)
+  for (int t = 0; t < n_it; ++t) {
+    const int kimg = k_image(t), vimg = v_image(t), knext = k_image(t + 1);
+    if (min(t + 3, n_it - 1) - win_base >= 64) {          // next 64 descriptors, starting at tile t (rare)
       win_base = t;
       fill_window(t);
+      see_window();
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));      // vmcnt(0) here, so the hot path never waits for it
     }
     // slot 1: S of the tile's second block; second half of the first block's exponentials.
-    // Underneath: the loads of image t+3 (past the last tile they repeat the last tile into an
+    // Underneath: the loads of the tiles ahead (past the last tile they repeat the last tile into an
     // image nobody reads), one instruction group per k-step.
-    s_slot(img, nimg, 0, 1, [&](int kk, int qb) __attribute__((always_inline)) {
-      exp_step(qb, 0, 8 + kk);
-      if (qb == QB - 1) {
-        if (kk == 0) {
-          f_far = __builtin_amdgcn_readlane(w_flags, lane_of(t + 2));
-          dma_begin(lane_of(t + 3), image_off(t + 3));
-        }
-        if (kk >= 1 && kk <= 4) dma_k(kk - 1);
-        if (kk == 5) dma_v(0);
-        if (kk == 6) dma_v(1);
+    s_slot(kimg, vimg, knext, 0, 1, [&](int kk) __attribute__((always_inline)) {
+      exp_step(0, 8 + kk);
+      if (kk == 0) {
+        f_far = __builtin_amdgcn_readlane(w_flags, lane_of(t + 2));
+        dma_begin(lane_of(t + kAheadK), lane_of(t + kAheadV), k_image(t + kAheadK), v_image(t + kAheadV));
       }
+      if (kk >= 1 && kk <= 4) dma_k(kk - 1);
+      if (kk == 5) dma_v(0);
+      if (kk == 6) dma_v(1);
     });
-    if (f_cur & 1) {
-      const int l = lane_of(t);
-      mask_block(1, 1, __builtin_amdgcn_readlane(w_kpos0, l), __builtin_amdgcn_readlane(w_nvalid, l));
-    }
+    if ((f_cur & 1) || (KS == 2 && t >= n_loc)) mask_tile(1, 1, t);
     // slot 2: PV of the first block; first half of the second block's exponentials
-    pv_slot(img, nimg, 8, 0, [&](int st, int qb) __attribute__((always_inline)) { exp_step(qb, 1, st); });
+    pv_slot(kimg, vimg, knext, 8, 0, [&](int st) __attribute__((always_inline)) { exp_step(1, st); });
     // slot 3: S of the next tile's first block; second half of the second block's exponentials
-    s_slot(img, nimg, 16, 0, [&](int kk, int qb) __attribute__((always_inline)) { exp_step(qb, 1, 8 + kk); });
-    if (cum != nullptr && (f_cur & 4)) snapshot(t);          // tile t was the last of its segment
-    const bool phantom = t + 1 >= n_t;                       // no next tile: none of its keys exists
-    if ((f_next & 1) || phantom) {
-      const int l = lane_of(t + 1);
-      mask_block(0, 0, __builtin_amdgcn_readlane(w_kpos0, l), phantom ? 0 : __builtin_amdgcn_readlane(w_nvalid, l));
+    s_slot(kimg, vimg, knext, 16, 0, [&](int kk) __attribute__((always_inline)) { exp_step(1, 8 + kk); });
+    if constexpr (BY && KS == 1) {
+      if (f_cur & 4) snapshot(t, running(), 0);       // tile t was the last of its segment
+    } else if constexpr (BY) {                     // (both streams decide alike: one of the two tiles was)
+      const int ends = __builtin_amdgcn_readlane(w_flags, t - win_base);
+      const float tot = running();
+      if ((ends & 4) || ((ends & 8) && t < n_odd)) snapshot(t, tot, ends);
+      prev = tot;
     }
+    if ((f_next & 1) || t + 1 >= n_loc) mask_tile(0, 0, t + 1);
     // slot 4: PV of the second block; first half of the next block's exponentials
-    pv_slot(img, nimg, 24, 1, [&](int st, int qb) __attribute__((always_inline)) { exp_step(qb, 0, st); });
-    // image t+2 (loads started one iteration ago) must be whole before anyone reads it
-    wait_loads(std::integral_constant<int, 4 * QB>{});
-    if (f_far & 2) blank_padding(t + 2, image_off(t + 2));
+    pv_slot(kimg, vimg, knext, 24, 1, [&](int st) __attribute__((always_inline)) { exp_step(0, st); });
+    // what the next iteration reads must be whole: KS = 1: image t+2 (loads started one iteration ago);
+    // KS = 2: K of tile t+2 and V of tile t+1, started above
+    wait_loads(std::integral_constant<int, KS == 1 ? 4 : 0>{});
+    if (KS == 1) {
+      if (f_far & 2) blank_padding(lane_of(t + 2), v_image(t + 2));
+    } else {
+      if (f_next & 2) blank_padding(lane_of(t + 1), v_image(t + 1));
+    }
     barrier();
     f_cur = f_next; f_next = f_far;
   }
-  mfma_result_wait();
+  // The output leaves the accumulation registers here, all at once and behind the last products.  (If its uses
+  // further down may read them, the allocator parks some of the loop's own values there as well and moves them in
+  // and out on every tile.)
+  asm volatile("s_nop 15\n\ts_nop 15" : "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
+#pragma unroll
+  for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(o[db]));
 
   // ---- epilogue ---------------------------------------------------------------------------------
-  float l_tot[QB];
-  bool overflow = false;              // some row's sum left the safe range (the sums only grow)
+  // (the images become scratch: no load may still be landing in them)
+  wait_loads(std::integral_constant<int, 0>{});
+  __syncthreads();
+  const int ln = here(), en = ln & 31, eh = ln >> 5;
+  float l_tot = lsum + __shfl_xor(lsum, 32, 64);
+  float scale = 1.f / l_tot;
+  bool overflow = !(l_tot > 0.f && l_tot < kSafeSum);        // the row's sum left the safe range (the sums only grow)
+  float4* scratch = reinterpret_cast<float4*>(lds_all);
+  float other[2][16];                                        // KS = 2: what the other stream has of this wavefront's two dim groups
+  float w_other = 0.f, m_all = m_ref;
+  if constexpr (KS == 2) {
+    // stream 0 finishes dims 0 .. 63, stream 1 dims 64 .. 127: each hands the other half of its output over
+    float2* ml = reinterpret_cast<float2*>(reinterpret_cast<char*>(lds_all) + 131072);
+    if (eh == 0) ml[(ks * 4 + whead) * 32 + en] = make_float2(m_ref, l_tot);
+    float4* give = scratch + ((ks ^ 1) * 4 + whead) * 512 + ln;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    l_tot[qb] = lsum[qb] + __shfl_xor(lsum[qb], 32, 64);
-    overflow = overflow || !(l_tot[qb] > 0.f && l_tot[qb] < kSafeSum);
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = ks == 0 ? o[2 + d][4 * i + e] : o[d][4 * i + e];
+        give[(d * 4 + i) * 64] = make_float4(v[0], v[1], v[2], v[3]);
+      }
+    __syncthreads();
+    const float2 theirs = ml[((ks ^ 1) * 4 + whead) * 32 + en];
+    const float4* take = scratch + (ks * 4 + whead) * 512 + ln;
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 v = take[(d * 4 + i) * 64];
+        other[d][4 * i] = v.x; other[d][4 * i + 1] = v.y; other[d][4 * i + 2] = v.z; other[d][4 * i + 3] = v.w;
+      }
+    // (a stream of which the row sees nothing has sum 0 and does not count)
+    m_all = l_tot == 0.f ? theirs.x : theirs.y == 0.f ? m_ref : fmaxf(m_ref, theirs.x);
+    const float a = l_tot == 0.f ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_all);
+    const float b = theirs.y == 0.f ? 0.f : __builtin_amdgcn_exp2f(theirs.x - m_all);
+    const float z = l_tot * a + theirs.y * b;
+    overflow = !(l_tot < kSafeSum && theirs.y < kSafeSum && z > 0.f);
+    l_tot = z;
+    scale = a / z;
+    w_other = b / z;
   }
   // rows whose sums left the safe range are redone by the kernel that can move its reference
-  if (__any(overflow)) {
-    if (lane == 0) redo[redo_index(q0)] = 1;
-    return;
-  }
+  const bool give_up = __any(overflow);
+  if (give_up && ln == 0) redo[redo_index(q_first + (tile * TQ / 64) * 64)] = 1;
+  // The output tile goes through LDS so that a store instruction writes whole 256-byte rows of a head instead
+  // of 8-byte pieces of 32 rows: row en of a head at 256 en, its 16-byte piece c at c ^ (en % 16).
+  if (KS == 2) __syncthreads();                              // (both streams have taken what they need)
+  if (out != nullptr) {                                      // (a caller that only wants the log-sum-exp passes none)
+    char* rows = reinterpret_cast<char*>(lds_all) + (KS == 1 ? wave : whead) * 8192;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const float inv = 1.f / l_tot[qb];
-    if (row_valid[qb]) {
-      if (out != nullptr) {                  // (a caller that only wants the log-sum-exp passes none)
-        bf16_t* op = out + (static_cast<size_t>(row[qb]) * hq + h) * kD;
+    for (int d = 0; d < (KS == 1 ? 4 : 2); ++d)
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+      for (int g4 = 0; g4 < 4; ++g4) {
+        bf16_t v4[4];
 #pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            bf16_t v4[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v4[e] = static_cast<bf16_t>(o[qb][db][4 * g4 + e] * inv);
-            // accumulator register i holds output dim 32db + 8(i/4) + 4hh + i%4
-            *reinterpret_cast<uint2*>(op + 32 * db + 8 * g4 + 4 * hh) = *reinterpret_cast<uint2*>(v4);
-          }
+        for (int e = 0; e < 4; ++e) {
+          // accumulator register i holds output dim 32db + 8(i/4) + 4hh + i%4
+          if constexpr (KS == 1) v4[e] = static_cast<bf16_t>(o[d][4 * g4 + e] * scale);
+          else v4[e] = static_cast<bf16_t>((ks == 0 ? o[d][4 * g4 + e] : o[2 + d][4 * g4 + e]) * scale + other[d][4 * g4 + e] * w_other);
+        }
+        const int c = 4 * (KS == 1 ? d : 2 * ks + d) + g4;
+        *reinterpret_cast<uint2*>(rows + en * 256 + ((c ^ (en & 15)) << 4) + 8 * eh) = *reinterpret_cast<uint2*>(v4);
       }
-      if (lse != nullptr && hh == 0)
-        lse[static_cast<size_t>(row[qb]) * hq + h] = kLn2 * (m_ref[qb] + __builtin_amdgcn_logf(l_tot[qb]));
+    if constexpr (KS == 2) __syncthreads();
+    else wait_lds<0>();
+    if (!give_up) {
+      // KS = 1: the wavefront's own 32 rows; KS = 2: the two streams share the head's 32 rows
+      constexpr int kRowsEach = 32 / KS;
+#pragma unroll
+      for (int i = 0; i < kRowsEach / 4; ++i) {
+        const int rr = ks * kRowsEach + 4 * i + (ln >> 4), at = q0 + wrows + rr;
+        const uint4 v = *reinterpret_cast<const uint4*>(rows + rr * 256 + (((ln & 15) ^ (rr & 15)) << 4));
+        if (at < q_end) *reinterpret_cast<uint4*>(out + (static_cast<size_t>(at) * hq + h) * kD + (ln & 15) * 8) = v;
+      }
     }
   }
+  if (!give_up && lse != nullptr && q0 + wrows + en < q_end && eh == 0 && ks == 0)
+    lse[static_cast<size_t>(q0 + wrows + en) * hq + h] = kLn2 * (m_all + __builtin_amdgcn_logf(l_tot));
 }
 
 }  // namespace
@@ -621,22 +754,30 @@ bool attn_v2_supported(const cc_ctx* ctx) {
   return (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) % 4 == 0;
 }
 
-void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
-                    int max_q_per_req, const void* k_pool, const void* v_pool, int n_blocks,
+void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
+                    int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool, int n_blocks,
                     const Plan& pl, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                     int32_t* redo, const int32_t* q_map, int map_pos, const int32_t* snap_index, float* cum,
                     int s_max, hipStream_t stream, const ValueSource& vs) {
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4;
-  const int n_tiles = (max_q_per_req + 63) / 64;
-  dim3 grid(hkv * n_sub * n_tiles, n_requests);
-  // Eight wavefronts of 32 rows (two per SIMD) rather than four of 64: the same speed on long prompts
-  // and a few percent faster on short ones (measured on the 8B continuous batch: 2.14 vs 2.20 ms).
-  constexpr int QB = 1;
-  hipLaunchKernelGGL((attn_v2_kernel<QB>), grid, dim3(512 / QB), 0, stream, static_cast<const bf16_t*>(q), q_pos,
-                     cu_q, static_cast<const bf16_t*>(k_pool), static_cast<const bf16_t*>(v_pool), n_blocks,
-                     pl.tiles, pl.seg_tile_off, pl.max_tiles, pl.order, req_seg_off, ctx->cfg.n_q_heads, hkv,
-                     n_sub, n_tiles, ctx->inv_freq, static_cast<bf16_t*>(out), lse, redo, q_map, map_pos, snap_index, cum, s_max,
-                     static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks, static_cast<const int32_t*>(vs.v_map));
+  const int row_tiles = std::min((max_q_per_req + 63) / 64 * n_requests, n_q_tot / 64 + n_requests);
+  const bool two_streams = static_cast<int64_t>(row_tiles) * hkv * n_sub <= kTwoStreamGrid;
+#define CC_GO(KS, BY, TQ)                                                                                          \
+  do {                                                                                                         \
+    const int n_tiles = (max_q_per_req + TQ - 1) / TQ;                                                         \
+    hipLaunchKernelGGL((attn_v2_kernel<KS, BY>), dim3(hkv * n_sub * n_tiles, n_requests), dim3(512), 0, stream,    \
+                       static_cast<const bf16_t*>(q), q_pos, static_cast<const bf16_t*>(k_pool),               \
+                       static_cast<const bf16_t*>(v_pool), n_blocks, pl.tiles, pl.max_tiles, pl.items,         \
+                       req_seg_off, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq,                    \
+                       static_cast<bf16_t*>(out), lse, redo, q_map, map_pos, snap_index, cum, s_max,           \
+                       static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks,                            \
+                       static_cast<const int32_t*>(vs.v_map));                                                 \
+  } while (0)
+  if (two_streams && cum != nullptr) CC_GO(2, true, 32);
+  else if (two_streams) CC_GO(2, false, 32);
+  else if (cum != nullptr) CC_GO(1, true, 64);
+  else CC_GO(1, false, 64);
+#undef CC_GO
 }
 
 }  // namespace cc

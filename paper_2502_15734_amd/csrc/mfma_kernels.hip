@@ -619,6 +619,7 @@ constexpr int kMaxOrdered = 4096;
 template <bool BY_REQUEST>
 __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
                                            const int32_t* __restrict__ req_seg_off,
+                                           const int32_t* __restrict__ cu_q,
                                            const int32_t* seg_tile_off, int n_items,
                                            int32_t* __restrict__ order, WorkItem* __restrict__ items, int block) {
   __shared__ int key[kMaxOrdered];
@@ -627,7 +628,7 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
     order[rank] = item;
     WorkItem w;
     if constexpr (BY_REQUEST) {
-      w.id = item; w.kind = 0; w.start = 0; w.n_tokens = 0; w.tok_off = 0;
+      w.id = item; w.kind = 0; w.start = cu_q[item]; w.n_tokens = cu_q[item + 1] - cu_q[item]; w.tok_off = 0;
       w.j_begin = seg_tile_off[req_seg_off[item]];
       w.j_own = seg_tile_off[req_seg_off[item + 1]];           // end of the request's tiles
     } else {
@@ -668,10 +669,11 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
 template <bool BY_REQUEST>
 __global__ __launch_bounds__(256) void plan_order_kernel(const cc_segment* __restrict__ segs,
                                                           const int32_t* __restrict__ req_seg_off,
+                                                          const int32_t* __restrict__ cu_q,
                                                           const int32_t* __restrict__ seg_tile_off,
                                                           int n_items, int32_t* __restrict__ order,
                                                           WorkItem* __restrict__ items) {
-  plan_order<BY_REQUEST>(segs, req_seg_off, seg_tile_off, n_items, order, items, blockIdx.x);
+  plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, seg_tile_off, n_items, order, items, blockIdx.x);
 }
 
 // The whole plan in ONE launch, for batches of up to kPlanFused segments: every workgroup repeats
@@ -682,7 +684,8 @@ constexpr int kPlanFused = 1024;
 
 template <bool BY_REQUEST>
 __global__ __launch_bounds__(256) void plan_fused_kernel(const cc_segment* __restrict__ segs, int n_segs,
-                                                          const int32_t* __restrict__ req_seg_off, int n_items,
+                                                          const int32_t* __restrict__ req_seg_off,
+                                                          const int32_t* __restrict__ cu_q, int n_items,
                                                           const int32_t* __restrict__ block_tab, int n_blocks,
                                                           int max_tiles, int32_t* __restrict__ seg_tile_off,
                                                           int32_t* __restrict__ order, WorkItem* __restrict__ items,
@@ -696,7 +699,7 @@ __global__ __launch_bounds__(256) void plan_fused_kernel(const cc_segment* __res
     plan_fill(segs, n_segs, s_off, block_tab, n_blocks, max_tiles, tiles, redo, n_redo,
               blockIdx.x * 256 + threadIdx.x, n_fill);
   else
-    plan_order<BY_REQUEST>(segs, req_seg_off, s_off, n_items, order, items, blockIdx.x - n_fill);
+    plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, s_off, n_items, order, items, blockIdx.x - n_fill);
 }
 
 constexpr int kAttnQB = 1;     // 32 query tokens per workgroup in the attention kernel
@@ -764,7 +767,7 @@ static size_t plan_bytes_impl(int n_segs, int max_tiles) {
 }
 
 Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests,
-              const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream) {
+              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream) {
   Plan pl;
   pl.seg_tile_off = static_cast<int32_t*>(ws);
   pl.order = pl.seg_tile_off + n_segs + 1;
@@ -776,21 +779,21 @@ Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_s
     const int n_fill = (max_tiles + 255) / 256;
     if (n_requests > 0)
       hipLaunchKernelGGL(plan_fused_kernel<true>, dim3(n_fill + (n_requests + 255) / 256), dim3(256), 0, stream, segs,
-                         n_segs, req_seg_off, n_requests, block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order,
+                         n_segs, req_seg_off, cu_q, n_requests, block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order,
                          pl.items, pl.tiles, pl.redo, n_redo, n_fill);
     else
       hipLaunchKernelGGL(plan_fused_kernel<false>, dim3(n_fill + (n_segs + 255) / 256), dim3(256), 0, stream, segs,
-                         n_segs, req_seg_off, n_segs, block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order,
+                         n_segs, req_seg_off, cu_q, n_segs, block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order,
                          pl.items, pl.tiles, pl.redo, n_redo, n_fill);
     return pl;
   }
   hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off);
   if (n_requests > 0)                                  // attention: the grid's y index walks requests
     hipLaunchKernelGGL(plan_order_kernel<true>, dim3((n_requests + 255) / 256), dim3(256), 0, stream, segs,
-                       req_seg_off, pl.seg_tile_off, n_requests, pl.order, pl.items);
+                       req_seg_off, cu_q, pl.seg_tile_off, n_requests, pl.order, pl.items);
   else                                                 // score: it walks segments
     hipLaunchKernelGGL(plan_order_kernel<false>, dim3((n_segs + 255) / 256), dim3(256), 0, stream, segs,
-                       req_seg_off, pl.seg_tile_off, n_segs, pl.order, pl.items);
+                       req_seg_off, cu_q, pl.seg_tile_off, n_segs, pl.order, pl.items);
   hipLaunchKernelGGL(plan_fill_kernel, dim3((max_tiles + 255) / 256), dim3(256), 0, stream, segs, n_segs,
                      pl.seg_tile_off, block_tab, n_blocks, max_tiles, pl.tiles, pl.redo, n_redo);
   return pl;
@@ -820,9 +823,9 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
   // tiles the wide one flagged (normally none: its workgroups read one flag and exit).
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && attn_v2_supported(ctx);
   const int n_redo = wide ? static_cast<int>(redo_entries(n_q_tot)) : 0;
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, block_tab, n_blocks, max_tiles, n_redo, stream);
+  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, cu_q, block_tab, n_blocks, max_tiles, n_redo, stream);
   if (wide)
-    launch_attn_v2(ctx, q, q_pos, cu_q, max_q_per_req, k_pool, v_pool, n_blocks, pl, req_seg_off, n_requests,
+    launch_attn_v2(ctx, q, q_pos, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, pl, req_seg_off, n_requests,
                    out, lse, pl.redo, q_map, map_pos, by != nullptr ? by->snap_index : nullptr,
                    by != nullptr ? by->cum : nullptr, by != nullptr ? by->s_max : 0, stream, vs);
   if (by != nullptr) {
@@ -850,7 +853,7 @@ void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) &&
                     (wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE);
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, 0, block_tab, n_blocks, max_tiles, n_redo, stream);
+  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, 0, nullptr, block_tab, n_blocks, max_tiles, n_redo, stream);
   if (wide)
     launch_score_v2(ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, pl.redo, stream);
   const int32_t* redo = pl.redo;

@@ -195,8 +195,8 @@ __device__ __forceinline__ f32x16 splat16(float v) {
 struct WorkItem {
   int32_t id;         // segment / request index
   int32_t kind;       // segment kind (score)
-  int32_t start;      // segment's logical start (score)
-  int32_t n_tokens;   // segment length (score)
+  int32_t start;      // segment's logical start (score); request's first row of the query list (attention)
+  int32_t n_tokens;   // segment length (score); rows of the request (attention)
   int32_t tok_off;    // segment's first row in per-token tensors (score)
   int32_t j_begin;    // first key tile of the request
   int32_t j_own;      // first tile of the segment itself (score); end of the request's tiles (attention)
@@ -205,10 +205,10 @@ struct WorkItem {
 static_assert(sizeof(WorkItem) == 32, "read as two 16-byte vectors");
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
 size_t plan_head_bytes(int n_segs);
-// n_requests > 0: dispatch order over requests (attention); 0: over segments (score).
+// n_requests > 0: dispatch order over requests (attention; cu_q delimits their rows); 0: over segments (score).
 // n_redo > 0: the plan also holds n_redo redo flags (after the tiles), cleared by the plan kernels.
 Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests,
-              const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream);
+              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream);
 
 // The wide attention kernel (64 query rows per wavefront) keeps one softmax reference per row; rows
 // whose sums leave the safe range are flagged in redo[] and redone by the narrow kernel, which can
@@ -217,8 +217,8 @@ Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_s
 __host__ __device__ inline int redo_index(int q0) { return q0 >> 5; }
 inline size_t redo_entries(int n_q_tot) { return static_cast<size_t>(n_q_tot) / 32 + 2; }
 
-void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
-                    int max_q_per_req, const void* k_pool, const void* v_pool, int n_blocks,
+void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
+                    int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool, int n_blocks,
                     const Plan& pl, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                     int32_t* redo, const int32_t* q_map, int map_pos, const int32_t* snap_index, float* cum,
                     int s_max, hipStream_t stream, const ValueSource& vs);

@@ -136,3 +136,32 @@ def test_matrix_products_of_every_tile_shape(op, n_out, rows, n_in):
     torch.cuda.synchronize()
     # half a unit in the last place of bf16, and fp32 sums of n_in products of size n_in^-1/2 in two orders
     assert float(((got.float() - want).abs() - 2.0 ** -8 * want.abs()).max()) <= 8 * n_in * 2.0 ** -24 * 4
+
+
+@pytest.mark.parametrize("lens,frac,question", [([5], 0.4, 1), ([64], 0.25, 15), ([70, 60], 0.25, 1), ([129, 1, 0, 190], 0.1, 33),
+                                                ([300], 0.4, 65), ([2000, 6250, 40], 0.004, 31)])
+def test_attention_in_two_key_streams(lens, frac, question):
+    # grids of a few workgroups (here: one to three row tiles of one KV head): the even and the odd 64-key tiles are
+    # walked apart.  One tile (an odd stream without keys), rows that see only the first tile, an odd count, rows
+    # around a 32-row tile, segments that end in either stream or have no tokens, more than 64 tiles per stream.
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("streams", "bf16", 4, 1, 128, 5.0e5, lens, [0] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [frac] * len(lens), question)], 1.0, seed=47)
+    b = DeviceBatch(w, poison=True)
+    b.rope_shift(); b.select(); b.gather(); b.sparse_prefill(); torch.cuda.synchronize()
+    sel = tuple(t.cpu().numpy()[: w.n_q_tot] for t in (b.sel_idx, b.q_row, b.q_pos, b.slot_map))
+    s = DeviceBatch(w, impl=P.CC_IMPL_SCALAR, poison=True)
+    s.rope_shift(); s.set_selection(*sel); s.gather(); s.sparse_prefill(); torch.cuda.synchronize()
+    n = w.n_q_tot
+    out, ref = b.out[:n].double(), s.out[:n].double()
+    assert float((out - ref).norm() / ref.norm()) <= H.TOL["bf16"]
+    # the rotated query is rounded to bf16 (a relative 2^-9 / sqrt(3) in the mean, per product of variance 1 / 128): a row
+    # that sees a single key shows it whole, 2^-9 / sqrt(3) = 1.1e-3; six of these
+    assert float((b.lse[:n] - s.lse[:n]).abs().max()) <= 6.8e-3
+    # the by-product form walks the same way: the same bits, and the question's masses of the separate kernel
+    out1, lse1, m1 = b.out[:n].clone(), b.lse[:n].clone(), s.question_mass().cpu()
+    m2 = b.sparse_prefill_mass().cpu()
+    assert torch.equal(out1, b.out[:n]) and torch.equal(lse1, b.lse[:n])
+    assert torch.isfinite(m2).all() and abs(float(m2.sum()) - question) <= 3e-3 * question
+    assert float((m1 - m2).abs().max()) <= 2e-2
