@@ -799,11 +799,12 @@ Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_s
   return pl;
 }
 
-// Fewest workgroups for which the wide SCORE kernel is chosen (three per compute unit of an MI355X:
-// below that the narrow kernel's twice as many, half as long workgroups fill the machine better;
-// measured on batches of 1-8 requests, 32 and 64 query heads: 10-25 % for the narrow kernel at
-// 200-600 workgroups, equal at ~800, 5-15 % for the wide one above).  The wide ATTENTION kernel is
-// faster at every size measured, down to 64 workgroups (7-25 %), so it has no such limit.
+// Fewest 128-token workgroups for which the wide SCORE kernel runs with four column blocks and one key stream (three
+// workgroups per compute unit of an MI355X); below that its small form (64 tokens, two key streams) fills the machine
+// better.  Whole cc_select call, narrow kernel (which ran there before, with a top-N that took 4-8 us longer) / small
+// form, us: 192 workgroups (5 x 512 tokens, 32 / 8 heads) 82 / 60, 384 (64 / 8 heads) 103 / 81, 96 (16 / 2) 98 / 57,
+// 320 (16 / 2, 9 x 1k) 254 / 162, 640 (9 x 1k, 32 / 8) 312 / 294; at 800 the four-column form is level with the narrow one.
+// The wide ATTENTION kernel is faster at every size measured, down to 64 workgroups (7-25 %), so it has no such limit.
 constexpr int kMinWideGrid = 768;
 
 bool attn_mfma_supported(const cc_ctx* ctx) { return group_supported(ctx); }
@@ -847,15 +848,15 @@ void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int
                        const int32_t* block_tab, const cc_segment* segs, int n_segs,
                        const int32_t* req_seg_off, int max_seg_tokens, float* mass,
                        void* plan_ws, int max_tiles, int n_tok, hipStream_t stream) {
-  // Wide kernel first where the head group allows it; the narrow kernel then redoes the granules
-  // the wide one flagged (normally none: its workgroups read two flags and exit).
+  // Wide kernel first where the head group allows it, in the form that suits the grid; the narrow kernel then
+  // redoes the granules the wide one flagged (normally none: its workgroups read two flags and exit).
   const int wide_wgs = ctx->cfg.n_q_heads / 4 * ((max_seg_tokens + 127) / 128) * n_segs;
-  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) &&
-                    (wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE);
+  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx);
+  const bool small = wide_wgs < kMinWideGrid && ctx->impl != CC_IMPL_MFMA_WIDE;
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
   const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, 0, nullptr, block_tab, n_blocks, max_tiles, n_redo, stream);
   if (wide)
-    launch_score_v2(ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, pl.redo, stream);
+    launch_score_v2(ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, pl.redo, small, stream);
   const int32_t* redo = pl.redo;
 #define CC_ARGS ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, redo, stream
   switch (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) {

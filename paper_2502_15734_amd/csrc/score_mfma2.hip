@@ -18,6 +18,10 @@
 // +-60) flags its tokens and the kernel that carries a movable reference redoes them (see the
 // launcher).
 //
+// Small grids take a second form: 64 tokens per workgroup and eight wavefronts, two key streams (see the kernel).
+// With one workgroup per compute unit the four-wavefront form has nothing to put beside its exponentials;
+// the second stream is that, and halves the chain of tiles: 5 x 512 tokens, 32 heads 66 -> 52 us (narrow kernel / this).
+//
 // Staging: four K-tile images in LDS (16 KiB each), filled by loads that write LDS directly
 // (global_load_lds, lane L of an instruction fills piece base + L):
 //   K piece (block b of 32 keys, k-step kk, half hh, MFMA row m):  (b*8+kk)*64 + hh*32 + m
@@ -36,8 +40,7 @@ namespace {
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-constexpr int kQB = 4;            // 32-token column blocks per wavefront
-constexpr int kTQ = 32 * kQB;     // tokens per workgroup
+constexpr int kFullQB = 4, kSmallQB = 2;   // 32-token column blocks per wavefront: big grids, small ones
 constexpr int kImageK = 1024;     // 16-byte pieces per K tile image
 constexpr int kBufs = 4;
 constexpr int kDepth = 4;         // operand reads in flight ahead of the MFMAs (each feeds four of them)
@@ -84,19 +87,26 @@ __device__ __forceinline__ u32x4 lds_to_acc(const uint4* p) {
   return r;
 }
 
-// RAGGED = false: the workgroups whose four column blocks all hold tokens of the chunk (straight-line
-//                  loop body; a chunk's last workgroup leaves at once if it holds fewer).
-// RAGGED = true : one workgroup per (segment, head group) for exactly those last workgroups: the
-//                  column blocks past the chunk's end cost no MFMA and no exponential (uniform
-//                  branches around them, which the straight-line form does not have to carry).
-template <bool RAGGED>
-__global__ __launch_bounds__(256, 2) void score_v2_kernel(
+// MODE = kFull: the workgroups whose column blocks all hold tokens of the chunk (straight-line
+//                loop body; a chunk's last workgroup leaves at once if it holds fewer).
+// MODE = kLast: one workgroup per (segment, head group) for exactly those last workgroups: the
+//                column blocks past the chunk's end cost no MFMA and no exponential (uniform
+//                branches around them, which the straight-line form does not have to carry).
+// MODE = kAny : all workgroups in one launch, with those branches (small grids: a launch costs more).
+// KS = 2: twice the wavefronts; 0-3 walk the even key tiles, 4-7 the odd ones, each stream with images of its
+// own.  No reference is subtracted, so the streams' sums are just added at the end.
+enum { kFull = 0, kLast = 1, kAny = 2 };
+template <int MODE, int kQB, int KS>
+__global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_pool, int n_blocks,
     const TileDesc* __restrict__ tiles, int max_tiles,
     const WorkItem* __restrict__ items, int hq, int hkv, int n_sub, int n_tiles_x,
     InvFreq inv_freq, float* __restrict__ mass, int32_t* __restrict__ redo) {
-  __shared__ uint4 lds_all[kBufs * kImageK];
-  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  constexpr int kTQ = 32 * kQB;               // tokens per workgroup
+  constexpr bool RAGGED = MODE != kFull;
+  __shared__ uint4 lds_all[KS * kBufs * kImageK];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = uniform(tid >> 6) & 3, ks = KS == 1 ? 0 : uniform(tid >> 8);      // head of the four; key stream
   const int n = lane & 31, hh = lane >> 5;
   const int per_tile = hkv * n_sub;
   const int rem = blockIdx.x % per_tile;
@@ -110,13 +120,13 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
   const uint4 i0 = ip[0], i1 = ip[1];
   const int sg_kind = uniform(i0.y), sg_start = uniform(i0.z), sg_ntok = uniform(i0.w);
   const int sg_tok_off = uniform(i1.x), j_begin = uniform(i1.y), j_own = uniform(i1.z);
-  // (RAGGED: the grid has one x-row per head group, and the tile is the chunk's last)
-  const int tile = RAGGED ? max(sg_ntok - 1, 0) / kTQ : n_tiles_x - 1 - blockIdx.x / per_tile;    // late (long) tiles are dispatched first
+  // (kLast: the grid has one x-row per head group, and the tile is the chunk's last)
+  const int tile = MODE == kLast ? max(sg_ntok - 1, 0) / kTQ : n_tiles_x - 1 - blockIdx.x / per_tile;    // late (long) tiles are dispatched first
   const int t0 = tile * kTQ;
   if (sg_kind != CC_SEG_CHUNK || t0 >= sg_ntok || sg_start == 0) return;
   // column blocks that hold tokens of the chunk
   const int n_cols = uniform((min(t0 + kTQ, sg_ntok) - t0 + 31) >> 5);
-  if (RAGGED ? n_cols == kQB : n_cols < kQB) return;
+  if (MODE == kLast ? n_cols == kQB : MODE == kFull && n_cols < kQB) return;
   // token of column block qb in this lane (clamped into the chunk)
   auto token = [&](int qb) __attribute__((always_inline)) { return min(t0 + 32 * qb + n, sg_ntok - 1); };
   const int p_min = sg_start + t0;
@@ -126,11 +136,14 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
   const int n_t = uniform(min(j_own + (p_max - sg_start) / kTile + 1, max_tiles) - j_begin);
   const int t_own = uniform(j_own - j_begin);                         // first tile of the token's own chunk
   if (n_t <= 0) return;
+  // iterations, and the one in which this wavefront's stream enters the token's own chunk (n_it: never)
+  const int n_it = (n_t + KS - 1) / KS;
+  const int it_own = KS == 1 ? t_own : (t_own - ks + 1) >> 1;
 
   // ---- load the query rows, rotate them to their positions, fold the softmax scale -------------
   // lane (n, hh) keeps, for k-step kk, dims 16kk + 8hh .. +7; dims < 64 pair with dims + 64.
   const float c2 = 0.08838834764831845f * kLog2e;            // log2(e) / sqrt(128)
-  __shared__ uint4 q_bounce[256];     // one piece per lane: the way into the accumulation registers
+  __shared__ uint4 q_bounce[256 * KS];     // one piece per lane: the way into the accumulation registers
   u32x4 qreg[kQB][8];
   // (called after the first tile loads are on their way, so that the trigonometry hides their latency)
   // The four column blocks of a lane sit 32 positions apart, so only the first block's angles take
@@ -190,8 +203,14 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
   // The descriptors of 64 consecutive tiles sit in vector registers, one tile per lane, and are
   // handed out with v_readlane: no memory access per tile.
   int win_base = 0;
-  TileDesc win = fetch_desc(tiles, j_begin + min(lane, n_t - 1), max_tiles);
-  auto desc_of = [&](int t) __attribute__((always_inline)) {           // t in [win_base, win_base + 64)
+  TileDesc win;
+  auto fill_window = [&](int base) __attribute__((always_inline)) {
+    const int j = KS * (base + lane) + ks;
+    win = fetch_desc(tiles, j_begin + min(j, n_t - 1), max_tiles);
+    if (KS > 1 && j >= n_t) win.nvalid = 0;            // (the odd stream may have one tile less: it is masked as a whole)
+  };
+  fill_window(0);
+  auto desc_of = [&](int t) __attribute__((always_inline)) {           // t: tile of the stream, in [win_base, win_base + 64)
     const int l = t - win_base;
     TileDesc d;
     d.kpos0 = __builtin_amdgcn_readlane(win.kpos0, l);
@@ -201,7 +220,7 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
     d.seg = 0; d.pad = 0;
     return d;
   };
-  auto image_off = [&](int t) __attribute__((always_inline)) { return (t & (kBufs - 1)) * (kImageK * 16); };   // bytes
+  auto image_off = [&](int t) __attribute__((always_inline)) { return (ks * kBufs + (t & (kBufs - 1))) * (kImageK * 16); };   // bytes
   // Loads of one K tile, straight into image `img_off`.  Wavefront w brings operand groups
   // 4w..4w+3: lane (hh, m) of group (b, kk) reads slot swap23(m % 16) of page 2b + m / 16, 16 bytes
   // at dim 16kk + 8hh.
@@ -278,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
   };
 
   // ---- prologue: images 0, 1, 2 ---------------------------------------------------------------------
-  TileDesc d0 = desc_of(0), d1 = desc_of(min(1, n_t - 1)), d2 = desc_of(min(2, n_t - 1)), d3 = d2;
+  TileDesc d0 = desc_of(0), d1 = desc_of(min(1, n_it - 1)), d2 = desc_of(min(2, n_it - 1)), d3 = d2;
   dma_tile(d0, image_off(0));
   dma_tile(d1, image_off(1));
   dma_tile(d2, image_off(2));
@@ -289,21 +308,21 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
   for (int s = 0; s < kDepth; ++s) ring[s] = piece(image_off(0), s);
 
   // ---- the tile loop --------------------------------------------------------------------------------
-  for (int t = 0; t < n_t; ++t) {
+  for (int t = 0; t < n_it; ++t) {
     const int img = image_off(t);
-    const int nimg = t + 1 < n_t ? image_off(t + 1) : img;
+    const int nimg = t + 1 < n_it ? image_off(t + 1) : img;
     if (t + 3 - win_base >= 64) {                        // next 64 descriptors (rare)
       win_base += 64;
-      win = fetch_desc(tiles, j_begin + min(win_base + lane, n_t - 1), max_tiles);
+      fill_window(win_base);
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));      // vmcnt(0) here, so the hot path never waits for it
     }
     // entering the token's own chunk: everything summed so far is prior-chunk mass
-    if (t == t_own) {
+    if (t == it_own) {
 #pragma unroll
       for (int qb = 0; qb < kQB; ++qb) { l_prior[qb] = l_run[qb]; l_run[qb] = 0.f; }
     }
     // loads of image t+3 (past the last tile they repeat the last tile into an image nobody reads)
-    d3 = desc_of(min(t + 3, n_t - 1));
+    d3 = desc_of(min(t + 3, n_it - 1));
     dma_tile(d3, image_off(t + 3));
     block(img, 0, img, 1, d0);
     block(img, 1, nimg, 0, d0);
@@ -314,6 +333,27 @@ __global__ __launch_bounds__(256, 2) void score_v2_kernel(
   }
 
   // ---- epilogue ---------------------------------------------------------------------------------
+  wait_loads(std::integral_constant<int, 0>{});        // (nothing may still be landing when the LDS is given back)
+  if constexpr (KS == 2) {
+    if (it_own >= n_it) {                                // (no tile of the chunk itself in this stream)
+#pragma unroll
+      for (int qb = 0; qb < kQB; ++qb) { l_prior[qb] = l_run[qb]; l_run[qb] = 0.f; }
+    }
+    float2* share = reinterpret_cast<float2*>(q_bounce) + wave * (kQB * 64) + lane;
+    static_assert(4 * kQB * 64 * sizeof(float2) <= sizeof(q_bounce), "the odd stream's sums must fit");
+    if (ks == 1) {
+#pragma unroll
+      for (int qb = 0; qb < kQB; ++qb) share[qb * 64] = make_float2(l_prior[qb], l_run[qb]);
+    }
+    __syncthreads();
+    if (ks == 1) return;
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) {
+      const float2 o = share[qb * 64];
+      l_prior[qb] += o.x;
+      l_run[qb] += o.y;
+    }
+  }
   bool bad = false;
   float lp[kQB], lt[kQB];
 #pragma unroll
@@ -344,22 +384,27 @@ bool score_v2_supported(const cc_ctx* ctx) {
 
 void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks, const Plan& pl,
                      const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int max_seg_tokens,
-                     float* mass, int32_t* redo, hipStream_t stream) {
+                     float* mass, int32_t* redo, bool small, hipStream_t stream) {
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4;
-  const int n_tiles = (max_seg_tokens + kTQ - 1) / kTQ;
-  dim3 grid(hkv * n_sub * n_tiles, n_segs);
+  const int tq = 32 * (small ? kSmallQB : kFullQB);
+  const int n_tiles = (max_seg_tokens + tq - 1) / tq;
+  const dim3 grid(hkv * n_sub * n_tiles, n_segs);
+#define CC_LAUNCH(GRID, KS, ...)                                                                              \
+  hipLaunchKernelGGL((score_v2_kernel<__VA_ARGS__, KS>), GRID, dim3(256 * KS), 0, stream, static_cast<const bf16_t*>(q), \
+                     static_cast<const bf16_t*>(k_pool), n_blocks, pl.tiles, pl.max_tiles, pl.items,           \
+                     ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq, mass, redo)
+  if (small) {
+    CC_LAUNCH(grid, 2, kAny, kSmallQB);
+    return;
+  }
   // The chunks' last, partly empty workgroups run as a launch of their own behind the others, so that
   // the straight-line body of the full workgroups does not have to carry the branches that skip empty
   // column blocks (inside one kernel those branches, or a second copy of the loop, cost the full
   // workgroups 4-5 %).  (Run beside the first launch on a second stream instead, the second launch
   // gains another 1 % of the call on the 8B batch: not worth a stream of the library's own.)
-  hipLaunchKernelGGL(score_v2_kernel<false>, grid, dim3(256), 0, stream, static_cast<const bf16_t*>(q),
-                     static_cast<const bf16_t*>(k_pool), n_blocks, pl.tiles, pl.max_tiles,
-                     pl.items, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq,
-                     mass, redo);
-  hipLaunchKernelGGL(score_v2_kernel<true>, dim3(hkv * n_sub, n_segs), dim3(256), 0, stream,
-                     static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k_pool), n_blocks, pl.tiles,
-                     pl.max_tiles, pl.items, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq, mass, redo);
+  CC_LAUNCH(grid, 1, kFull, kFullQB);
+  CC_LAUNCH(dim3(hkv * n_sub, n_segs), 1, kLast, kFullQB);
+#undef CC_LAUNCH
 }
 
 }  // namespace cc

@@ -165,3 +165,27 @@ def test_attention_in_two_key_streams(lens, frac, question):
     assert torch.equal(out1, b.out[:n]) and torch.equal(lse1, b.lse[:n])
     assert torch.isfinite(m2).all() and abs(float(m2.sum()) - question) <= 3e-3 * question
     assert float((m1 - m2).abs().max()) <= 2e-2
+
+
+@pytest.mark.parametrize("hq", [4, 8])
+@pytest.mark.parametrize("lens", [[5, 3], [64, 64], [1, 129], [63, 65, 1, 0, 190], [128, 130], [2000, 6250, 40]])
+def test_scores_in_two_key_streams(hq, lens):
+    # grids below the wide form's: 64-token workgroups whose even and odd 64-key tiles are walked apart.  A stream without
+    # tiles of the chunk itself or with one tile less, chunks around a 32-token column block and a 64-token tile, a
+    # segment without tokens, more than 64 tiles per stream.
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("scores2", "bf16", hq, 1, 128, 5.0e5, lens, [7] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [0.2] * len(lens), 9)], 1.0, seed=53)
+    for gain in (1.0, 40.0):
+        got = []
+        for impl in (P.CC_IMPL_AUTO, P.CC_IMPL_MFMA_NARROW):
+            b = DeviceBatch(w, impl=impl, poison=True)
+            b.q.mul_(gain)
+            b.rope_shift(); b.select(); torch.cuda.synchronize()
+            got.append(b.scores.cpu().double())
+        # both round the rotated query to bf16, from angles that differ by 1e-6: about one row in sixteen gets one element that
+        # rounds the other way, 2^-8 of a product of 0.1 in a logit, a quarter of that in one head's mass, a few times that at
+        # worst; larger queries (some sums leave the safe range and are redone) in proportion
+        assert torch.isfinite(got[0]).all() and float((got[0] - got[1]).abs().max()) <= 2e-4 * gain
+        assert float(got[1].max()) > 0.1
