@@ -674,6 +674,7 @@ exp_step(0, i);
   float4* scratch = reinterpret_cast<float4*>(lds_all);
   float other[2][16];                                        // KS = 2: what the other stream has of this wavefront's two dim groups
   float w_other = 0.f, m_all = m_ref;
+  bool none = false;                                         // KS = 2: the row sees no key of this stream
   if constexpr (KS == 2) {
     // stream 0 finishes dims 0 .. 63, stream 1 dims 64 .. 127: each hands the other half of its output over
     float2* ml = reinterpret_cast<float2*>(reinterpret_cast<char*>(lds_all) + 131072);
@@ -698,7 +699,16 @@ exp_step(0, i);
         const float4 v = take[(d * 4 + i) * 64];
         other[d][4 * i] = v.x; other[d][4 * i + 1] = v.y; other[d][4 * i + 2] = v.z; other[d][4 * i + 3] = v.w;
       }
-    // (a stream of which the row sees nothing has sum 0 and does not count)
+    // (a stream of which the row sees nothing has sum 0 and does not count.  By selection and not by a weight of 0: such a
+    // stream may have multiplied values of a tile behind the workgroup's last position by its zeros, and these
+    // need not be finite)
+    none = l_tot == 0.f;
+    if (theirs.y == 0.f) {
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) other[d][i] = 0.f;
+    }
     m_all = l_tot == 0.f ? theirs.x : theirs.y == 0.f ? m_ref : fmaxf(m_ref, theirs.x);
     const float a = l_tot == 0.f ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_all);
     const float b = theirs.y == 0.f ? 0.f : __builtin_amdgcn_exp2f(theirs.x - m_all);
@@ -725,7 +735,7 @@ exp_step(0, i);
         for (int e = 0; e < 4; ++e) {
           // accumulator register i holds output dim 32db + 8(i/4) + 4hh + i%4
           if constexpr (KS == 1) v4[e] = static_cast<bf16_t>(o[d][4 * g4 + e] * scale);
-          else v4[e] = static_cast<bf16_t>((ks == 0 ? o[d][4 * g4 + e] : o[2 + d][4 * g4 + e]) * scale + other[d][4 * g4 + e] * w_other);
+          else v4[e] = static_cast<bf16_t>((none ? 0.f : (ks == 0 ? o[d][4 * g4 + e] : o[2 + d][4 * g4 + e]) * scale) + other[d][4 * g4 + e] * w_other);
         }
         const int c = 4 * (KS == 1 ? d : 2 * ks + d) + g4;
         *reinterpret_cast<uint2*>(rows + en * 256 + ((c ^ (en & 15)) << 4) + 8 * eh) = *reinterpret_cast<uint2*>(v4);

@@ -189,3 +189,34 @@ def test_scores_in_two_key_streams(hq, lens):
         # worst; larger queries (some sums leave the safe range and are redone) in proportion
         assert torch.isfinite(got[0]).all() and float((got[0] - got[1]).abs().max()) <= 2e-4 * gain
         assert float(got[1].max()) > 0.1
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv,lens,fracs,cut", [
+    # two key streams: 32 rows that see the first 64-key tile only, tiles of both streams behind it
+    ("bf16", 128, 4, 1, [64, 70], [0.5, 0.1], 64), ("bf16", 128, 8, 2, [64, 300, 20], [0.5, 0.1, 0.3], 64)])
+def test_values_behind_a_rows_position_do_not_reach_it(dtype, d, hq, hkv, lens, fracs, cut):
+    # values of every token at position `cut` and later are not finite; rows in front of it must be what they are without
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("behind", dtype, hq, hkv, d, 1.0e4, lens, [2] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), fracs, 5)], 1.0, seed=61)
+    b = DeviceBatch(w, poison=True)
+    b.rope_shift(); b.select()
+    got = []
+    for plant in (False, True):
+        if plant:
+            bad = [float("nan"), float("inf"), -float("inf")]
+            pos = 0
+            for c, n in enumerate(lens):
+                for t in range(max(cut - pos, 0), n):
+                    blk = int(w.store_tab[int(w.store_tab_off[c]) + t // 16])
+                    b.v_store[blk, :, :, t % 16] = bad[t % 3]
+                pos += n
+            b.v_new[cut:] = bad[0]
+            b.rope_shift()                                       # (the value map points into the store again)
+        b.sparse_prefill_fused(); torch.cuda.synchronize()
+        n = w.n_q_tot
+        front = b.q_pos[:n] < cut
+        got.append((b.out[:n][front].clone(), b.lse[:n][front].clone()))
+    assert int(front.sum()) > 0 and torch.isfinite(got[0][0]).all()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
