@@ -125,6 +125,36 @@ __global__ __launch_bounds__(256) void qk_f32_kernel(
       for (int c = 0; c < kC; ++c) vr[b][c] = load4(vp + 16 * c * kBlock);
     }
   };
+  // A row takes nothing from a key behind its position, but the product would give it 0 x value, and the value
+  // need not be finite.  So in a block of which some row sees only a part, values that are not finite leave the
+  // product; the rows that see their key (the first n_vis of the block) get them here.
+  auto select_not_finite = [&](int b, const f32x4& w, int n_vis) __attribute__((always_inline)) {
+    auto finite = [](float v) __attribute__((always_inline)) { return fabsf(v) < INFINITY; };
+    bool all = true;
+#pragma unroll
+    for (int c = 0; c < (SCORE ? 0 : kC); ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) all = all && finite(vr[b][c][e]);
+    if (__all(all)) return;
+#pragma unroll 1
+    for (int gk = 0; gk < 4; ++gk)                   // lanes (., gk) hold the values and weights of keys 4 gk + e
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float we = __shfl(w[e], n + 16 * gk, 64);
+        const bool sees = 4 * gk + e < n_vis;
+#pragma unroll
+        for (int c = 0; c < (SCORE ? 0 : kC); ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float v = __shfl(vr[b][c][e], 4 * g + i + 16 * gk, 64);
+            if (sees && !finite(v)) o[c][i] += we * v;
+          }
+      }
+#pragma unroll
+    for (int c = 0; c < (SCORE ? 0 : kC); ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vr[b][c][e] = finite(vr[b][c][e]) ? vr[b][c][e] : 0.f;
+  };
   auto use_block = [&](int b, const BlockItem& it) __attribute__((always_inline)) {
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -167,6 +197,7 @@ __global__ __launch_bounds__(256) void qk_f32_kernel(
 #pragma unroll
           for (int i = 0; i < 4; ++i) vr[b][c][i] = 4 * g + i < it.nvalid ? vr[b][c][i] : 0.f;
       }
+      if (__any(lim + 4 * g < it.nvalid)) select_not_finite(b, s, lim + 4 * g);
 #pragma unroll
       for (int c = 0; c < kC; ++c)
 #pragma unroll

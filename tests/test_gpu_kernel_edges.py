@@ -193,7 +193,10 @@ def test_scores_in_two_key_streams(hq, lens):
 
 @pytest.mark.parametrize("dtype,d,hq,hkv,lens,fracs,cut", [
     # two key streams: 32 rows that see the first 64-key tile only, tiles of both streams behind it
-    ("bf16", 128, 4, 1, [64, 70], [0.5, 0.1], 64), ("bf16", 128, 8, 2, [64, 300, 20], [0.5, 0.1, 0.3], 64)])
+    ("bf16", 128, 4, 1, [64, 70], [0.5, 0.1], 64), ("bf16", 128, 8, 2, [64, 300, 20], [0.5, 0.1, 0.3], 64),
+    # fp32 arithmetic: rows in front of and behind `cut` share a 16-row tile, `cut` inside and at the edge of a 16-token block
+    ("f32", 64, 4, 2, [40, 30], [0.5, 0.2], 37), ("f32", 128, 3, 1, [21, 300, 20], [0.4, 0.02, 0.3], 16),
+    ("bf16", 64, 6, 2, [40, 30], [0.5, 0.2], 37), ("bf16", 128, 3, 1, [700, 5], [0.01, 0.4], 301)])
 def test_values_behind_a_rows_position_do_not_reach_it(dtype, d, hq, hkv, lens, fracs, cut):
     # values of every token at position `cut` and later are not finite; rows in front of it must be what they are without
     import paper_2502_15734_amd as P
@@ -220,3 +223,32 @@ def test_values_behind_a_rows_position_do_not_reach_it(dtype, d, hq, hkv, lens, 
         got.append((b.out[:n][front].clone(), b.lse[:n][front].clone()))
     assert int(front.sum()) > 0 and torch.isfinite(got[0][0]).all()
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("dtype,d,hq,hkv", [("f32", 64, 4, 2), ("f32", 128, 3, 1), ("bf16", 64, 6, 2), ("bf16", 128, 3, 1)])
+def test_fp32_arithmetic_gives_values_that_are_not_finite_to_the_rows_that_see_them(dtype, d, hq, hkv):
+    # single dimensions of single tokens, one or two in a block; rows in front of, at and behind each of them in one tile
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("infs", dtype, hq, hkv, d, 1.0e4, [70, 90], [2, 2], [W.RequestSpec([0, 1], [0.3, 0.2], 20)], 1.0, seed=67)
+    bad = [float("nan"), float("inf"), -float("inf")]
+    got = []
+    for impl in (P.CC_IMPL_AUTO, P.CC_IMPL_SCALAR):
+        b = DeviceBatch(w, impl=impl, poison=True)
+        for i, (c, t) in enumerate([(0, 9), (0, 33), (0, 34), (1, 0), (1, 15), (1, 88)]):
+            b.v_store[int(w.store_tab[int(w.store_tab_off[c]) + t // 16]), :, (11 * i) % d, t % 16] = bad[i % 3]
+        b.v_new[163, :, 5 + 16] = bad[1]                          # a token of the question (positions 160 to 179)
+        b.rope_shift(); b.select()
+        if got:
+            b.set_selection(*got[0][0])
+        sel = tuple(t.cpu().numpy()[: w.n_q_tot] for t in (b.sel_idx, b.q_row, b.q_pos, b.slot_map))
+        b.sparse_prefill_fused(); torch.cuda.synchronize()
+        got.append((sel, b.out.cpu().double(), b.lse.cpu()))
+    a, s = got[0][1], got[1][1]
+    assert not torch.isfinite(s).all() and torch.isfinite(s).any(dim=-1).all()
+    for what in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(what(a), what(s))
+    ok = torch.isfinite(s)
+    # (two orders of fp32 sums over 180 keys, and a rounding of a bf16 output that may flip)
+    assert float((a - s)[ok].norm() / s[ok].norm()) <= 8 * math.sqrt(180) * 2.0 ** -24 + 1e-6 + (2.0 ** -9 if dtype == "bf16" else 0.0)
+    assert torch.isfinite(got[0][2]).all()
