@@ -146,9 +146,10 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
   __shared__ uint4 q_bounce[256 * KS];     // one piece per lane: the way into the accumulation registers
   u32x4 qreg[kQB][8];
   // (called after the first tile loads are on their way, so that the trigonometry hides their latency)
-  // The four column blocks of a lane sit 32 positions apart, so only the first block's angles take
+  // The column blocks of a lane sit 32 positions apart.  With four of them only the first block's angles take
   // the double-precision path; each further block turns them by the fixed angle 32 f (a single-
-  // precision product is exact enough for that small angle).  Columns past the chunk's end get a
+  // precision product is exact enough for that small angle).  The small form takes every angle in double precision, like
+  // the narrow kernel whose grids it runs.  Columns past the chunk's end get a
   // query row and a position that do not belong together; nothing of theirs is written.
   auto load_queries = [&]() __attribute__((always_inline)) {
     const bf16_t* qp[kQB];
@@ -169,6 +170,7 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
         const double f = inv_freq.f[16 * kk + 8 * hh + j];
         rot_cos_sin_fast(sg_start + t0 + n, f, &cs[j], &sn[j]);
         cs[j] *= c2; sn[j] *= c2;
+        if (kQB == kSmallQB) continue;
         const float turn = static_cast<float>(f) * (32.f * 0.15915494309189535f);    // revolutions
         ct[j] = __builtin_amdgcn_cosf(turn);
         st[j] = __builtin_amdgcn_sinf(turn);
@@ -180,6 +182,13 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
           const float x = static_cast<float>(xv[qb][j]), y = static_cast<float>(yv[qb][j]);
           xv[qb][j] = static_cast<bf16_t>(x * cs[j] - y * sn[j]);
           yv[qb][j] = static_cast<bf16_t>(y * cs[j] + x * sn[j]);
+          if (kQB == kSmallQB) {
+            if (qb + 1 < kQB) {
+              rot_cos_sin_fast(sg_start + t0 + 32 * (qb + 1) + n, inv_freq.f[16 * kk + 8 * hh + j], &cs[j], &sn[j]);
+              cs[j] *= c2; sn[j] *= c2;
+            }
+            continue;
+          }
           const float c = cs[j], s_ = sn[j];
           cs[j] = c * ct[j] - s_ * st[j];
           sn[j] = s_ * ct[j] + c * st[j];
