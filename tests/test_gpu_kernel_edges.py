@@ -254,3 +254,27 @@ def test_fp32_arithmetic_gives_values_that_are_not_finite_to_the_rows_that_see_t
     # (two orders of fp32 sums over 180 keys, and a rounding of a bf16 output that may flip)
     assert float((a - s)[ok].norm() / s[ok].norm()) <= 8 * math.sqrt(180) * 2.0 ** -24 + 1e-6 + (2.0 ** -9 if dtype == "bf16" else 0.0)
     assert torch.isfinite(got[0][2]).all()
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(64, 4, 2), (64, 8, 2), (128, 3, 1)])
+@pytest.mark.parametrize("lens", [[20, 36], [17, 60, 45], [150, 200, 180]])
+def test_fp32_arithmetic_is_no_further_from_64_bits_than_the_scalar_kernels(d, hq, hkv, lens):
+    # (both read the same fp32 keys and values; a logit summed in one chain of d additions fails this on the short prompts)
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("err", "f32", hq, hkv, d, 1.0e4, lens, [3] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [0.2] * len(lens), 20)], 1.0, seed=71)
+    err, sel = [], None
+    for impl in (P.CC_IMPL_AUTO, P.CC_IMPL_SCALAR):
+        b = DeviceBatch(w, impl=impl, cow=False)
+        b.rope_shift()
+        if sel is None:
+            b.select()
+            sel = tuple(t.cpu().numpy()[: w.n_q_tot] for t in (b.sel_idx, b.q_row, b.q_pos, b.slot_map))
+        else:
+            b.set_selection(*sel)
+        b.sparse_prefill_fused(); torch.cuda.synchronize()
+        k, v = H.request_context_from_pools(w, 0, b.k_req.cpu().double().numpy(), b.v_req.cpu().double().numpy())
+        out, _ = O.causal_attention_rows_dense(O.rotate(w.q[sel[1]].astype(np.float64), sel[2], 1.0e4), sel[2], k, v)
+        err.append(H.rel_l2(b.out.cpu().numpy(), out))
+    assert err[0] <= err[1], err
