@@ -121,10 +121,14 @@ const char* cc_last_error(const cc_ctx* ctx);
  * picks the fastest MFMA kernels built for the configuration (bf16 arithmetic for bf16 tensors with
  * head_dim 128 and head groups of 1, 2, 4 or 8, fp32 arithmetic for everything else),
  * CC_IMPL_SCALAR forces the plain ones, CC_IMPL_MFMA_NARROW the MFMA kernels that give a
- * wavefront 32 query rows (64 tokens in the score stage; the only MFMA form for head groups of
- * 1 or 2), CC_IMPL_MFMA_WIDE the ones that give it 64 (128) even where AUTO would find the
- * launch of the score stage too small for them (head groups that are a multiple of 4; narrow
- * otherwise). */
+ * workgroup one head group and 32 query rows (64 tokens in the score stage; the only MFMA form for
+ * head groups of 1 or 2).  For head groups that are a multiple of 4 AUTO runs the wide kernels: four
+ * heads and 64 rows (128 tokens) per workgroup, or, on grids that leave compute units idle, a form with
+ * half of that whose key tiles are walked in two streams; CC_IMPL_MFMA_WIDE runs the first of these at
+ * every size (narrow kernels for other head groups).  The forms sum in different orders, and P is
+ * rounded to bf16 against another softmax reference, so with AUTO the last bits of a request's results
+ * depend on the size of the batch it runs in (cc_linear, cc_qkv_project and cc_gated_linear: on n_rows,
+ * which decides the tile and the split of the contraction). */
 int cc_set_impl(cc_ctx* ctx, int impl);
 
 /* ---- (a) re-position cached keys ----------------------------------------------------------

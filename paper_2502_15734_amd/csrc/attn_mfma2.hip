@@ -771,7 +771,8 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
                     int s_max, hipStream_t stream, const ValueSource& vs) {
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4;
   const int row_tiles = std::min((max_q_per_req + 63) / 64 * n_requests, n_q_tot / 64 + n_requests);
-  const bool two_streams = static_cast<int64_t>(row_tiles) * hkv * n_sub <= kTwoStreamGrid;
+  // (CC_IMPL_MFMA_WIDE: the one-stream form at every size, as the score stage runs its 128-token form then)
+  const bool two_streams = static_cast<int64_t>(row_tiles) * hkv * n_sub <= kTwoStreamGrid && ctx->impl != CC_IMPL_MFMA_WIDE;
 #define CC_GO(KS, BY, TQ)                                                                                          \
   do {                                                                                                         \
     const int n_tiles = (max_q_per_req + TQ - 1) / TQ;                                                         \

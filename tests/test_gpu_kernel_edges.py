@@ -278,3 +278,49 @@ def test_fp32_arithmetic_is_no_further_from_64_bits_than_the_scalar_kernels(d, h
         out, _ = O.causal_attention_rows_dense(O.rotate(w.q[sel[1]].astype(np.float64), sel[2], 1.0e4), sel[2], k, v)
         err.append(H.rel_l2(b.out.cpu().numpy(), out))
     assert err[0] <= err[1], err
+
+
+def test_wide_runs_the_form_of_large_grids_at_every_size():
+    # one request alone, asked for the wide kernels, and as one of 32 equal ones whose grid AUTO gives to the same form
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    got = []
+    for n, impl in ((1, P.CC_IMPL_MFMA_WIDE), (32, P.CC_IMPL_AUTO)):
+        w = W.custom("alone", "bf16", 8, 2, 128, 5.0e5, [300, 290, 210], [4, 4, 4],
+                     [W.RequestSpec([0, 1, 2], [0.2, 0.2, 0.2], 30)] * n, 1.0 / math.sqrt(128), seed=83)
+        one = w.n_tok // n
+        rng = np.random.default_rng(5)
+        for t in (w.q, w.k_new, w.v_new):
+            t[:] = np.tile(rng.standard_normal((one,) + t.shape[1:]).astype(t.dtype), (n, 1, 1))
+        b = DeviceBatch(w, impl=impl, poison=True)
+        b.rope_shift(); b.select_from_scores(torch.from_numpy(np.tile(rng.random(one).astype(np.float32), n)).cuda())
+        b.sparse_prefill_fused(); torch.cuda.synchronize()
+        m = w.n_q_tot // n
+        got.append((b.out[:m].clone(), b.lse[:m].clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("impl", ["AUTO", "MFMA_WIDE"])
+@pytest.mark.parametrize("low", [(0, 32), (64, 96), (64, 128)])
+def test_rows_whose_reference_lies_far_below_later_keys(impl, low):
+    # keys with logits around -100 in the first block of the even (or only) or of the odd key stream: its sums leave fp32's
+    # range and the rows are redone by the kernel that moves its reference
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("lowref2", "bf16", 8, 2, 128, 5.0e5, [300, 180, 150], [0, 0, 0],
+                 [W.RequestSpec([0, 1, 2], [0.25, 0.25, 0.25], 40)], 1.0 / math.sqrt(128), seed=21)
+    w.q[:, :, 60:64] = 2.0
+    w.q[:, :, 124:128] = 0.0
+    blocks = w.store_tab[w.store_tab_off[0]: w.store_tab_off[1]]
+    for t in range(*low):
+        w.k_store[blocks[t // 16], :, t % 16, 60:64] = -141.0
+        w.k_store[blocks[t // 16], :, t % 16, 124:128] = 0.0
+    w.k_new[low[0]:low[1], :, 60:64] = -141.0
+    w.k_new[low[0]:low[1], :, 124:128] = 0.0
+    b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+    b.step(); torch.cuda.synchronize()
+    ref = O.run_request(w, 0, selected_override=H.gpu_selection(w, b.sel_idx.cpu().numpy())[0])
+    assert H.rel_l2(b.out.float().cpu().numpy(), ref.out) <= H.TOL["bf16"]
+    # (rows that see nothing but such keys: bf16 keys of magnitude 141, half a unit in the last place of four of them)
+    only = (ref.q_pos < low[1]) if low[0] == 0 else np.zeros(len(ref.q_pos), dtype=bool)
+    assert (np.abs(b.lse.cpu().numpy() - ref.lse) <= np.where(only[:, None], 0.8, 2e-3)).all()
