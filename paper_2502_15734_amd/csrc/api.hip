@@ -184,7 +184,7 @@ int cc_select(cc_ctx* ctx, const void* q, int32_t n_tok, const void* k_pool, int
       cc::align_up(static_cast<size_t>(n_tok) * ctx->cfg.n_q_heads * sizeof(float), 256));
   void* plan_ws = reinterpret_cast<char*>(keys) + cc::align_up(static_cast<size_t>(n_tok) * sizeof(uint32_t), 256);
   if (ctx->impl != CC_IMPL_SCALAR && cc::score_mfma_supported(ctx))
-    cc::launch_score_mfma(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off,
+    cc::launch_score_mfma(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off, n_requests,
                           max_seg_tokens, mass, plan_ws, max_tiles_for(n_tok, n_segs), n_tok, st);
   else
     cc::launch_score_plain(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off,

@@ -72,7 +72,7 @@ bool score_mfma_supported(const cc_ctx* ctx);
 size_t mfma_plan_bytes(int n_segs, int max_tiles, int n_q_max);
 void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
                        const int32_t* block_tab, const cc_segment* segs, int n_segs,
-                       const int32_t* req_seg_off, int max_seg_tokens, float* mass,
+                       const int32_t* req_seg_off, int n_requests, int max_seg_tokens, float* mass,
                        void* plan_ws, int max_tiles, int n_tok, hipStream_t stream);
 // given = false: mass [n_tok][Hq], score = mean over heads (0 for a chunk at position 0);
 // given = true: mass [n_tok] are the scores themselves

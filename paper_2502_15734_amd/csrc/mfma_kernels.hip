@@ -799,13 +799,27 @@ Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_s
   return pl;
 }
 
-// Fewest 128-token workgroups for which the wide SCORE kernel runs with four column blocks and one key stream (three
-// workgroups per compute unit of an MI355X); below that its small form (64 tokens, two key streams) fills the machine
-// better.  Whole cc_select call, narrow kernel (which ran there before, with a top-N that took 4-8 us longer) / small
-// form, us: 192 workgroups (5 x 512 tokens, 32 / 8 heads) 82 / 60, 384 (64 / 8 heads) 103 / 81, 96 (16 / 2) 98 / 57,
-// 320 (16 / 2, 9 x 1k) 254 / 162, 640 (9 x 1k, 32 / 8) 312 / 294; at 800 the four-column form is level with the narrow one.
+// Which SCORE kernel runs.  From kMinWideGrid 128-token workgroups on (three per compute unit of an MI355X) the wide one
+// with four column blocks and one key stream.  Below, its small form (64 tokens, two key streams, one workgroup per
+// compute unit) as long as its workgroups run in about one round, or in two with prompts long enough that the longest chain of
+// tiles decides: it halves that chain.  In between the narrow kernel, of which two workgroups share a unit (later where a
+// KV head has 8 query heads: a narrow workgroup takes all of them, so there are half as many).  Whole
+// cc_select call, narrow / small, us, by 64-token workgroups (chunks behind the first) and tokens of a prompt: 256 workgroups:
+// 768 34.7 / 34.5, 1.2k 47.9 / 42.6, 3k 88.6 / 74.0; 336 to 352: 1.2k 51.2 / 56.9, 2.1k 71.6 / 73.7 (32 / 8 heads) and
+// 84.7 / 73.9 (64 / 8), 3.5k 102 / 85; 512: 1.5k 61 / 73, 2.6k 83.2 / 86.5 and 95.4 / 85.3, 4.6k 129 / 114, 9k 273 / 193; 640:
+// 3k 118 / 126, 5.4k 165 / 178; 1024: 2.3k 115 / 135, 4.6k 190 / 207, 9k 353 / 375.
 // The wide ATTENTION kernel is faster at every size measured, down to 64 workgroups (7-25 %), so it has no such limit.
 constexpr int kMinWideGrid = 768;
+constexpr int kOneRoundScore = 288, kTwoRoundScore = 540;
+
+// (the chunks' lengths are on the device: their 64-token workgroups are estimated from the batch's tokens, taking a request's
+// segments for equally long chunks and a short question; the first chunk is not scored)
+static bool small_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
+  const int64_t per_req = std::max(n_segs / n_requests, 2), scored = per_req > 2 ? per_req - 2 : 1, chunks = scored + 1;
+  const int64_t groups = static_cast<int64_t>(n_q_heads / 4) * n_tok * scored / (64 * chunks);
+  const int tokens_per_group = n_q_heads / n_kv_heads > 4 ? 4 : 7;
+  return groups <= std::max(kOneRoundScore, std::min(n_tok / n_requests / tokens_per_group, kTwoRoundScore));
+}
 
 bool attn_mfma_supported(const cc_ctx* ctx) { return group_supported(ctx); }
 bool score_mfma_supported(const cc_ctx* ctx) { return group_supported(ctx); }
@@ -846,13 +860,14 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
 
 void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
                        const int32_t* block_tab, const cc_segment* segs, int n_segs,
-                       const int32_t* req_seg_off, int max_seg_tokens, float* mass,
+                       const int32_t* req_seg_off, int n_requests, int max_seg_tokens, float* mass,
                        void* plan_ws, int max_tiles, int n_tok, hipStream_t stream) {
-  // Wide kernel first where the head group allows it, in the form that suits the grid; the narrow kernel then
+  // Wide kernel first where the head group and the grid allow it; the narrow kernel then
   // redoes the granules the wide one flagged (normally none: its workgroups read two flags and exit).
   const int wide_wgs = ctx->cfg.n_q_heads / 4 * ((max_seg_tokens + 127) / 128) * n_segs;
-  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx);
-  const bool small = wide_wgs < kMinWideGrid && ctx->impl != CC_IMPL_MFMA_WIDE;
+  const bool big = wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE;
+  const bool small = !big && small_score_grid(ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, n_tok, n_segs, n_requests);
+  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && (big || small);
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
   const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, 0, nullptr, block_tab, n_blocks, max_tiles, n_redo, stream);
   if (wide)

@@ -324,3 +324,18 @@ def test_rows_whose_reference_lies_far_below_later_keys(impl, low):
     # (rows that see nothing but such keys: bf16 keys of magnitude 141, half a unit in the last place of four of them)
     only = (ref.q_pos < low[1]) if low[0] == 0 else np.zeros(len(ref.q_pos), dtype=bool)
     assert (np.abs(b.lse.cpu().numpy() - ref.lse) <= np.where(only[:, None], 0.8, 2e-3)).all()
+
+
+@pytest.mark.parametrize("hq,hkv,n,lens", [(32, 8, 4, [512] * 3), (64, 8, 4, [100] * 5)])
+def test_scores_of_grids_between_the_two_wide_forms_come_from_the_narrow_kernel(hq, hkv, n, lens):
+    # more 64-token workgroups than two key streams have a round for, prompts too short to gain from the shorter chain
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("between", "bf16", hq, hkv, 128, 5.0e5, lens, [3] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [0.1] * len(lens), 20)] * n, 1.0 / math.sqrt(128), seed=89)
+    got = []
+    for impl in (P.CC_IMPL_AUTO, P.CC_IMPL_MFMA_NARROW):
+        b = DeviceBatch(w, impl=impl)
+        b.rope_shift(); b.select(); torch.cuda.synchronize()
+        got.append(b.scores.cpu())
+    assert torch.equal(got[0], got[1])
