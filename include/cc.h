@@ -316,7 +316,7 @@ int cc_sparse_prefill_static(cc_ctx* ctx, const void* q, const void* k_new, cons
 /* ---- (c'') partial prefill that also returns the question's attention to every chunk --------
  * cc_sparse_prefill (same steps, same out and lse, bit for bit) plus seg_mass as cc_question_mass
  * defines it, in one call.  Where the attention kernel that runs can give the masses as a
- * by-product it does (the 64-row MFMA kernel: at the last key tile of every segment it stores the
+ * by-product it does (the wide MFMA kernel: at the last key tile of every segment it stores the
  * log-sum-exp over all keys so far for the question rows; a row's weight on a segment is then
  * exp(cum_s - lse) - exp(cum_{s-1} - lse); rows it leaves to the other kernel because their
  * logits overflowed its fixed softmax reference are walked again, rarely, by a scalar kernel);
@@ -347,7 +347,7 @@ int cc_sparse_prefill_mass(cc_ctx* ctx, const void* q, const void* k_new, const 
  * cc_chunk_attention defines them and, if seg_mass is not NULL, seg_mass as cc_question_mass
  * defines it (it is the row of the pair matrix that belongs to the request's question segment),
  * in one call: the chunk-cache metadata of Sec. 3.4.3 at the cost of the prefill that produces
- * the cache.  Where the 64-row MFMA kernel runs, the sums come from the by-product of
+ * the cache.  Where the wide MFMA kernel runs, the sums come from the by-product of
  * cc_sparse_prefill_mass kept for EVERY row; otherwise from cc_chunk_attention's passes after the
  * attention.  The by-product path needs the rows of segment s at [sel_off, sel_off + n_select) of
  * the compact list, as cc_select lays them out.

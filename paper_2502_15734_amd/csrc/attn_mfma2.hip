@@ -32,7 +32,8 @@
 // sum leaves the safe range are flagged and redone by the kernel that can move its reference
 // (see the launcher).
 //
-// Staging: four tile images in LDS, filled by loads that write LDS directly (global_load_lds, 16
+// Staging: tile images in LDS (KS = 1: four of K and V; KS = 2: three of K and two of V per key stream), filled by
+// loads that write LDS directly (global_load_lds, 16
 // bytes per lane: lane L of an instruction fills piece base + L, so the image layout is chosen by
 // the global address each lane is given).  KS = 1: wavefronts 0-3 bring the four K pages (16 tokens) of a tile,
 // 4-7 the four V pages; KS = 2: the four wavefronts of a key stream bring a K and a V page each of their own
@@ -46,8 +47,8 @@
 // An MFMA operand read takes contiguous runs of 128 bytes that alternate between the two halves
 // of the 256-byte bank sweep (K) or one contiguous KiB (V): no bank conflicts.  In iteration t the wavefronts
 // read image t and (for S of the next tile's first block) image t+1.  KS = 1: they start the loads of image t+3
-// and, before the iteration's barrier, wait for their loads of image t+2; KS = 2 (two images per stream): they
-// start the loads of image t+1's successor into the image they left in the last iteration, and wait for
+// and, before the iteration's barrier, wait for their loads of image t+2; KS = 2: they
+// start the loads of K of tile t+2 and of V of tile t+1, into the images they left in the last iteration, and wait for
 // them at the iteration's end.  One s_barrier per tile.
 // Block padding: K padding never reaches a product (its S entries are masked by selection); V
 // padding would, as 0 x garbage, so the wavefront that loaded a V page blanks the page's padding
@@ -76,8 +77,11 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 constexpr int kImage = 2048;    // 16-byte pieces per tile image (K: 1024, V: 1024)
 constexpr int kBufs = 4;
 // Two key streams up to this many 64-row workgroups.  A compute unit holds one workgroup; twice as many with half
-// the tiles fill units that would idle and still run in one round, or nearly.  Measured (4 query heads per KV
-// head, one stream / two, us): 64 workgroups 59 / 44, 112: 61 / 46, 144 (10k keys): 201 / 152, 192: 67 / 63, 256: 72 / 85.
+// the tiles fill units that would idle and still run in one round, or nearly.  Up to 160 they are ahead whatever the
+// batch; behind that it hangs on how unevenly its requests fill their last tiles, and what one or two requests would gain
+// four lose.  cc_sparse_prefill, one stream / two, us: 112 workgroups 52 / 45 (1 request of 1.2k), 128: 62 / 53 (4 of 1.2k), 214 /
+// 159 (1 of 10k), 160: 94 / 77 (1 of 3k), 65 / 61 (4 of 1.2k), 55.5 / 53.9 (4 of 1.2k, 8 heads); 192: 220 / 173 (1 of 10k), 99 / 82
+// (2 of 3k), 101 / 116 (4 of 3k), 224: 58 / 60 (2 of 1.2k), 61 / 67 (4 of 1.2k), 256: 232 / 197 (1 of 10k), 106 / 125 (4 of 3k).
 constexpr int kTwoStreamGrid = 160;
 #ifndef CC_RING_DEPTH
 #define CC_RING_DEPTH 8
@@ -157,7 +161,7 @@ __device__ __forceinline__ void wait_lds() {
 template <int KS, bool BY>
 __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos,
-    const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool, int n_blocks,
+    const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool,
     const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     int n_sub, int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ redo, const int32_t* __restrict__ q_map, int map_pos,
@@ -325,10 +329,8 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   // (with a row map, list row j takes its query from row q_map[j] of q - and, if map_pos, its
   // position from q_pos[q_map[j]]; results are always indexed by the list row)
   int row, src_row, p;
-  bool row_valid;
   {
     row = min(q0 + wrows + n, q_end - 1);
-    row_valid = q0 + wrows + n < q_end;
     src_row = q_map != nullptr ? q_map[row] : row;
     p = q_pos[map_pos ? src_row : row];
   }
@@ -566,8 +568,9 @@ exp_step(0, i);
   // such moves need in front of a matrix instruction.)
   // By-product for rows that ask for it (snap_index >= 0: the question rows; or every row): when the tile that
   // has just been closed is the last one of its segment, the log-sum-exp over all keys up to here
-  // goes to cum[snap row][head][segment's index in its request].  The reference never moves in this
-  // kernel, so these running sums subtract exactly.  (Rare: once per segment of the request.)
+  // goes to cum[snap row][head][segment's index in its request].  A stream's reference never moves in this
+  // kernel, so with one stream these running sums subtract exactly; two streams' sums meet under the larger of
+  // their references, which rounds each once.  (Rare: once per segment of the request.)
   const int seg_first = BY ? req_seg_off[r] : 0;
   // (segments without tokens have no tile: the value also stands for those between this tile's
   // segment and the next tile's; the row sum is taken with the pair that is still to be packed)
@@ -765,7 +768,7 @@ bool attn_v2_supported(const cc_ctx* ctx) {
 }
 
 void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
-                    int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool, int n_blocks,
+                    int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,
                     const Plan& pl, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                     int32_t* redo, const int32_t* q_map, int map_pos, const int32_t* snap_index, float* cum,
                     int s_max, hipStream_t stream, const ValueSource& vs) {
@@ -778,7 +781,7 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
     const int n_tiles = (max_q_per_req + TQ - 1) / TQ;                                                         \
     hipLaunchKernelGGL((attn_v2_kernel<KS, BY>), dim3(hkv * n_sub * n_tiles, n_requests), dim3(512), 0, stream,    \
                        static_cast<const bf16_t*>(q), q_pos, static_cast<const bf16_t*>(k_pool),               \
-                       static_cast<const bf16_t*>(v_pool), n_blocks, pl.tiles, pl.max_tiles, pl.items,         \
+                       static_cast<const bf16_t*>(v_pool), pl.tiles, pl.max_tiles, pl.items,                   \
                        req_seg_off, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq,                    \
                        static_cast<bf16_t*>(out), lse, redo, q_map, map_pos, snap_index, cum, s_max,           \
                        static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks,                            \

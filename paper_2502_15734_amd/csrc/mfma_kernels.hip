@@ -840,7 +840,7 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
   const int n_redo = wide ? static_cast<int>(redo_entries(n_q_tot)) : 0;
   const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, cu_q, block_tab, n_blocks, max_tiles, n_redo, stream);
   if (wide)
-    launch_attn_v2(ctx, q, q_pos, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, pl, req_seg_off, n_requests,
+    launch_attn_v2(ctx, q, q_pos, n_q_tot, max_q_per_req, k_pool, v_pool, pl, req_seg_off, n_requests,
                    out, lse, pl.redo, q_map, map_pos, by != nullptr ? by->snap_index : nullptr,
                    by != nullptr ? by->cum : nullptr, by != nullptr ? by->s_max : 0, stream, vs);
   if (by != nullptr) {

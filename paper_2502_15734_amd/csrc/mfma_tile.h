@@ -210,7 +210,7 @@ size_t plan_head_bytes(int n_segs);
 Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests,
               const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream);
 
-// The wide attention kernel (64 query rows per wavefront) keeps one softmax reference per row; rows
+// The wide attention kernel (64 query rows per workgroup, 32 in two key streams) keeps one softmax reference per row; rows
 // whose sums leave the safe range are flagged in redo[] and redone by the narrow kernel, which can
 // move its reference.  q0 is the first row of the 64-row tile (the request's first row + 64 k);
 // two tiles of different requests may share an entry, which only costs a spurious redo.
@@ -218,7 +218,7 @@ __host__ __device__ inline int redo_index(int q0) { return q0 >> 5; }
 inline size_t redo_entries(int n_q_tot) { return static_cast<size_t>(n_q_tot) / 32 + 2; }
 
 void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
-                    int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool, int n_blocks,
+                    int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,
                     const Plan& pl, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                     int32_t* redo, const int32_t* q_map, int map_pos, const int32_t* snap_index, float* cum,
                     int s_max, hipStream_t stream, const ValueSource& vs);
