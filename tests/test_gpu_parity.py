@@ -524,7 +524,7 @@ def _projected_reference(w, b, r, gsel):
     return O.run_request(w, r, selected_override=gsel, k_new=kf, v_new=vf, q=qf)
 
 
-@pytest.mark.parametrize("impl", ["wide", "narrow"])      # the two MFMA projection kernels
+@pytest.mark.parametrize("impl", ["wide", "narrow"])      # (scores and attention; the projection is the same MFMA GEMM)
 @pytest.mark.parametrize("scale", [0.06])
 def test_config5_scaled_with_projection(scale, impl):
     from paper_2502_15734_amd.pipeline import DeviceBatch
