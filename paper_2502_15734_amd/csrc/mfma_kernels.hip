@@ -591,8 +591,10 @@ __device__ __forceinline__ void plan_fill(const cc_segment* __restrict__ segs, i
     d.blk[i] = (b >= 0 && b < n_blocks) ? b : -1;
   }
   d.seg = lo;
-  d.pad = 0;
-  tiles[j] = d;
+  uint32_t* to = reinterpret_cast<uint32_t*>(tiles + j);      // (all but `work`, which is written by others)
+  *reinterpret_cast<uint4*>(to) = make_uint4(d.kpos0, d.nvalid, d.blk[0], d.blk[1]);
+  *reinterpret_cast<uint2*>(to + 4) = make_uint2(d.blk[2], d.blk[3]);
+  to[6] = d.seg;
 }
 
 __global__ __launch_bounds__(256) void plan_fill_kernel(const cc_segment* __restrict__ segs, int n_segs,
@@ -609,8 +611,6 @@ __global__ __launch_bounds__(256) void plan_fill_kernel(const cc_segment* __rest
 // otherwise item = segment, key = end of the segment (0 for segments that are not scored).
 // order[rank] = item; ties keep index order, so the result is always a permutation.  More than
 // kMaxOrdered items: identity.
-constexpr int kMaxOrdered = 4096;
-
 //
 // Beside order[] one 32-byte work item per rank is written, so that a workgroup of the
 // wide kernels finds everything it needs to start with ONE load instead of a chain of dependent
@@ -666,6 +666,116 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
   emit(rank, i);
 }
 
+// The list of workgroups (WorkList), by one whole workgroup of 256 threads: row tiles counted per request, numbered
+// through, and put into buckets by the number of key tiles they see, longest first.  (Which of a bucket's tiles
+// comes first is left to chance: it decides when a workgroup starts, not what it computes.)
+__device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ segs, int n_segs,
+                          const int32_t* __restrict__ req_seg_off, int n_requests, const int32_t* __restrict__ cu_q,
+                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles) {
+  constexpr int kBuckets = 512;
+  __shared__ int off[kMaxSorted + 1], low[kMaxSorted], bucket[kBuckets], wsum[4], longest;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const bool scored = list.kind == WorkList::kScored;
+  auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
+  auto entry = [&](int r, int k) { return static_cast<int32_t>(static_cast<uint32_t>(r) << 16) | k; };
+  if (n_requests > kMaxSorted) {
+    // request by request, each where its own key tiles begin (its scored tokens have no more) or behind as many rows and requests
+    for (int j = tid; j < max_tiles - 1; j += 256) tiles[j].work = -1;
+    if (tid == 0) tiles[max_tiles - 1].work = max_tiles - 1;
+    __threadfence_block();
+    __syncthreads();
+    for (int r = tid; r < n_requests; r += 256) {
+      int rows = 0, first;
+      if (scored) {
+        for (int s = req_seg_off[r]; s < req_seg_off[r + 1]; ++s) rows += is_scored(segs[s]) ? segs[s].n_tokens : 0;
+        first = seg_tile_off[req_seg_off[r]];
+      } else {
+        rows = cu_q[r + 1] - cu_q[r];
+        first = cu_q[r] / list.rows + r;
+      }
+      const int n = (rows + list.rows - 1) / list.rows;
+      for (int k = 0; k < n && first + k < max_tiles - 1; ++k) tiles[first + k].work = entry(r, n - 1 - k);
+    }
+    return;
+  }
+  // rows, then row tiles of every request; low: position of its first scored token
+  for (int r = tid; r < n_requests; r += 256) { off[r] = scored ? 0 : max(cu_q[r + 1] - cu_q[r], 0); low[r] = 0x7fffffff; }
+  for (int b = tid; b < kBuckets; b += 256) bucket[b] = 0;
+  if (tid == 0) longest = 1;
+  __syncthreads();
+  for (int s = tid; s < n_segs; s += 256) {
+    const cc_segment sg = segs[s];
+    if (scored && is_scored(sg) && sg.req >= 0 && sg.req < n_requests) {
+      atomicAdd(&off[sg.req], sg.n_tokens);
+      atomicMin(&low[sg.req], sg.logical_start);
+    }
+    atomicMax(&longest, sg.logical_start + max(sg.n_tokens, 0));
+  }
+  __syncthreads();
+  int carry = 0;
+  for (int r0 = 0; r0 < n_requests; r0 += 256) {           // exclusive scan in place (off[n_requests]: all)
+    const int r = r0 + tid, n = r < n_requests ? (off[r] + list.rows - 1) / list.rows : 0;
+    int incl = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int base = carry;
+    for (int ww = 0; ww < w; ++ww) base += wsum[ww];
+    carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (r < n_requests) off[r] = base + incl - n;
+    __syncthreads();
+  }
+  if (tid == 0) off[n_requests] = carry;
+  __syncthreads();
+  const int total = min(carry, max_tiles - 1);
+  int shift = 0;
+  while ((longest / kTile >> shift) >= kBuckets) ++shift;
+  // (bucket 0 holds the longest)
+  auto look_up = [&](int j, int* r, int* k) {
+    int lo = 0, hi = n_requests - 1;                       // last request with off[r] <= j
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (off[mid] <= j) lo = mid; else hi = mid - 1;
+    }
+    *r = lo;
+    *k = j - off[lo];
+    const int last = scored ? low[lo] + list.rows * (*k + 1)
+                            : list.q_pos[min(cu_q[lo] + list.rows * (*k + 1), cu_q[lo + 1]) - 1];
+    return kBuckets - 1 - min(max(last / kTile >> shift, 0), kBuckets - 1);
+  };
+  for (int j = tid; j < total; j += 256) {
+    int r, k;
+    atomicAdd(&bucket[look_up(j, &r, &k)], 1);
+  }
+  __syncthreads();
+  {
+    const int a = bucket[2 * tid], b = bucket[2 * tid + 1];
+    int incl = a + b;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int base = 0;
+    for (int ww = 0; ww < w; ++ww) base += wsum[ww];
+    bucket[2 * tid] = base + incl - a - b;
+    bucket[2 * tid + 1] = base + incl - b;
+  }
+  __syncthreads();
+  for (int j = tid; j < total; j += 256) {
+    int r, k;
+    const int at = atomicAdd(&bucket[look_up(j, &r, &k)], 1);
+    tiles[at].work = entry(r, k);
+  }
+  if (tid == 0) tiles[max_tiles - 1].work = total;
+}
+
 template <bool BY_REQUEST>
 __global__ __launch_bounds__(256) void plan_order_kernel(const cc_segment* __restrict__ segs,
                                                           const int32_t* __restrict__ req_seg_off,
@@ -676,9 +786,17 @@ __global__ __launch_bounds__(256) void plan_order_kernel(const cc_segment* __res
   plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, seg_tile_off, n_items, order, items, blockIdx.x);
 }
 
+__global__ __launch_bounds__(256) void plan_list_kernel(WorkList list, const cc_segment* __restrict__ segs, int n_segs,
+                                                         const int32_t* __restrict__ req_seg_off, int n_requests,
+                                                         const int32_t* __restrict__ cu_q,
+                                                         const int32_t* __restrict__ seg_tile_off,
+                                                         TileDesc* __restrict__ tiles, int max_tiles) {
+  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles);
+}
+
 // The whole plan in ONE launch, for batches of up to kPlanFused segments: every workgroup repeats
-// the (tiny) scan into LDS, then the first n_fill workgroups write descriptors and the others the
-// dispatch order.  Two launches and two waits between dependent kernels fewer per call, which is
+// the (tiny) scan into LDS, then the first n_fill workgroups write descriptors, the others the
+// dispatch order, and the last one the list of workgroups if there is to be one.  Two launches and two waits between dependent kernels fewer per call, which is
 // what a single request's step (a dozen kernels of a few microseconds) is made of.
 constexpr int kPlanFused = 1024;
 
@@ -690,7 +808,7 @@ __global__ __launch_bounds__(256) void plan_fused_kernel(const cc_segment* __res
                                                           int max_tiles, int32_t* __restrict__ seg_tile_off,
                                                           int32_t* __restrict__ order, WorkItem* __restrict__ items,
                                                           TileDesc* __restrict__ tiles, int32_t* __restrict__ redo,
-                                                          int n_redo, int n_fill) {
+                                                          int n_redo, int n_fill, int n_requests, WorkList list) {
   __shared__ int32_t s_off[kPlanFused + 1];
   plan_scan(segs, n_segs, s_off);
   if (blockIdx.x == 0)
@@ -698,8 +816,10 @@ __global__ __launch_bounds__(256) void plan_fused_kernel(const cc_segment* __res
   if (static_cast<int>(blockIdx.x) < n_fill)
     plan_fill(segs, n_segs, s_off, block_tab, n_blocks, max_tiles, tiles, redo, n_redo,
               blockIdx.x * 256 + threadIdx.x, n_fill);
-  else
+  else if (list.kind == WorkList::kNone || blockIdx.x + 1 < gridDim.x)
     plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, s_off, n_items, order, items, blockIdx.x - n_fill);
+  else
+    plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, s_off, tiles, max_tiles);
 }
 
 constexpr int kAttnQB = 1;     // 32 query tokens per workgroup in the attention kernel
@@ -766,8 +886,9 @@ static size_t plan_bytes_impl(int n_segs, int max_tiles) {
   return plan_head_bytes(n_segs) + static_cast<size_t>(max_tiles) * sizeof(TileDesc);
 }
 
-Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests,
-              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream) {
+Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,
+              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, const WorkList& list,
+              hipStream_t stream) {
   Plan pl;
   pl.seg_tile_off = static_cast<int32_t*>(ws);
   pl.order = pl.seg_tile_off + n_segs + 1;
@@ -775,26 +896,30 @@ Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_s
   pl.tiles = reinterpret_cast<TileDesc*>(static_cast<char*>(ws) + plan_head_bytes(n_segs));
   pl.max_tiles = max_tiles;
   pl.redo = n_redo > 0 ? reinterpret_cast<int32_t*>(pl.tiles + max_tiles) : nullptr;
+  const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256, n_order = (n_items + 255) / 256;
+  const bool listed = list.kind != WorkList::kNone;
   if (n_segs <= kPlanFused) {
-    const int n_fill = (max_tiles + 255) / 256;
-    if (n_requests > 0)
-      hipLaunchKernelGGL(plan_fused_kernel<true>, dim3(n_fill + (n_requests + 255) / 256), dim3(256), 0, stream, segs,
-                         n_segs, req_seg_off, cu_q, n_requests, block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order,
-                         pl.items, pl.tiles, pl.redo, n_redo, n_fill);
-    else
-      hipLaunchKernelGGL(plan_fused_kernel<false>, dim3(n_fill + (n_segs + 255) / 256), dim3(256), 0, stream, segs,
-                         n_segs, req_seg_off, cu_q, n_segs, block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order,
-                         pl.items, pl.tiles, pl.redo, n_redo, n_fill);
+    const dim3 grid(n_fill + n_order + (listed ? 1 : 0));
+#define CC_FUSED(BY_REQUEST)                                                                                        \
+  hipLaunchKernelGGL(plan_fused_kernel<BY_REQUEST>, grid, dim3(256), 0, stream, segs, n_segs, req_seg_off, cu_q, n_items,  \
+                     block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order, pl.items, pl.tiles, pl.redo, n_redo, n_fill, \
+                     n_requests, list)
+    if (by_request) CC_FUSED(true);
+    else CC_FUSED(false);
+#undef CC_FUSED
     return pl;
   }
   hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off);
-  if (n_requests > 0)                                  // attention: the grid's y index walks requests
-    hipLaunchKernelGGL(plan_order_kernel<true>, dim3((n_requests + 255) / 256), dim3(256), 0, stream, segs,
-                       req_seg_off, cu_q, pl.seg_tile_off, n_requests, pl.order, pl.items);
+  if (by_request)                                      // attention: the grid's y index walks requests
+    hipLaunchKernelGGL(plan_order_kernel<true>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
+                       n_items, pl.order, pl.items);
   else                                                 // score: it walks segments
-    hipLaunchKernelGGL(plan_order_kernel<false>, dim3((n_segs + 255) / 256), dim3(256), 0, stream, segs,
-                       req_seg_off, cu_q, pl.seg_tile_off, n_segs, pl.order, pl.items);
-  hipLaunchKernelGGL(plan_fill_kernel, dim3((max_tiles + 255) / 256), dim3(256), 0, stream, segs, n_segs,
+    hipLaunchKernelGGL(plan_order_kernel<false>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
+                       n_items, pl.order, pl.items);
+  if (listed)
+    hipLaunchKernelGGL(plan_list_kernel, dim3(1), dim3(256), 0, stream, list, segs, n_segs, req_seg_off, n_requests, cu_q,
+                       pl.seg_tile_off, pl.tiles, max_tiles);
+  hipLaunchKernelGGL(plan_fill_kernel, dim3(n_fill), dim3(256), 0, stream, segs, n_segs,
                      pl.seg_tile_off, block_tab, n_blocks, max_tiles, pl.tiles, pl.redo, n_redo);
   return pl;
 }
@@ -838,7 +963,7 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
   // tiles the wide one flagged (normally none: its workgroups read one flag and exit).
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && attn_v2_supported(ctx);
   const int n_redo = wide ? static_cast<int>(redo_entries(n_q_tot)) : 0;
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, cu_q, block_tab, n_blocks, max_tiles, n_redo, stream);
+  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, true, cu_q, block_tab, n_blocks, max_tiles, n_redo, WorkList(), stream);
   if (wide)
     launch_attn_v2(ctx, q, q_pos, n_q_tot, max_q_per_req, k_pool, v_pool, pl, req_seg_off, n_requests,
                    out, lse, pl.redo, q_map, map_pos, by != nullptr ? by->snap_index : nullptr,
@@ -867,11 +992,13 @@ void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int
   const int wide_wgs = ctx->cfg.n_q_heads / 4 * ((max_seg_tokens + 127) / 128) * n_segs;
   const bool big = wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE;
   const bool small = !big && small_score_grid(ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, n_tok, n_segs, n_requests);
-  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && (big || small);
+  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && (big || small) &&
+                    n_tok <= 64 * kMaxListed;
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, 0, nullptr, block_tab, n_blocks, max_tiles, n_redo, stream);
-  if (wide)
-    launch_score_v2(ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, pl.redo, small, stream);
+  WorkList list;
+  if (wide) { list.kind = WorkList::kScored; list.rows = small ? 64 : 128; }
+  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, stream);
+  if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, stream);
   const int32_t* redo = pl.redo;
 #define CC_ARGS ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, redo, stream
   switch (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) {

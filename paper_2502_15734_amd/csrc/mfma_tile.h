@@ -31,7 +31,7 @@ struct TileDesc {
   int32_t nvalid;    // keys of the tile that exist (1..64); the rest is block padding
   int32_t blk[4];    // physical block of each of the four 16-token pages (-1: none)
   int32_t seg;       // segment the tile belongs to
-  int32_t pad;
+  int32_t work;      // (not of this tile) entry of the list of workgroups, see WorkList
 };
 static_assert(sizeof(TileDesc) == 32, "descriptor is read as two 16-byte vectors");
 
@@ -43,7 +43,7 @@ __device__ __forceinline__ TileDesc to_scalar(const TileDesc& v) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) d.blk[i] = __builtin_amdgcn_readfirstlane(v.blk[i]);
   d.seg = 0;
-  d.pad = 0;
+  d.work = 0;
   return d;
 }
 
@@ -171,6 +171,50 @@ struct Stager {
   }
 };
 
+// Cosines and sines of a query position's angles, times `scale`: rotation pairs i, i + 1 for the lower half of the
+// wavefront, i + 8, i + 9 for the upper one.  i is wave-uniform, so that the frequencies come with scalar loads.
+__device__ __forceinline__ float4 query_turn(const InvFreq& inv_freq, int pos, int i, int hh, float scale) {
+  const double lo0 = inv_freq.f[i], lo1 = inv_freq.f[i + 1], hi0 = inv_freq.f[i + 8], hi1 = inv_freq.f[i + 9];
+  float4 t;
+  rot_cos_sin_fast(pos, hh ? hi0 : lo0, &t.x, &t.y);
+  rot_cos_sin_fast(pos, hh ? hi1 : lo1, &t.z, &t.w);
+  t.x *= scale; t.y *= scale; t.z *= scale; t.w *= scale;
+  return t;
+}
+// The 32 query rows of a wavefront (row: the row of column lane % 32; one head), on their way into the lanes that
+// multiply them.  Loaded as whole 256-byte rows, 16 lanes each: in the operand layout an instruction would ask for 32
+// bytes of 32 rows, and the lines it touches, not the bytes, are what such loads cost.
+__device__ __forceinline__ void load_query_rows(uint4 (&raw)[8], const bf16_t* __restrict__ q, int row, int hq, int h, int lane) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = __shfl(row, 4 * i + (lane >> 4), 64);
+    raw[i] = *reinterpret_cast<const uint4*>(q + (static_cast<size_t>(r) * hq + h) * kD + (lane & 15) * 8);
+  }
+}
+// ... and regrouped through 8 KiB of LDS of the wavefront's own: afterwards raw[k] holds dims 16k + 8 (lane / 32) .. + 7 of column
+// lane % 32 (pieces of a row are permuted by its number, so that neither side meets a bank conflict)
+__device__ __forceinline__ void regroup_query_rows(uint4 (&raw)[8], char* own, int lane) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = 4 * i + (lane >> 4);
+    *reinterpret_cast<uint4*>(own + r * 256 + (((lane & 15) ^ (r & 15)) << 4)) = raw[i];
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (other lanes' pieces: an order the compiler does not see)
+  const int r = lane & 31;
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    raw[k] = *reinterpret_cast<const uint4*>(own + r * 256 + (((2 * k + (lane >> 5)) ^ (r & 15)) << 4));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+// two bf16 pairs (x, y) packed in a word each, turned by the two angles of t
+__device__ __forceinline__ void turn_words(uint32_t& x, uint32_t& y, const float4& t) {
+  const float x0 = __uint_as_float(x << 16), x1 = __uint_as_float(x & 0xffff0000u);
+  const float y0 = __uint_as_float(y << 16), y1 = __uint_as_float(y & 0xffff0000u);
+  const float a0 = x0 * t.x - y0 * t.y, a1 = x1 * t.z - y1 * t.w, b0 = y0 * t.x + x0 * t.y, b1 = y1 * t.z + x1 * t.w;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(x) : "v"(a0), "v"(a1));
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(y) : "v"(b0), "v"(b1));
+}
+
 __device__ __forceinline__ float max16(const f32x16& v) {
   float a = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
   float b = fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7]));
@@ -203,12 +247,24 @@ struct WorkItem {
   int32_t pad;
 };
 static_assert(sizeof(WorkItem) == 32, "read as two 16-byte vectors");
+// List of workgroups, longest first: entry i sits in tiles[i].work - request << 16 | row tile of it (-1: none) - and the
+// number of entries in tiles[max_tiles - 1].work.  Rows: the scored tokens of a request (numbered through over its
+// chunks) or its rows of the query list.
+struct WorkList {
+  enum Kind { kNone, kScored, kQueries } kind = kNone;
+  int rows = 0;                     // rows of a workgroup
+  const int32_t* q_pos = nullptr;   // kQueries: position of every row
+};
+constexpr int kMaxOrdered = 4096;      // segments or requests that are sorted for the dispatch order
+constexpr int kMaxSorted = 2048;       // requests whose workgroups are sorted (else request by request, with gaps)
+constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
 size_t plan_head_bytes(int n_segs);
-// n_requests > 0: dispatch order over requests (attention; cu_q delimits their rows); 0: over segments (score).
+// by_request: dispatch order over requests (attention; cu_q delimits their rows), else over segments (score).
+// list: the list of workgroups to build beside it.
 // n_redo > 0: the plan also holds n_redo redo flags (after the tiles), cleared by the plan kernels.
-Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests,
-              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, hipStream_t stream);
+Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,
+              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, const WorkList& list, hipStream_t stream);
 
 // The wide attention kernel (64 query rows per workgroup, 32 in two key streams) keeps one softmax reference per row; rows
 // whose sums leave the safe range are flagged in redo[] and redone by the narrow kernel, which can
@@ -226,8 +282,8 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
 // The wide score kernel (128 tokens per wavefront, no softmax reference) flags 64-row granules of
 // the per-token tensors whose sums left the safe range; the narrow kernel redoes them.
 inline size_t score_redo_entries(int n_tok) { return static_cast<size_t>(n_tok) / 64 + 2; }
-void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks, const Plan& pl,
-                     const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int max_seg_tokens,
-                     float* mass, int32_t* redo, bool small, hipStream_t stream);
+void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const Plan& pl, const cc_segment* segs,
+                     const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, bool small,
+                     hipStream_t stream);
 
 }  // namespace cc

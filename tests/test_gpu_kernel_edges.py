@@ -339,3 +339,33 @@ def test_scores_of_grids_between_the_two_wide_forms_come_from_the_narrow_kernel(
         b.rope_shift(); b.select(); torch.cuda.synchronize()
         got.append(b.scores.cpu())
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("hq,lens,chunks", [
+    (4, [40, 1, 63, 65, 0, 128, 200, 31], [[0, 1, 2, 3, 4, 5, 6, 7], [6, 0], [3], [1, 1, 1, 2]]),
+    (8, [130, 126, 257, 5], [[0, 1, 2, 3], [3, 3, 3, 0, 2]]),
+    (4, [9, 3, 20], [[0, 1, 2] * 30, [2, 1]]),                  # more than 64 segments in a request
+    (4, [17, 33], [[0, 1, 0]] * 300),                           # more than 1024 segments
+    (4, [17, 20], [[0, 1]] * 2100),                             # more requests than are sorted
+])
+def test_scores_of_tokens_numbered_through_the_chunks_of_a_request(hq, lens, chunks):
+    # a workgroup's 128 (64) tokens begin and end anywhere in a chunk and may lie in many: each column takes its own prior
+    # chunks' mass where its own chunk begins
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("through", "bf16", hq, 1, 128, 5.0e5, lens, [7] * len(lens),
+                 [W.RequestSpec(c, [0.2] * len(c), 5) for c in chunks], 1.0, seed=97)
+    longest = max(sum(lens[i] for i in c) for c in chunks)
+    for gain in (1.0, 40.0):
+        got = {}
+        for impl in ("MFMA_NARROW", "MFMA_WIDE", "AUTO"):
+            b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+            b.q.mul_(gain)
+            b.rope_shift(); b.select(); torch.cuda.synchronize()
+            got[impl] = b.scores.cpu().double()
+        # (the bound of test_scores_in_two_key_streams: every form takes every angle in double precision)
+        bound = (4 * math.sqrt(longest) * 2.0 ** -24 + 1e-6) * gain
+        for impl in ("MFMA_WIDE", "AUTO"):
+            assert torch.isfinite(got[impl]).all()
+            assert float((got[impl] - got["MFMA_NARROW"]).abs().max()) <= bound
+    assert float(got["MFMA_NARROW"].max()) > 0.1
