@@ -55,12 +55,18 @@
 // slots in LDS before the barrier, in a branch only a segment's last tile takes.
 //
 // What bounds it: long prompts, the two wavefronts' MFMAs and exponentials (32 x 32 clocks of matrix pipe and 32
-// exponentials per wavefront and tile); short ones, the latency in front of and behind the loop.  Hence the
-// prologue: one load names the rows and the key tiles, the first pages are on their way before the rows' positions
+// exponentials per wavefront and tile) at the clock the chip holds under them (1.75-1.85 GHz); short ones, the latency in
+// front of and behind the loop.  Hence the
+// prologue: the first pages and the query rows (whole rows each, regrouped in LDS) are on their way before the positions
 // are known, a head computes a quarter of the angles and shares them, visible tiles are counted in the
 // window; and the epilogue turns the output in LDS so that stores write whole rows.  Measured against a chain of
 // dependent loads, each wavefront's own angles and 8-byte stores: one request of 2.6k tokens 65 -> 59 us (two
 // streams: 44), the 8B batch of 32 1883 -> 1773, 4 x 32k tokens 3270 -> 3165 (1.2 PFLOP/s).
+// Several requests: which workgroup takes which rows is in the plan's list (WorkList), because a grid of (row tiles) x (requests)
+// starts the last request's long workgroups when nothing is left to run beside them: 70B on a quarter of the heads, 8
+// requests of 10k tokens, cc_sparse_prefill and what is in front of it 514 -> 457 us; 6 requests of 3-6k tokens 318 -> 310.
+// KS = 1: the rows of a sparse list lie far apart, so the first 32 see several tiles fewer than the second 32; their
+// wavefronts stop multiplying there and only bring in their share of the tiles.
 #include <algorithm>
 #include <type_traits>
 
@@ -145,12 +151,6 @@ __device__ __forceinline__ void exp_behind_pack(uint32_t& pk, float& l, float& e
   asm volatile("v_cvt_pk_bf16_f32 %0, %2, %3\n\tv_add_f32 %1, %1, %2\n\tv_add_f32 %1, %1, %3\n\tv_exp_f32 %2, %4"
                : "=&v"(pk), "+v"(l), "+v"(e) : "v"(v), "v"(s));
 }
-__device__ __forceinline__ void lds_to_acc(const uint4* p, u32x4& r0, u32x4& r1) {
-  typedef __attribute__((address_space(3))) const uint4 lds_piece;
-  const uint32_t addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_piece*)p));   // LDS byte offset
-  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:8192\n\ts_waitcnt lgkmcnt(0)"
-               : "=&a"(r0), "=&a"(r1) : "v"(addr) : "memory");
-}
 // s_waitcnt with only the LDS counter set (vector-memory and export counters left alone)
 template <int N>
 __device__ __forceinline__ void wait_lds() {
@@ -162,37 +162,60 @@ template <int KS, bool BY>
 __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos,
     const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool,
-    const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
-    int n_sub, int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
+    const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ order, int listed,
+    const int32_t* __restrict__ req_seg_off, int hq, int hkv, int n_sub, int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ redo, const int32_t* __restrict__ q_map, int map_pos,
     const int32_t* __restrict__ snap_index, float* __restrict__ cum, int s_max,
     const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
   constexpr int TQ = KS == 1 ? 64 : 32;     // query rows per workgroup
   // LDS: KS = 1: four images of K | V; KS = 2: per key stream three K images and two V images
-  // (and 16 KiB more that the queries pass through on their way into the accumulation registers; KS = 2 has an
-  // image to spare for that)
-  __shared__ uint4 lds_all[KS == 1 ? kBufs * kImage + 1024 : 5 * kImage];
+  __shared__ uint4 lds_all[KS == 1 ? kBufs * kImage : 5 * kImage];
   auto here = [&]() __attribute__((always_inline)) { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t & 63; };
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int n = lane & 31, hh = lane >> 5;
   const int whead = wave & 3, wgrp = wave >> 2;              // this wavefront's head of the four; row half or key stream
   const int ks = KS == 1 ? 0 : wgrp, wrows = KS == 1 ? 32 * wgrp : 0;
   const int per_tile = hkv * n_sub;
-  const int tile = n_tiles_x - 1 - blockIdx.x / per_tile;    // late (long) tiles are dispatched first
   const int rem = blockIdx.x % per_tile;
   const int kvh = rem % hkv, hsub = rem / hkv;
   const int h = kvh * (4 * n_sub) + hsub * 4 + whead;
 
   // ---- which queries ------------------------------------------------------------------------
-  const uint4* ip = reinterpret_cast<const uint4*>(items + blockIdx.y);
-  const uint4 i0 = ip[0], i1 = ip[1];
-  const int r = uniform(i0.x), q_first = uniform(i0.z), q_end = q_first + uniform(i0.w);
-  const int j_begin = uniform(i1.y), j_end = min(uniform(i1.z), max_tiles);
+  // (from the plan's list of workgroups, or where there is none from a grid of row tiles, long ones first, by requests
+  // in the order of their length)
+  int req, tile;
+  if (listed) {
+    const int at = blockIdx.x / per_tile, e = tiles[at].work;
+    if (at >= uniform(tiles[max_tiles - 1].work) || uniform(e) == -1) return;
+    req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> 16));
+    tile = uniform(e & 0xffff);
+  } else {
+    req = uniform(order[blockIdx.y]);
+    tile = n_tiles_x - 1 - blockIdx.x / per_tile;
+  }
+  const WorkItem item = items[req];
+  const int q_first = uniform(item.row), q_end = q_first + uniform(item.n_rows);
+  const int j_begin = uniform(item.j_begin), j_end = min(uniform(item.j_end), max_tiles);
   const int q0 = q_first + tile * TQ;
   if (q0 >= q_end) return;
   const int n_all = j_end - j_begin;
   if (n_all <= 0) return;
   const char* lds_bytes = reinterpret_cast<const char*>(lds_all);
+  // ---- rows and positions: asked for first, whole rows each (see load_query_rows) ---------------------
+  // (with a row map, list row j takes its query from row q_map[j] of q - and, if map_pos, its
+  // position from q_pos[q_map[j]]; results are always indexed by the list row)
+  int src_row, p, p_other = 0;
+  {
+    const int row = min(q0 + wrows + n, q_end - 1);
+    src_row = q_map != nullptr ? q_map[row] : row;
+    p = q_pos[map_pos ? src_row : row];
+    if (KS == 1) {
+      const int other = min(q0 + (32 - wrows) + n, q_end - 1);
+      p_other = q_pos[map_pos ? (q_map != nullptr ? q_map[other] : other) : other];
+    }
+  }
+  uint4 rows[8];
+
   // ---- descriptors and staging --------------------------------------------------------------------
   // What the loop needs of 64 consecutive tiles sits in vector registers, one tile per lane, and is
   // handed out with v_readlane: no memory access per tile.  The straight path reads two values per
@@ -235,6 +258,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     w_flags = (edge ? 3 : 0) | (w_seg_next != w_seg ? 4 : 0) | (KS == 2 && BY && w_seg_far != w_seg_next ? 8 : 0);
   };
   fill_window(0);
+  load_query_rows(rows, q, src_row, hq, h, lane);
   // byte offset of the K / V image of (local) tile t (KS = 1: one image, V behind K)
   auto k_image = [&](int t) __attribute__((always_inline)) { return KS == 1 ? (t & (kBufs - 1)) * (kImage * 16) : ks * 49152 + (t % 3) * 16384; };
   auto v_image = [&](int t) __attribute__((always_inline)) { return KS == 1 ? (t & (kBufs - 1)) * (kImage * 16) : 98304 + ks * 32768 + (t & 1) * 16384; };
@@ -310,12 +334,12 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   };
 
   // ---- first tiles: on their way before anything about the rows is known ------------------------------
-  // (KS = 1: images 0, 1, 2; KS = 2: K of the stream's tiles 0 and 1, V of tile 0.  Tiles no row sees are
+  // (KS = 1: images 0, 1, image 2 when the queries are turned; KS = 2: K of the stream's tiles 0 and 1, V of tile 0.  Tiles no row sees are
   // loaded in vain; past the request's last tile that tile is repeated.)
   constexpr int kAheadK = KS == 1 ? 3 : 2, kAheadV = KS == 1 ? 3 : 1;
+  constexpr int kFirstV = KS == 1 ? 2 : 1;
   const int n_av = (n_all - ks + KS - 1) / KS;                // tiles of the stream in the whole request
-#pragma unroll
-  for (int t = 0; t < kAheadK; ++t) {
+  auto first_loads = [&](int t) __attribute__((always_inline)) {
     const int l = max(min(t, n_av - 1), 0);
     dma_begin(l, l, k_image(t), v_image(t));
 #pragma unroll
@@ -324,30 +348,22 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
       dma_v(0);
       dma_v(1);
     }
-  }
+  };
+  first_loads(0);
+  first_loads(1);
 
-  // (with a row map, list row j takes its query from row q_map[j] of q - and, if map_pos, its
-  // position from q_pos[q_map[j]]; results are always indexed by the list row)
-  int row, src_row, p;
-  {
-    row = min(q0 + wrows + n, q_end - 1);
-    src_row = q_map != nullptr ? q_map[row] : row;
-    p = q_pos[map_pos ? src_row : row];
-  }
   // first and last position over all rows of the workgroup (every wavefront walks the same tiles)
-  int pmx = p, pmn = p;
-  if constexpr (KS == 1) {
-    const int other = min(q0 + (32 - wrows) + n, q_end - 1);
-    const int po = q_pos[map_pos ? (q_map != nullptr ? q_map[other] : other) : other];
-    pmx = max(p, po); pmn = min(p, po);
-  }
-  const int p_max = uniform(wave_max_i(pmx)), p_min = uniform(wave_min_i(pmn));
+  const int p_mine = uniform(wave_max_i(p));
+  const int p_max = KS == 1 ? max(p_mine, uniform(wave_max_i(p_other))) : p_mine;
+  const int p_min = uniform(wave_min_i(KS == 1 ? min(p, p_other) : p));
 
   // ---- tiles of the request whose first key some query of the workgroup sees ------------------
   // (tiles are listed in prompt order, so these form a prefix)
   // (counted in the window; while all 64 are visible, those behind it are taken to be, until the window moves there)
   int n_odd = 0;                 // (tiles of the odd stream)
-  int n_it, n_loc;               // iterations of the workgroup; tiles of this wavefront's key stream (the odd one may have none)
+  // iterations of the workgroup; tiles of this wavefront's key stream (the odd one may have none); tiles it multiplies
+  // (KS = 1: those its own 32 rows see)
+  int n_it, n_loc, n_mine;
   auto see_window = [&]() __attribute__((always_inline)) {
     if (w_kpos0 + kTile - 1 > p_min) w_flags |= 1;
     const int jl = KS * (win_base + here()) + ks;
@@ -355,11 +371,14 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     n_loc = seen == ~0ull ? n_av : win_base + __popcll(seen);
     if constexpr (KS == 1) {
       n_loc = n_it = max(n_loc, 1);
+      const uint64_t own = __ballot(jl < n_all && w_kpos0 <= p_mine);
+      n_mine = own == ~0ull ? n_av : max(win_base + __popcll(own), 1);
     } else {
       const uint64_t pair = __ballot((jl ^ 1) < n_all && w_pair <= p_max);
       const int n_other = pair == ~0ull ? (n_all - (ks ^ 1) + 1) / 2 : win_base + __popcll(pair);
       n_it = max(max(n_loc, n_other), 1);
       if (BY) n_odd = min(n_loc, n_other);
+      n_mine = n_it;
     }
   };
   see_window();
@@ -368,45 +387,36 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   // lane (n, hh) keeps, for k-step kk, dims 16kk + 8hh .. +7; dims < 64 pair with dims + 64.
   const float c2 = 0.08838834764831845f * kLog2e;            // log2(e) / sqrt(128)
   u32x4 qreg[8];
+  // The four heads share the angles (KS = 2: so do the two streams): a wavefront computes a quarter (an eighth) of them.
   auto load_queries = [&]() __attribute__((always_inline)) {
-    const bf16_t* qp = q + (static_cast<size_t>(src_row) * hq + h) * kD + 8 * hh;
-    uint4 qx[4], qy[4];
+    char* lds_w = const_cast<char*>(lds_bytes);
+    // scratch: KS = 1: images 2 and 3; KS = 2: the streams' third K and second V images
+    regroup_query_rows(rows, lds_w + (KS == 1 ? 2 * (kImage * 16) + wave * 8192
+                                              : (whead < 2 ? k_image(2) + whead * 8192 : v_image(1) + (whead - 2) * 8192)), lane);
+    barrier();
+    float4* turns = reinterpret_cast<float4*>(lds_w + (KS == 1 ? 2 * (kImage * 16) + wgrp * 16384 : 2 * 16384)) + lane;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      qx[kk] = *reinterpret_cast<const uint4*>(qp + 16 * kk);
-      qy[kk] = *reinterpret_cast<const uint4*>(qp + 16 * kk + 64);
-    }
-    float4* turns = reinterpret_cast<float4*>(const_cast<char*>(lds_bytes) + (KS == 1 ? k_image(3) + wgrp * 16384 : k_image(2))) + lane;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float4 t;
-      rot_cos_sin_fast(p, inv_freq.f[16 * whead + 8 * hh + 2 * i], &t.x, &t.y);
-      rot_cos_sin_fast(p, inv_freq.f[16 * whead + 8 * hh + 2 * i + 1], &t.z, &t.w);
-      t.x *= c2; t.y *= c2; t.z *= c2; t.w *= c2;
-      turns[(whead * 4 + i) * 64] = t;
+    for (int i = 0; i < 4 / KS; ++i) {             // (float4 number c: rotation pairs 16 (c / 4) + 8 hh + 2 (c % 4), + 1)
+      const int c = KS == 1 ? 4 * whead + i : 2 * wave + i;
+      turns[c * 64] = query_turn(inv_freq, p, 16 * (c >> 2) + 2 * (c & 3), hh, c2);
     }
     wait_lds<0>();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    barrier();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      bf16x8 xv = __builtin_bit_cast(bf16x8, qx[kk]), yv = __builtin_bit_cast(bf16x8, qy[kk]);
+      u32x4 xv = __builtin_bit_cast(u32x4, rows[kk]), yv = __builtin_bit_cast(u32x4, rows[kk + 4]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float4 t = turns[(kk * 4 + i) * 64];
-        const float x0 = static_cast<float>(xv[2 * i]), y0 = static_cast<float>(yv[2 * i]);
-        const float x1 = static_cast<float>(xv[2 * i + 1]), y1 = static_cast<float>(yv[2 * i + 1]);
-        xv[2 * i] = static_cast<bf16_t>(x0 * t.x - y0 * t.y);
-        yv[2 * i] = static_cast<bf16_t>(y0 * t.x + x0 * t.y);
-        xv[2 * i + 1] = static_cast<bf16_t>(x1 * t.z - y1 * t.w);
-        yv[2 * i + 1] = static_cast<bf16_t>(y1 * t.z + x1 * t.w);
+        uint32_t x = xv[i], y = yv[i];
+        turn_words(x, y, turns[(kk * 4 + i) * 64]);
+        xv[i] = x;
+        yv[i] = y;
       }
-      // (a lane reads back what it wrote itself)
-      uint4* bounce = reinterpret_cast<uint4*>(const_cast<char*>(lds_bytes) + (KS == 1 ? 131072 : v_image(1))) + (KS == 1 ? tid : tid & 255);
-      bounce[0] = __builtin_bit_cast(uint4, xv);
-      bounce[512] = __builtin_bit_cast(uint4, yv);
-      lds_to_acc(bounce, qreg[kk], qreg[kk + 4]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(qreg[kk][i]) : "v"(xv[i]));
+        asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(qreg[kk + 4][i]) : "v"(yv[i]));
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -517,11 +527,12 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   load_queries();
   wait_loads(std::integral_constant<int, 0>{});
 #pragma unroll
-  for (int t = 0; t < kAheadV; ++t) {
+  for (int t = 0; t < kFirstV; ++t) {
     const int l = max(min(t, n_av - 1), 0);
     if (__builtin_amdgcn_readlane(w_flags, l) & 2) blank_padding(l, v_image(t));
   }
   __syncthreads();
+  if (KS == 1) first_loads(2);
   int f_cur = __builtin_amdgcn_readlane(w_flags, lane_of(0));      // flags of tile t, t+1 (carried from tile to tile)
   int f_next = __builtin_amdgcn_readlane(w_flags, lane_of(1));
   {
@@ -571,7 +582,7 @@ exp_step(0, i);
   // goes to cum[snap row][head][segment's index in its request].  A stream's reference never moves in this
   // kernel, so with one stream these running sums subtract exactly; two streams' sums meet under the larger of
   // their references, which rounds each once.  (Rare: once per segment of the request.)
-  const int seg_first = BY ? req_seg_off[r] : 0;
+  const int seg_first = BY ? req_seg_off[req] : 0;
   // (segments without tokens have no tile: the value also stands for those between this tile's
   // segment and the next tile's; the row sum is taken with the pair that is still to be packed)
   // KS = 2: the even stream writes what a segment that ends with its tile leaves, the odd one likewise; each needs the
@@ -611,14 +622,31 @@ exp_step(0, i);
     wait_lds<0>();                                 // (see blank_padding)
   };
   int f_far = 0;                                   // flags of tile t+2
-  for (int t = 0; t < n_it; ++t) {
-    const int kimg = k_image(t), vimg = v_image(t), knext = k_image(t + 1);
-    if (min(t + 3, n_it - 1) - win_base >= 64) {          // next 64 descriptors, starting at tile t (rare)
+  // next 64 descriptors, starting at tile t (rare)
+  auto move_window = [&](int t) __attribute__((always_inline)) {
+    if (min(t + 3, n_it - 1) - win_base >= 64) {
       win_base = t;
       fill_window(t);
       see_window();
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));      // vmcnt(0) here, so the hot path never waits for it
     }
+  };
+  // what the next iteration reads must be whole: KS = 1: image t+2 (loads started one iteration ago);
+  // KS = 2: K of tile t+2 and V of tile t+1, started in this iteration
+  auto end_tile = [&](int t) __attribute__((always_inline)) {
+    wait_loads(std::integral_constant<int, KS == 1 ? 4 : 0>{});
+    if (KS == 1) {
+      if (f_far & 2) blank_padding(lane_of(t + 2), v_image(t + 2));
+    } else {
+      if (f_next & 2) blank_padding(lane_of(t + 1), v_image(t + 1));
+    }
+    barrier();
+    f_cur = f_next; f_next = f_far;
+  };
+  int t = 0;
+  for (; t < n_mine; ++t) {
+    const int kimg = k_image(t), vimg = v_image(t), knext = k_image(t + 1);
+    move_window(t);
     // slot 1: S of the tile's second block; second half of the first block's exponentials.
     // Underneath: the loads of the tiles ahead (past the last tile they repeat the last tile into an
     // image nobody reads), one instruction group per k-step.
@@ -645,19 +673,27 @@ exp_step(0, i);
       if ((ends & 4) || ((ends & 8) && t < n_odd)) snapshot(t, tot, ends);
       prev = tot;
     }
-    if ((f_next & 1) || t + 1 >= n_loc) mask_tile(0, 0, t + 1);
+    if ((f_next & 1) || t + 1 >= (KS == 1 ? n_mine : n_loc)) mask_tile(0, 0, t + 1);
     // slot 4: PV of the second block; first half of the next block's exponentials
     pv_slot(kimg, vimg, knext, 24, 1, [&](int st) __attribute__((always_inline)) { exp_step(0, st); });
-    // what the next iteration reads must be whole: KS = 1: image t+2 (loads started one iteration ago);
-    // KS = 2: K of tile t+2 and V of tile t+1, started above
-    wait_loads(std::integral_constant<int, KS == 1 ? 4 : 0>{});
-    if (KS == 1) {
-      if (f_far & 2) blank_padding(lane_of(t + 2), v_image(t + 2));
-    } else {
-      if (f_next & 2) blank_padding(lane_of(t + 1), v_image(t + 1));
+    end_tile(t);
+  }
+  // KS = 1: tiles that only the workgroup's other rows see: this wavefront brings in its share of the tiles ahead and
+  // leaves the matrix pipe to the other half
+  if constexpr (KS == 1) {
+    for (; t < n_it; ++t) {
+      move_window(t);
+      f_far = __builtin_amdgcn_readlane(w_flags, lane_of(t + 2));
+      dma_begin(lane_of(t + kAheadK), lane_of(t + kAheadV), k_image(t + kAheadK), v_image(t + kAheadV));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) dma_k(j);
+      dma_v(0);
+      dma_v(1);
+      if constexpr (BY) {
+        if (f_cur & 4) snapshot(t, running(), 0);
+      }
+      end_tile(t);
     }
-    barrier();
-    f_cur = f_next; f_next = f_far;
   }
   // The output leaves the accumulation registers here, all at once and behind the last products.  (If its uses
   // further down may read them, the allocator parks some of the loop's own values there as well and moves them in
@@ -767,21 +803,49 @@ bool attn_v2_supported(const cc_ctx* ctx) {
   return (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) % 4 == 0;
 }
 
+// (CC_IMPL_MFMA_WIDE: the one-stream form at every size, as the score stage runs its 128-token form then)
+static bool attn_two_streams(const cc_ctx* ctx, int n_q_tot, int max_q_per_req, int n_requests) {
+  const int row_tiles = std::min((max_q_per_req + 63) / 64 * n_requests, n_q_tot / 64 + n_requests);
+  return static_cast<int64_t>(row_tiles) * (ctx->cfg.n_q_heads / 4) <= kTwoStreamGrid && ctx->impl != CC_IMPL_MFMA_WIDE;
+}
+
+// A list pays from about one and a half rounds of workgroups on (a compute unit holds one), as soon as there are several
+// requests: below, the second round is the short tiles of one request either way and the list's making (4 us) is lost.
+// Grid / list, us: 320 workgroups 242 / 247 (2 requests of 8.1k tokens), 350: 176 / 180 (3), 480: 256 / 232 (4), 700: 387 /
+// 359 (6), 1100: 516 / 487 (9), 1700: 733 / 727 (14).
+constexpr int kListedGrid = 400;
+
+WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int max_q_per_req, int n_requests, int max_tiles) {
+  WorkList list;
+  const int heads = ctx->cfg.n_q_heads / 4, row_tiles = n_q_tot / 64 + n_requests;
+  // (a list must have room for every row tile)
+  if (q_pos == nullptr || n_requests == 1 || static_cast<int64_t>(row_tiles) * heads <= kListedGrid || row_tiles > max_tiles - 1 ||
+      max_q_per_req > 64 * kMaxListed || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
+    return list;
+  list.kind = WorkList::kQueries;
+  list.rows = 64;
+  list.places = std::max(256 / heads, 1);
+  list.q_pos = q_pos;
+  return list;
+}
+
 void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
                     int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,
                     const Plan& pl, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                     int32_t* redo, const int32_t* q_map, int map_pos, const int32_t* snap_index, float* cum,
-                    int s_max, hipStream_t stream, const ValueSource& vs) {
+                    int s_max, const WorkList& list, hipStream_t stream, const ValueSource& vs) {
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4;
-  const int row_tiles = std::min((max_q_per_req + 63) / 64 * n_requests, n_q_tot / 64 + n_requests);
-  // (CC_IMPL_MFMA_WIDE: the one-stream form at every size, as the score stage runs its 128-token form then)
-  const bool two_streams = static_cast<int64_t>(row_tiles) * hkv * n_sub <= kTwoStreamGrid && ctx->impl != CC_IMPL_MFMA_WIDE;
+  const bool two_streams = attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests);
+  // (how many rows a request has is on the device: the list is an upper bound, what is too much leaves at once)
+  const int listed = list.kind != WorkList::kNone;
+  const int entries = n_requests <= kMaxSorted ? std::min(n_q_tot / 64 + n_requests, pl.max_tiles - 1) : pl.max_tiles - 1;
 #define CC_GO(KS, BY, TQ)                                                                                          \
   do {                                                                                                         \
     const int n_tiles = (max_q_per_req + TQ - 1) / TQ;                                                         \
-    hipLaunchKernelGGL((attn_v2_kernel<KS, BY>), dim3(hkv * n_sub * n_tiles, n_requests), dim3(512), 0, stream,    \
+    const dim3 grid = listed ? dim3(hkv * n_sub * entries) : dim3(hkv * n_sub * n_tiles, n_requests);          \
+    hipLaunchKernelGGL((attn_v2_kernel<KS, BY>), grid, dim3(512), 0, stream,                                    \
                        static_cast<const bf16_t*>(q), q_pos, static_cast<const bf16_t*>(k_pool),               \
-                       static_cast<const bf16_t*>(v_pool), pl.tiles, pl.max_tiles, pl.items,                   \
+                       static_cast<const bf16_t*>(v_pool), pl.tiles, pl.max_tiles, pl.items, pl.order, listed, \
                        req_seg_off, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq,                    \
                        static_cast<bf16_t*>(out), lse, redo, q_map, map_pos, snap_index, cum, s_max,           \
                        static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks,                            \

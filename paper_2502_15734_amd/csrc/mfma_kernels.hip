@@ -612,9 +612,9 @@ __global__ __launch_bounds__(256) void plan_fill_kernel(const cc_segment* __rest
 // order[rank] = item; ties keep index order, so the result is always a permutation.  More than
 // kMaxOrdered items: identity.
 //
-// Beside order[] one 32-byte work item per rank is written, so that a workgroup of the
-// wide kernels finds everything it needs to start with ONE load instead of a chain of dependent
-// ones (order -> segment -> request -> tile offsets).  Called by whole workgroups; `block` is the
+// Beside order[] a work item per request is written (attention), so that a workgroup of the
+// wide kernel finds what it needs of a request with ONE load instead of a chain of dependent
+// ones (request -> segments -> tile offsets).  Called by whole workgroups; `block` is the
 // workgroup's index among those that do this.
 template <bool BY_REQUEST>
 __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
@@ -626,19 +626,13 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
   const int i = block * 256 + threadIdx.x;
   auto emit = [&](int rank, int item) {
     order[rank] = item;
-    WorkItem w;
     if constexpr (BY_REQUEST) {
-      w.id = item; w.kind = 0; w.start = cu_q[item]; w.n_tokens = cu_q[item + 1] - cu_q[item]; w.tok_off = 0;
+      WorkItem w = {};
+      w.row = cu_q[item]; w.n_rows = cu_q[item + 1] - cu_q[item];
       w.j_begin = seg_tile_off[req_seg_off[item]];
-      w.j_own = seg_tile_off[req_seg_off[item + 1]];           // end of the request's tiles
-    } else {
-      const cc_segment sg = segs[item];
-      w.id = item; w.kind = sg.kind; w.start = sg.logical_start; w.n_tokens = sg.n_tokens; w.tok_off = sg.tok_off;
-      w.j_begin = seg_tile_off[req_seg_off[sg.req]];
-      w.j_own = seg_tile_off[item];
+      w.j_end = seg_tile_off[req_seg_off[item + 1]];
+      items[item] = w;
     }
-    w.pad = 0;
-    items[rank] = w;
   };
   if (n_items > kMaxOrdered) {
     if (i < n_items) emit(i, i);
@@ -666,14 +660,21 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
   emit(rank, i);
 }
 
-// The list of workgroups (WorkList), by one whole workgroup of 256 threads: row tiles counted per request, numbered
-// through, and put into buckets by the number of key tiles they see, longest first.  (Which of a bucket's tiles
-// comes first is left to chance: it decides when a workgroup starts, not what it computes.)
+// The list of workgroups (WorkList), by one whole workgroup of 256 threads.  Row tiles are counted per request and
+// numbered through; a tile's work is the number of key tiles it sees.  The list begins request by request, long tiles
+// first: the workgroups that run at a time then walk the same keys, which an XCD's L2 holds once (all tiles in the order
+// of their work instead: 8B batch of 32 requests 2077 -> 2243 us, 4 x 32 k tokens 8.1 -> 8.2 ms).  The shortest tiles of all requests
+// come last, long before short: they fill what the long ones leave at the end.  They are as many as make up the longest
+// tile's work on every place, but none longer than kShortest key tiles, whose keys and values (32 KiB a tile and KV head) would
+// not fit an XCD's L2 either (8 requests of 10k tokens on 600 workgroups: none of them 505 us, as many as
+// make up half of that work 481, this 452; 3 of 20k on 500: 784 and 664, without the limit 677).  (Which of two tiles of the same work comes first is left to
+// chance: it decides when a workgroup starts, not what it computes.)
 __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ segs, int n_segs,
                           const int32_t* __restrict__ req_seg_off, int n_requests, const int32_t* __restrict__ cu_q,
                           const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles) {
-  constexpr int kBuckets = 512;
-  __shared__ int off[kMaxSorted + 1], low[kMaxSorted], bucket[kBuckets], wsum[4], longest;
+  constexpr int kBuckets = 512, kShortest = 160;
+  __shared__ int off[kMaxSorted + 1], low[kMaxSorted], n_short[kMaxSorted], bucket[kBuckets], wsum[4], longest, first_short;
+  __shared__ uint32_t seen[kMaxSortedTiles];               // of a row tile: its request << 16 | its bucket
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const bool scored = list.kind == WorkList::kScored;
   auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
@@ -699,7 +700,7 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
     return;
   }
   // rows, then row tiles of every request; low: position of its first scored token
-  for (int r = tid; r < n_requests; r += 256) { off[r] = scored ? 0 : max(cu_q[r + 1] - cu_q[r], 0); low[r] = 0x7fffffff; }
+  for (int r = tid; r < n_requests; r += 256) { off[r] = scored ? 0 : max(cu_q[r + 1] - cu_q[r], 0); low[r] = 0x7fffffff; n_short[r] = 0; }
   for (int b = tid; b < kBuckets; b += 256) bucket[b] = 0;
   if (tid == 0) longest = 1;
   __syncthreads();
@@ -732,48 +733,85 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
   if (tid == 0) off[n_requests] = carry;
   __syncthreads();
   const int total = min(carry, max_tiles - 1);
-  int shift = 0;
-  while ((longest / kTile >> shift) >= kBuckets) ++shift;
-  // (bucket 0 holds the longest)
-  auto look_up = [&](int j, int* r, int* k) {
-    int lo = 0, hi = n_requests - 1;                       // last request with off[r] <= j
+  if (tid == 0) tiles[max_tiles - 1].work = total;
+  auto request_of = [&](int j) {                           // last request with off[r] <= j
+    int lo = 0, hi = n_requests - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (off[mid] <= j) lo = mid; else hi = mid - 1;
     }
-    *r = lo;
-    *k = j - off[lo];
-    const int last = scored ? low[lo] + list.rows * (*k + 1)
-                            : list.q_pos[min(cu_q[lo] + list.rows * (*k + 1), cu_q[lo + 1]) - 1];
-    return kBuckets - 1 - min(max(last / kTile >> shift, 0), kBuckets - 1);
+    return lo;
   };
-  for (int j = tid; j < total; j += 256) {
-    int r, k;
-    atomicAdd(&bucket[look_up(j, &r, &k)], 1);
+  // one request, or all start at once, or too many to sort: request by request
+  if (n_requests == 1 || total <= list.places || total > kMaxSortedTiles) {
+    for (int j = tid; j < total; j += 256) {
+      const int r = request_of(j), end = min(off[r + 1], total);
+      tiles[off[r] + end - 1 - j].work = entry(r, j - off[r]);
+    }
+    return;
   }
-  __syncthreads();
-  {
-    const int a = bucket[2 * tid], b = bucket[2 * tid + 1];
-    int incl = a + b;
+  int shift = 0;
+  while ((longest / kTile >> shift) >= kBuckets) ++shift;
+  // (bucket 0 holds the longest)
+  for (int j = tid; j < total; j += 256) {
+    const int r = request_of(j), k = j - off[r];
+    const int last = scored ? low[r] + list.rows * (k + 1) : list.q_pos[min(cu_q[r] + list.rows * (k + 1), cu_q[r + 1]) - 1];
+    const int at = kBuckets - 1 - min(max(last / kTile >> shift, 0), kBuckets - 1);
+    seen[j] = static_cast<uint32_t>(r) << 16 | static_cast<uint32_t>(at);
+    atomicAdd(&bucket[at], 1);
+  }
+  auto scan_256 = [&](int v) {                             // inclusive sum over the workgroup's threads
+    int incl = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const int up = __shfl_up(incl, o, 64);
       if (lane >= o) incl += up;
     }
+    __syncthreads();
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
-    int base = 0;
-    for (int ww = 0; ww < w; ++ww) base += wsum[ww];
-    bucket[2 * tid] = base + incl - a - b;
-    bucket[2 * tid + 1] = base + incl - b;
+    for (int ww = 0; ww < w; ++ww) incl += wsum[ww];
+    return incl;
+  };
+  const int cap = max(kBuckets - 1 - (kShortest >> shift), 0);      // (first bucket that may count as short)
+  if (tid == 0) first_short = cap;
+  __syncthreads();
+  {
+    // thread i has buckets 2 i, 2 i + 1; work behind them, in key tiles
+    const int a = bucket[2 * tid] * (kBuckets - 2 * tid), b = bucket[2 * tid + 1] * (kBuckets - 1 - 2 * tid);
+    const int incl = scan_256(a + b), all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    const int behind = all - incl, enough = list.places * ((longest / kTile >> shift) + 1);
+    if (behind < enough && behind + b >= enough) first_short = max(2 * tid + 1, cap);
+    else if (behind + b < enough && behind + b + a >= enough) first_short = max(2 * tid, cap);
+    bucket[2 * tid] = bucket[2 * tid + 1] = 0;
+  }
+  __syncthreads();
+  for (int j = tid; j < total; j += 256)
+    if (static_cast<int>(seen[j] & 0xffff) >= first_short) atomicAdd(&n_short[seen[j] >> 16], 1);
+  __syncthreads();
+  // a request's first n_short tiles are the short ones (its rows are mostly in prompt order)
+  for (int j = tid; j < total; j += 256) {
+    const int r = seen[j] >> 16;
+    if (j - off[r] < n_short[r]) atomicAdd(&bucket[seen[j] & 0xffff], 1);
+  }
+  __syncthreads();
+  const int a = bucket[2 * tid], b = bucket[2 * tid + 1], incl = scan_256(a + b);
+  const int n_long = total - (wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+  bucket[2 * tid] = incl - a - b;
+  bucket[2 * tid + 1] = incl - b;
+  int before = 0;                                          // long tiles of the requests in front
+  for (int r0 = 0; r0 < n_requests; r0 += 256) {
+    const int r = r0 + tid, first = r < n_requests ? min(off[r], total) : total, end = r < n_requests ? min(off[r + 1], total) : total;
+    const int n = end - first - (r < n_requests ? n_short[r] : 0), upto = scan_256(n);
+    if (r < n_requests) low[r] = before + upto - n;
+    before += wsum[0] + wsum[1] + wsum[2] + wsum[3];
   }
   __syncthreads();
   for (int j = tid; j < total; j += 256) {
-    int r, k;
-    const int at = atomicAdd(&bucket[look_up(j, &r, &k)], 1);
+    const int r = seen[j] >> 16, k = j - off[r], n = min(off[r + 1], total) - off[r];
+    const int at = k < n_short[r] ? n_long + atomicAdd(&bucket[seen[j] & 0xffff], 1) : low[r] + n - 1 - k;
     tiles[at].work = entry(r, k);
   }
-  if (tid == 0) tiles[max_tiles - 1].work = total;
 }
 
 template <bool BY_REQUEST>
@@ -963,11 +1001,13 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
   // tiles the wide one flagged (normally none: its workgroups read one flag and exit).
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && attn_v2_supported(ctx);
   const int n_redo = wide ? static_cast<int>(redo_entries(n_q_tot)) : 0;
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, true, cu_q, block_tab, n_blocks, max_tiles, n_redo, WorkList(), stream);
+  WorkList list;
+  if (wide) list = attn_v2_list(ctx, map_pos == 0 ? q_pos : nullptr, n_q_tot, max_q_per_req, n_requests, max_tiles);
+  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, true, cu_q, block_tab, n_blocks, max_tiles, n_redo, list, stream);
   if (wide)
     launch_attn_v2(ctx, q, q_pos, n_q_tot, max_q_per_req, k_pool, v_pool, pl, req_seg_off, n_requests,
                    out, lse, pl.redo, q_map, map_pos, by != nullptr ? by->snap_index : nullptr,
-                   by != nullptr ? by->cum : nullptr, by != nullptr ? by->s_max : 0, stream, vs);
+                   by != nullptr ? by->cum : nullptr, by != nullptr ? by->s_max : 0, list, stream, vs);
   if (by != nullptr) {
     by->wide = wide;
     by->redo = pl.redo;
@@ -996,7 +1036,11 @@ void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int
                     n_tok <= 64 * kMaxListed;
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
   WorkList list;
-  if (wide) { list.kind = WorkList::kScored; list.rows = small ? 64 : 128; }
+  if (wide) {
+    list.kind = WorkList::kScored;
+    list.rows = small ? 64 : 128;
+    list.places = std::max((small ? 256 : 512) / (ctx->cfg.n_q_heads / 4), 1);
+  }
   const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, stream);
   if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, stream);
   const int32_t* redo = pl.redo;

@@ -234,29 +234,26 @@ __device__ __forceinline__ f32x16 splat16(float v) {
 }  // namespace tile
 
 // ---- tile plan (built by plan kernels on the stream, kept in the caller's workspace) ----------
-// What the workgroups of grid row y need to start: the segment (score) or request (attention) of
-// dispatch rank y and where its key tiles begin.
+// What a workgroup of the wide attention kernel needs of a request.
 struct WorkItem {
-  int32_t id;         // segment / request index
-  int32_t kind;       // segment kind (score)
-  int32_t start;      // segment's logical start (score); request's first row of the query list (attention)
-  int32_t n_tokens;   // segment length (score); rows of the request (attention)
-  int32_t tok_off;    // segment's first row in per-token tensors (score)
-  int32_t j_begin;    // first key tile of the request
-  int32_t j_own;      // first tile of the segment itself (score); end of the request's tiles (attention)
-  int32_t pad;
+  int32_t row, n_rows;       // its rows of the query list
+  int32_t j_begin, j_end;    // its key tiles
+  int32_t pad[4];
 };
-static_assert(sizeof(WorkItem) == 32, "read as two 16-byte vectors");
-// List of workgroups, longest first: entry i sits in tiles[i].work - request << 16 | row tile of it (-1: none) - and the
+static_assert(sizeof(WorkItem) == 32, "room for two 16-byte vectors");
+
+// List of workgroups in the order they start: entry i sits in tiles[i].work - request << 16 | row tile of it (-1: none) - and the
 // number of entries in tiles[max_tiles - 1].work.  Rows: the scored tokens of a request (numbered through over its
 // chunks) or its rows of the query list.
 struct WorkList {
   enum Kind { kNone, kScored, kQueries } kind = kNone;
   int rows = 0;                     // rows of a workgroup
+  int places = 0;                   // workgroups of one head group that run at a time
   const int32_t* q_pos = nullptr;   // kQueries: position of every row
 };
 constexpr int kMaxOrdered = 4096;      // segments or requests that are sorted for the dispatch order
 constexpr int kMaxSorted = 2048;       // requests whose workgroups are sorted (else request by request, with gaps)
+constexpr int kMaxSortedTiles = 4096;  // row tiles that are sorted
 constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
 size_t plan_head_bytes(int n_segs);
@@ -277,7 +274,9 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
                     int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,
                     const Plan& pl, const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                     int32_t* redo, const int32_t* q_map, int map_pos, const int32_t* snap_index, float* cum,
-                    int s_max, hipStream_t stream, const ValueSource& vs);
+                    int s_max, const WorkList& list, hipStream_t stream, const ValueSource& vs);
+// its list of workgroups (kNone where there is none); q_pos: by list row, or null
+WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int max_q_per_req, int n_requests, int max_tiles);
 
 // The wide score kernel (128 tokens per wavefront, no softmax reference) flags 64-row granules of
 // the per-token tensors whose sums left the safe range; the narrow kernel redoes them.

@@ -369,3 +369,35 @@ def test_scores_of_tokens_numbered_through_the_chunks_of_a_request(hq, lens, chu
             assert torch.isfinite(got[impl]).all()
             assert float((got[impl] - got["MFMA_NARROW"]).abs().max()) <= bound
     assert float(got["MFMA_NARROW"].max()) > 0.1
+
+
+@pytest.mark.parametrize("hq,hkv,lens,reqs", [
+    (8, 2, [200, 90, 330], [([0, 1, 2], 0.3, 20), ([2, 2], 0.02, 1), ([1], 1.0, 64), ([0], 0.0, 3)]),
+    (8, 1, [700, 64], [([0, 0, 0, 0], 0.11, 70), ([1, 0], 0.5, 9)] * 5),      # rows far apart: the halves see other tiles
+    (4, 1, [17, 20], [([0, 1], 0.2, 2)] * 2100),                               # more requests than are sorted
+    (4, 1, [40], [([0], 1.0, 2)] * 3),                                         # (nearly) every token is a row
+])
+def test_attention_of_several_requests_from_the_list_of_workgroups(hq, hkv, lens, reqs):
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("listed", "bf16", hq, hkv, 128, 5.0e5, lens, [3] * len(lens),
+                 [W.RequestSpec(c, [f] * len(c), u) for c, f, u in reqs], 1.0 / math.sqrt(128), seed=101)
+    scores = torch.from_numpy(np.random.default_rng(5).random(w.n_tok).astype(np.float32)).cuda()
+    got = {}
+    for impl in ("MFMA_NARROW", "MFMA_WIDE", "AUTO"):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+        b.rope_shift(); b.select_from_scores(scores); b.sparse_prefill_fused(); torch.cuda.synchronize()
+        n = w.n_q_tot
+        got[impl] = b.out[:n].double().cpu().numpy(), b.lse[:n].double().cpu()
+    for impl in ("MFMA_WIDE", "AUTO"):
+        # both round P and the output to bf16: 2^-9 each, twice; the sums of up to n keys: sqrt(n) 2^-24, the hardware's
+        # exponential and logarithm 1e-6 each, twice
+        assert np.isfinite(got[impl][0]).all()
+        assert H.rel_l2(got[impl][0], got["MFMA_NARROW"][0]) <= 4 * 2.0 ** -9
+        assert float((got[impl][1] - got["MFMA_NARROW"][1]).abs().max()) <= 2 * (60 * 2.0 ** -24 + 2e-6) * 8
+    # the by-product form walks the same list: the same bits
+    out1, lse1 = b.out[:n].clone(), b.lse[:n].clone()
+    b.rope_shift(); b.select_from_scores(scores); mass = b.sparse_prefill_mass(fused=True).cpu()
+    assert torch.equal(out1, b.out[:n]) and torch.equal(lse1, b.lse[:n])
+    sums = torch.zeros(w.n_requests).index_add_(0, torch.from_numpy(w.segments[:, W.SEG_REQ].astype(np.int64)), mass)
+    assert float((sums - torch.tensor([float(u) for _, _, u in reqs])).abs().max()) <= 3e-3 * max(u for _, _, u in reqs)
