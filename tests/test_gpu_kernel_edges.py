@@ -401,3 +401,29 @@ def test_attention_of_several_requests_from_the_list_of_workgroups(hq, hkv, lens
     assert torch.equal(out1, b.out[:n]) and torch.equal(lse1, b.lse[:n])
     sums = torch.zeros(w.n_requests).index_add_(0, torch.from_numpy(w.segments[:, W.SEG_REQ].astype(np.int64)), mass)
     assert float((sums - torch.tensor([float(u) for _, _, u in reqs])).abs().max()) <= 3e-3 * max(u for _, _, u in reqs)
+
+
+@pytest.mark.parametrize("hq,hkv,lens,fracs,question", [(4, 1, [3, 1], [1.0, 1.0], 1), (8, 2, [70, 33, 16], [0.3, 1.0, 0.1], 5),
+                                                        (24, 3, [130], [0.5], 2), (8, 1, [40, 300], [1.0, 0.2], 17)])
+def test_weight_a_row_keeps_on_itself(hq, hkv, lens, fracs, question):
+    # rows of four heads at a time, a wavefront per row, four rows per workgroup (remainders 1, 2, 3); groups of 4 and 8 heads
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("self", "bf16", hq, hkv, 128, 5.0e5, lens, [5] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), fracs, question)], 1.0 / math.sqrt(128), seed=103)
+    b = DeviceBatch(w, poison=True)
+    b.rope_shift(); b.select_from_scores(torch.from_numpy(np.random.default_rng(9).random(w.n_tok).astype(np.float32)).cuda())
+    b.gather(); b.sparse_prefill()
+    _, self_mass, _ = b.chunk_attention()
+    torch.cuda.synchronize()
+    # own weights in double precision from what the call itself read: the rows' queries, the fixed pages, its log-sum-exp
+    n, k_pool = w.n_q_tot, b.k_req.double().cpu().numpy()
+    pos, slot = b.q_pos[:n].cpu().numpy(), b.slot_map[:n].cpu().numpy()
+    ang = pos[:, None] * (5.0e5 ** (-2.0 * np.arange(64) / 128))[None]
+    c, s = np.cos(ang)[:, None], np.sin(ang)[:, None]
+    x, y = np.split(b.q[b.q_row[:n].long()].double().cpu().numpy(), 2, axis=2)
+    k = k_pool[slot // 16, :, slot % 16].repeat(hq // hkv, axis=1)
+    logit = (np.concatenate([x * c - y * s, y * c + x * s], axis=2) * k).sum(axis=2) / math.sqrt(128)
+    own = np.exp(logit - b.lse[:n].double().cpu().numpy()).mean(axis=1)
+    ref = np.array([own[(pos >= g[W.SEG_START]) & (pos < g[W.SEG_START] + g[W.SEG_NTOK])].sum() for g in w.segments])
+    # fp32: 128 products and the sum over up to n rows and hq heads, the angle's 1e-6, the exponential's 1e-6
+    assert np.abs(self_mass.cpu().numpy() - ref).max() <= 1e-5 * max(1.0, ref.max())
