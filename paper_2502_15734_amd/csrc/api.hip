@@ -333,14 +333,16 @@ int cc_sparse_prefill(cc_ctx* ctx, const void* q, const void* k_new, const void*
   cc::ValueSource vs;
   if (!value_source(ctx, fn, shared, &vs)) return CC_ERR_INVALID_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  cc::launch_rope_scatter(ctx, k_new, v_new, q_pos, slot_map, n_q_tot, k_pool, v_pool, n_blocks, src_rows, st, vs);
+  const cc::ScatterJob scatter{k_new, v_new, src_rows, q_pos, slot_map, n_q_tot, k_pool, v_pool, n_blocks, vs};
   if (ctx->impl != CC_IMPL_SCALAR && cc::attn_mfma_supported(ctx))
     cc::launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks,
                          block_tab, segs, n_segs, req_seg_off, n_requests, out, lse, workspace,
-                         max_tiles_for(n_ctx_tokens, n_segs), src_rows, 0, st, nullptr, vs);
-  else
+                         max_tiles_for(n_ctx_tokens, n_segs), src_rows, 0, st, nullptr, vs, &scatter);
+  else {
+    cc::launch_rope_scatter(ctx, scatter, st);
     cc::launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks,
                            block_tab, segs, req_seg_off, n_requests, out, lse, src_rows, 0, st, vs);
+  }
   return cc::check_launch(ctx, fn);
 }
 
@@ -420,21 +422,23 @@ int cc_sparse_prefill_mass(cc_ctx* ctx, const void* q, const void* k_new, const 
                 "cc_sparse_prefill_mass: workspace smaller than cc_sparse_prefill_mass_workspace_bytes()");
   cc::ValueSource vs;
   if (!value_source(ctx, fn, shared, &vs)) return CC_ERR_INVALID_ARG;
-  cc::launch_rope_scatter(ctx, k_new, v_new, q_pos, slot_map, n_q_tot, k_pool, v_pool, n_blocks, src_rows, st, vs);
+  const cc::ScatterJob scatter{k_new, v_new, src_rows, q_pos, slot_map, n_q_tot, k_pool, v_pool, n_blocks, vs};
   if (max_question_rows == 0) {                               // no question rows: plain attention, zero masses
     if (ctx->impl != CC_IMPL_SCALAR && cc::attn_mfma_supported(ctx))
       cc::launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab,
                            segs, n_segs, req_seg_off, n_requests, out, lse, workspace,
-                           max_tiles_for(n_ctx_tokens, n_segs), src_rows, 0, st, nullptr, vs);
-    else
+                           max_tiles_for(n_ctx_tokens, n_segs), src_rows, 0, st, nullptr, vs, &scatter);
+    else {
+      cc::launch_rope_scatter(ctx, scatter, st);
       cc::launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab,
                              segs, req_seg_off, n_requests, out, lse, src_rows, 0, st, vs);
+    }
     cc::launch_fill_zero(seg_mass, n_segs, st);
     return cc::check_launch(ctx, fn);
   }
   cc::launch_prefill_mass(ctx, q, src_rows, q_pos, cu_q, n_q_tot, max_q_per_req, max_question_rows, max_segs_per_req,
                           k_pool, v_pool, n_blocks, block_tab, segs, n_segs, req_seg_off, n_requests,
-                          n_ctx_tokens, out, lse, seg_mass, workspace, max_tiles_for(n_ctx_tokens, n_segs), st, vs);
+                          n_ctx_tokens, out, lse, seg_mass, workspace, max_tiles_for(n_ctx_tokens, n_segs), st, scatter);
   return cc::check_launch(ctx, fn);
 }
 
@@ -488,12 +492,12 @@ int cc_sparse_prefill_pairs(cc_ctx* ctx, const void* q, const void* k_new, const
                 "cc_sparse_prefill_pairs: workspace smaller than cc_sparse_prefill_pairs_workspace_bytes()");
   cc::ValueSource vs;
   if (!value_source(ctx, fn, shared, &vs)) return CC_ERR_INVALID_ARG;
-  cc::launch_rope_scatter(ctx, k_new, v_new, q_pos, slot_map, n_q_tot, k_pool, v_pool, n_blocks, src_rows, st, vs);
+  const cc::ScatterJob scatter{k_new, v_new, src_rows, q_pos, slot_map, n_q_tot, k_pool, v_pool, n_blocks, vs};
   cc::launch_fill_zero(pair_mass, n_pairs, st);               // pairs no row of the list falls into stay 0
   cc::launch_prefill_pairs(ctx, q, src_rows, q_pos, slot_map, cu_q, n_q_tot, max_q_per_req, max_segs_per_req, k_pool,
                            v_pool, n_blocks, block_tab, segs, n_segs, req_seg_off, n_requests, n_ctx_tokens,
                            out, lse, seg_mass, pair_mass, n_pairs, self_mass, workspace,
-                           max_tiles_for(n_ctx_tokens, n_segs), st, vs);
+                           max_tiles_for(n_ctx_tokens, n_segs), st, scatter);
   return cc::check_launch(ctx, fn);
 }
 
@@ -508,7 +512,7 @@ int cc_scatter_kv(cc_ctx* ctx, const void* k_new, const void* v_new, const int32
   CC_REQUIRE(n_blocks > 0, "sizes must be positive");
   CC_REQUIRE(aligned16(k_new) && aligned16(v_new) && aligned16(k_pool) && aligned16(v_pool),
              "tensors must be 16-byte aligned");
-  cc::launch_rope_scatter(ctx, k_new, v_new, q_pos, slot_map, n_rows, k_pool, v_pool, n_blocks, nullptr,
+  cc::launch_rope_scatter(ctx, cc::ScatterJob{k_new, v_new, nullptr, q_pos, slot_map, n_rows, k_pool, v_pool, n_blocks, cc::ValueSource()},
                           static_cast<hipStream_t>(stream));
   return cc::check_launch(ctx, fn);
 }

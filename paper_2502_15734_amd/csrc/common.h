@@ -81,10 +81,16 @@ void launch_topn(const cc_ctx* ctx, const float* mass, const int32_t* block_tab,
                  int32_t* q_pos, int32_t* slot_map, float* scores, uint32_t* key_buf,
                  bool given, hipStream_t stream);
 
-void launch_rope_scatter(const cc_ctx* ctx, const void* k_new, const void* v_new,
-                         const int32_t* q_pos, const int32_t* slot_map, int n_q_tot, void* k_pool,
-                         void* v_pool, int n_blocks, const int32_t* src_rows, hipStream_t stream,
-                         const ValueSource& vs = ValueSource());
+// New K, V rows and the slots they go to (cc_scatter_kv; step 1 of the prefill calls).
+struct ScatterJob {
+  const void *k_new, *v_new;
+  const int32_t *src_rows, *q_pos, *slot_map;
+  int n_rows;
+  void *k_pool, *v_pool;
+  int n_blocks;
+  ValueSource vs;
+};
+void launch_rope_scatter(const cc_ctx* ctx, const ScatterJob& job, hipStream_t stream);
 void launch_list_order_check(const int32_t* slot_map, int n_rows, int n_blocks, int32_t* mark,
                              int32_t* n_violations, hipStream_t stream);
 void launch_attn_plain(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
@@ -110,7 +116,8 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
                       int n_blocks, const int32_t* block_tab, const cc_segment* segs, int n_segs,
                       const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                       void* plan_ws, int max_tiles, const int32_t* q_map, int map_pos, hipStream_t stream,
-                      const AttnByProduct* by = nullptr, const ValueSource& vs = ValueSource());
+                      const AttnByProduct* by = nullptr, const ValueSource& vs = ValueSource(),
+                      const ScatterJob* scatter = nullptr);      // (a scatter to run in front of the attention)
 
 // attention mass of the question rows on every segment (focus.hip)
 void launch_fill_zero(float* p, int n, hipStream_t stream);
@@ -138,7 +145,7 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
                          const void* v_pool, int n_blocks, const int32_t* block_tab, const cc_segment* segs,
                          int n_segs, const int32_t* req_seg_off, int n_requests, int n_ctx_tokens, void* out,
                          float* lse, float* seg_mass, void* workspace, int max_tiles, hipStream_t stream,
-                         const ValueSource& vs = ValueSource());
+                         const ScatterJob& scatter);
 
 // ... and with the whole segment-to-segment matrix (every row's cumulative sums are kept)
 size_t prefill_pairs_bytes(const cc_ctx* ctx, int n_ctx_tokens, int n_segs, int max_tiles, int n_q_tot,
@@ -149,7 +156,7 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
                           int n_segs, const int32_t* req_seg_off, int n_requests, int n_ctx_tokens, void* out,
                           float* lse, float* seg_mass, float* pair_mass, int n_pairs, float* self_mass,
                           void* workspace, int max_tiles, hipStream_t stream,
-                          const ValueSource& vs = ValueSource());
+                          const ScatterJob& scatter);
 
 // attention for head groups that are a multiple of 4: 64 query rows per wavefront (attn_mfma2.hip)
 bool attn_v2_supported(const cc_ctx* ctx);

@@ -734,7 +734,8 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
                          const void* v_pool, int n_blocks, const int32_t* block_tab, const cc_segment* segs,
                          int n_segs, const int32_t* req_seg_off, int n_requests, int n_ctx_tokens, void* out,
                          float* lse, float* seg_mass, void* workspace, int max_tiles, hipStream_t stream,
-                         const ValueSource& vs) {
+                         const ScatterJob& scatter) {
+  const ValueSource& vs = scatter.vs;
   const int hq = ctx->cfg.n_q_heads, hkv = ctx->cfg.n_kv_heads;
   const size_t cap = static_cast<size_t>(n_requests) * max_question_rows;
   char* w = static_cast<char*>(workspace);
@@ -767,8 +768,9 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
     hipLaunchKernelGGL(fill_kernel, dim3(static_cast<unsigned>((n_cum + 255) / 256)), dim3(256), 0, stream, cum, n_cum,
                        -INFINITY);
     launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
-                     n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs);
+                     n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs, &scatter);
   } else {
+    launch_rope_scatter(ctx, scatter, stream);
     launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                        req_seg_off, n_requests, out, lse, src_rows, 0, stream, vs);
   }
@@ -811,7 +813,8 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
                           const void* v_pool, int n_blocks, const int32_t* block_tab, const cc_segment* segs,
                           int n_segs, const int32_t* req_seg_off, int n_requests, int n_ctx_tokens, void* out,
                           float* lse, float* seg_mass, float* pair_mass, int n_pairs, float* self_mass,
-                          void* workspace, int max_tiles, hipStream_t stream, const ValueSource& vs) {
+                          void* workspace, int max_tiles, hipStream_t stream, const ScatterJob& scatter) {
+  const ValueSource& vs = scatter.vs;
   const int hq = ctx->cfg.n_q_heads, hkv = ctx->cfg.n_kv_heads;
   char* w = static_cast<char*>(workspace);
   void* plan_ws = w;
@@ -829,8 +832,9 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
     hipLaunchKernelGGL(fill_kernel, dim3(static_cast<unsigned>((n_cum + 255) / 256)), dim3(256), 0, stream, cum, n_cum,
                        -INFINITY);
     launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
-                     n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs);
+                     n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs, &scatter);
   } else {
+    launch_rope_scatter(ctx, scatter, stream);
     launch_attn_plain(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                        req_seg_off, n_requests, out, lse, src_rows, 0, stream, vs);
   }

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "mfma_tile.h"
+#include "scatter.h"
 
 namespace cc {
 
@@ -531,13 +532,28 @@ __global__ __launch_bounds__(64 * G, 2) void sparse_qk_kernel(
   }   // rounds
 }
 
+// ---- LDS of the plan's parts (no workgroup runs two of them) ---------------------------------------
+constexpr int kPlanFused = 1024;       // segments up to which the whole plan is one launch
+constexpr int kListBuckets = 512;
+struct PlanLds {
+  int32_t seg_tile_off[kPlanFused + 1];
+  int wsum[4], carry;
+  union {
+    int key[kMaxOrdered];              // dispatch order
+    struct {                           // list of workgroups
+      int off[kMaxSorted + 1], low[kMaxSorted], n_short[kMaxSorted], bucket[kListBuckets], longest, first_short;
+      uint32_t seen[kMaxSortedTiles];  // of a row tile: its request << 16 | its bucket
+    } list;
+  };
+};
+
 // ---- plan: the key tiles of every segment, in prompt order ---------------------------------------
 // seg_tile_off[s] = number of tiles before segment s (exclusive scan of ceil(n_tokens/64)); run by
 // one whole workgroup of 256 threads, into global memory or into LDS.
 __device__ __forceinline__ void plan_scan(const cc_segment* __restrict__ segs, int n_segs,
-                                          int32_t* seg_tile_off) {
-  __shared__ int wsum[4];
-  __shared__ int carry_s;
+                                          int32_t* seg_tile_off, PlanLds& lds) {
+  int (&wsum)[4] = lds.wsum;
+  int& carry_s = lds.carry;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   if (tid == 0) carry_s = 0;
   __syncthreads();
@@ -565,7 +581,8 @@ __device__ __forceinline__ void plan_scan(const cc_segment* __restrict__ segs, i
 
 __global__ __launch_bounds__(256) void plan_scan_kernel(const cc_segment* __restrict__ segs, int n_segs,
                                                          int32_t* __restrict__ seg_tile_off) {
-  plan_scan(segs, n_segs, seg_tile_off);
+  __shared__ PlanLds lds;
+  plan_scan(segs, n_segs, seg_tile_off, lds);
 }
 
 // descriptor of tile j (and the redo flags cleared, spread over the n_fill workgroups that do this)
@@ -621,8 +638,8 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
                                            const int32_t* __restrict__ req_seg_off,
                                            const int32_t* __restrict__ cu_q,
                                            const int32_t* seg_tile_off, int n_items,
-                                           int32_t* __restrict__ order, WorkItem* __restrict__ items, int block) {
-  __shared__ int key[kMaxOrdered];
+                                           int32_t* __restrict__ order, WorkItem* __restrict__ items, int block, PlanLds& lds) {
+  int (&key)[kMaxOrdered] = lds.key;
   const int i = block * 256 + threadIdx.x;
   auto emit = [&](int rank, int item) {
     order[rank] = item;
@@ -671,10 +688,11 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
 // chance: it decides when a workgroup starts, not what it computes.)
 __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ segs, int n_segs,
                           const int32_t* __restrict__ req_seg_off, int n_requests, const int32_t* __restrict__ cu_q,
-                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles) {
-  constexpr int kBuckets = 512, kShortest = 160;
-  __shared__ int off[kMaxSorted + 1], low[kMaxSorted], n_short[kMaxSorted], bucket[kBuckets], wsum[4], longest, first_short;
-  __shared__ uint32_t seen[kMaxSortedTiles];               // of a row tile: its request << 16 | its bucket
+                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles, PlanLds& lds) {
+  constexpr int kBuckets = kListBuckets, kShortest = 160;
+  int (&off)[kMaxSorted + 1] = lds.list.off, (&low)[kMaxSorted] = lds.list.low, (&n_short)[kMaxSorted] = lds.list.n_short;
+  int (&bucket)[kListBuckets] = lds.list.bucket, (&wsum)[4] = lds.wsum, &longest = lds.list.longest, &first_short = lds.list.first_short;
+  uint32_t (&seen)[kMaxSortedTiles] = lds.list.seen;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const bool scored = list.kind == WorkList::kScored;
   auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
@@ -821,7 +839,8 @@ __global__ __launch_bounds__(256) void plan_order_kernel(const cc_segment* __res
                                                           const int32_t* __restrict__ seg_tile_off,
                                                           int n_items, int32_t* __restrict__ order,
                                                           WorkItem* __restrict__ items) {
-  plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, seg_tile_off, n_items, order, items, blockIdx.x);
+  __shared__ PlanLds lds;
+  plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, seg_tile_off, n_items, order, items, blockIdx.x, lds);
 }
 
 __global__ __launch_bounds__(256) void plan_list_kernel(WorkList list, const cc_segment* __restrict__ segs, int n_segs,
@@ -829,35 +848,58 @@ __global__ __launch_bounds__(256) void plan_list_kernel(WorkList list, const cc_
                                                          const int32_t* __restrict__ cu_q,
                                                          const int32_t* __restrict__ seg_tile_off,
                                                          TileDesc* __restrict__ tiles, int max_tiles) {
-  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles);
+  __shared__ PlanLds lds;
+  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles, lds);
 }
 
 // The whole plan in ONE launch, for batches of up to kPlanFused segments: every workgroup repeats
 // the (tiny) scan into LDS, then the first n_fill workgroups write descriptors, the others the
-// dispatch order, and the last one the list of workgroups if there is to be one.  Two launches and two waits between dependent kernels fewer per call, which is
-// what a single request's step (a dozen kernels of a few microseconds) is made of.
-constexpr int kPlanFused = 1024;
+// dispatch order, and the last one the list of workgroups if there is to be one.  Two launches and two waits between dependent
+// kernels fewer per call, which is what a single request's step (a dozen kernels of a few microseconds) is made of.
+struct PlanArgs {
+  const cc_segment* segs;
+  const int32_t *req_seg_off, *cu_q, *block_tab;
+  int n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_groups;      // n_groups: workgroups of the plan
+  int32_t *seg_tile_off, *order, *redo;
+  WorkItem* items;
+  TileDesc* tiles;
+  WorkList list;
+};
 
 template <bool BY_REQUEST>
-__global__ __launch_bounds__(256) void plan_fused_kernel(const cc_segment* __restrict__ segs, int n_segs,
-                                                          const int32_t* __restrict__ req_seg_off,
-                                                          const int32_t* __restrict__ cu_q, int n_items,
-                                                          const int32_t* __restrict__ block_tab, int n_blocks,
-                                                          int max_tiles, int32_t* __restrict__ seg_tile_off,
-                                                          int32_t* __restrict__ order, WorkItem* __restrict__ items,
-                                                          TileDesc* __restrict__ tiles, int32_t* __restrict__ redo,
-                                                          int n_redo, int n_fill, int n_requests, WorkList list) {
-  __shared__ int32_t s_off[kPlanFused + 1];
-  plan_scan(segs, n_segs, s_off);
-  if (blockIdx.x == 0)
-    for (int s = threadIdx.x; s <= n_segs; s += 256) seg_tile_off[s] = s_off[s];
-  if (static_cast<int>(blockIdx.x) < n_fill)
-    plan_fill(segs, n_segs, s_off, block_tab, n_blocks, max_tiles, tiles, redo, n_redo,
-              blockIdx.x * 256 + threadIdx.x, n_fill);
-  else if (list.kind == WorkList::kNone || blockIdx.x + 1 < gridDim.x)
-    plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, s_off, n_items, order, items, blockIdx.x - n_fill);
+__device__ __forceinline__ void plan_part(const PlanArgs& a, int block, PlanLds& lds) {
+  plan_scan(a.segs, a.n_segs, lds.seg_tile_off, lds);
+  if (block == 0)
+    for (int s = threadIdx.x; s <= a.n_segs; s += 256) a.seg_tile_off[s] = lds.seg_tile_off[s];
+  if (block < a.n_fill)
+    plan_fill(a.segs, a.n_segs, lds.seg_tile_off, a.block_tab, a.n_blocks, a.max_tiles, a.tiles, a.redo, a.n_redo,
+              block * 256 + threadIdx.x, a.n_fill);
+  else if (a.list.kind == WorkList::kNone || block + 1 < a.n_groups)
+    plan_order<BY_REQUEST>(a.segs, a.req_seg_off, a.cu_q, lds.seg_tile_off, a.n_items, a.order, a.items, block - a.n_fill, lds);
   else
-    plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, s_off, tiles, max_tiles);
+    plan_list(a.list, a.segs, a.n_segs, a.req_seg_off, a.n_requests, a.cu_q, lds.seg_tile_off, a.tiles, a.max_tiles, lds);
+}
+
+template <bool BY_REQUEST>
+__global__ __launch_bounds__(256) void plan_fused_kernel(PlanArgs a) {
+  __shared__ PlanLds lds;
+  plan_part<BY_REQUEST>(a, blockIdx.x, lds);
+}
+
+// The attention's plan and the scatter in front of it need nothing of each other: its first workgroups make the plan, the
+// others scatter.  (A plan launched behind the scatter: 4 us of one request's step, with a list 10 - 15 us of a batch's.)
+__global__ __launch_bounds__(256) void scatter_plan_kernel(
+    PlanArgs a, const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, const int32_t* __restrict__ q_pos,
+    const int32_t* __restrict__ slot_map, int n_q_tot, int hkv, InvFreq inv_freq, bf16_t* __restrict__ k_pool,
+    bf16_t* __restrict__ v_pool, int n_blocks, const int32_t* __restrict__ src_rows, const bf16_t* __restrict__ v_shared,
+    int n_shared_blocks, int32_t* __restrict__ v_map) {
+  __shared__ PlanLds lds;
+  const int block = blockIdx.x;
+  if (block < a.n_groups)
+    plan_part<true>(a, block, lds);
+  else
+    rope_scatter_rows<bf16_t, kD>(block - a.n_groups, k_new, v_new, q_pos, slot_map, n_q_tot, hkv, inv_freq, k_pool, v_pool,
+                                  n_blocks, src_rows, v_shared, n_shared_blocks, v_map);
 }
 
 constexpr int kAttnQB = 1;     // 32 query tokens per workgroup in the attention kernel
@@ -924,9 +966,9 @@ static size_t plan_bytes_impl(int n_segs, int max_tiles) {
   return plan_head_bytes(n_segs) + static_cast<size_t>(max_tiles) * sizeof(TileDesc);
 }
 
-Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,
+Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,
               const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, const WorkList& list,
-              hipStream_t stream) {
+              const ScatterJob* scatter, hipStream_t stream) {
   Plan pl;
   pl.seg_tile_off = static_cast<int32_t*>(ws);
   pl.order = pl.seg_tile_off + n_segs + 1;
@@ -937,16 +979,23 @@ Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_s
   const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256, n_order = (n_items + 255) / 256;
   const bool listed = list.kind != WorkList::kNone;
   if (n_segs <= kPlanFused) {
-    const dim3 grid(n_fill + n_order + (listed ? 1 : 0));
-#define CC_FUSED(BY_REQUEST)                                                                                        \
-  hipLaunchKernelGGL(plan_fused_kernel<BY_REQUEST>, grid, dim3(256), 0, stream, segs, n_segs, req_seg_off, cu_q, n_items,  \
-                     block_tab, n_blocks, max_tiles, pl.seg_tile_off, pl.order, pl.items, pl.tiles, pl.redo, n_redo, n_fill, \
-                     n_requests, list)
-    if (by_request) CC_FUSED(true);
-    else CC_FUSED(false);
-#undef CC_FUSED
+    const int n_groups = n_fill + n_order + (listed ? 1 : 0);
+    const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_groups,
+                     pl.seg_tile_off, pl.order, pl.redo, pl.items, pl.tiles, list};
+    if (by_request && scatter != nullptr && scatter->n_rows > 0)
+      hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + kScatterRows - 1) / kScatterRows), dim3(256), 0, stream,
+                         a, static_cast<const bf16_t*>(scatter->k_new), static_cast<const bf16_t*>(scatter->v_new),
+                         scatter->q_pos, scatter->slot_map, scatter->n_rows, ctx->cfg.n_kv_heads, ctx->inv_freq,
+                         static_cast<bf16_t*>(scatter->k_pool), static_cast<bf16_t*>(scatter->v_pool), scatter->n_blocks,
+                         scatter->src_rows, static_cast<const bf16_t*>(scatter->vs.v_shared), scatter->vs.n_shared_blocks,
+                         scatter->vs.v_map);
+    else if (by_request)
+      hipLaunchKernelGGL(plan_fused_kernel<true>, dim3(n_groups), dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL(plan_fused_kernel<false>, dim3(n_groups), dim3(256), 0, stream, a);
     return pl;
   }
+  if (scatter != nullptr) launch_rope_scatter(ctx, *scatter, stream);
   hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off);
   if (by_request)                                      // attention: the grid's y index walks requests
     hipLaunchKernelGGL(plan_order_kernel<true>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
@@ -996,14 +1045,14 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
                       int n_blocks, const int32_t* block_tab, const cc_segment* segs, int n_segs,
                       const int32_t* req_seg_off, int n_requests, void* out, float* lse,
                       void* plan_ws, int max_tiles, const int32_t* q_map, int map_pos, hipStream_t stream,
-                      const AttnByProduct* by, const ValueSource& vs) {
+                      const AttnByProduct* by, const ValueSource& vs, const ScatterJob* scatter) {
   // Wide kernel first where the head group allows it; the narrow kernel then redoes the 64-row
   // tiles the wide one flagged (normally none: its workgroups read one flag and exit).
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && attn_v2_supported(ctx);
   const int n_redo = wide ? static_cast<int>(redo_entries(n_q_tot)) : 0;
   WorkList list;
   if (wide) list = attn_v2_list(ctx, map_pos == 0 ? q_pos : nullptr, n_q_tot, max_q_per_req, n_requests, max_tiles);
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, true, cu_q, block_tab, n_blocks, max_tiles, n_redo, list, stream);
+  const Plan pl = run_plan(ctx, plan_ws, segs, n_segs, req_seg_off, n_requests, true, cu_q, block_tab, n_blocks, max_tiles, n_redo, list, scatter, stream);
   if (wide)
     launch_attn_v2(ctx, q, q_pos, n_q_tot, max_q_per_req, k_pool, v_pool, pl, req_seg_off, n_requests,
                    out, lse, pl.redo, q_map, map_pos, by != nullptr ? by->snap_index : nullptr,
@@ -1041,7 +1090,7 @@ void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int
     list.rows = small ? 64 : 128;
     list.places = std::max((small ? 256 : 512) / (ctx->cfg.n_q_heads / 4), 1);
   }
-  const Plan pl = run_plan(plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, stream);
+  const Plan pl = run_plan(ctx, plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, nullptr, stream);
   if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, stream);
   const int32_t* redo = pl.redo;
 #define CC_ARGS ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, redo, stream

@@ -252,16 +252,17 @@ struct WorkList {
   const int32_t* q_pos = nullptr;   // kQueries: position of every row
 };
 constexpr int kMaxOrdered = 4096;      // segments or requests that are sorted for the dispatch order
-constexpr int kMaxSorted = 2048;       // requests whose workgroups are sorted (else request by request, with gaps)
-constexpr int kMaxSortedTiles = 4096;  // row tiles that are sorted
+constexpr int kMaxSorted = 512;       // requests whose workgroups are sorted (else request by request, with gaps)
+constexpr int kMaxSortedTiles = 2048;  // row tiles that are sorted
 constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
 size_t plan_head_bytes(int n_segs);
 // by_request: dispatch order over requests (attention; cu_q delimits their rows), else over segments (score).
-// list: the list of workgroups to build beside it.
+// list: the list of workgroups to build beside it.  scatter: a scatter to run beside it (attention), or null.
 // n_redo > 0: the plan also holds n_redo redo flags (after the tiles), cleared by the plan kernels.
-Plan run_plan(void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,
-              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, const WorkList& list, hipStream_t stream);
+Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,
+              const int32_t* cu_q, const int32_t* block_tab, int n_blocks, int max_tiles, int n_redo, const WorkList& list,
+              const ScatterJob* scatter, hipStream_t stream);
 
 // The wide attention kernel (64 query rows per workgroup, 32 in two key streams) keeps one softmax reference per row; rows
 // whose sums leave the safe range are flagged in redo[] and redone by the narrow kernel, which can
