@@ -183,13 +183,15 @@ int cc_select(cc_ctx* ctx, const void* q, int32_t n_tok, const void* k_pool, int
       static_cast<char*>(workspace) +
       cc::align_up(static_cast<size_t>(n_tok) * ctx->cfg.n_q_heads * sizeof(float), 256));
   void* plan_ws = reinterpret_cast<char*>(keys) + cc::align_up(static_cast<size_t>(n_tok) * sizeof(uint32_t), 256);
-  if (ctx->impl != CC_IMPL_SCALAR && cc::score_mfma_supported(ctx))
-    cc::launch_score_mfma(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off, n_requests,
-                          max_seg_tokens, mass, plan_ws, max_tiles_for(n_tok, n_segs), n_tok, st);
-  else
+  const cc::TopnJob topn{block_tab, segs, n_segs, sel_idx, q_row, q_pos, slot_map, scores, keys};
+  if (ctx->impl != CC_IMPL_SCALAR && cc::score_mfma_supported(ctx)) {
+    cc::launch_select_mfma(ctx, q, k_pool, n_blocks, req_seg_off, n_requests, max_seg_tokens, mass, plan_ws,
+                           max_tiles_for(n_tok, n_segs), n_tok, topn, st);
+  } else {
     cc::launch_score_plain(ctx, q, k_pool, n_blocks, block_tab, segs, n_segs, req_seg_off,
                             max_seg_tokens, mass, st);
-  cc::launch_topn(ctx, mass, block_tab, segs, n_segs, sel_idx, q_row, q_pos, slot_map, scores, keys, false, st);
+    cc::launch_topn(ctx, mass, topn, false, st);
+  }
   return cc::check_launch(ctx, fn);
 }
 
@@ -211,7 +213,7 @@ int cc_select_from_scores(cc_ctx* ctx, const float* scores, int32_t n_tok, const
   uint32_t* keys = reinterpret_cast<uint32_t*>(
       static_cast<char*>(workspace) +
       cc::align_up(static_cast<size_t>(n_tok) * ctx->cfg.n_q_heads * sizeof(float), 256));
-  cc::launch_topn(ctx, scores, block_tab, segs, n_segs, sel_idx, q_row, q_pos, slot_map, nullptr, keys, true,
+  cc::launch_topn(ctx, scores, cc::TopnJob{block_tab, segs, n_segs, sel_idx, q_row, q_pos, slot_map, nullptr, keys}, true,
                   static_cast<hipStream_t>(stream));
   return cc::check_launch(ctx, fn);
 }

@@ -66,20 +66,25 @@ void launch_score_plain(const cc_ctx* ctx, const void* q, const void* k_pool, in
                          const int32_t* block_tab, const cc_segment* segs, int n_segs,
                          const int32_t* req_seg_off, int max_seg_tokens, float* mass,
                          hipStream_t stream);
+// The selection that follows the scores.
+struct TopnJob {
+  const int32_t* block_tab;
+  const cc_segment* segs;
+  int n_segs;
+  int32_t *sel_idx, *q_row, *q_pos, *slot_map;
+  float* scores;
+  uint32_t* key_buf;
+};
 bool score_mfma_supported(const cc_ctx* ctx);
 // bytes of the tile plan (per-segment tile offsets + tile descriptors, and the redo flags of up to
 // n_q_max query rows) the MFMA kernels need
 size_t mfma_plan_bytes(int n_segs, int max_tiles, int n_q_max);
-void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
-                       const int32_t* block_tab, const cc_segment* segs, int n_segs,
-                       const int32_t* req_seg_off, int n_requests, int max_seg_tokens, float* mass,
-                       void* plan_ws, int max_tiles, int n_tok, hipStream_t stream);
+void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
+                        const int32_t* req_seg_off, int n_requests, int max_seg_tokens, float* mass,
+                        void* plan_ws, int max_tiles, int n_tok, const TopnJob& topn, hipStream_t stream);
 // given = false: mass [n_tok][Hq], score = mean over heads (0 for a chunk at position 0);
 // given = true: mass [n_tok] are the scores themselves
-void launch_topn(const cc_ctx* ctx, const float* mass, const int32_t* block_tab,
-                 const cc_segment* segs, int n_segs, int32_t* sel_idx, int32_t* q_row,
-                 int32_t* q_pos, int32_t* slot_map, float* scores, uint32_t* key_buf,
-                 bool given, hipStream_t stream);
+void launch_topn(const cc_ctx* ctx, const float* mass, const TopnJob& job, bool given, hipStream_t stream);
 
 // New K, V rows and the slots they go to (cc_scatter_kv; step 1 of the prefill calls).
 struct ScatterJob {

@@ -31,6 +31,7 @@
 
 #include "mfma_tile.h"
 #include "scatter.h"
+#include "topn.h"
 
 namespace cc {
 
@@ -81,12 +82,13 @@ __device__ __forceinline__ void stage_direct(uint4* lds, const bf16_t* __restric
 //                and walks those, one KV head after the other; without flags - the normal case -
 //                it is gone after one round of loads, so the pass costs a few hundred short
 //                workgroups instead of one per (tile, KV head).
+// (item: the segment or request of this workgroup)
 template <int G, bool SCORE, int QB, bool REDO>
-__global__ __launch_bounds__(64 * G, 2) void sparse_qk_kernel(
-    const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos, const int32_t* __restrict__ cu_q,
+__device__ __forceinline__ void sparse_qk(
+    int y_item, const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos, const int32_t* __restrict__ cu_q,
     const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool, int n_blocks,
     const TileDesc* __restrict__ tiles, const int32_t* __restrict__ seg_tile_off, int max_tiles,
-    const int32_t* __restrict__ order, const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
+    const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
     float* __restrict__ mass, const int32_t* __restrict__ redo, const int32_t* __restrict__ q_map,
     int map_pos, const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
@@ -104,7 +106,6 @@ __global__ __launch_bounds__(64 * G, 2) void sparse_qk_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int n = lane & 31, hh = lane >> 5;
   // ---- which row tiles ----------------------------------------------------------------------
-  const int y_item = order[blockIdx.y];     // segment (score; heaviest first) or request (attention; longest context first)
   cc_segment sg_own = {};
   int q_first = 0, q_end = 0;
   if constexpr (SCORE) sg_own = segs[y_item];
@@ -532,6 +533,36 @@ __global__ __launch_bounds__(64 * G, 2) void sparse_qk_kernel(
   }   // rounds
 }
 
+template <int G, bool SCORE, int QB, bool REDO>
+__global__ __launch_bounds__(64 * G, 2) void sparse_qk_kernel(
+    const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos, const int32_t* __restrict__ cu_q,
+    const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool, int n_blocks,
+    const TileDesc* __restrict__ tiles, const int32_t* __restrict__ seg_tile_off, int max_tiles,
+    const int32_t* __restrict__ order, const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
+    int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
+    float* __restrict__ mass, const int32_t* __restrict__ redo, const int32_t* __restrict__ q_map,
+    int map_pos, const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
+  // segment (score; heaviest first) or request (attention; longest context first)
+  sparse_qk<G, SCORE, QB, REDO>(order[blockIdx.y], q, q_pos, cu_q, k_pool, v_pool, n_blocks, tiles, seg_tile_off, max_tiles, segs, req_seg_off, hq, hkv, n_tiles_x, inv_freq, out, lse, mass, redo, q_map, map_pos, v_shared, n_shared_blocks, v_map);
+}
+
+// Behind the wide score kernel: a segment's workgroup redoes its flagged tokens (normally none) and then selects.  (As
+// launches of their own the second pass, which mostly reads its flags and leaves, was 5 us of a single request's step.)
+template <int G, int QB>
+__global__ __launch_bounds__(64 * G, 2) void redo_topn_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_pool, int n_blocks, const TileDesc* __restrict__ tiles,
+    const int32_t* __restrict__ seg_tile_off, int max_tiles, const cc_segment* __restrict__ segs,
+    const int32_t* __restrict__ req_seg_off, int hq, int hkv, int n_tiles_x, InvFreq inv_freq, float* mass,
+    const int32_t* __restrict__ redo, const int32_t* __restrict__ block_tab, int32_t* __restrict__ sel_idx,
+    int32_t* __restrict__ q_row, int32_t* __restrict__ q_pos, int32_t* __restrict__ slot_map, float* __restrict__ scores,
+    uint32_t* key_buf) {
+  sparse_qk<G, true, QB, true>(blockIdx.x, q, nullptr, nullptr, k_pool, nullptr, n_blocks, tiles, seg_tile_off, max_tiles, segs,
+                               req_seg_off, hq, hkv, n_tiles_x, inv_freq, nullptr, nullptr, mass, redo, nullptr, 0, nullptr, 0,
+                               nullptr);
+  __syncthreads();                                    // (what it wrote is read by the other wavefronts)
+  topn_block<G>(blockIdx.x, mass, hq, false, block_tab, segs, sel_idx, q_row, q_pos, slot_map, scores, key_buf);
+}
+
 // ---- LDS of the plan's parts (no workgroup runs two of them) ---------------------------------------
 constexpr int kPlanFused = 1024;       // segments up to which the whole plan is one launch
 constexpr int kListBuckets = 512;
@@ -925,24 +956,30 @@ void launch_attn_g(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const
 #undef CC_KARGS
 }
 
+// the narrow score kernel over everything, or - behind the wide one (redo) - over what that flagged; then the selection
 template <int G>
-void launch_score_g(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks, const Plan& pl,
-                    const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int max_seg_tokens,
-                    float* mass, const int32_t* redo, hipStream_t stream) {
+void launch_select_g(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks, const Plan& pl,
+                     const int32_t* req_seg_off, int max_seg_tokens, float* mass, const int32_t* redo, const TopnJob& topn,
+                     hipStream_t stream) {
   const int hkv = ctx->cfg.n_kv_heads, n_tiles = (max_seg_tokens + 32 * kScoreQB - 1) / (32 * kScoreQB);
-#define CC_KARGS static_cast<const bf16_t*>(q), static_cast<const int32_t*>(nullptr),                             \
-                 static_cast<const int32_t*>(nullptr), static_cast<const bf16_t*>(k_pool),                      \
-                 static_cast<const bf16_t*>(nullptr), n_blocks, pl.tiles, pl.seg_tile_off, pl.max_tiles,        \
-                 pl.order, segs, req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq,                  \
-                 static_cast<bf16_t*>(nullptr), static_cast<float*>(nullptr), mass, redo,                       \
-                 static_cast<const int32_t*>(nullptr), 0, static_cast<const bf16_t*>(nullptr), 0,               \
-                 static_cast<const int32_t*>(nullptr)
-  if (redo != nullptr)
-    hipLaunchKernelGGL((sparse_qk_kernel<G, true, kScoreQB, true>), dim3(1, n_segs), dim3(64 * G), 0, stream, CC_KARGS);
-  else
-    hipLaunchKernelGGL((sparse_qk_kernel<G, true, kScoreQB, false>), dim3(hkv * n_tiles, n_segs), dim3(64 * G), 0, stream,
-                       CC_KARGS);
-#undef CC_KARGS
+  if constexpr (G % 4 == 0) {
+    if (redo != nullptr) {
+      hipLaunchKernelGGL((redo_topn_kernel<G, kScoreQB>), dim3(topn.n_segs), dim3(64 * G), 0, stream, static_cast<const bf16_t*>(q),
+                         static_cast<const bf16_t*>(k_pool), n_blocks, pl.tiles, pl.seg_tile_off, pl.max_tiles, topn.segs,
+                         req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq, mass, redo, topn.block_tab, topn.sel_idx,
+                         topn.q_row, topn.q_pos, topn.slot_map, topn.scores, topn.key_buf);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((sparse_qk_kernel<G, true, kScoreQB, false>), dim3(hkv * n_tiles, topn.n_segs), dim3(64 * G), 0, stream,
+                     static_cast<const bf16_t*>(q), static_cast<const int32_t*>(nullptr),
+                     static_cast<const int32_t*>(nullptr), static_cast<const bf16_t*>(k_pool),
+                     static_cast<const bf16_t*>(nullptr), n_blocks, pl.tiles, pl.seg_tile_off, pl.max_tiles,
+                     pl.order, topn.segs, req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq,
+                     static_cast<bf16_t*>(nullptr), static_cast<float*>(nullptr), mass, redo,
+                     static_cast<const int32_t*>(nullptr), 0, static_cast<const bf16_t*>(nullptr), 0,
+                     static_cast<const int32_t*>(nullptr));
+  launch_topn(ctx, mass, topn, false, stream);
 }
 
 bool group_supported(const cc_ctx* ctx) {
@@ -1072,10 +1109,12 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
 #undef CC_ARGS
 }
 
-void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
-                       const int32_t* block_tab, const cc_segment* segs, int n_segs,
-                       const int32_t* req_seg_off, int n_requests, int max_seg_tokens, float* mass,
-                       void* plan_ws, int max_tiles, int n_tok, hipStream_t stream) {
+void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int n_blocks,
+                        const int32_t* req_seg_off, int n_requests, int max_seg_tokens, float* mass,
+                        void* plan_ws, int max_tiles, int n_tok, const TopnJob& topn, hipStream_t stream) {
+  const cc_segment* segs = topn.segs;
+  const int32_t* block_tab = topn.block_tab;
+  const int n_segs = topn.n_segs;
   // Wide kernel first where the head group and the grid allow it; the narrow kernel then
   // redoes the granules the wide one flagged (normally none: its workgroups read two flags and exit).
   const int wide_wgs = ctx->cfg.n_q_heads / 4 * ((max_seg_tokens + 127) / 128) * n_segs;
@@ -1093,12 +1132,12 @@ void launch_score_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, int
   const Plan pl = run_plan(ctx, plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, nullptr, stream);
   if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, stream);
   const int32_t* redo = pl.redo;
-#define CC_ARGS ctx, q, k_pool, n_blocks, pl, segs, n_segs, req_seg_off, max_seg_tokens, mass, redo, stream
+#define CC_ARGS ctx, q, k_pool, n_blocks, pl, req_seg_off, max_seg_tokens, mass, redo, topn, stream
   switch (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) {
-    case 1: launch_score_g<1>(CC_ARGS); break;
-    case 2: launch_score_g<2>(CC_ARGS); break;
-    case 4: launch_score_g<4>(CC_ARGS); break;
-    default: launch_score_g<8>(CC_ARGS); break;
+    case 1: launch_select_g<1>(CC_ARGS); break;
+    case 2: launch_select_g<2>(CC_ARGS); break;
+    case 4: launch_select_g<4>(CC_ARGS); break;
+    default: launch_select_g<8>(CC_ARGS); break;
   }
 #undef CC_ARGS
 }
