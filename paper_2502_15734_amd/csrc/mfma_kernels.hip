@@ -929,7 +929,7 @@ __global__ __launch_bounds__(256) void scatter_plan_kernel(
   if (block < a.n_groups)
     plan_part<true>(a, block, lds);
   else
-    rope_scatter_rows<bf16_t, kD>(block - a.n_groups, k_new, v_new, q_pos, slot_map, n_q_tot, hkv, inv_freq, k_pool, v_pool,
+    rope_scatter_rows<bf16_t, kD>(block - a.n_groups, scatter_rows(n_q_tot), k_new, v_new, q_pos, slot_map, n_q_tot, hkv, inv_freq, k_pool, v_pool,
                                   n_blocks, src_rows, v_shared, n_shared_blocks, v_map);
 }
 
@@ -1020,7 +1020,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
     const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_groups,
                      pl.seg_tile_off, pl.order, pl.redo, pl.items, pl.tiles, list};
     if (by_request && scatter != nullptr && scatter->n_rows > 0)
-      hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + kScatterRows - 1) / kScatterRows), dim3(256), 0, stream,
+      hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + scatter_rows(scatter->n_rows) - 1) / scatter_rows(scatter->n_rows)), dim3(256), 0, stream,
                          a, static_cast<const bf16_t*>(scatter->k_new), static_cast<const bf16_t*>(scatter->v_new),
                          scatter->q_pos, scatter->slot_map, scatter->n_rows, ctx->cfg.n_kv_heads, ctx->inv_freq,
                          static_cast<bf16_t*>(scatter->k_pool), static_cast<bf16_t*>(scatter->v_pool), scatter->n_blocks,

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void rope_scatter_kernel(
     const int32_t* __restrict__ slot_map, int n_q_tot, int hkv, InvFreq inv_freq,
     T* __restrict__ k_pool, T* __restrict__ v_pool, int n_blocks, const int32_t* __restrict__ src_rows,
     const T* __restrict__ v_shared, int n_shared_blocks, int32_t* __restrict__ v_map) {
-  rope_scatter_rows<T, D>(blockIdx.x, k_new, v_new, q_pos, slot_map, n_q_tot, hkv, inv_freq, k_pool, v_pool, n_blocks, src_rows,
+  rope_scatter_rows<T, D>(blockIdx.x, scatter_rows(n_q_tot), k_new, v_new, q_pos, slot_map, n_q_tot, hkv, inv_freq, k_pool, v_pool, n_blocks, src_rows,
                           v_shared, n_shared_blocks, v_map);
 }
 
@@ -80,7 +80,7 @@ void launch_rope_scatter(const cc_ctx* ctx, const ScatterJob& job, hipStream_t s
   const bool bf = ctx->cfg.dtype == CC_BF16;
   const int d = ctx->cfg.head_dim, hkv = ctx->cfg.n_kv_heads;
 #define CC_LAUNCH(T, D)                                                                          \
-  hipLaunchKernelGGL((rope_scatter_kernel<T, D>), dim3((job.n_rows + kScatterRows - 1) / kScatterRows), dim3(256), 0, stream, \
+  hipLaunchKernelGGL((rope_scatter_kernel<T, D>), dim3((job.n_rows + scatter_rows(job.n_rows) - 1) / scatter_rows(job.n_rows)), dim3(256), 0, stream, \
                      static_cast<const T*>(job.k_new), static_cast<const T*>(job.v_new), job.q_pos, job.slot_map, \
                      job.n_rows, hkv, ctx->inv_freq, static_cast<T*>(job.k_pool), static_cast<T*>(job.v_pool),  \
                      job.n_blocks, job.src_rows, static_cast<const T*>(job.vs.v_shared), job.vs.n_shared_blocks, job.vs.v_map)

@@ -726,9 +726,9 @@ void launch_gated_linear(const cc_ctx* ctx, const void* x, const void* w_gate, c
 }
 
 // ---- root-mean-square normalisation: y = x / sqrt(mean(x^2) + eps) * gain ---------------------------
-// One wavefront per row (four rows per workgroup).  Rows of up to 64 x 16 pieces of 16 bytes stay
-// in registers between the sum of squares and the scaling, so each row moves once in and once out
-// of HBM; longer rows are read a second time.
+// Rows of 256 to 1024 pieces of 16 bytes take a workgroup each (rms_norm_row_kernel), others a wavefront (four rows per
+// workgroup).  A row stays in registers between the sum of squares and the scaling, so that it moves once in
+// and once out of HBM; rows of more than 1024 pieces are read a second time.
 // the elements of a 16-byte piece as floats, and back, without taking the piece's address (which
 // would move a register array to scratch memory)
 __device__ __forceinline__ void piece_to_floats(const uint4& p, float (&f)[8], bf16_t*) {
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const T* x, const T* __re
   const int row = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
   if (row >= n_rows) return;
   constexpr int kPer = 16 / sizeof(T);                 // elements per 16-byte piece
-  constexpr int kKeep = 16;                            // pieces a lane keeps
+  constexpr int kKeep = 4;                             // pieces a lane keeps
   const T* xr = x + static_cast<size_t>(row) * hidden;
   T* yr = y + static_cast<size_t>(row) * hidden;
   const int n_pieces = hidden / kPer;                  // (the call checks that hidden is a multiple of kPer)
@@ -796,15 +796,64 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const T* x, const T* __re
   }
 }
 
+// A workgroup of four wavefronts per row.  With a wavefront per row a short list leaves most compute units without one, and a
+// lane's chain is four times as long: 449 x 4096 in a decoder layer 6.9 -> 5.2 us, 230 x 8192 11.5 -> 5.5, 14000 x 4096 47 -> 40 (5.7 TB/s),
+// 14000 x 8192 93 -> 80.
+template <typename T>
+__global__ __launch_bounds__(256) void rms_norm_row_kernel(const T* x, const T* __restrict__ gain, float eps, int hidden, T* y) {   // (y may be x)
+  constexpr int kPer = 16 / sizeof(T), kKeep = 4;      // elements per 16-byte piece; pieces a thread keeps
+  __shared__ float part[4];
+  const int tid = threadIdx.x, n_pieces = hidden / kPer;
+  const T* xr = x + static_cast<size_t>(blockIdx.x) * hidden;
+  T* yr = y + static_cast<size_t>(blockIdx.x) * hidden;
+  uint4 held[kKeep], g[kKeep];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i) {
+    const int p = tid + 256 * i;
+    held[i] = p < n_pieces ? *reinterpret_cast<const uint4*>(xr + p * kPer) : uint4{0, 0, 0, 0};
+    g[i] = p < n_pieces ? *reinterpret_cast<const uint4*>(gain + p * kPer) : uint4{0, 0, 0, 0};
+  }
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i) {
+    float f[kPer];
+    piece_to_floats(held[i], f, static_cast<T*>(nullptr));
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) ss += f[e] * f[e];
+  }
+  ss = wave_sum(ss);
+  if ((tid & 63) == 0) part[tid >> 6] = ss;
+  __syncthreads();
+  const float scale = rsqrtf((part[0] + part[1] + part[2] + part[3]) / static_cast<float>(hidden) + eps);
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i) {
+    const int p = tid + 256 * i;
+    if (p >= n_pieces) continue;
+    float f[kPer], w[kPer];
+    T o[kPer];
+    piece_to_floats(held[i], f, static_cast<T*>(nullptr));
+    piece_to_floats(g[i], w, static_cast<T*>(nullptr));
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) o[e] = from_float<T>(f[e] * scale * w[e]);
+    *reinterpret_cast<uint4*>(yr + p * kPer) = *reinterpret_cast<uint4*>(o);
+  }
+}
+
 void launch_rms_norm(const cc_ctx* ctx, const void* x, const void* gain, float eps, int n_rows, int hidden, void* y,
                      hipStream_t stream) {
-  const dim3 grid((n_rows + 3) / 4);
-  if (ctx->cfg.dtype == CC_BF16)
-    hipLaunchKernelGGL(rms_norm_kernel<bf16_t>, grid, dim3(256), 0, stream, static_cast<const bf16_t*>(x),
-                       static_cast<const bf16_t*>(gain), eps, n_rows, hidden, static_cast<bf16_t*>(y));
-  else
-    hipLaunchKernelGGL(rms_norm_kernel<float>, grid, dim3(256), 0, stream, static_cast<const float*>(x),
-                       static_cast<const float*>(gain), eps, n_rows, hidden, static_cast<float*>(y));
+  const bool bf = ctx->cfg.dtype == CC_BF16;
+  const int n_pieces = hidden / (bf ? 8 : 4);
+  const bool by_row = n_pieces >= 256 && n_pieces <= 256 * 4;
+  const dim3 grid(by_row ? n_rows : (n_rows + 3) / 4);
+#define CC_LAUNCH(T)                                                                                             \
+  do {                                                                                                           \
+    const T *xt = static_cast<const T*>(x), *gt = static_cast<const T*>(gain);                                   \
+    if (by_row) hipLaunchKernelGGL(rms_norm_row_kernel<T>, grid, dim3(256), 0, stream, xt, gt, eps, hidden, static_cast<T*>(y)); \
+    else hipLaunchKernelGGL(rms_norm_kernel<T>, grid, dim3(256), 0, stream, xt, gt, eps, n_rows, hidden, static_cast<T*>(y)); \
+  } while (0)
+  if (bf) CC_LAUNCH(bf16_t);
+  else CC_LAUNCH(float);
+#undef CC_LAUNCH
 }
 
 }  // namespace cc

@@ -8,7 +8,7 @@ namespace cc {
 
 // Rotate-and-scatter of the recomputed K/V rows into their cache slots.  Rows of the compact query
 // list that fall into the same 16-token block are adjacent (the order cc_select emits) and form a
-// run.  A workgroup looks at kScatterRows consecutive rows and handles every run that STARTS among them (a
+// run.  A workgroup looks at `rows` consecutive rows and handles every run that STARTS among them (a
 // run may reach into the next workgroup's rows; it is still handled where it starts); its four
 // wavefronts each take a quarter of the KV heads.
 //   K rows are token-major and written directly, in 16-byte pieces.
@@ -19,26 +19,27 @@ namespace cc {
 // Bound by bytes (a page of values in and out per run) once enough runs are in flight, so nothing of
 // a run passes through LDS and no wavefront waits for another: runs are found with one load and
 // ballots, source rows and slots travel by lane permutes.
-// kScatterRows = 4: one or two candidates start too many workgroups that find nothing on dense lists, eight or
-// sixteen leave too few runs in flight on short or scattered ones (8 KV heads, d = 128: 449 rows
-// 17 -> 9 us, 39.9 k scattered rows 236 -> 160, 20 k dense rows 43 -> 40 us against a workgroup that
-// walked 16 candidates with three barriers per run).
-constexpr int kScatterRows = 4;
+// Rows per workgroup: 4 on long lists, where fewer candidates start too many workgroups that find nothing on dense lists and
+// eight or sixteen leave too few runs in flight on scattered ones.  Short lists: a run is a chain of four dependent loads,
+// so that a workgroup should have one.  8 KV heads, d = 128, every seventh token / all of them, us with 4, 2, 1 rows: 230 rows 12.5,
+// 10.2, 9.4 / 8.8, 9.0, 8.7; 1000: 17.6, 12.8, 10.9 / 9.5, 9.7, 9.1; 2000: 20.3, 18.3, 16.3 / 9.7, 9.8, 11.3; 4000: 39.9, 38.3, 35.1 /
+// 11.5, 13.5, 16.1; 16000: 116, 114, 113 / 36, 39, 76.
+__host__ __device__ inline int scatter_rows(int n_rows) { return n_rows <= 1024 ? 1 : n_rows <= 2048 ? 2 : 4; }
 
 // (block: the workgroup's number among those that do this)
 template <typename T, int D>
 __device__ __forceinline__ void rope_scatter_rows(
-    int block, const T* __restrict__ k_new, const T* __restrict__ v_new, const int32_t* __restrict__ q_pos,
+    int block, int rows, const T* __restrict__ k_new, const T* __restrict__ v_new, const int32_t* __restrict__ q_pos,
     const int32_t* __restrict__ slot_map, int n_q_tot, int hkv, InvFreq inv_freq,
     T* __restrict__ k_pool, T* __restrict__ v_pool, int n_blocks, const int32_t* __restrict__ src_rows,
     const T* __restrict__ v_shared, int n_shared_blocks, int32_t* __restrict__ v_map) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int base = block * kScatterRows;
+  const int base = block * rows;
   // lane i looks at row base - 1 + i: the row before the first candidate, the candidates, and the
   // rows a run that starts at the last of them can still cover
   int slot = -1, row = 0, pos = 0;
   const int j = base - 1 + lane;
-  if (lane < kScatterRows + kBlock && j >= 0 && j < n_q_tot) {
+  if (lane < rows + kBlock && j >= 0 && j < n_q_tot) {
     slot = slot_map[j];
     row = src_rows != nullptr ? src_rows[j] : j;             // (row of k_new, v_new this list row reads)
     pos = q_pos[j];
@@ -46,7 +47,7 @@ __device__ __forceinline__ void rope_scatter_rows(
   }
   const int my_blk = slot >= 0 ? slot / kBlock : -1;
   const int before = __shfl_up(my_blk, 1, 64);
-  unsigned long long starts = __ballot(lane >= 1 && lane <= kScatterRows && my_blk >= 0 && before != my_blk);
+  unsigned long long starts = __ballot(lane >= 1 && lane <= rows && my_blk >= 0 && before != my_blk);
   // this wavefront's KV heads
   const int per = (hkv + 3) / 4, h_first = wave * per;
   const int nh = max(min(per, hkv - h_first), 0);

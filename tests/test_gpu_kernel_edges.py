@@ -427,3 +427,50 @@ def test_weight_a_row_keeps_on_itself(hq, hkv, lens, fracs, question):
     ref = np.array([own[(pos >= g[W.SEG_START]) & (pos < g[W.SEG_START] + g[W.SEG_NTOK])].sum() for g in w.segments])
     # fp32: 128 products and the sum over up to n rows and hq heads, the angle's 1e-6, the exponential's 1e-6
     assert np.abs(self_mass.cpu().numpy() - ref).max() <= 1e-5 * max(1.0, ref.max())
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1025, 2047, 2050])
+@pytest.mark.parametrize("dense", [False, True])
+def test_scatter_with_one_two_and_four_rows_per_workgroup(n, dense):
+    import paper_2502_15734_amd as P
+    ctx = P.Context(8, 2, 128, 5.0e5, P.CC_BF16)
+    rng = np.random.default_rng(n)
+    tok = n if dense else 5 * n
+    nb = (tok + 15) // 16 + 3
+    idx = np.arange(n) if dense else np.sort(rng.choice(tok, n, replace=False))
+    blocks = rng.permutation(nb)
+    slot = torch.tensor((blocks[idx // 16] * 16 + idx % 16).astype(np.int32), device="cuda")
+    pos = torch.tensor((idx + 7).astype(np.int32), device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    k_new, v_new, k_pool, v_pool = rnd(n, 2, 128), rnd(n, 2, 128), rnd(nb, 2, 16, 128), rnd(nb, 2, 128, 16)
+    k_ref, v_ref = k_pool.double(), v_pool.clone()
+    ang = pos.double()[:, None] * (5.0e5 ** (-2.0 * torch.arange(64, dtype=torch.float64, device="cuda") / 128))[None]
+    c, s = ang.cos()[:, None], ang.sin()[:, None]
+    x, y = k_new.double().split(64, dim=2)
+    b, o = slot.long() // 16, slot.long() % 16
+    k_ref[b, :, o] = torch.cat([x * c - y * s, y * c + x * s], dim=2)
+    v_ref[b, :, :, o] = v_new
+    ctx.scatter_kv(k_new, v_new, pos, slot, k_pool, v_pool)
+    torch.cuda.synchronize()
+    assert torch.equal(v_pool, v_ref)                         # (values are copied; everything else stays)
+    # one rounding to bf16 (2^-9 of a value of up to 6) and angles good to 1e-6
+    assert float((k_pool.double() - k_ref).abs().max()) <= 2.0 ** -8 * 8
+
+
+@pytest.mark.parametrize("hidden", [2040, 2048, 2056, 8192, 8200])
+def test_rms_norm_where_rows_change_from_wavefronts_to_workgroups(hidden):
+    import paper_2502_15734_amd as P
+    ctx = P.Context(8, 2, 128, 5.0e5, P.CC_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(hidden)
+    for n in (1, 5):
+        x = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+        g = torch.empty(hidden, dtype=torch.bfloat16, device="cuda").normal_(1.0, 0.1, generator=gen)
+        ref = x.double() / (x.double().pow(2).mean(dim=1, keepdim=True) + 1e-5).sqrt() * g.double()
+        y = torch.empty_like(x)
+        ctx.rms_norm(x, g, 1e-5, y)
+        ctx.rms_norm(x, g, 1e-5, x)                           # (in place)
+        torch.cuda.synchronize()
+        assert torch.equal(x, y)
+        # the rounding to bf16, and 1e-6 of the scale
+        assert ((y.double() - ref).abs() <= ref.abs() * (2.0 ** -8 + 2e-6)).all()
