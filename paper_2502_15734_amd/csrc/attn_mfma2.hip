@@ -813,14 +813,18 @@ static bool attn_two_streams(const cc_ctx* ctx, int n_q_tot, int max_q_per_req, 
 // requests: below, the second round is the short tiles of one request either way and the list's making (4 us) is lost.
 // Grid / list, us: 320 workgroups 242 / 247 (2 requests of 8.1k tokens), 350: 176 / 180 (3), 480: 256 / 232 (4), 700: 387 /
 // 359 (6), 1100: 516 / 487 (9), 1700: 733 / 727 (14).
-constexpr int kListedGrid = 400;
+// Beyond four rounds the tail is a small part, and prompts of more than kListedTiles key tiles (8 MiB of keys and values per KV head) lose more
+// from short tiles of several requests side by side: 4 x 32k tokens on 1700 workgroups, the whole layer 7.72 / 7.77 ms; 8 x 20k on 6000
+// the same; but 3 x 20k on 500 784 / 664 us, and the 8B batch of 32 x 5k on 5100 1 % faster listed.
+constexpr int kListedGrid = 400, kListedRounds = 1024, kListedTiles = 256;
 
 WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int max_q_per_req, int n_requests, int max_tiles) {
   WorkList list;
   const int heads = ctx->cfg.n_q_heads / 4, row_tiles = n_q_tot / 64 + n_requests;
+  const int64_t grid = static_cast<int64_t>(row_tiles) * heads;
   // (a list must have room for every row tile)
-  if (q_pos == nullptr || n_requests == 1 || static_cast<int64_t>(row_tiles) * heads <= kListedGrid || row_tiles > max_tiles - 1 ||
-      max_q_per_req > 64 * kMaxListed || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
+  if (q_pos == nullptr || n_requests == 1 || grid <= kListedGrid || row_tiles > max_tiles - 1 ||
+      (grid > kListedRounds && max_tiles / n_requests > kListedTiles) || max_q_per_req > 64 * kMaxListed || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
     return list;
   list.kind = WorkList::kQueries;
   list.rows = 64;
