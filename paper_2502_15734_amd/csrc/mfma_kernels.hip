@@ -1053,10 +1053,12 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
 // compute unit) as long as its workgroups run in about one round, or in two with prompts long enough that the longest chain of
 // tiles decides: it halves that chain.  In between the narrow kernel, of which two workgroups share a unit (later where a
 // KV head has 8 query heads: a narrow workgroup takes all of them, so there are half as many).  Whole
-// cc_select call, narrow / small, us, by 64-token workgroups (chunks behind the first) and tokens of a prompt: 256 workgroups:
-// 768 34.7 / 34.5, 1.2k 47.9 / 42.6, 3k 88.6 / 74.0; 336 to 352: 1.2k 51.2 / 56.9, 2.1k 71.6 / 73.7 (32 / 8 heads) and
-// 84.7 / 73.9 (64 / 8), 3.5k 102 / 85; 512: 1.5k 61 / 73, 2.6k 83.2 / 86.5 and 95.4 / 85.3, 4.6k 129 / 114, 9k 273 / 193; 640:
-// 3k 118 / 126, 5.4k 165 / 178; 1024: 2.3k 115 / 135, 4.6k 190 / 207, 9k 353 / 375.
+// cc_select call, narrow / small, us, by the 64-token workgroups that the rule estimates and the chunks of the requests.  32 / 8
+// heads: 130 (3 x 512) 49.9 / 38.7, 258 (5 x 512) 72.2 / 52.3, 304 (2 of 5 x 300) 56.8 / 52.5, 389 (3 of 3 x 512) 58.0 / 59.1,
+// 413 (8 of 3 x 200) 40.6 / 52.2, 519 (4 of 3 x 512) 63.4 / 66.8, 602 (9 x 600) 163 / 158, 758 (4 of 6 x 300) 96.8 / 100.  64 / 8:
+// 416 (4 of 5 x 100) 41.2 / 52.6, 608 (2 of 5 x 300) 77.1 / 83.3.  16 / 2: 301 (9 x 600) 178 / 95.0, 608 (8 of 5 x 300) 76.6 / 82.1,
+// 704 (4 of 5 x 700) 144 / 137, 1102 (2 of 12 x 800) 428 / 379, and 371 with the large form: long prompts on few heads are where
+// the line could lie lower.
 // The wide ATTENTION kernel is faster at every size measured, down to 64 workgroups (7-25 %), so it has no such limit.
 constexpr int kMinWideGrid = 768;
 constexpr int kOneRoundScore = 288, kTwoRoundScore = 540;
