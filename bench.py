@@ -32,8 +32,8 @@ MEASURED_MFMA_BF16_TFLOPS = 1700.0
 # scaled by a copy of known size) is where roofline.traffic comes from - it is not measured in this run.
 TRAFFIC_PROFILE = os.path.join("profiles", "hot_path_kernels_config3_8b_continuous_batch.md")
 TRAFFIC_WORKLOAD = 3
-KERNELS_OF_CALL = {"cc_rope_shift": ("rope_shift_kernel",), "cc_select": ("score_v2_kernel", "topn_kernel", "sparse_qk_kernel<G=4,SCORE"),
-                   "cc_sparse_prefill": ("attn_v2_kernel", "rope_scatter_kernel", "sparse_qk_kernel<G=4,ATTN")}
+KERNELS_OF_CALL = {"cc_rope_shift": ("rope_shift_kernel",), "cc_select": ("score_v2_kernel", "topn_kernel"),
+                   "cc_sparse_prefill": ("attn_v2_kernel", "scatter_plan_kernel", "sparse_qk_kernel<G=4,ATTN")}
 
 
 def profiled_traffic_bytes(call: str):
