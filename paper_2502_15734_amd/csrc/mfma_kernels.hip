@@ -1123,7 +1123,7 @@ void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, in
   const bool big = wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE;
   const bool small = !big && small_score_grid(ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, n_tok, n_segs, n_requests);
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && (big || small) &&
-                    n_tok <= 64 * kMaxListed;
+                    n_tok <= 64 * kMaxListed && n_requests <= kMaxListed;      // (what a list entry can name: 16 bits each; empty requests count)
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
   WorkList list;
   if (wide) {

@@ -371,6 +371,31 @@ def test_scores_of_tokens_numbered_through_the_chunks_of_a_request(hq, lens, chu
     assert float(got["MFMA_NARROW"].max()) > 0.1
 
 
+@pytest.mark.parametrize("n_requests", [65536, 65537])
+def test_scores_behind_many_empty_requests(n_requests):
+    # a list entry names its request by 16 bits: the last one it can name, and one more (then the kernel that walks segments)
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    lens = [70, 129, 200]
+    w = W.custom("empty", "bf16", 8, 1, 128, 5.0e5, lens, [7] * 3, [W.RequestSpec([0, 1, 2], [0.2] * 3, 5)], 1.0, seed=98)
+    got = {}
+    for impl in ("MFMA_NARROW", "AUTO"):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+        b.rope_shift()
+        if impl == "AUTO":
+            seg = b.segments.cpu().numpy().copy()
+            assert (seg[:, 0] == 0).all()
+            seg[:, 0] = n_requests - 1
+            off = np.zeros(n_requests + 1, dtype=np.int32)
+            off[n_requests] = len(seg)
+            b.segments, b.req_seg_off, b.n_requests = torch.from_numpy(seg).cuda(), torch.from_numpy(off).cuda(), n_requests
+        b.select(); torch.cuda.synchronize()
+        got[impl] = b.scores.cpu().double()
+    # (the bound of test_scores_in_two_key_streams)
+    assert torch.isfinite(got["AUTO"]).all() and float(got["MFMA_NARROW"].max()) > 0.1
+    assert float((got["AUTO"] - got["MFMA_NARROW"]).abs().max()) <= 4 * math.sqrt(sum(lens)) * 2.0 ** -24 + 1e-6
+
+
 @pytest.mark.parametrize("hq,hkv,lens,reqs", [
     (8, 2, [200, 90, 330], [([0, 1, 2], 0.3, 20), ([2, 2], 0.02, 1), ([1], 1.0, 64), ([0], 0.0, 3)]),
     (8, 1, [700, 64], [([0, 0, 0, 0], 0.11, 70), ([1, 0], 0.5, 9)] * 5),      # rows far apart: the halves see other tiles
