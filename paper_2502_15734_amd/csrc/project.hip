@@ -796,39 +796,59 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const T* x, const T* __re
   }
 }
 
-// A workgroup of four wavefronts per row.  With a wavefront per row a short list leaves most compute units without one, and a
-// lane's chain is four times as long: 449 x 4096 in a decoder layer 6.9 -> 5.2 us, 230 x 8192 11.5 -> 5.5, 14000 x 4096 47 -> 40 (5.7 TB/s),
-// 14000 x 8192 93 -> 80.
+// ss plus the squares of a piece, element by element; a row's first piece begins with its second square, and every
+// product goes into its sum unrounded.  (Written out because it decides the last bit of a sum in fp32, and that turns roundings to bf16
+// which each product of a decoder layer passes on.)
+template <int kPer>
+__device__ __forceinline__ float add_squares(float ss, const float (&f)[kPer], bool first) {
+  if (first) ss = fmaf(f[0], f[0], f[1] * f[1]);
+#pragma unroll
+  for (int e = 0; e < kPer; ++e)
+    if (!first || e >= 2) ss = fmaf(f[e], f[e], ss);
+  return ss;
+}
+
+// A workgroup of four wavefronts per row: with a wavefront per row a short list leaves most compute units without one, and a
+// lane has four times as many pieces to wait for.  The sum of squares is that of the kernel above, bit for bit:
+// lane l adds the elements of pieces l, l + 64, l + 128, ... in this order, so the wavefronts have consecutive shares of the
+// pieces and hand the lanes' sums on, and the 64 sums meet in wave_sum.  bf16, a wavefront per row / this, us: 449 x 4096 in a decoder
+// layer 7.4 / 5.3, 230 x 8192 10.8 / 5.2, 13824 x 4096 43 / 36 (6.3 TB/s), back to back 14000 x 8192 93 / 79, fp32 14000 x 4096 90 / 78.
 template <typename T>
 __global__ __launch_bounds__(256) void rms_norm_row_kernel(const T* x, const T* __restrict__ gain, float eps, int hidden, T* y) {   // (y may be x)
   constexpr int kPer = 16 / sizeof(T), kKeep = 4;      // elements per 16-byte piece; pieces a thread keeps
-  __shared__ float part[4];
-  const int tid = threadIdx.x, n_pieces = hidden / kPer;
+  __shared__ float sums[64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_pieces = hidden / kPer;
+  const int share = (n_pieces + 255) / 256, first = 64 * share * wave + lane;      // piece i of this thread: first + 64 i, i < share
   const T* xr = x + static_cast<size_t>(blockIdx.x) * hidden;
   T* yr = y + static_cast<size_t>(blockIdx.x) * hidden;
   uint4 held[kKeep], g[kKeep];
-  float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < kKeep; ++i) {
-    const int p = tid + 256 * i;
-    held[i] = p < n_pieces ? *reinterpret_cast<const uint4*>(xr + p * kPer) : uint4{0, 0, 0, 0};
-    g[i] = p < n_pieces ? *reinterpret_cast<const uint4*>(gain + p * kPer) : uint4{0, 0, 0, 0};
+    const int p = first + 64 * i;
+    const bool there = i < share && p < n_pieces;
+    held[i] = there ? *reinterpret_cast<const uint4*>(xr + p * kPer) : uint4{0, 0, 0, 0};
+    g[i] = there ? *reinterpret_cast<const uint4*>(gain + p * kPer) : uint4{0, 0, 0, 0};
   }
 #pragma unroll
-  for (int i = 0; i < kKeep; ++i) {
-    float f[kPer];
-    piece_to_floats(held[i], f, static_cast<T*>(nullptr));
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+      float ss = w == 0 ? 0.f : sums[lane];
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) ss += f[e] * f[e];
+      for (int i = 0; i < kKeep; ++i) {
+        if (i >= share) break;
+        float f[kPer];
+        piece_to_floats(held[i], f, static_cast<T*>(nullptr));
+        ss = add_squares(ss, f, w == 0 && i == 0);
+      }
+      sums[lane] = ss;
+    }
+    __syncthreads();
   }
-  ss = wave_sum(ss);
-  if ((tid & 63) == 0) part[tid >> 6] = ss;
-  __syncthreads();
-  const float scale = rsqrtf((part[0] + part[1] + part[2] + part[3]) / static_cast<float>(hidden) + eps);
+  const float scale = rsqrtf(wave_sum(sums[lane]) / static_cast<float>(hidden) + eps);
 #pragma unroll
   for (int i = 0; i < kKeep; ++i) {
-    const int p = tid + 256 * i;
-    if (p >= n_pieces) continue;
+    const int p = first + 64 * i;
+    if (i >= share || p >= n_pieces) continue;
     float f[kPer], w[kPer];
     T o[kPer];
     piece_to_floats(held[i], f, static_cast<T*>(nullptr));

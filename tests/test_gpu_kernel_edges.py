@@ -499,3 +499,23 @@ def test_rms_norm_where_rows_change_from_wavefronts_to_workgroups(hidden):
         assert torch.equal(x, y)
         # the rounding to bf16, and 1e-6 of the scale
         assert ((y.double() - ref).abs() <= ref.abs() * (2.0 ** -8 + 2e-6)).all()
+
+
+@pytest.mark.parametrize("pieces", [255, 256, 257, 320, 511, 512, 513, 768, 1000, 1023, 1024])
+def test_rms_norm_sums_a_row_in_one_order_whatever_its_length(pieces):
+    # 16-byte pieces of a row.  The same row with zeros behind it, 16 or 64 times as long, is summed by a wavefront alone: its sum of
+    # squares has to have the same bits (bf16: the squares are exact in fp32, so only the order decides), and with eps = 0
+    # its scale is then 4 or 8 times the short row's, exactly
+    import paper_2502_15734_amd as P
+    ctx = P.Context(8, 2, 128, 5.0e5, P.CC_BF16)
+    hidden, n, times = 8 * pieces, 96, 64 if pieces < 256 else 16
+    gen = torch.Generator(device="cuda").manual_seed(pieces)
+    x = torch.zeros((n, times * hidden), dtype=torch.bfloat16, device="cuda")
+    x[:, :hidden] = torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    g = torch.empty(times * hidden, dtype=torch.bfloat16, device="cuda").normal_(1.0, 0.1, generator=gen)
+    long, short = torch.empty_like(x), torch.empty((n, hidden), dtype=torch.bfloat16, device="cuda")
+    ctx.rms_norm(x, g, 0.0, long)
+    ctx.rms_norm(x[:, :hidden].contiguous(), g[:hidden].contiguous(), 0.0, short)
+    torch.cuda.synchronize()
+    assert torch.equal(long[:, :hidden].float(), short.float() * math.sqrt(times))
+    assert float(short.float().pow(2).mean()) > 0.5
