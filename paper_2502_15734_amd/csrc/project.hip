@@ -728,7 +728,7 @@ void launch_gated_linear(const cc_ctx* ctx, const void* x, const void* w_gate, c
 // ---- root-mean-square normalisation: y = x / sqrt(mean(x^2) + eps) * gain ---------------------------
 // Rows of 256 to 1024 pieces of 16 bytes take a workgroup each (rms_norm_row_kernel), others a wavefront (four rows per
 // workgroup).  A row stays in registers between the sum of squares and the scaling, so that it moves once in
-// and once out of HBM; rows of more than 1024 pieces are read a second time.
+// and once out of HBM; what a row has behind its first 1024 pieces is read a second time.
 // the elements of a 16-byte piece as floats, and back, without taking the piece's address (which
 // would move a register array to scratch memory)
 __device__ __forceinline__ void piece_to_floats(const uint4& p, float (&f)[8], bf16_t*) {
@@ -743,40 +743,45 @@ __device__ __forceinline__ void piece_to_floats(const uint4& p, float (&f)[4], f
   f[0] = __uint_as_float(p.x); f[1] = __uint_as_float(p.y); f[2] = __uint_as_float(p.z); f[3] = __uint_as_float(p.w);
 }
 
-template <typename T>
+// ss plus the squares of a piece, element by element; the first piece of a row that is kept whole begins with its second square,
+// and every product goes into its sum unrounded.  (Written out because it decides the last bit of a sum in fp32, and that turns roundings to bf16
+// which each product of a decoder layer passes on.)
+template <int kPer>
+__device__ __forceinline__ float add_squares(float ss, const float (&f)[kPer], bool first) {
+  if (first) ss = fmaf(f[0], f[0], f[1] * f[1]);
+#pragma unroll
+  for (int e = 0; e < kPer; ++e)
+    if (!first || e >= 2) ss = fmaf(f[e], f[e], ss);
+  return ss;
+}
+
+// kKeep: 16-byte pieces a lane keeps.  4: whole rows (up to 256 pieces).  16: the first 1024 pieces of a long one, the others are read
+// twice; without any kept, the rows in flight outgrow what is cached between the two reads.  fp32, none / these kept, us: 14000 x 8192
+// 257 / 217, 2000 x 8192 37.5 / 31.0, 4000 x 12288 118 / 113, 14000 x 16384 552 / 504; bf16 449 x 16384 22.7 / 18.2.
+template <typename T, int kKeep>
 __global__ __launch_bounds__(256) void rms_norm_kernel(const T* x, const T* __restrict__ gain, float eps,
                                                        int n_rows, int hidden, T* y) {          // (y may be x)
   const int row = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
   if (row >= n_rows) return;
   constexpr int kPer = 16 / sizeof(T);                 // elements per 16-byte piece
-  constexpr int kKeep = 4;                             // pieces a lane keeps
+  constexpr bool kWhole = kKeep == 4;
   const T* xr = x + static_cast<size_t>(row) * hidden;
   T* yr = y + static_cast<size_t>(row) * hidden;
   const int n_pieces = hidden / kPer;                  // (the call checks that hidden is a multiple of kPer)
-  const bool keep = n_pieces <= 64 * kKeep;
   uint4 held[kKeep];
+  auto piece = [&](int p) __attribute__((always_inline)) { return *reinterpret_cast<const uint4*>(xr + p * kPer); };
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i) held[i] = lane + 64 * i < n_pieces ? piece(lane + 64 * i) : uint4{0, 0, 0, 0};
   float ss = 0.f;
-  if (keep) {
+  auto add = [&](const uint4& in, bool first) __attribute__((always_inline)) {
+    float f[kPer];
+    piece_to_floats(in, f, static_cast<T*>(nullptr));
+    ss = add_squares(ss, f, first);
+  };
 #pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-      const int p = lane + 64 * i;
-      held[i] = p < n_pieces ? *reinterpret_cast<const uint4*>(xr + p * kPer) : uint4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-      float f[kPer];
-      piece_to_floats(held[i], f, static_cast<T*>(nullptr));
-#pragma unroll
-      for (int e = 0; e < kPer; ++e) ss += f[e] * f[e];
-    }
-  } else {
-    for (int p = lane; p < n_pieces; p += 64) {
-      T v[kPer];
-      *reinterpret_cast<uint4*>(v) = *reinterpret_cast<const uint4*>(xr + p * kPer);
-#pragma unroll
-      for (int e = 0; e < kPer; ++e) ss += to_float(v[e]) * to_float(v[e]);
-    }
-  }
+  for (int i = 0; i < kKeep; ++i) add(held[i], kWhole && i == 0);
+  if constexpr (!kWhole)
+    for (int p = lane + 64 * kKeep; p < n_pieces; p += 64) add(piece(p), false);
   const float scale = rsqrtf(wave_sum(ss) / static_cast<float>(hidden) + eps);
   auto scaled = [&](const uint4& in, int p) __attribute__((always_inline)) {
     float f[kPer], g[kPer];
@@ -787,25 +792,11 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const T* x, const T* __re
     for (int e = 0; e < kPer; ++e) o[e] = from_float<T>(f[e] * scale * g[e]);
     *reinterpret_cast<uint4*>(yr + p * kPer) = *reinterpret_cast<uint4*>(o);
   };
-  if (keep) {
 #pragma unroll
-    for (int i = 0; i < kKeep; ++i)
-      if (lane + 64 * i < n_pieces) scaled(held[i], lane + 64 * i);
-  } else {
-    for (int p = lane; p < n_pieces; p += 64) scaled(*reinterpret_cast<const uint4*>(xr + p * kPer), p);
-  }
-}
-
-// ss plus the squares of a piece, element by element; a row's first piece begins with its second square, and every
-// product goes into its sum unrounded.  (Written out because it decides the last bit of a sum in fp32, and that turns roundings to bf16
-// which each product of a decoder layer passes on.)
-template <int kPer>
-__device__ __forceinline__ float add_squares(float ss, const float (&f)[kPer], bool first) {
-  if (first) ss = fmaf(f[0], f[0], f[1] * f[1]);
-#pragma unroll
-  for (int e = 0; e < kPer; ++e)
-    if (!first || e >= 2) ss = fmaf(f[e], f[e], ss);
-  return ss;
+  for (int i = 0; i < kKeep; ++i)
+    if (lane + 64 * i < n_pieces) scaled(held[i], lane + 64 * i);
+  if constexpr (!kWhole)
+    for (int p = lane + 64 * kKeep; p < n_pieces; p += 64) scaled(piece(p), p);
 }
 
 // A workgroup of four wavefronts per row: with a wavefront per row a short list leaves most compute units without one, and a
@@ -869,7 +860,8 @@ void launch_rms_norm(const cc_ctx* ctx, const void* x, const void* gain, float e
   do {                                                                                                           \
     const T *xt = static_cast<const T*>(x), *gt = static_cast<const T*>(gain);                                   \
     if (by_row) hipLaunchKernelGGL(rms_norm_row_kernel<T>, grid, dim3(256), 0, stream, xt, gt, eps, hidden, static_cast<T*>(y)); \
-    else hipLaunchKernelGGL(rms_norm_kernel<T>, grid, dim3(256), 0, stream, xt, gt, eps, n_rows, hidden, static_cast<T*>(y)); \
+    else if (n_pieces < 256) hipLaunchKernelGGL((rms_norm_kernel<T, 4>), grid, dim3(256), 0, stream, xt, gt, eps, n_rows, hidden, static_cast<T*>(y)); \
+    else hipLaunchKernelGGL((rms_norm_kernel<T, 16>), grid, dim3(256), 0, stream, xt, gt, eps, n_rows, hidden, static_cast<T*>(y)); \
   } while (0)
   if (bf) CC_LAUNCH(bf16_t);
   else CC_LAUNCH(float);

@@ -519,3 +519,23 @@ def test_rms_norm_sums_a_row_in_one_order_whatever_its_length(pieces):
     torch.cuda.synchronize()
     assert torch.equal(long[:, :hidden].float(), short.float() * math.sqrt(times))
     assert float(short.float().pow(2).mean()) > 0.5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pieces", [1025, 1087, 1088, 2048, 2050])
+def test_rms_norm_of_rows_whose_end_is_read_twice(dtype, pieces):
+    import paper_2502_15734_amd as P
+    bf = dtype == "bf16"
+    torch_dtype, hidden = (torch.bfloat16, 8 * pieces) if bf else (torch.float32, 4 * pieces)
+    ctx = P.Context(8, 2, 128, 5.0e5, P.CC_BF16 if bf else P.CC_F32)
+    gen = torch.Generator(device="cuda").manual_seed(pieces)
+    x = torch.empty((5, hidden), device="cuda").normal_(generator=gen).to(torch_dtype)
+    g = torch.empty(hidden, device="cuda").normal_(1.0, 0.1, generator=gen).to(torch_dtype)
+    ref = x.double() / (x.double().pow(2).mean(dim=1, keepdim=True) + 1e-5).sqrt() * g.double()
+    y = torch.empty_like(x)
+    ctx.rms_norm(x, g, 1e-5, y)
+    ctx.rms_norm(x, g, 1e-5, x)                               # (in place)
+    torch.cuda.synchronize()
+    assert torch.equal(x, y)
+    # the rounding of the result (two of fp32), and of the scale's sum: up to 260 terms a lane and six steps, rsqrt 1e-7 each way
+    assert ((y.double() - ref).abs() <= ref.abs() * ((2.0 ** -8 if bf else 2.0 ** -22) + 2e-6)).all()
