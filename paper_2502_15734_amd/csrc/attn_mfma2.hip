@@ -816,6 +816,8 @@ static bool attn_two_streams(const cc_ctx* ctx, int n_q_tot, int max_q_per_req, 
 // Beyond four rounds the tail is a small part, and prompts of more than kListedTiles key tiles (8 MiB of keys and values per KV head) lose more
 // from short tiles of several requests side by side: 4 x 32k tokens on 1700 workgroups, the whole layer 7.72 / 7.77 ms; 8 x 20k on 6000
 // the same; but 3 x 20k on 500 784 / 664 us, and the 8B batch of 32 x 5k on 5100 1 % faster listed.
+// Nor for more requests than are sorted: such a list has gaps, and each is a workgroup that holds a compute unit for two dependent
+// loads: the layer of 2000 requests of 2 x 17-60 tokens 1420 us without, 1752 with it, of 600 of 5-8 x 500-1000 on 8 / 2 heads 9.6 / 10.0 ms.
 constexpr int kListedGrid = 400, kListedRounds = 1024, kListedTiles = 256;
 
 WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int max_q_per_req, int n_requests, int max_tiles) {
@@ -823,7 +825,7 @@ WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int 
   const int heads = ctx->cfg.n_q_heads / 4, row_tiles = n_q_tot / 64 + n_requests;
   const int64_t grid = static_cast<int64_t>(row_tiles) * heads;
   // (a list must have room for every row tile)
-  if (q_pos == nullptr || n_requests == 1 || grid <= kListedGrid || row_tiles > max_tiles - 1 ||
+  if (q_pos == nullptr || n_requests == 1 || n_requests > kMaxSorted || grid <= kListedGrid || row_tiles > max_tiles - 1 ||
       (grid > kListedRounds && max_tiles / n_requests > kListedTiles) || max_q_per_req > 64 * kMaxListed || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
     return list;
   list.kind = WorkList::kQueries;
@@ -842,7 +844,7 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
   const bool two_streams = attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests);
   // (how many rows a request has is on the device: the list is an upper bound, what is too much leaves at once)
   const int listed = list.kind != WorkList::kNone;
-  const int entries = n_requests <= kMaxSorted ? std::min(n_q_tot / 64 + n_requests, pl.max_tiles - 1) : pl.max_tiles - 1;
+  const int entries = n_q_tot / 64 + n_requests;
 #define CC_GO(KS, BY, TQ)                                                                                          \
   do {                                                                                                         \
     const int n_tiles = (max_q_per_req + TQ - 1) / TQ;                                                         \

@@ -729,21 +729,15 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
   auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
   auto entry = [&](int r, int k) { return static_cast<int32_t>(static_cast<uint32_t>(r) << 16) | k; };
   if (n_requests > kMaxSorted) {
-    // request by request, each where its own key tiles begin (its scored tokens have no more) or behind as many rows and requests
+    // (scores only) request by request, each where its own key tiles begin: its scored tokens have no more
     for (int j = tid; j < max_tiles - 1; j += 256) tiles[j].work = -1;
     if (tid == 0) tiles[max_tiles - 1].work = max_tiles - 1;
     __threadfence_block();
     __syncthreads();
     for (int r = tid; r < n_requests; r += 256) {
-      int rows = 0, first;
-      if (scored) {
-        for (int s = req_seg_off[r]; s < req_seg_off[r + 1]; ++s) rows += is_scored(segs[s]) ? segs[s].n_tokens : 0;
-        first = seg_tile_off[req_seg_off[r]];
-      } else {
-        rows = cu_q[r + 1] - cu_q[r];
-        first = cu_q[r] / list.rows + r;
-      }
-      const int n = (rows + list.rows - 1) / list.rows;
+      int rows = 0;
+      for (int s = req_seg_off[r]; s < req_seg_off[r + 1]; ++s) rows += is_scored(segs[s]) ? segs[s].n_tokens : 0;
+      const int first = seg_tile_off[req_seg_off[r]], n = (rows + list.rows - 1) / list.rows;
       for (int k = 0; k < n && first + k < max_tiles - 1; ++k) tiles[first + k].work = entry(r, n - 1 - k);
     }
     return;

@@ -252,7 +252,7 @@ struct WorkList {
   const int32_t* q_pos = nullptr;   // kQueries: position of every row
 };
 constexpr int kMaxOrdered = 4096;      // segments or requests that are sorted for the dispatch order
-constexpr int kMaxSorted = 512;       // requests whose workgroups are sorted (else request by request, with gaps)
+constexpr int kMaxSorted = 512;       // requests whose workgroups are sorted (more: scores request by request with gaps, attention without a list)
 constexpr int kMaxSortedTiles = 2048;  // row tiles that are sorted
 constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };

@@ -539,3 +539,39 @@ def test_rms_norm_of_rows_whose_end_is_read_twice(dtype, pieces):
     assert torch.equal(x, y)
     # the rounding of the result (two of fp32), and of the scale's sum: up to 260 terms a lane and six steps, rsqrt 1e-7 each way
     assert ((y.double() - ref).abs() <= ref.abs() * ((2.0 ** -8 if bf else 2.0 ** -22) + 2e-6)).all()
+
+
+def plan_list_of(ws, at, n_tok, n_segs):
+    """The list of workgroups that a call left in the tile plan at byte `at` of its workspace, as (request, row tile) pairs;
+    None if the workspace, filled with 0x7f before the call, holds no list."""
+    up, max_tiles = lambda n: -(-n // 256) * 256, n_tok // 64 + n_segs + 1
+    first = at + up(4 * (2 * n_segs + 1)) + up(32 * n_segs)
+    work = ws[first: first + 32 * max_tiles].cpu().numpy().view(np.int32).reshape(-1, 8)[:, 7]
+    if work[-1] == 0x7f7f7f7f:
+        return None
+    return [(int(e) >> 16 & 0xffff, int(e) & 0xffff) for e in work[: int(work[-1])] if e != -1]
+
+
+@pytest.mark.parametrize("n_requests", [512, 513])
+def test_attention_lists_the_workgroups_of_as_many_requests_as_it_sorts(n_requests):
+    # more requests: a list would have gaps, and the grid of (row tiles) x (requests) runs
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    reqs = [([0, 1], 0.2, 2), ([2, 0], 1.0, 5), ([1], 0.0, 1), ([2, 1, 0], 0.5, 33)]
+    reqs = [reqs[i % 4] for i in range(n_requests)]
+    w = W.custom("many", "bf16", 4, 1, 128, 5.0e5, [17, 20, 130], [3] * 3,
+                 [W.RequestSpec(c, [f] * len(c), u) for c, f, u in reqs], 1.0 / math.sqrt(128), seed=107)
+    scores = torch.from_numpy(np.random.default_rng(5).random(w.n_tok).astype(np.float32)).cuda()
+    got = {}
+    for impl in ("MFMA_NARROW", "AUTO"):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+        b.ws_prefill.fill_(0x7f)
+        b.rope_shift(); b.select_from_scores(scores); b.sparse_prefill_fused(); torch.cuda.synchronize()
+        got[impl] = b.out[:w.n_q_tot].double().cpu().numpy()
+    entries = plan_list_of(b.ws_prefill, 0, w.n_tok, len(w.segments))
+    if n_requests == 512:
+        assert sorted(entries) == [(r, k) for r in range(512) for k in range(-(-int(w.cu_q[r + 1] - w.cu_q[r]) // 64))]
+    else:
+        assert entries is None
+    # (the bound of test_attention_of_several_requests_from_the_list_of_workgroups)
+    assert np.isfinite(got["AUTO"]).all() and H.rel_l2(got["AUTO"], got["MFMA_NARROW"]) <= 4 * 2.0 ** -9
