@@ -1007,8 +1007,9 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   pl.tiles = reinterpret_cast<TileDesc*>(static_cast<char*>(ws) + plan_head_bytes(n_segs));
   pl.max_tiles = max_tiles;
   pl.redo = n_redo > 0 ? reinterpret_cast<int32_t*>(pl.tiles + max_tiles) : nullptr;
-  const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256, n_order = (n_items + 255) / 256;
   const bool listed = list.kind != WorkList::kNone;
+  const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256;
+  const int n_order = listed && !by_request ? 0 : (n_items + 255) / 256;      // (the wide score kernel goes by the list alone)
   if (n_segs <= kPlanFused) {
     const int n_groups = n_fill + n_order + (listed ? 1 : 0);
     const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_groups,
@@ -1031,7 +1032,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   if (by_request)                                      // attention: the grid's y index walks requests
     hipLaunchKernelGGL(plan_order_kernel<true>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
                        n_items, pl.order, pl.items);
-  else                                                 // score: it walks segments
+  else if (n_order > 0)                                // score without a list: it walks segments
     hipLaunchKernelGGL(plan_order_kernel<false>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
                        n_items, pl.order, pl.items);
   if (listed)

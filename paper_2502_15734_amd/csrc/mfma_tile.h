@@ -257,7 +257,7 @@ constexpr int kMaxSortedTiles = 2048;  // row tiles that are sorted
 constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
 size_t plan_head_bytes(int n_segs);
-// by_request: dispatch order over requests (attention; cu_q delimits their rows), else over segments (score).
+// by_request: dispatch order over requests (attention; cu_q delimits their rows), else over segments (score; none where a list is made).
 // list: the list of workgroups to build beside it.  scatter: a scatter to run beside it (attention), or null.
 // n_redo > 0: the plan also holds n_redo redo flags (after the tiles), cleared by the plan kernels.
 Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, const int32_t* req_seg_off, int n_requests, bool by_request,

@@ -575,3 +575,22 @@ def test_attention_lists_the_workgroups_of_as_many_requests_as_it_sorts(n_reques
         assert entries is None
     # (the bound of test_attention_of_several_requests_from_the_list_of_workgroups)
     assert np.isfinite(got["AUTO"]).all() and H.rel_l2(got["AUTO"], got["MFMA_NARROW"]) <= 4 * 2.0 ** -9
+
+
+@pytest.mark.parametrize("requests", [2, 400])
+def test_scores_from_a_list_make_no_order_of_segments(requests):
+    # (one launch for the whole plan; several beyond 1024 segments)
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("order", "bf16", 4, 1, 128, 5.0e5, [17, 33], [7] * 2, [W.RequestSpec([0, 1, 0], [0.2] * 3, 5)] * requests, 1.0, seed=109)
+    n_segs, up = len(w.segments), lambda n: -(-n // 256) * 256
+    got = {}
+    for impl in ("MFMA_NARROW", "MFMA_WIDE"):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+        b.ws_select.fill_(0x7f)
+        b.rope_shift(); b.select(); torch.cuda.synchronize()
+        at = up(w.n_tok * 4 * 4) + up(w.n_tok * 4) + 4 * (n_segs + 1)              # behind masses, keys and tile offsets
+        got[impl] = b.ws_select[at: at + 4 * n_segs].cpu().numpy().view(np.int32), b.scores.cpu().double()
+    assert (np.sort(got["MFMA_NARROW"][0]) == np.arange(n_segs)).all() and (got["MFMA_WIDE"][0] == 0x7f7f7f7f).all()
+    # (the bound of test_scores_in_two_key_streams)
+    assert float((got["MFMA_WIDE"][1] - got["MFMA_NARROW"][1]).abs().max()) <= 4 * math.sqrt(72) * 2.0 ** -24 + 1e-6
