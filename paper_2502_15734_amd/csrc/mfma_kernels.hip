@@ -708,7 +708,8 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
   emit(rank, i);
 }
 
-// The list of workgroups (WorkList), by one whole workgroup of 256 threads.  Row tiles are counted per request and
+// The list of workgroups (WorkList), by one whole workgroup of 256 threads, or several where it is not sorted (list_groups; block: the
+// workgroup's number among them).  Row tiles are counted per request and
 // numbered through; a tile's work is the number of key tiles it sees.  The list begins request by request, long tiles
 // first: the workgroups that run at a time then walk the same keys, which an XCD's L2 holds once (all tiles in the order
 // of their work instead: 8B batch of 32 requests 2077 -> 2243 us, 4 x 32 k tokens 8.1 -> 8.2 ms).  The shortest tiles of all requests
@@ -717,9 +718,11 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
 // not fit an XCD's L2 either (8 requests of 10k tokens on 600 workgroups: none of them 505 us, as many as
 // make up half of that work 481, this 452; 3 of 20k on 500: 784 and 664, without the limit 677).  (Which of two tiles of the same work comes first is left to
 // chance: it decides when a workgroup starts, not what it computes.)
+__host__ __device__ inline int list_groups(int n_requests) { return n_requests > kMaxSorted ? (n_requests + 255) / 256 : 1; }
+
 __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ segs, int n_segs,
                           const int32_t* __restrict__ req_seg_off, int n_requests, const int32_t* __restrict__ cu_q,
-                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles, PlanLds& lds) {
+                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles, int block, PlanLds& lds) {
   constexpr int kBuckets = kListBuckets, kShortest = 160;
   int (&off)[kMaxSorted + 1] = lds.list.off, (&low)[kMaxSorted] = lds.list.low, (&n_short)[kMaxSorted] = lds.list.n_short;
   int (&bucket)[kListBuckets] = lds.list.bucket, (&wsum)[4] = lds.wsum, &longest = lds.list.longest, &first_short = lds.list.first_short;
@@ -729,16 +732,24 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
   auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
   auto entry = [&](int r, int k) { return static_cast<int32_t>(static_cast<uint32_t>(r) << 16) | k; };
   if (n_requests > kMaxSorted) {
-    // (scores only) request by request, each where its own key tiles begin: its scored tokens have no more
-    for (int j = tid; j < max_tiles - 1; j += 256) tiles[j].work = -1;
-    if (tid == 0) tiles[max_tiles - 1].work = max_tiles - 1;
-    __threadfence_block();
-    __syncthreads();
-    for (int r = tid; r < n_requests; r += 256) {
+    // (scores only) request by request, each where its own key tiles begin: its scored tokens have no more.  A lane counts a
+    // request's, a wavefront writes all places of its 64 requests.  (One workgroup that first emptied the whole list: 19 us
+    // for 2000 requests of two short chunks, this 10.)
+    const int r = block * 256 + tid;
+    int first = 0, end = 0, n = 0;
+    if (r < n_requests) {
+      const int s0 = req_seg_off[r], s1 = req_seg_off[r + 1];
       int rows = 0;
-      for (int s = req_seg_off[r]; s < req_seg_off[r + 1]; ++s) rows += is_scored(segs[s]) ? segs[s].n_tokens : 0;
-      const int first = seg_tile_off[req_seg_off[r]], n = (rows + list.rows - 1) / list.rows;
-      for (int k = 0; k < n && first + k < max_tiles - 1; ++k) tiles[first + k].work = entry(r, n - 1 - k);
+      for (int s = s0; s < s1; ++s) rows += is_scored(segs[s]) ? segs[s].n_tokens : 0;
+      first = r == 0 ? 0 : seg_tile_off[s0];
+      end = min(seg_tile_off[s1], max_tiles - 1);
+      n = (rows + list.rows - 1) / list.rows;
+      if (r + 1 == n_requests) tiles[max_tiles - 1].work = end;
+    }
+    for (int l = 0; l < 64; ++l) {
+      const int first_l = __builtin_amdgcn_readlane(first, l), end_l = __builtin_amdgcn_readlane(end, l), n_l = __builtin_amdgcn_readlane(n, l);
+      for (int j = first_l + lane; j < end_l; j += 64)
+        tiles[j].work = j - first_l < n_l ? entry(r - lane + l, n_l - 1 - (j - first_l)) : -1;
     }
     return;
   }
@@ -874,17 +885,17 @@ __global__ __launch_bounds__(256) void plan_list_kernel(WorkList list, const cc_
                                                          const int32_t* __restrict__ seg_tile_off,
                                                          TileDesc* __restrict__ tiles, int max_tiles) {
   __shared__ PlanLds lds;
-  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles, lds);
+  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles, blockIdx.x, lds);
 }
 
 // The whole plan in ONE launch, for batches of up to kPlanFused segments: every workgroup repeats
 // the (tiny) scan into LDS, then the first n_fill workgroups write descriptors, the others the
-// dispatch order, and the last one the list of workgroups if there is to be one.  Two launches and two waits between dependent
+// dispatch order, and the last n_list the list of workgroups if there is to be one.  Two launches and two waits between dependent
 // kernels fewer per call, which is what a single request's step (a dozen kernels of a few microseconds) is made of.
 struct PlanArgs {
   const cc_segment* segs;
   const int32_t *req_seg_off, *cu_q, *block_tab;
-  int n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_groups;      // n_groups: workgroups of the plan
+  int n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups;      // n_groups: workgroups of the plan
   int32_t *seg_tile_off, *order, *redo;
   WorkItem* items;
   TileDesc* tiles;
@@ -899,10 +910,11 @@ __device__ __forceinline__ void plan_part(const PlanArgs& a, int block, PlanLds&
   if (block < a.n_fill)
     plan_fill(a.segs, a.n_segs, lds.seg_tile_off, a.block_tab, a.n_blocks, a.max_tiles, a.tiles, a.redo, a.n_redo,
               block * 256 + threadIdx.x, a.n_fill);
-  else if (a.list.kind == WorkList::kNone || block + 1 < a.n_groups)
+  else if (block < a.n_groups - a.n_list)
     plan_order<BY_REQUEST>(a.segs, a.req_seg_off, a.cu_q, lds.seg_tile_off, a.n_items, a.order, a.items, block - a.n_fill, lds);
   else
-    plan_list(a.list, a.segs, a.n_segs, a.req_seg_off, a.n_requests, a.cu_q, lds.seg_tile_off, a.tiles, a.max_tiles, lds);
+    plan_list(a.list, a.segs, a.n_segs, a.req_seg_off, a.n_requests, a.cu_q, lds.seg_tile_off, a.tiles, a.max_tiles,
+              block - (a.n_groups - a.n_list), lds);
 }
 
 template <bool BY_REQUEST>
@@ -1010,9 +1022,10 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   const bool listed = list.kind != WorkList::kNone;
   const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256;
   const int n_order = listed && !by_request ? 0 : (n_items + 255) / 256;      // (the wide score kernel goes by the list alone)
+  const int n_list = listed ? list_groups(n_requests) : 0;
   if (n_segs <= kPlanFused) {
-    const int n_groups = n_fill + n_order + (listed ? 1 : 0);
-    const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_groups,
+    const int n_groups = n_fill + n_order + n_list;
+    const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups,
                      pl.seg_tile_off, pl.order, pl.redo, pl.items, pl.tiles, list};
     if (by_request && scatter != nullptr && scatter->n_rows > 0)
       hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + scatter_rows(scatter->n_rows) - 1) / scatter_rows(scatter->n_rows)), dim3(256), 0, stream,
@@ -1036,7 +1049,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
     hipLaunchKernelGGL(plan_order_kernel<false>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
                        n_items, pl.order, pl.items);
   if (listed)
-    hipLaunchKernelGGL(plan_list_kernel, dim3(1), dim3(256), 0, stream, list, segs, n_segs, req_seg_off, n_requests, cu_q,
+    hipLaunchKernelGGL(plan_list_kernel, dim3(n_list), dim3(256), 0, stream, list, segs, n_segs, req_seg_off, n_requests, cu_q,
                        pl.seg_tile_off, pl.tiles, max_tiles);
   hipLaunchKernelGGL(plan_fill_kernel, dim3(n_fill), dim3(256), 0, stream, segs, n_segs,
                      pl.seg_tile_off, block_tab, n_blocks, max_tiles, pl.tiles, pl.redo, n_redo);

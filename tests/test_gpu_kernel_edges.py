@@ -594,3 +594,35 @@ def test_scores_from_a_list_make_no_order_of_segments(requests):
     assert (np.sort(got["MFMA_NARROW"][0]) == np.arange(n_segs)).all() and (got["MFMA_WIDE"][0] == 0x7f7f7f7f).all()
     # (the bound of test_scores_in_two_key_streams)
     assert float((got["MFMA_WIDE"][1] - got["MFMA_NARROW"][1]).abs().max()) <= 4 * math.sqrt(72) * 2.0 ** -24 + 1e-6
+
+
+def assert_scores_agree(got, ref, hq):
+    """Scores of two forms over batches of many tokens (poisoned: a token whose mass nobody wrote would have 3e38)."""
+    # Among 1e7 query elements a few are rounded to bf16 the other way (the two forms contract the rotation's products differently):
+    # one such moves a logit by up to 2^-8 |q| |k| / sqrt(128), 5e-3 for |q| = |k| = 4, with a random sign per key; over the 17 or more keys
+    # of a token and with the slope m (1 - m) <= 1/4 of a mass that is 5e-3 / 4 / 4 of one head's.  Most tokens have none: the sums alone.
+    d = (got - ref).abs()
+    assert float(d.max()) <= 2.0 ** -8 * 16 / math.sqrt(128) / 16 / hq
+    assert float(d.pow(2).mean().sqrt()) <= 1e-6
+
+
+@pytest.mark.parametrize("n_requests", [512, 513, 769])
+def test_scores_of_as_many_requests_as_are_sorted_and_more(n_requests):
+    # every row tile of every request once, whatever else lies between them (empty chunks and requests without a scored token too)
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    kinds = [[0, 1], [2, 0, 2, 1], [3], [1, 3, 0], [2, 2, 2], [3, 3]]
+    w = W.custom("sorted", "bf16", 4, 1, 128, 5.0e5, [17, 65, 200, 0], [7] * 4,
+                 [W.RequestSpec(kinds[i % 6], [0.2] * len(kinds[i % 6]), 5) for i in range(n_requests)], 1.0, seed=113)
+    up, seg = lambda n: -(-n // 256) * 256, w.segments
+    got = {}
+    for impl in ("MFMA_NARROW", "MFMA_WIDE"):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+        b.ws_select.fill_(0x7f)
+        b.rope_shift(); b.select(); torch.cuda.synchronize()
+        got[impl] = b.scores.cpu().double()
+    scored = np.zeros(n_requests, dtype=np.int64)
+    np.add.at(scored, seg[:, W.SEG_REQ], np.where((seg[:, W.SEG_KIND] == W.KIND_CHUNK) & (seg[:, W.SEG_START] > 0), seg[:, W.SEG_NTOK], 0))
+    entries = plan_list_of(b.ws_select, up(w.n_tok * 4 * 4) + up(w.n_tok * 4), w.n_tok, len(seg))
+    assert sorted(entries) == [(r, k) for r in range(n_requests) for k in range(-(-int(scored[r]) // 128))]
+    assert_scores_agree(got["MFMA_WIDE"], got["MFMA_NARROW"], 4)
