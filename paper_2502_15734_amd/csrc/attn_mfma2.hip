@@ -186,7 +186,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   int req, tile;
   if (listed) {
     const int at = blockIdx.x / per_tile, e = tiles[at].work;
-    if (at >= uniform(tiles[max_tiles - 1].work) || uniform(e) == -1) return;
+    if (at >= uniform(tiles[max_tiles - 1].work)) return;
     req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> 16));
     tile = uniform(e & 0xffff);
   } else {
@@ -816,8 +816,8 @@ static bool attn_two_streams(const cc_ctx* ctx, int n_q_tot, int max_q_per_req, 
 // Beyond four rounds the tail is a small part, and prompts of more than kListedTiles key tiles (8 MiB of keys and values per KV head) lose more
 // from short tiles of several requests side by side: 4 x 32k tokens on 1700 workgroups, the whole layer 7.72 / 7.77 ms; 8 x 20k on 6000
 // the same; but 3 x 20k on 500 784 / 664 us, and the 8B batch of 32 x 5k on 5100 1 % faster listed.
-// Nor for more requests than are sorted: such a list has gaps, and each is a workgroup that holds a compute unit for two dependent
-// loads: the layer of 2000 requests of 2 x 17-60 tokens 1420 us without, 1752 with it, of 600 of 5-8 x 500-1000 on 8 / 2 heads 9.6 / 10.0 ms.
+// Nor for more requests than are sorted (with a list that began each request where its key tiles begin, the layer of 2000 requests of
+// 2 x 17-60 tokens 1420 us without, 1752 with it, of 600 of 5-8 x 500-1000 on 8 / 2 heads 9.6 / 10.0 ms).
 constexpr int kListedGrid = 400, kListedRounds = 1024, kListedTiles = 256;
 
 WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int max_q_per_req, int n_requests, int max_tiles) {

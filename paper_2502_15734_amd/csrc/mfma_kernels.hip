@@ -610,9 +610,11 @@ __device__ __forceinline__ void plan_scan(const cc_segment* __restrict__ segs, i
   __syncthreads();
 }
 
+// (n_listed: count to begin at 0 for the list's workgroups, or null)
 __global__ __launch_bounds__(256) void plan_scan_kernel(const cc_segment* __restrict__ segs, int n_segs,
-                                                         int32_t* __restrict__ seg_tile_off) {
+                                                         int32_t* __restrict__ seg_tile_off, int32_t* __restrict__ n_listed) {
   __shared__ PlanLds lds;
+  if (n_listed != nullptr && threadIdx.x == 0) *n_listed = 0;
   plan_scan(segs, n_segs, seg_tile_off, lds);
 }
 
@@ -708,8 +710,8 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
   emit(rank, i);
 }
 
-// The list of workgroups (WorkList), by one whole workgroup of 256 threads, or several where it is not sorted (list_groups; block: the
-// workgroup's number among them).  Row tiles are counted per request and
+// The list of workgroups (WorkList), by one whole workgroup of 256 threads, or several where it is not sorted (block: the
+// workgroup's number among n_groups).  Row tiles are counted per request and
 // numbered through; a tile's work is the number of key tiles it sees.  The list begins request by request, long tiles
 // first: the workgroups that run at a time then walk the same keys, which an XCD's L2 holds once (all tiles in the order
 // of their work instead: 8B batch of 32 requests 2077 -> 2243 us, 4 x 32 k tokens 8.1 -> 8.2 ms).  The shortest tiles of all requests
@@ -718,11 +720,28 @@ __device__ __forceinline__ void plan_order(const cc_segment* __restrict__ segs,
 // not fit an XCD's L2 either (8 requests of 10k tokens on 600 workgroups: none of them 505 us, as many as
 // make up half of that work 481, this 452; 3 of 20k on 500: 784 and 664, without the limit 677).  (Which of two tiles of the same work comes first is left to
 // chance: it decides when a workgroup starts, not what it computes.)
-__host__ __device__ inline int list_groups(int n_requests) { return n_requests > kMaxSorted ? (n_requests + 255) / 256 : 1; }
+// (more requests than are sorted, plan in launches of its own: a workgroup per 256 segments)
+inline int list_groups(int n_requests, int n_segs) { return n_requests > kMaxSorted && n_segs > kPlanFused ? (n_segs + 255) / 256 : 1; }
+
+// inclusive sum over a workgroup's 256 threads; wsum: the wavefronts' sums
+__device__ __forceinline__ int scan_256(int v, int (&wsum)[4]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  __syncthreads();
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  for (int ww = 0; ww < w; ++ww) incl += wsum[ww];
+  return incl;
+}
 
 __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ segs, int n_segs,
                           const int32_t* __restrict__ req_seg_off, int n_requests, const int32_t* __restrict__ cu_q,
-                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles, int block, PlanLds& lds) {
+                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles, int block, int n_groups, PlanLds& lds) {
   constexpr int kBuckets = kListBuckets, kShortest = 160;
   int (&off)[kMaxSorted + 1] = lds.list.off, (&low)[kMaxSorted] = lds.list.low, (&n_short)[kMaxSorted] = lds.list.n_short;
   int (&bucket)[kListBuckets] = lds.list.bucket, (&wsum)[4] = lds.wsum, &longest = lds.list.longest, &first_short = lds.list.first_short;
@@ -732,24 +751,38 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
   auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
   auto entry = [&](int r, int k) { return static_cast<int32_t>(static_cast<uint32_t>(r) << 16) | k; };
   if (n_requests > kMaxSorted) {
-    // (scores only) request by request, each where its own key tiles begin: its scored tokens have no more.  A lane counts a
-    // request's, a wavefront writes all places of its 64 requests.  (One workgroup that first emptied the whole list: 19 us
-    // for 2000 requests of two short chunks, this 10.)
-    const int r = block * 256 + tid;
-    int first = 0, end = 0, n = 0;
-    if (r < n_requests) {
-      const int s0 = req_seg_off[r], s1 = req_seg_off[r + 1];
-      int rows = 0;
-      for (int s = s0; s < s1; ++s) rows += is_scored(segs[s]) ? segs[s].n_tokens : 0;
-      first = r == 0 ? 0 : seg_tile_off[s0];
-      end = min(seg_tile_off[s1], max_tiles - 1);
-      n = (rows + list.rows - 1) / list.rows;
-      if (r + 1 == n_requests) tiles[max_tiles - 1].work = end;
-    }
-    for (int l = 0; l < 64; ++l) {
-      const int first_l = __builtin_amdgcn_readlane(first, l), end_l = __builtin_amdgcn_readlane(end, l), n_l = __builtin_amdgcn_readlane(n, l);
-      for (int j = first_l + lane; j < end_l; j += 64)
-        tiles[j].work = j - first_l < n_l ? entry(r - lane + l, n_l - 1 - (j - first_l)) : -1;
+    // (scores only) request by request, by the thread that has its first segment.  Without gaps: the places of a list that begins
+    // each request where its key tiles begin come in a pattern, which the dispatcher gives to some of the XCDs and shader
+    // engines only (4 query heads, 2100 requests of 4 x 500 tokens: 12 of 32 places, 11.3 ms; 6.6 without).
+    for (int s0 = 256 * block, base = 0; s0 < (n_groups > 1 ? min(256 * (block + 1), n_segs) : n_segs); s0 += 256) {
+      const int s = s0 + tid;
+      const cc_segment sg = segs[min(s, n_segs - 1)];
+      const bool first = s < n_segs && sg.req >= 0 && sg.req < n_requests && (s == 0 || segs[s - 1].req != sg.req);
+      const int cnt = s < n_segs && is_scored(sg) ? sg.n_tokens : 0;
+      int rows = cnt;                                      // inclusive sum inside the wavefront, then the request's
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(rows, o, 64);
+        if (lane >= o) rows += up;
+      }
+      const uint64_t next = __ballot(first) & ~(~0ull >> (63 - lane));      // requests that begin behind this lane
+      const int last = next != 0 ? __ffsll(static_cast<unsigned long long>(next)) - 2 : 63;
+      rows = __shfl(rows, last, 64) - rows + cnt;
+      if (first && next == 0)
+        for (int t = s - lane + 64; t < n_segs && segs[t].req == sg.req; ++t) rows += is_scored(segs[t]) ? segs[t].n_tokens : 0;
+      const int n = first ? (rows + list.rows - 1) / list.rows : 0, incl = scan_256(n, wsum);
+      const int all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+      if (n_groups > 1) {                                  // (places in any order of the workgroups)
+        if (tid == 0) lds.carry = atomicAdd(&tiles[max_tiles - 1].work, all);
+        __syncthreads();
+        base = lds.carry;
+      }
+      for (int l = 0; l < 64; ++l) {
+        const int at = base + __builtin_amdgcn_readlane(incl - n, l), n_l = __builtin_amdgcn_readlane(n, l), r = __builtin_amdgcn_readlane(sg.req, l);
+        for (int k = lane; k < n_l && at + k < max_tiles - 1; k += 64) tiles[at + k].work = entry(r, n_l - 1 - k);
+      }
+      base += all;
+      if (n_groups == 1 && tid == 0) tiles[max_tiles - 1].work = min(base, max_tiles - 1);
     }
     return;
   }
@@ -814,26 +847,13 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
     seen[j] = static_cast<uint32_t>(r) << 16 | static_cast<uint32_t>(at);
     atomicAdd(&bucket[at], 1);
   }
-  auto scan_256 = [&](int v) {                             // inclusive sum over the workgroup's threads
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
-    }
-    __syncthreads();
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    for (int ww = 0; ww < w; ++ww) incl += wsum[ww];
-    return incl;
-  };
   const int cap = max(kBuckets - 1 - (kShortest >> shift), 0);      // (first bucket that may count as short)
   if (tid == 0) first_short = cap;
   __syncthreads();
   {
     // thread i has buckets 2 i, 2 i + 1; work behind them, in key tiles
     const int a = bucket[2 * tid] * (kBuckets - 2 * tid), b = bucket[2 * tid + 1] * (kBuckets - 1 - 2 * tid);
-    const int incl = scan_256(a + b), all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    const int incl = scan_256(a + b, wsum), all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
     const int behind = all - incl, enough = list.places * ((longest / kTile >> shift) + 1);
     if (behind < enough && behind + b >= enough) first_short = max(2 * tid + 1, cap);
     else if (behind + b < enough && behind + b + a >= enough) first_short = max(2 * tid, cap);
@@ -849,14 +869,14 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
     if (j - off[r] < n_short[r]) atomicAdd(&bucket[seen[j] & 0xffff], 1);
   }
   __syncthreads();
-  const int a = bucket[2 * tid], b = bucket[2 * tid + 1], incl = scan_256(a + b);
+  const int a = bucket[2 * tid], b = bucket[2 * tid + 1], incl = scan_256(a + b, wsum);
   const int n_long = total - (wsum[0] + wsum[1] + wsum[2] + wsum[3]);
   bucket[2 * tid] = incl - a - b;
   bucket[2 * tid + 1] = incl - b;
   int before = 0;                                          // long tiles of the requests in front
   for (int r0 = 0; r0 < n_requests; r0 += 256) {
     const int r = r0 + tid, first = r < n_requests ? min(off[r], total) : total, end = r < n_requests ? min(off[r + 1], total) : total;
-    const int n = end - first - (r < n_requests ? n_short[r] : 0), upto = scan_256(n);
+    const int n = end - first - (r < n_requests ? n_short[r] : 0), upto = scan_256(n, wsum);
     if (r < n_requests) low[r] = before + upto - n;
     before += wsum[0] + wsum[1] + wsum[2] + wsum[3];
   }
@@ -885,12 +905,12 @@ __global__ __launch_bounds__(256) void plan_list_kernel(WorkList list, const cc_
                                                          const int32_t* __restrict__ seg_tile_off,
                                                          TileDesc* __restrict__ tiles, int max_tiles) {
   __shared__ PlanLds lds;
-  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles, blockIdx.x, lds);
+  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles, blockIdx.x, gridDim.x, lds);
 }
 
 // The whole plan in ONE launch, for batches of up to kPlanFused segments: every workgroup repeats
 // the (tiny) scan into LDS, then the first n_fill workgroups write descriptors, the others the
-// dispatch order, and the last n_list the list of workgroups if there is to be one.  Two launches and two waits between dependent
+// dispatch order, and the last one (n_list = 1) the list of workgroups if there is to be one.  Two launches and two waits between dependent
 // kernels fewer per call, which is what a single request's step (a dozen kernels of a few microseconds) is made of.
 struct PlanArgs {
   const cc_segment* segs;
@@ -914,7 +934,7 @@ __device__ __forceinline__ void plan_part(const PlanArgs& a, int block, PlanLds&
     plan_order<BY_REQUEST>(a.segs, a.req_seg_off, a.cu_q, lds.seg_tile_off, a.n_items, a.order, a.items, block - a.n_fill, lds);
   else
     plan_list(a.list, a.segs, a.n_segs, a.req_seg_off, a.n_requests, a.cu_q, lds.seg_tile_off, a.tiles, a.max_tiles,
-              block - (a.n_groups - a.n_list), lds);
+              block - (a.n_groups - a.n_list), a.n_list, lds);
 }
 
 template <bool BY_REQUEST>
@@ -1022,7 +1042,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   const bool listed = list.kind != WorkList::kNone;
   const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256;
   const int n_order = listed && !by_request ? 0 : (n_items + 255) / 256;      // (the wide score kernel goes by the list alone)
-  const int n_list = listed ? list_groups(n_requests) : 0;
+  const int n_list = listed ? list_groups(n_requests, n_segs) : 0;
   if (n_segs <= kPlanFused) {
     const int n_groups = n_fill + n_order + n_list;
     const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups,
@@ -1041,7 +1061,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
     return pl;
   }
   if (scatter != nullptr) launch_rope_scatter(ctx, *scatter, stream);
-  hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off);
+  hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off, n_list > 1 ? &pl.tiles[max_tiles - 1].work : nullptr);
   if (by_request)                                      // attention: the grid's y index walks requests
     hipLaunchKernelGGL(plan_order_kernel<true>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
                        n_items, pl.order, pl.items);

@@ -242,7 +242,7 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 32, "room for two 16-byte vectors");
 
-// List of workgroups in the order they start: entry i sits in tiles[i].work - request << 16 | row tile of it (-1: none) - and the
+// List of workgroups in the order they start: entry i sits in tiles[i].work - request << 16 | row tile of it - and the
 // number of entries in tiles[max_tiles - 1].work.  Rows: the scored tokens of a request (numbered through over its
 // chunks) or its rows of the query list.
 struct WorkList {
@@ -252,7 +252,7 @@ struct WorkList {
   const int32_t* q_pos = nullptr;   // kQueries: position of every row
 };
 constexpr int kMaxOrdered = 4096;      // segments or requests that are sorted for the dispatch order
-constexpr int kMaxSorted = 512;       // requests whose workgroups are sorted (more: scores request by request with gaps, attention without a list)
+constexpr int kMaxSorted = 512;       // requests whose workgroups are sorted (more: scores request by request, attention without a list)
 constexpr int kMaxSortedTiles = 2048;  // row tiles that are sorted
 constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };

@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
 
   // ---- which tokens ---------------------------------------------------------------------------
   const int e = tiles[entry].work, n_list = tiles[max_tiles - 1].work;
-  if (entry >= uniform(n_list) || uniform(e) == -1) return;
+  if (entry >= uniform(n_list)) return;
   const int req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> 16)), u0 = uniform(e & 0xffff) * kTQ;
   const int seg_begin = uniform(req_seg_off[req]), seg_end = uniform(req_seg_off[req + 1]);
   const int j_begin = uniform(seg_tile_off[seg_begin]);
@@ -442,7 +442,7 @@ void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4, per_tile = hkv * n_sub;
   // (the chunks' lengths are on the device: the grid is an upper bound, what is too much leaves at once)
   const int rows = small ? 32 * kSmallQB : 32 * kBigQB;
-  const int entries = n_requests <= kMaxSorted ? std::min(n_tok / rows + n_requests, pl.max_tiles - 1) : pl.max_tiles - 1;
+  const int entries = std::min(n_tok / rows + n_requests, pl.max_tiles - 1);
 #define CC_LAUNCH(...)                                                                                        \
   hipLaunchKernelGGL((score_v2_kernel<__VA_ARGS__>), dim3(per_tile * entries), dim3(small ? 512 : 256), 0, stream, static_cast<const bf16_t*>(q), \
                      static_cast<const bf16_t*>(k_pool), pl.tiles, pl.max_tiles, segs, req_seg_off, pl.seg_tile_off,  \

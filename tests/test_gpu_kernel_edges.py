@@ -549,7 +549,7 @@ def plan_list_of(ws, at, n_tok, n_segs):
     work = ws[first: first + 32 * max_tiles].cpu().numpy().view(np.int32).reshape(-1, 8)[:, 7]
     if work[-1] == 0x7f7f7f7f:
         return None
-    return [(int(e) >> 16 & 0xffff, int(e) & 0xffff) for e in work[: int(work[-1])] if e != -1]
+    return [(int(e) >> 16 & 0xffff, int(e) & 0xffff) for e in work[: int(work[-1])]]
 
 
 @pytest.mark.parametrize("n_requests", [512, 513])
@@ -606,14 +606,20 @@ def assert_scores_agree(got, ref, hq):
     assert float(d.pow(2).mean().sqrt()) <= 1e-6
 
 
-@pytest.mark.parametrize("n_requests", [512, 513, 769])
-def test_scores_of_as_many_requests_as_are_sorted_and_more(n_requests):
-    # every row tile of every request once, whatever else lies between them (empty chunks and requests without a scored token too)
+MIXED = [[0, 1], [2, 0, 2, 1], [3], [1, 3, 0], [2, 2, 2], [3, 3]]
+
+
+@pytest.mark.parametrize("n_requests,kinds,long", [
+    (512, MIXED, 0), (513, MIXED, 0), (769, MIXED, 0),
+    (1201, MIXED, 150),                                         # one request of many chunks
+    (600, [[0, 2], [], []], 0),                                 # up to 1024 segments: the whole plan is one launch
+])
+def test_scores_of_as_many_requests_as_are_sorted_and_more(n_requests, kinds, long):
+    # every row tile of every request once and nothing else, whatever lies between them (empty chunks and requests without a scored token too)
     import paper_2502_15734_amd as P
     from paper_2502_15734_amd.pipeline import DeviceBatch
-    kinds = [[0, 1], [2, 0, 2, 1], [3], [1, 3, 0], [2, 2, 2], [3, 3]]
-    w = W.custom("sorted", "bf16", 4, 1, 128, 5.0e5, [17, 65, 200, 0], [7] * 4,
-                 [W.RequestSpec(kinds[i % 6], [0.2] * len(kinds[i % 6]), 5) for i in range(n_requests)], 1.0, seed=113)
+    kinds = [kinds[i % len(kinds)] if i != 7 else kinds[7 % len(kinds)] + [0] * long for i in range(n_requests)]
+    w = W.custom("sorted", "bf16", 4, 1, 128, 5.0e5, [17, 65, 200, 0], [7] * 4, [W.RequestSpec(k, [0.2] * len(k), 5) for k in kinds], 1.0, seed=113)
     up, seg = lambda n: -(-n // 256) * 256, w.segments
     got = {}
     for impl in ("MFMA_NARROW", "MFMA_WIDE"):
