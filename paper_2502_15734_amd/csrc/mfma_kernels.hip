@@ -1100,6 +1100,18 @@ static bool small_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_seg
   return groups <= std::max(kOneRoundScore, std::min(n_tok / n_requests / tokens_per_group, kTwoRoundScore));
 }
 
+// Where the wide kernel would run on a big grid, but a request has one scored chunk (with the question three segments) and that
+// fits a workgroup of the narrow one, a wide workgroup is as good as half empty and its longer prologue decides.  Whole call, wide /
+// narrow, us, two chunks and a question.  64 / 8 heads: 100 requests, chunks of 20-30 tokens 91.9 / 72.5, 60-64 94.7 / 81.1, but
+// 60-80 (two narrow workgroups a chunk) 112 / 131, and three chunks of 17-33 115 / 123.  32 / 8: 100 of 40-50 62.1 / 44.6.
+// 16 / 2: 300 of 40-50 94.4 / 81.7.  The narrow kernel needs a dispatch order of the segments, beyond kPlanFused in a launch of its own, which only many heads
+// outweigh: 1000 of 40-50 on 8 / 1 151 / 175, 16 / 2 227 / 237, 32 / 8 367 / 315, 64 / 8 683 / 633; nor is anything scored of a chunk and a question
+// (1000 on 32 / 8: 34 / 83).
+static bool one_score_tile(int n_q_heads, int max_seg_tokens, int n_segs, int n_requests) {
+  return max_seg_tokens <= 32 * kScoreQB && n_segs > 2 * static_cast<int64_t>(n_requests) &&
+         n_segs <= 3 * static_cast<int64_t>(n_requests) && (n_segs <= kPlanFused || n_q_heads >= 32);
+}
+
 bool attn_mfma_supported(const cc_ctx* ctx) { return group_supported(ctx); }
 bool score_mfma_supported(const cc_ctx* ctx) { return group_supported(ctx); }
 
@@ -1149,8 +1161,9 @@ void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, in
   // redoes the granules the wide one flagged (normally none: its workgroups read two flags and exit).
   const int wide_wgs = ctx->cfg.n_q_heads / 4 * ((max_seg_tokens + 127) / 128) * n_segs;
   const bool big = wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE;
+  const bool one_tile = one_score_tile(ctx->cfg.n_q_heads, max_seg_tokens, n_segs, n_requests) && ctx->impl != CC_IMPL_MFMA_WIDE;
   const bool small = !big && small_score_grid(ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, n_tok, n_segs, n_requests);
-  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && (big || small) &&
+  const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && ((big && !one_tile) || small) &&
                     n_tok <= 64 * kMaxListed && n_requests <= kMaxListed;      // (what a list entry can name: 16 bits each; empty requests count)
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
   WorkList list;

@@ -632,3 +632,25 @@ def test_scores_of_as_many_requests_as_are_sorted_and_more(n_requests, kinds, lo
     entries = plan_list_of(b.ws_select, up(w.n_tok * 4 * 4) + up(w.n_tok * 4), w.n_tok, len(seg))
     assert sorted(entries) == [(r, k) for r in range(n_requests) for k in range(-(-int(scored[r]) // 128))]
     assert_scores_agree(got["MFMA_WIDE"], got["MFMA_NARROW"], 4)
+
+
+@pytest.mark.parametrize("hq,hkv,n,lens,chunks,listed", [
+    (64, 8, 20, [64, 30], 2, False), (64, 8, 20, [65, 30], 2, True), (64, 8, 20, [64, 30], 3, True),
+    (32, 8, 341, [17, 64], 2, False), (32, 8, 342, [17, 64], 2, False),      # (1024 segments in one launch of the plan)
+    (16, 2, 341, [17, 64], 2, False), (16, 2, 342, [17, 64], 2, True),
+])
+def test_scores_of_single_chunks_that_fit_a_narrow_workgroup(hq, hkv, n, lens, chunks, listed):
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("single", "bf16", hq, hkv, 128, 5.0e5, lens, [7] * 2,
+                 [W.RequestSpec([(i + j) % 2 for j in range(chunks)], [0.2] * chunks, 9) for i in range(n)], 1.0 / math.sqrt(128), seed=131)
+    up, got = lambda k: -(-k // 256) * 256, []
+    for impl in (P.CC_IMPL_MFMA_NARROW, P.CC_IMPL_AUTO):
+        b = DeviceBatch(w, impl=impl, poison=True)
+        b.ws_select.fill_(0x7f)
+        b.rope_shift(); b.select(); torch.cuda.synchronize()
+        got.append(b.scores.cpu().double())
+    entries = plan_list_of(b.ws_select, up(w.n_tok * hq * 4) + up(w.n_tok * 4), w.n_tok, len(w.segments))
+    assert (entries is not None) == listed
+    assert listed or torch.equal(got[0], got[1])
+    assert_scores_agree(got[1], got[0], hq)
