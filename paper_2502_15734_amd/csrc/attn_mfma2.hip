@@ -162,7 +162,7 @@ template <int KS, bool BY>
 __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     const bf16_t* __restrict__ q, const int32_t* __restrict__ q_pos,
     const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool,
-    const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ order, int listed,
+    const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ order, int tile_bits,
     const int32_t* __restrict__ req_seg_off, int hq, int hkv, int n_sub, int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ redo, const int32_t* __restrict__ q_map, int map_pos,
     const int32_t* __restrict__ snap_index, float* __restrict__ cum, int s_max,
@@ -182,13 +182,13 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
 
   // ---- which queries ------------------------------------------------------------------------
   // (from the plan's list of workgroups, or where there is none from a grid of row tiles, long ones first, by requests
-  // in the order of their length)
+  // in the order of their length; tile_bits: of a list entry, 0: no list)
   int req, tile;
-  if (listed) {
+  if (tile_bits != 0) {
     const int at = blockIdx.x / per_tile, e = tiles[at].work;
     if (at >= uniform(tiles[max_tiles - 1].work)) return;
-    req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> 16));
-    tile = uniform(e & 0xffff);
+    req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> tile_bits));
+    tile = uniform(e & ((1u << tile_bits) - 1));
   } else {
     req = uniform(order[blockIdx.y]);
     tile = n_tiles_x - 1 - blockIdx.x / per_tile;
@@ -826,10 +826,11 @@ WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int 
   const int64_t grid = static_cast<int64_t>(row_tiles) * heads;
   // (a list must have room for every row tile)
   if (q_pos == nullptr || n_requests == 1 || n_requests > kMaxSorted || grid <= kListedGrid || row_tiles > max_tiles - 1 ||
-      (grid > kListedRounds && max_tiles / n_requests > kListedTiles) || max_q_per_req > 64 * kMaxListed || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
+      (grid > kListedRounds && max_tiles / n_requests > kListedTiles) || !list_can_name(n_requests, (max_q_per_req + 63) / 64) || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
     return list;
   list.kind = WorkList::kQueries;
   list.rows = 64;
+  list.tile_bits = list_tile_bits(n_requests);
   list.places = std::max(256 / heads, 1);
   list.q_pos = q_pos;
   return list;
@@ -851,7 +852,7 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
     const dim3 grid = listed ? dim3(hkv * n_sub * entries) : dim3(hkv * n_sub * n_tiles, n_requests);          \
     hipLaunchKernelGGL((attn_v2_kernel<KS, BY>), grid, dim3(512), 0, stream,                                    \
                        static_cast<const bf16_t*>(q), q_pos, static_cast<const bf16_t*>(k_pool),               \
-                       static_cast<const bf16_t*>(v_pool), pl.tiles, pl.max_tiles, pl.items, pl.order, listed, \
+                       static_cast<const bf16_t*>(v_pool), pl.tiles, pl.max_tiles, pl.items, pl.order, list.tile_bits, \
                        req_seg_off, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq,                    \
                        static_cast<bf16_t*>(out), lse, redo, q_map, map_pos, snap_index, cum, s_max,           \
                        static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks,                            \

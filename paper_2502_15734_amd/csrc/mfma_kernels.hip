@@ -749,7 +749,7 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const bool scored = list.kind == WorkList::kScored;
   auto is_scored = [&](const cc_segment& sg) { return sg.kind == CC_SEG_CHUNK && sg.logical_start > 0 && sg.n_tokens > 0; };
-  auto entry = [&](int r, int k) { return static_cast<int32_t>(static_cast<uint32_t>(r) << 16) | k; };
+  auto entry = [&](int r, int k) { return static_cast<int32_t>(static_cast<uint32_t>(r) << list.tile_bits) | k; };
   if (n_requests > kMaxSorted) {
     // (scores only) request by request, by the thread that has its first segment.  Without gaps: the places of a list that begins
     // each request where its key tiles begin come in a pattern, which the dispatcher gives to some of the XCDs and shader
@@ -1163,17 +1163,19 @@ void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, in
   const bool big = wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE;
   const bool one_tile = one_score_tile(ctx->cfg.n_q_heads, max_seg_tokens, n_segs, n_requests) && ctx->impl != CC_IMPL_MFMA_WIDE;
   const bool small = !big && small_score_grid(ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, n_tok, n_segs, n_requests);
+  const int rows = small ? 64 : 128;
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && ((big && !one_tile) || small) &&
-                    n_tok <= 64 * kMaxListed && n_requests <= kMaxListed;      // (what a list entry can name: 16 bits each; empty requests count)
+                    list_can_name(n_requests, n_tok / rows + 1);      // (empty requests count; a request may have all tokens)
   const int n_redo = wide ? static_cast<int>(score_redo_entries(n_tok)) : 0;
   WorkList list;
   if (wide) {
     list.kind = WorkList::kScored;
-    list.rows = small ? 64 : 128;
+    list.rows = rows;
+    list.tile_bits = list_tile_bits(n_requests);
     list.places = std::max((small ? 256 : 512) / (ctx->cfg.n_q_heads / 4), 1);
   }
   const Plan pl = run_plan(ctx, plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, nullptr, stream);
-  if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, stream);
+  if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, list, stream);
   const int32_t* redo = pl.redo;
 #define CC_ARGS ctx, q, k_pool, n_blocks, pl, req_seg_off, max_seg_tokens, mass, redo, topn, stream
   switch (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) {

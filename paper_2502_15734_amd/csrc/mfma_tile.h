@@ -242,19 +242,27 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 32, "room for two 16-byte vectors");
 
-// List of workgroups in the order they start: entry i sits in tiles[i].work - request << 16 | row tile of it - and the
+// List of workgroups in the order they start: entry i sits in tiles[i].work - request << tile_bits | row tile of it - and the
 // number of entries in tiles[max_tiles - 1].work.  Rows: the scored tokens of a request (numbered through over its
 // chunks) or its rows of the query list.
 struct WorkList {
   enum Kind { kNone, kScored, kQueries } kind = kNone;
   int rows = 0;                     // rows of a workgroup
+  int tile_bits = 0;                // bits of an entry that name the row tile
   int places = 0;                   // workgroups of one head group that run at a time
   const int32_t* q_pos = nullptr;   // kQueries: position of every row
 };
 constexpr int kMaxOrdered = 4096;      // segments or requests that are sorted for the dispatch order
 constexpr int kMaxSorted = 512;       // requests whose workgroups are sorted (more: scores request by request, attention without a list)
 constexpr int kMaxSortedTiles = 2048;  // row tiles that are sorted
-constexpr int kMaxListed = 65536;      // row tiles of a request that an entry can name
+// What the requests leave of an entry's 32 bits, and whether that names as many row tiles of one request.  (With half of the bits for
+// each, calls of more than 4.2 M tokens had no list, however short their requests: 2100 of 4 x 500 tokens on 32 / 8 heads 40.9 ms, now 35.4.)
+inline int list_tile_bits(int n_requests) {
+  int bits = 31;
+  while (bits > 0 && (n_requests - 1) >> (32 - bits) != 0) --bits;
+  return bits;
+}
+inline bool list_can_name(int n_requests, int row_tiles) { return row_tiles <= static_cast<int64_t>(1) << list_tile_bits(n_requests); }
 struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
 size_t plan_head_bytes(int n_segs);
 // by_request: dispatch order over requests (attention; cu_q delimits their rows), else over segments (score; none where a list is made).
@@ -284,6 +292,6 @@ WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int 
 inline size_t score_redo_entries(int n_tok) { return static_cast<size_t>(n_tok) / 64 + 2; }
 void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const Plan& pl, const cc_segment* segs,
                      const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, bool small,
-                     hipStream_t stream);
+                     const WorkList& list, hipStream_t stream);
 
 }  // namespace cc

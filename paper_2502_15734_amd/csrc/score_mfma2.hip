@@ -103,7 +103,7 @@ __device__ __forceinline__ u32x4 to_acc(const u32x4& v) {
 template <int kQB, int KS>
 __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_pool,
-    const TileDesc* __restrict__ tiles, int max_tiles, const cc_segment* __restrict__ segs,
+    const TileDesc* __restrict__ tiles, int max_tiles, int tile_bits, const cc_segment* __restrict__ segs,
     const int32_t* __restrict__ req_seg_off, const int32_t* __restrict__ seg_tile_off, int hq, int hkv, int n_sub,
     InvFreq inv_freq, float* __restrict__ mass, int32_t* __restrict__ redo) {
   constexpr int kTQ = 32 * kQB;               // tokens per workgroup
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
   // ---- which tokens ---------------------------------------------------------------------------
   const int e = tiles[entry].work, n_list = tiles[max_tiles - 1].work;
   if (entry >= uniform(n_list)) return;
-  const int req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> 16)), u0 = uniform(e & 0xffff) * kTQ;
+  const int req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> tile_bits)), u0 = uniform(e & ((1u << tile_bits) - 1)) * kTQ;
   const int seg_begin = uniform(req_seg_off[req]), seg_end = uniform(req_seg_off[req + 1]);
   const int j_begin = uniform(seg_tile_off[seg_begin]);
   // The scored tokens of the request are numbered through; this workgroup has u0 .. u0 + kTQ - 1.  A lane looks at one
@@ -438,14 +438,14 @@ bool score_v2_supported(const cc_ctx* ctx) {
 
 void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const Plan& pl, const cc_segment* segs,
                      const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, bool small,
-                     hipStream_t stream) {
+                     const WorkList& list, hipStream_t stream) {
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4, per_tile = hkv * n_sub;
   // (the chunks' lengths are on the device: the grid is an upper bound, what is too much leaves at once)
   const int rows = small ? 32 * kSmallQB : 32 * kBigQB;
   const int entries = std::min(n_tok / rows + n_requests, pl.max_tiles - 1);
 #define CC_LAUNCH(...)                                                                                        \
   hipLaunchKernelGGL((score_v2_kernel<__VA_ARGS__>), dim3(per_tile * entries), dim3(small ? 512 : 256), 0, stream, static_cast<const bf16_t*>(q), \
-                     static_cast<const bf16_t*>(k_pool), pl.tiles, pl.max_tiles, segs, req_seg_off, pl.seg_tile_off,  \
+                     static_cast<const bf16_t*>(k_pool), pl.tiles, pl.max_tiles, list.tile_bits, segs, req_seg_off, pl.seg_tile_off,  \
                      ctx->cfg.n_q_heads, hkv, n_sub, ctx->inv_freq, mass, redo)
   if (small) CC_LAUNCH(kSmallQB, 2);
   else CC_LAUNCH(kBigQB, 1);

@@ -373,7 +373,7 @@ def test_scores_of_tokens_numbered_through_the_chunks_of_a_request(hq, lens, chu
 
 @pytest.mark.parametrize("n_requests", [65536, 65537])
 def test_scores_behind_many_empty_requests(n_requests):
-    # a list entry names its request by 16 bits: the last one it can name, and one more (then the kernel that walks segments)
+    # a list entry has 32 bits for request and row tile: 16 for the one and 16 for the other, 17 and 15
     import paper_2502_15734_amd as P
     from paper_2502_15734_amd.pipeline import DeviceBatch
     lens = [70, 129, 200]
@@ -541,7 +541,7 @@ def test_rms_norm_of_rows_whose_end_is_read_twice(dtype, pieces):
     assert ((y.double() - ref).abs() <= ref.abs() * ((2.0 ** -8 if bf else 2.0 ** -22) + 2e-6)).all()
 
 
-def plan_list_of(ws, at, n_tok, n_segs):
+def plan_list_of(ws, at, n_tok, n_segs, n_requests):
     """The list of workgroups that a call left in the tile plan at byte `at` of its workspace, as (request, row tile) pairs;
     None if the workspace, filled with 0x7f before the call, holds no list."""
     up, max_tiles = lambda n: -(-n // 256) * 256, n_tok // 64 + n_segs + 1
@@ -549,7 +549,9 @@ def plan_list_of(ws, at, n_tok, n_segs):
     work = ws[first: first + 32 * max_tiles].cpu().numpy().view(np.int32).reshape(-1, 8)[:, 7]
     if work[-1] == 0x7f7f7f7f:
         return None
-    return [(int(e) >> 16 & 0xffff, int(e) & 0xffff) for e in work[: int(work[-1])]]
+    bits = min(31, 32 - (n_requests - 1).bit_length())              # (what the requests leave of an entry names the row tile)
+    e = work[: int(work[-1])].view(np.uint32).astype(np.int64)
+    return list(zip((e >> bits).tolist(), (e & (1 << bits) - 1).tolist()))
 
 
 @pytest.mark.parametrize("n_requests", [512, 513])
@@ -568,7 +570,7 @@ def test_attention_lists_the_workgroups_of_as_many_requests_as_it_sorts(n_reques
         b.ws_prefill.fill_(0x7f)
         b.rope_shift(); b.select_from_scores(scores); b.sparse_prefill_fused(); torch.cuda.synchronize()
         got[impl] = b.out[:w.n_q_tot].double().cpu().numpy()
-    entries = plan_list_of(b.ws_prefill, 0, w.n_tok, len(w.segments))
+    entries = plan_list_of(b.ws_prefill, 0, w.n_tok, len(w.segments), n_requests)
     if n_requests == 512:
         assert sorted(entries) == [(r, k) for r in range(512) for k in range(-(-int(w.cu_q[r + 1] - w.cu_q[r]) // 64))]
     else:
@@ -629,7 +631,7 @@ def test_scores_of_as_many_requests_as_are_sorted_and_more(n_requests, kinds, lo
         got[impl] = b.scores.cpu().double()
     scored = np.zeros(n_requests, dtype=np.int64)
     np.add.at(scored, seg[:, W.SEG_REQ], np.where((seg[:, W.SEG_KIND] == W.KIND_CHUNK) & (seg[:, W.SEG_START] > 0), seg[:, W.SEG_NTOK], 0))
-    entries = plan_list_of(b.ws_select, up(w.n_tok * 4 * 4) + up(w.n_tok * 4), w.n_tok, len(seg))
+    entries = plan_list_of(b.ws_select, up(w.n_tok * 4 * 4) + up(w.n_tok * 4), w.n_tok, len(seg), n_requests)
     assert sorted(entries) == [(r, k) for r in range(n_requests) for k in range(-(-int(scored[r]) // 128))]
     assert_scores_agree(got["MFMA_WIDE"], got["MFMA_NARROW"], 4)
 
@@ -650,7 +652,38 @@ def test_scores_of_single_chunks_that_fit_a_narrow_workgroup(hq, hkv, n, lens, c
         b.ws_select.fill_(0x7f)
         b.rope_shift(); b.select(); torch.cuda.synchronize()
         got.append(b.scores.cpu().double())
-    entries = plan_list_of(b.ws_select, up(w.n_tok * hq * 4) + up(w.n_tok * 4), w.n_tok, len(w.segments))
+    entries = plan_list_of(b.ws_select, up(w.n_tok * hq * 4) + up(w.n_tok * 4), w.n_tok, len(w.segments), n)
     assert (entries is not None) == listed
     assert listed or torch.equal(got[0], got[1])
     assert_scores_agree(got[1], got[0], hq)
+
+
+@pytest.mark.parametrize("n_requests,chunk", [(2100, 500), (525, 2000), (420, 2500)])
+def test_scores_of_more_tokens_than_16_bits_of_row_tiles(n_requests, chunk):
+    # 4.2 M tokens in one call (four chunks a request): more than 65536 row tiles of 64, though no request has more than 160
+    import paper_2502_15734_amd as P
+    n_seg, n_tok, up = 4 * n_requests, 4 * n_requests * chunk, lambda n: -(-n // 256) * 256
+    assert n_tok > 64 * 65536
+    hq, pages = 4, -(-chunk // 16)
+    ctx = P.Context(hq, 1, 128, 5.0e5, P.CC_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(127)
+    rnd = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, 1.0 / math.sqrt(128), generator=gen)
+    q, k = rnd(n_tok, hq, 128), rnd(4 * pages, 1, 16, 128)                      # (all requests have the same keys)
+    seg, i = np.zeros((n_seg, 8), dtype=np.int32), np.arange(n_seg)
+    seg[:, W.SEG_REQ], seg[:, W.SEG_START], seg[:, W.SEG_NTOK] = i // 4, i % 4 * chunk, chunk
+    seg[:, W.SEG_TAB], seg[:, W.SEG_NSEL], seg[:, W.SEG_TOK], seg[:, W.SEG_SEL] = i % 4 * pages, 1, i * chunk, i
+    ints = lambda v: torch.from_numpy(np.ascontiguousarray(v, dtype=np.int32)).cuda()
+    lists = [torch.zeros(n_seg, dtype=torch.int32, device="cuda") for _ in range(4)]
+    tab, segs, off = ints(np.arange(4 * pages)), ints(seg), ints(4 * np.arange(n_requests + 1))
+    got = []
+    for impl in (P.CC_IMPL_MFMA_NARROW, P.CC_IMPL_AUTO):
+        ctx.set_impl(impl)
+        ws = torch.full((ctx.select_workspace_bytes(n_tok, n_seg),), 0x7f, dtype=torch.uint8, device="cuda")      # (masses of 3e38)
+        scores = torch.zeros(n_tok, dtype=torch.float32, device="cuda")
+        ctx.select(q, k, tab, segs, off, n_requests, chunk, *lists, scores, ws)
+        torch.cuda.synchronize()
+        got.append(scores)
+    entries = plan_list_of(ws, up(n_tok * hq * 4) + up(n_tok * 4), n_tok, n_seg, n_requests)
+    assert entries is not None and sorted(entries) == [(r, t) for r in range(n_requests) for t in range(-(-3 * chunk // 128))]
+    assert_scores_agree(got[1].double(), got[0].double(), hq)
+    assert float(got[0].max()) > 0.1
