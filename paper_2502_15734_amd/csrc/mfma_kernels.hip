@@ -647,15 +647,6 @@ __device__ __forceinline__ void plan_fill(const cc_segment* __restrict__ segs, i
   to[6] = d.seg;
 }
 
-__global__ __launch_bounds__(256) void plan_fill_kernel(const cc_segment* __restrict__ segs, int n_segs,
-                                                         const int32_t* __restrict__ seg_tile_off,
-                                                         const int32_t* __restrict__ block_tab, int n_blocks,
-                                                         int max_tiles, TileDesc* __restrict__ tiles,
-                                                         int32_t* __restrict__ redo, int n_redo) {
-  plan_fill(segs, n_segs, seg_tile_off, block_tab, n_blocks, max_tiles, tiles, redo, n_redo,
-            blockIdx.x * 256 + threadIdx.x, gridDim.x);
-}
-
 // Dispatch order of the grid's y index: items sorted by decreasing key-side work, so that the last
 // workgroups to start are the short ones.  BY_REQUEST: item = request, key = end of its context;
 // otherwise item = segment, key = end of the segment (0 for segments that are not scored).
@@ -741,7 +732,7 @@ __device__ __forceinline__ int scan_256(int v, int (&wsum)[4]) {
 
 __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ segs, int n_segs,
                           const int32_t* __restrict__ req_seg_off, int n_requests, const int32_t* __restrict__ cu_q,
-                          const int32_t* seg_tile_off, TileDesc* __restrict__ tiles, int max_tiles, int block, int n_groups, PlanLds& lds) {
+                          TileDesc* __restrict__ tiles, int max_tiles, int block, int n_groups, PlanLds& lds) {
   constexpr int kBuckets = kListBuckets, kShortest = 160;
   int (&off)[kMaxSorted + 1] = lds.list.off, (&low)[kMaxSorted] = lds.list.low, (&n_short)[kMaxSorted] = lds.list.n_short;
   int (&bucket)[kListBuckets] = lds.list.bucket, (&wsum)[4] = lds.wsum, &longest = lds.list.longest, &first_short = lds.list.first_short;
@@ -888,34 +879,15 @@ __device__ void plan_list(const WorkList& list, const cc_segment* __restrict__ s
   }
 }
 
-template <bool BY_REQUEST>
-__global__ __launch_bounds__(256) void plan_order_kernel(const cc_segment* __restrict__ segs,
-                                                          const int32_t* __restrict__ req_seg_off,
-                                                          const int32_t* __restrict__ cu_q,
-                                                          const int32_t* __restrict__ seg_tile_off,
-                                                          int n_items, int32_t* __restrict__ order,
-                                                          WorkItem* __restrict__ items) {
-  __shared__ PlanLds lds;
-  plan_order<BY_REQUEST>(segs, req_seg_off, cu_q, seg_tile_off, n_items, order, items, blockIdx.x, lds);
-}
-
-__global__ __launch_bounds__(256) void plan_list_kernel(WorkList list, const cc_segment* __restrict__ segs, int n_segs,
-                                                         const int32_t* __restrict__ req_seg_off, int n_requests,
-                                                         const int32_t* __restrict__ cu_q,
-                                                         const int32_t* __restrict__ seg_tile_off,
-                                                         TileDesc* __restrict__ tiles, int max_tiles) {
-  __shared__ PlanLds lds;
-  plan_list(list, segs, n_segs, req_seg_off, n_requests, cu_q, seg_tile_off, tiles, max_tiles, blockIdx.x, gridDim.x, lds);
-}
-
-// The whole plan in ONE launch, for batches of up to kPlanFused segments: every workgroup repeats
-// the (tiny) scan into LDS, then the first n_fill workgroups write descriptors, the others the
-// dispatch order, and the last one (n_list = 1) the list of workgroups if there is to be one.  Two launches and two waits between dependent
-// kernels fewer per call, which is what a single request's step (a dozen kernels of a few microseconds) is made of.
+// The whole plan in ONE launch: the first n_fill workgroups write descriptors, the next the
+// dispatch order, and the last n_list the list of workgroups if there is to be one.  Up to kPlanFused segments every workgroup
+// repeats the (tiny) scan into LDS, which saves a launch and a wait between dependent kernels: a single request's step is a dozen
+// kernels of a few microseconds.  More segments: the scan is a launch in front.
 struct PlanArgs {
   const cc_segment* segs;
   const int32_t *req_seg_off, *cu_q, *block_tab;
   int n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups;      // n_groups: workgroups of the plan
+  bool scanned;                      // seg_tile_off is there
   int32_t *seg_tile_off, *order, *redo;
   WorkItem* items;
   TileDesc* tiles;
@@ -924,21 +896,25 @@ struct PlanArgs {
 
 template <bool BY_REQUEST>
 __device__ __forceinline__ void plan_part(const PlanArgs& a, int block, PlanLds& lds) {
-  plan_scan(a.segs, a.n_segs, lds.seg_tile_off, lds);
-  if (block == 0)
-    for (int s = threadIdx.x; s <= a.n_segs; s += 256) a.seg_tile_off[s] = lds.seg_tile_off[s];
+  const int32_t* seg_tile_off = a.seg_tile_off;
+  if (!a.scanned) {
+    plan_scan(a.segs, a.n_segs, lds.seg_tile_off, lds);
+    if (block == 0)
+      for (int s = threadIdx.x; s <= a.n_segs; s += 256) a.seg_tile_off[s] = lds.seg_tile_off[s];
+    seg_tile_off = lds.seg_tile_off;
+  }
   if (block < a.n_fill)
-    plan_fill(a.segs, a.n_segs, lds.seg_tile_off, a.block_tab, a.n_blocks, a.max_tiles, a.tiles, a.redo, a.n_redo,
+    plan_fill(a.segs, a.n_segs, seg_tile_off, a.block_tab, a.n_blocks, a.max_tiles, a.tiles, a.redo, a.n_redo,
               block * 256 + threadIdx.x, a.n_fill);
   else if (block < a.n_groups - a.n_list)
-    plan_order<BY_REQUEST>(a.segs, a.req_seg_off, a.cu_q, lds.seg_tile_off, a.n_items, a.order, a.items, block - a.n_fill, lds);
+    plan_order<BY_REQUEST>(a.segs, a.req_seg_off, a.cu_q, seg_tile_off, a.n_items, a.order, a.items, block - a.n_fill, lds);
   else
-    plan_list(a.list, a.segs, a.n_segs, a.req_seg_off, a.n_requests, a.cu_q, lds.seg_tile_off, a.tiles, a.max_tiles,
+    plan_list(a.list, a.segs, a.n_segs, a.req_seg_off, a.n_requests, a.cu_q, a.tiles, a.max_tiles,
               block - (a.n_groups - a.n_list), a.n_list, lds);
 }
 
 template <bool BY_REQUEST>
-__global__ __launch_bounds__(256) void plan_fused_kernel(PlanArgs a) {
+__global__ __launch_bounds__(256) void plan_kernel(PlanArgs a) {
   __shared__ PlanLds lds;
   plan_part<BY_REQUEST>(a, blockIdx.x, lds);
 }
@@ -1043,36 +1019,23 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256;
   const int n_order = listed && !by_request ? 0 : (n_items + 255) / 256;      // (the wide score kernel goes by the list alone)
   const int n_list = listed ? list_groups(n_requests, n_segs) : 0;
-  if (n_segs <= kPlanFused) {
-    const int n_groups = n_fill + n_order + n_list;
-    const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups,
-                     pl.seg_tile_off, pl.order, pl.redo, pl.items, pl.tiles, list};
-    if (by_request && scatter != nullptr && scatter->n_rows > 0)
-      hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + scatter_rows(scatter->n_rows) - 1) / scatter_rows(scatter->n_rows)), dim3(256), 0, stream,
-                         a, static_cast<const bf16_t*>(scatter->k_new), static_cast<const bf16_t*>(scatter->v_new),
-                         scatter->q_pos, scatter->slot_map, scatter->n_rows, ctx->cfg.n_kv_heads, ctx->inv_freq,
-                         static_cast<bf16_t*>(scatter->k_pool), static_cast<bf16_t*>(scatter->v_pool), scatter->n_blocks,
-                         scatter->src_rows, static_cast<const bf16_t*>(scatter->vs.v_shared), scatter->vs.n_shared_blocks,
-                         scatter->vs.v_map);
-    else if (by_request)
-      hipLaunchKernelGGL(plan_fused_kernel<true>, dim3(n_groups), dim3(256), 0, stream, a);
-    else
-      hipLaunchKernelGGL(plan_fused_kernel<false>, dim3(n_groups), dim3(256), 0, stream, a);
-    return pl;
-  }
-  if (scatter != nullptr) launch_rope_scatter(ctx, *scatter, stream);
-  hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off, n_list > 1 ? &pl.tiles[max_tiles - 1].work : nullptr);
-  if (by_request)                                      // attention: the grid's y index walks requests
-    hipLaunchKernelGGL(plan_order_kernel<true>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
-                       n_items, pl.order, pl.items);
-  else if (n_order > 0)                                // score without a list: it walks segments
-    hipLaunchKernelGGL(plan_order_kernel<false>, dim3(n_order), dim3(256), 0, stream, segs, req_seg_off, cu_q, pl.seg_tile_off,
-                       n_items, pl.order, pl.items);
-  if (listed)
-    hipLaunchKernelGGL(plan_list_kernel, dim3(n_list), dim3(256), 0, stream, list, segs, n_segs, req_seg_off, n_requests, cu_q,
-                       pl.seg_tile_off, pl.tiles, max_tiles);
-  hipLaunchKernelGGL(plan_fill_kernel, dim3(n_fill), dim3(256), 0, stream, segs, n_segs,
-                     pl.seg_tile_off, block_tab, n_blocks, max_tiles, pl.tiles, pl.redo, n_redo);
+  const int n_groups = n_fill + n_order + n_list;
+  const bool scanned = n_segs > kPlanFused;
+  if (scanned)
+    hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(256), 0, stream, segs, n_segs, pl.seg_tile_off, n_list > 1 ? &pl.tiles[max_tiles - 1].work : nullptr);
+  const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups, scanned,
+                   pl.seg_tile_off, pl.order, pl.redo, pl.items, pl.tiles, list};
+  if (by_request && scatter != nullptr && scatter->n_rows > 0)
+    hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + scatter_rows(scatter->n_rows) - 1) / scatter_rows(scatter->n_rows)), dim3(256), 0, stream,
+                       a, static_cast<const bf16_t*>(scatter->k_new), static_cast<const bf16_t*>(scatter->v_new),
+                       scatter->q_pos, scatter->slot_map, scatter->n_rows, ctx->cfg.n_kv_heads, ctx->inv_freq,
+                       static_cast<bf16_t*>(scatter->k_pool), static_cast<bf16_t*>(scatter->v_pool), scatter->n_blocks,
+                       scatter->src_rows, static_cast<const bf16_t*>(scatter->vs.v_shared), scatter->vs.n_shared_blocks,
+                       scatter->vs.v_map);
+  else if (by_request)                                 // attention: the grid's y index walks requests
+    hipLaunchKernelGGL(plan_kernel<true>, dim3(n_groups), dim3(256), 0, stream, a);
+  else                                                 // score without a list: it walks segments
+    hipLaunchKernelGGL(plan_kernel<false>, dim3(n_groups), dim3(256), 0, stream, a);
   return pl;
 }
 
