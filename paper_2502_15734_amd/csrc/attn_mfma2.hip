@@ -824,8 +824,9 @@ WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int 
   WorkList list;
   const int heads = ctx->cfg.n_q_heads / 4, row_tiles = n_q_tot / 64 + n_requests;
   const int64_t grid = static_cast<int64_t>(row_tiles) * heads;
-  // (a list must have room for every row tile)
-  if (q_pos == nullptr || n_requests == 1 || n_requests > kMaxSorted || grid <= kListedGrid || row_tiles > max_tiles - 1 ||
+  // (a list must have room for every row tile, and one that cannot be sorted is worse than the order of the requests: 150 requests of
+  // 7-9 x 200-500 tokens on 8 / 1 heads, 2200 row tiles, whole layer 1.28 / 1.22 ms)
+  if (q_pos == nullptr || n_requests == 1 || n_requests > kMaxSorted || grid <= kListedGrid || row_tiles > std::min(max_tiles - 1, kMaxSortedTiles) ||
       (grid > kListedRounds && max_tiles / n_requests > kListedTiles) || !list_can_name(n_requests, (max_q_per_req + 63) / 64) || attn_two_streams(ctx, n_q_tot, max_q_per_req, n_requests))
     return list;
   list.kind = WorkList::kQueries;

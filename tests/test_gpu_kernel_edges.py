@@ -687,3 +687,22 @@ def test_scores_of_more_tokens_than_16_bits_of_row_tiles(n_requests, chunk):
     assert entries is not None and sorted(entries) == [(r, t) for r in range(n_requests) for t in range(-(-3 * chunk // 128))]
     assert_scores_agree(got[1].double(), got[0].double(), hq)
     assert float(got[0].max()) > 0.1
+
+
+@pytest.mark.parametrize("question,listed", [(2, True), (3, False)])
+def test_attention_lists_as_many_row_tiles_as_it_sorts(question, listed):
+    # 512 requests of 192 and 193 rows: 2048 and 2056 row tiles by the launcher's bound
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("tiles", "bf16", 4, 1, 128, 5.0e5, [190], [3], [W.RequestSpec([0], [1.0], question)] * 512, 1.0 / math.sqrt(128), seed=137)
+    scores, got = torch.zeros(w.n_tok, device="cuda"), []
+    for impl in (P.CC_IMPL_MFMA_NARROW, P.CC_IMPL_AUTO):
+        b = DeviceBatch(w, impl=impl, poison=True)
+        b.ws_prefill.fill_(0x7f)
+        b.rope_shift(); b.select_from_scores(scores); b.sparse_prefill_fused(); torch.cuda.synchronize()
+        got.append(b.out[:w.n_q_tot].double().cpu().numpy())
+    entries = plan_list_of(b.ws_prefill, 0, w.n_tok, len(w.segments), 512)
+    assert (entries is not None) == listed
+    assert not listed or sorted(entries) == [(r, k) for r in range(512) for k in range(3)]
+    # (the bound of test_attention_of_several_requests_from_the_list_of_workgroups)
+    assert np.isfinite(got[1]).all() and H.rel_l2(got[1], got[0]) <= 4 * 2.0 ** -9
