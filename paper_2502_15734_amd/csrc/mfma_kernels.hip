@@ -1039,39 +1039,49 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   return pl;
 }
 
-// Which SCORE kernel runs.  From kMinWideGrid 128-token workgroups on (three per compute unit of an MI355X) the wide one
+// Which SCORE kernel runs.  From one round of 128-token workgroups on (two per compute unit of an MI355X: kMinWideGrid) the wide one
 // with four column blocks and one key stream.  Below, its small form (64 tokens, two key streams, one workgroup per
 // compute unit) as long as its workgroups run in about one round, or in two with prompts long enough that the longest chain of
 // tiles decides: it halves that chain.  In between the narrow kernel, of which two workgroups share a unit (later where a
-// KV head has 8 query heads: a narrow workgroup takes all of them, so there are half as many).  Whole
-// cc_select call, narrow / small, us, by the 64-token workgroups that the rule estimates and the chunks of the requests.  32 / 8
+// KV head has 8 query heads: a narrow workgroup takes all of them, so there are half as many, and the wide one's line is lower).  Whole
+// cc_select call, narrow / wide, us, by the 128-token workgroups that the rule estimates and the chunks of the requests.  32 / 8
+// heads: 288 (3 of 40 x 17-60) 133 / 151, 288 (12 of 3 x 160) 49 / 56, 320 (8 of 6 x 100) 53 / 72, 384 (6 of 3 x 440) 82 / 87,
+// 448 (2 of 6 x 700) 185 / 204, 488 (12 x 700) 347 / 314, 560 (12 x 800) 412 / 372, 576 (12 of 20 x 17-60) 135 / 105.  8 heads per KV head: 280 (16 / 2, 12 x 800)
+// 293 / 282, 288 (16 / 2, 6 of 40 x 17-60) 138 / 155, 368 (64 / 8, 30 x 100) 169 / 167, 448 (64 / 8, 4 of 10 x 100) 101 / 86, 560 (16 / 2, 2 of 12 x 800) 433 / 374.
+// Narrow / small, by the 64-token workgroups that the rule estimates.  32 / 8
 // heads: 130 (3 x 512) 49.9 / 38.7, 258 (5 x 512) 72.2 / 52.3, 304 (2 of 5 x 300) 56.8 / 52.5, 389 (3 of 3 x 512) 58.0 / 59.1,
 // 413 (8 of 3 x 200) 40.6 / 52.2, 519 (4 of 3 x 512) 63.4 / 66.8, 602 (9 x 600) 163 / 158, 758 (4 of 6 x 300) 96.8 / 100.  64 / 8:
 // 416 (4 of 5 x 100) 41.2 / 52.6, 608 (2 of 5 x 300) 77.1 / 83.3.  16 / 2: 301 (9 x 600) 178 / 95.0, 608 (8 of 5 x 300) 76.6 / 82.1,
-// 704 (4 of 5 x 700) 144 / 137, 1102 (2 of 12 x 800) 428 / 379, and 371 with the large form: long prompts on few heads are where
-// the line could lie lower.
+// 704 (4 of 5 x 700) 144 / 137.
 // The wide ATTENTION kernel is faster at every size measured, down to 64 workgroups (7-25 %), so it has no such limit.
-constexpr int kMinWideGrid = 768;
+constexpr int kMinWideGrid = 512, kMinWideGrid8 = 360;
 constexpr int kOneRoundScore = 288, kTwoRoundScore = 540;
 
-// (the chunks' lengths are on the device: their 64-token workgroups are estimated from the batch's tokens, taking a request's
+// (the chunks' lengths are on the device: the workgroups are estimated from the batch's tokens, taking a request's
 // segments for equally long chunks and a short question; the first chunk is not scored)
-static bool small_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
+static int64_t scored_tokens(int n_tok, int n_segs, int n_requests) {
   const int64_t per_req = std::max(n_segs / n_requests, 2), scored = per_req > 2 ? per_req - 2 : 1, chunks = scored + 1;
-  const int64_t groups = static_cast<int64_t>(n_q_heads / 4) * n_tok * scored / (64 * chunks);
+  return n_tok * scored / chunks;
+}
+static bool wide_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
+  const int64_t requests = std::min(n_requests, n_segs), per_request = scored_tokens(n_tok, n_segs, n_requests) / requests;
+  return n_q_heads / 4 * requests * ((per_request + 127) / 128) >= (n_q_heads / n_kv_heads > 4 ? kMinWideGrid8 : kMinWideGrid);
+}
+static bool small_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
+  const int64_t groups = n_q_heads / 4 * scored_tokens(n_tok, n_segs, n_requests) / 64;
   const int tokens_per_group = n_q_heads / n_kv_heads > 4 ? 4 : 7;
   return groups <= std::max(kOneRoundScore, std::min(n_tok / n_requests / tokens_per_group, kTwoRoundScore));
 }
 
-// Where the wide kernel would run on a big grid, but a request has one scored chunk (with the question three segments) and that
-// fits a workgroup of the narrow one, a wide workgroup is as good as half empty and its longer prologue decides.  Whole call, wide /
+// Where there is a workgroup for every compute unit, but a request has one scored chunk (with the question three segments) and that
+// fits a workgroup of the narrow kernel, a wide workgroup is as good as half empty and its longer prologue decides.  Whole call, wide /
 // narrow, us, two chunks and a question.  64 / 8 heads: 100 requests, chunks of 20-30 tokens 91.9 / 72.5, 60-64 94.7 / 81.1, but
 // 60-80 (two narrow workgroups a chunk) 112 / 131, and three chunks of 17-33 115 / 123.  32 / 8: 100 of 40-50 62.1 / 44.6.
-// 16 / 2: 300 of 40-50 94.4 / 81.7.  The narrow kernel needs a dispatch order of the segments, beyond kPlanFused in a launch of its own, which only many heads
-// outweigh: 1000 of 40-50 on 8 / 1 151 / 175, 16 / 2 227 / 237, 32 / 8 367 / 315, 64 / 8 683 / 633; nor is anything scored of a chunk and a question
+// 16 / 2: 300 of 40-50 94.4 / 81.7.  The narrow kernel needs a dispatch order of the segments, which takes some 20 us beyond kPlanFused and only many heads
+// outweigh: 1000 of 40-50 on 8 / 1 146 / 170, 16 / 2 223 / 233, 32 / 8 362 / 311, 64 / 8 673 / 627.  Nothing is scored of a chunk and a question
 // (1000 on 32 / 8: 34 / 83).
 static bool one_score_tile(int n_q_heads, int max_seg_tokens, int n_segs, int n_requests) {
-  return max_seg_tokens <= 32 * kScoreQB && n_segs > 2 * static_cast<int64_t>(n_requests) &&
+  return static_cast<int64_t>(n_q_heads / 4) * n_requests >= 256 && max_seg_tokens <= 32 * kScoreQB && n_segs > 2 * static_cast<int64_t>(n_requests) &&
          n_segs <= 3 * static_cast<int64_t>(n_requests) && (n_segs <= kPlanFused || n_q_heads >= 32);
 }
 
@@ -1122,10 +1132,11 @@ void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, in
   const int n_segs = topn.n_segs;
   // Wide kernel first where the head group and the grid allow it; the narrow kernel then
   // redoes the granules the wide one flagged (normally none: its workgroups read two flags and exit).
-  const int wide_wgs = ctx->cfg.n_q_heads / 4 * ((max_seg_tokens + 127) / 128) * n_segs;
-  const bool big = wide_wgs >= kMinWideGrid || ctx->impl == CC_IMPL_MFMA_WIDE;
-  const bool one_tile = one_score_tile(ctx->cfg.n_q_heads, max_seg_tokens, n_segs, n_requests) && ctx->impl != CC_IMPL_MFMA_WIDE;
-  const bool small = !big && small_score_grid(ctx->cfg.n_q_heads, ctx->cfg.n_kv_heads, n_tok, n_segs, n_requests);
+  const int hq = ctx->cfg.n_q_heads, hkv = ctx->cfg.n_kv_heads;
+  const bool forced = ctx->impl == CC_IMPL_MFMA_WIDE;
+  const bool one_tile = !forced && one_score_tile(hq, max_seg_tokens, n_segs, n_requests);
+  const bool big = forced || wide_score_grid(hq, hkv, n_tok, n_segs, n_requests);
+  const bool small = !big && !one_tile && small_score_grid(hq, hkv, n_tok, n_segs, n_requests);
   const int rows = small ? 64 : 128;
   const bool wide = ctx->impl != CC_IMPL_MFMA_NARROW && score_v2_supported(ctx) && ((big && !one_tile) || small) &&
                     list_can_name(n_requests, n_tok / rows + 1);      // (empty requests count; a request may have all tokens)

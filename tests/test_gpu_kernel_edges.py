@@ -637,7 +637,7 @@ def test_scores_of_as_many_requests_as_are_sorted_and_more(n_requests, kinds, lo
 
 
 @pytest.mark.parametrize("hq,hkv,n,lens,chunks,listed", [
-    (64, 8, 20, [64, 30], 2, False), (64, 8, 20, [65, 30], 2, True), (64, 8, 20, [64, 30], 3, True),
+    (64, 8, 24, [64, 30], 2, False), (64, 8, 24, [65, 30], 2, True), (64, 8, 24, [64, 30], 3, True),
     (32, 8, 341, [17, 64], 2, False), (32, 8, 342, [17, 64], 2, False),      # (1024 segments in one launch of the plan)
     (16, 2, 341, [17, 64], 2, False), (16, 2, 342, [17, 64], 2, True),
 ])
@@ -706,3 +706,29 @@ def test_attention_lists_as_many_row_tiles_as_it_sorts(question, listed):
     assert not listed or sorted(entries) == [(r, k) for r in range(512) for k in range(3)]
     # (the bound of test_attention_of_several_requests_from_the_list_of_workgroups)
     assert np.isfinite(got[1]).all() and H.rel_l2(got[1], got[0]) <= 4 * 2.0 ** -9
+
+
+@pytest.mark.parametrize("hq,hkv,n,lens,chunks,rows", [
+    (32, 8, 3, [17, 58], 40, 0), (32, 8, 6, [17, 58], 40, 128),            # 264, 576 workgroups of 128 tokens
+    (16, 2, 6, [17, 58], 40, 0), (16, 2, 8, [17, 58], 40, 128),            # 288, 384
+    (16, 2, 12, [17, 20], 20, 64),                                         # as many chunks, few tokens
+])
+def test_score_kernels_are_chosen_by_the_workgroups_there_are(hq, hkv, n, lens, chunks, rows):
+    # and not by the longest chunk times the number of chunks
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("grid", "bf16", hq, hkv, 128, 5.0e5, lens, [7] * 2,
+                 [W.RequestSpec([j % 2 for j in range(chunks)], [0.2] * chunks, 9)] * n, 1.0 / math.sqrt(128), seed=139)
+    up, got = lambda k: -(-k // 256) * 256, []
+    for impl in (P.CC_IMPL_MFMA_NARROW, P.CC_IMPL_AUTO):
+        b = DeviceBatch(w, impl=impl, poison=True)
+        b.ws_select.fill_(0x7f)
+        b.rope_shift(); b.select(); torch.cuda.synchronize()
+        got.append(b.scores.cpu().double())
+    entries = plan_list_of(b.ws_select, up(w.n_tok * hq * 4) + up(w.n_tok * 4), w.n_tok, len(w.segments), n)
+    scored = sum(lens[j % 2] for j in range(1, chunks))
+    if rows == 0:
+        assert entries is None and torch.equal(got[0], got[1])
+    else:
+        assert sorted(entries) == [(r, k) for r in range(n) for k in range(-(-scored // rows))]
+    assert_scores_agree(got[1], got[0], hq)
