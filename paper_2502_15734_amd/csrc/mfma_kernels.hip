@@ -914,7 +914,7 @@ __device__ __forceinline__ void plan_part(const PlanArgs& a, int block, PlanLds&
 }
 
 template <bool BY_REQUEST>
-__global__ __launch_bounds__(256) void plan_kernel(PlanArgs a) {
+__global__ __launch_bounds__(256) void plan_fused_kernel(PlanArgs a) {
   __shared__ PlanLds lds;
   plan_part<BY_REQUEST>(a, blockIdx.x, lds);
 }
@@ -1033,9 +1033,9 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
                        scatter->src_rows, static_cast<const bf16_t*>(scatter->vs.v_shared), scatter->vs.n_shared_blocks,
                        scatter->vs.v_map);
   else if (by_request)                                 // attention: the grid's y index walks requests
-    hipLaunchKernelGGL(plan_kernel<true>, dim3(n_groups), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(plan_fused_kernel<true>, dim3(n_groups), dim3(256), 0, stream, a);
   else                                                 // score without a list: it walks segments
-    hipLaunchKernelGGL(plan_kernel<false>, dim3(n_groups), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(plan_fused_kernel<false>, dim3(n_groups), dim3(256), 0, stream, a);
   return pl;
 }
 

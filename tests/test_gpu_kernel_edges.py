@@ -399,9 +399,9 @@ def test_scores_behind_many_empty_requests(n_requests):
 @pytest.mark.parametrize("hq,hkv,lens,reqs", [
     (8, 2, [200, 90, 330], [([0, 1, 2], 0.3, 20), ([2, 2], 0.02, 1), ([1], 1.0, 64), ([0], 0.0, 3)]),
     (8, 1, [700, 64], [([0, 0, 0, 0], 0.11, 70), ([1, 0], 0.5, 9)] * 5),      # rows far apart: the halves see other tiles
-    (4, 1, [17, 20], [([0, 1], 0.2, 2)] * 2100),                               # more requests than are sorted
+    (4, 1, [17, 20], [([0, 1], 0.2, 2)] * 2100),                               # more requests than are sorted, no list
     (4, 1, [40], [([0], 1.0, 2)] * 3),                                         # (nearly) every token is a row
-])
+])                                                                             # (small grids have no list: test_attention_from_a_sorted_list)
 def test_attention_of_several_requests_from_the_list_of_workgroups(hq, hkv, lens, reqs):
     import paper_2502_15734_amd as P
     from paper_2502_15734_amd.pipeline import DeviceBatch
@@ -420,7 +420,7 @@ def test_attention_of_several_requests_from_the_list_of_workgroups(hq, hkv, lens
         assert np.isfinite(got[impl][0]).all()
         assert H.rel_l2(got[impl][0], got["MFMA_NARROW"][0]) <= 4 * 2.0 ** -9
         assert float((got[impl][1] - got["MFMA_NARROW"][1]).abs().max()) <= 2 * (60 * 2.0 ** -24 + 2e-6) * 8
-    # the by-product form walks the same list: the same bits
+    # the by-product form takes the same rows in the same workgroups: the same bits
     out1, lse1 = b.out[:n].clone(), b.lse[:n].clone()
     b.rope_shift(); b.select_from_scores(scores); mass = b.sparse_prefill_mass(fused=True).cpu()
     assert torch.equal(out1, b.out[:n]) and torch.equal(lse1, b.lse[:n])
@@ -732,3 +732,85 @@ def test_score_kernels_are_chosen_by_the_workgroups_there_are(hq, hkv, n, lens, 
     else:
         assert sorted(entries) == [(r, k) for r in range(n) for k in range(-(-scored // rows))]
     assert_scores_agree(got[1], got[0], hq)
+
+
+@pytest.mark.parametrize("hq,hkv,lens,reqs,listed", [
+    # 64, 65, 63 and many rows, none of a chunk, most of the row tiles in two requests
+    (32, 8, [60, 700, 3, 200], [([0], 1.0, 4), ([0], 1.0, 5), ([0], 1.0, 3), ([1, 1, 2], 1.0, 70), ([3, 1], 0.0, 1), ([1, 3, 1], 0.4, 64)] * 7, "sorted"),
+    (16, 2, [1500, 40], [([0] * 6, 0.9, 9)] + [([1], 0.5, 2)] * 60, "sorted"),                     # short tiles of very uneven requests
+    (8, 1, [129, 30], [([0, 1, 0], 0.7, 33), ([1, 1], 1.0, 1)] * 90, "sorted"),                   # many requests of few tiles
+    (4, 1, [60], [([0], 1.0, 4)] * 200, ""), (4, 1, [60], [([0], 1.0, 4)] * 201, "at once"),  # 400 workgroups by the launcher's bound, 402
+    (4, 1, [1000, 50], [([0] * 33, 0.8, 40), ([1, 1], 1.0, 3), ([1], 0.2, 64)], "sorted"),    # a prompt beyond 512 x 64 tokens: two key tiles per step of the sorting
+])
+def test_attention_from_a_sorted_list(hq, hkv, lens, reqs, listed):
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("sorted", "bf16", hq, hkv, 128, 5.0e5, lens, [3] * len(lens),
+                 [W.RequestSpec(c, [f] * len(c), u) for c, f, u in reqs], 1.0 / math.sqrt(128), seed=149)
+    rows, heads, n_requests = np.diff(w.cu_q), hq // 4, w.n_requests
+    tiles = int((-(-rows // 64)).sum())
+    assert 2 <= n_requests <= 512 and (256 // heads < tiles <= 2048) == (listed == "sorted")      # (what starts at once is not sorted)
+    scores, got = torch.from_numpy(np.random.default_rng(5).random(w.n_tok).astype(np.float32)).cuda(), {}
+    for impl in ("MFMA_NARROW", "AUTO"):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+        b.ws_prefill.fill_(0x7f)
+        b.out.fill_(float("nan"))
+        b.rope_shift(); b.select_from_scores(scores); b.sparse_prefill_fused(); torch.cuda.synchronize()
+        n = w.n_q_tot
+        got[impl] = b.out[:n].double().cpu().numpy(), b.lse[:n].double().cpu()
+    entries = plan_list_of(b.ws_prefill, 0, w.n_tok, len(w.segments), n_requests)
+    assert (entries is not None) == (listed != "")
+    if listed:
+        assert sorted(entries) == [(r, k) for r in range(n_requests) for k in range(-(-int(rows[r]) // 64))]
+    # (the bounds of test_attention_of_several_requests_from_the_list_of_workgroups; sums of up to n keys)
+    assert np.isfinite(got["AUTO"][0]).all() and H.rel_l2(got["AUTO"][0], got["MFMA_NARROW"][0]) <= 4 * 2.0 ** -9
+    longest = max(sum(lens[i] for i in c) + u for c, _, u in reqs)
+    assert float((got["AUTO"][1] - got["MFMA_NARROW"][1]).abs().max()) <= 2 * (max(60, math.sqrt(longest)) * 2.0 ** -24 + 2e-6) * 8
+
+
+@pytest.mark.parametrize("impl,hq,hkv,lens,chunks", [
+    ("MFMA_WIDE", 32, 8, [300, 40, 129, 17], [[0, 1, 2], [1, 1], [0, 0, 0, 3], [2], [3, 2, 0]] * 7),       # 128 tokens a workgroup
+    ("MFMA_WIDE", 64, 8, [900, 20], [[0, 0, 0]] + [[1, 1]] * 40),
+    ("AUTO", 4, 1, [700, 33, 250], [[0] * 9, [1, 1, 1], [2, 0, 0, 2, 0]] * 2 + [[1, 2]]),                  # 64 tokens
+    ("AUTO", 4, 1, [1000, 50], [[0] * 33, [1, 1], [1, 1, 1]]),                                             # ... a prompt beyond 512 x 64 tokens
+    ("MFMA_WIDE", 8, 1, [1000, 50], [[0] * 34, [1, 1], [1, 1, 1]]),
+])
+def test_scores_from_a_sorted_list(impl, hq, hkv, lens, chunks):
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("sorted", "bf16", hq, hkv, 128, 5.0e5, lens, [7] * len(lens), [W.RequestSpec(c, [0.2] * len(c), 5) for c in chunks], 1.0, seed=151)
+    rows = 128 if impl == "MFMA_WIDE" else 64
+    tiles = [-(-sum(lens[i] for i in c[1:]) // rows) for c in chunks]
+    assert (512 if rows == 128 else 256) // (hq // 4) < sum(tiles) <= 2048        # (more than run at a time: sorted)
+    up, got = lambda k: -(-k // 256) * 256, []
+    for form in ("MFMA_NARROW", impl):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + form), poison=True)
+        b.ws_select.fill_(0x7f)                                                    # (masses of 3e38)
+        b.rope_shift(); b.select(); torch.cuda.synchronize()
+        got.append(b.scores.cpu().double())
+    entries = plan_list_of(b.ws_select, up(w.n_tok * hq * 4) + up(w.n_tok * 4), w.n_tok, len(w.segments), w.n_requests)
+    assert sorted(entries) == [(r, k) for r in range(w.n_requests) for k in range(tiles[r])]
+    # (the bounds of assert_scores_agree and, for the sums of many keys, of test_scores_in_two_key_streams)
+    sums, d = 4 * math.sqrt(max(sum(lens[i] for i in c) for c in chunks)) * 2.0 ** -24, (got[1] - got[0]).abs()
+    assert float(d.max()) <= 2.0 ** -8 * 16 / math.sqrt(128) / 16 / hq + sums and float(d.pow(2).mean().sqrt()) <= 1e-6 + sums
+
+
+@pytest.mark.parametrize("n", [8192, 8193])
+@pytest.mark.parametrize("frac", [0.1, 0.6])
+def test_selection_behind_wide_scores_of_eight_heads_per_kv_head(n, frac):
+    # (eight wavefronts: keys stay in registers up to 8192 tokens.)  Every other token finds nothing in the chunk before: ties
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("topn8", "bf16", 8, 1, 128, 5.0e5, [40, n], [0, 0], [W.RequestSpec([0, 1], [0.2, frac], 3)], 1.0 / math.sqrt(128), seed=157)
+    w.q[::2, :, 60:64] = 2.0
+    w.q[:, :, 124:128] = 0.0
+    for blk in w.store_tab[w.store_tab_off[0]: w.store_tab_off[1]]:
+        w.k_store[blk, :, :, 60:64] = -141.0
+        w.k_store[blk, :, :, 124:128] = 0.0
+    b = DeviceBatch(w, impl=P.CC_IMPL_MFMA_WIDE, poison=True)
+    b.rope_shift(); b.select(); torch.cuda.synchronize()
+    scores = b.scores.cpu().numpy().astype(np.float64)
+    sg = H.chunk_segments(w, 0)[1]
+    own = scores[int(sg[W.SEG_TOK]): int(sg[W.SEG_TOK]) + n]
+    assert (own == 0).sum() > n // 4 and (own > 0).sum() > n // 4
+    assert np.array_equal(H.gpu_selection(w, b.sel_idx.cpu().numpy())[0][1], O.top_n(own, int(sg[W.SEG_NSEL])))
