@@ -1131,7 +1131,7 @@ void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, in
   const int32_t* block_tab = topn.block_tab;
   const int n_segs = topn.n_segs;
   // Wide kernel first where the head group and the grid allow it; the narrow kernel then
-  // redoes the granules the wide one flagged (normally none: its workgroups read two flags and exit).
+  // redoes the granules the wide one flagged (normally none: a segment's workgroup reads its flags and goes on to select).
   const int hq = ctx->cfg.n_q_heads, hkv = ctx->cfg.n_kv_heads;
   const bool forced = ctx->impl == CC_IMPL_MFMA_WIDE;
   const bool one_tile = !forced && one_score_tile(hq, max_seg_tokens, n_segs, n_requests);

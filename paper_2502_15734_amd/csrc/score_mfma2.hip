@@ -55,7 +55,7 @@ namespace {
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-constexpr int kBigQB = 4, kSmallQB = 2;   // 32-token column blocks per wavefront: big grids, small ones and tails
+constexpr int kBigQB = 4, kSmallQB = 2;   // 32-token column blocks per wavefront: big grids, small ones
 constexpr int kImageK = 1024;     // 16-byte pieces per K tile image
 constexpr int kBufs = 4;
 // p = exp2(S) with no reference: sums outside this range leave too little headroom (above) or may
