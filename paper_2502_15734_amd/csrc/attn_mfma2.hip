@@ -644,6 +644,9 @@ exp_step(0, i);
     f_cur = f_next; f_next = f_far;
   };
   int t = 0;
+  // (Where the loop lies in the lines of the instruction cache shows: 70B on 8 requests of 10k tokens 1527 us with what is
+  // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20.  The form with the by-product is no faster for it.)
+  if constexpr (KS == 1 && !BY) asm volatile(".p2align 6");
   for (; t < n_mine; ++t) {
     const int kimg = k_image(t), vimg = v_image(t), knext = k_image(t + 1);
     move_window(t);
