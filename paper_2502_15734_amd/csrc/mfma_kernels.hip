@@ -1026,7 +1026,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   const PlanArgs a{segs, req_seg_off, cu_q, block_tab, n_segs, n_items, n_requests, n_blocks, max_tiles, n_redo, n_fill, n_list, n_groups, scanned,
                    pl.seg_tile_off, pl.order, pl.redo, pl.items, pl.tiles, list};
   if (by_request && scatter != nullptr && scatter->n_rows > 0)
-    hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + (scatter->n_rows + scatter_rows(scatter->n_rows) - 1) / scatter_rows(scatter->n_rows)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(scatter_plan_kernel, dim3(n_groups + scatter_groups(scatter->n_rows)), dim3(256), 0, stream,
                        a, static_cast<const bf16_t*>(scatter->k_new), static_cast<const bf16_t*>(scatter->v_new),
                        scatter->q_pos, scatter->slot_map, scatter->n_rows, ctx->cfg.n_kv_heads, ctx->inv_freq,
                        static_cast<bf16_t*>(scatter->k_pool), static_cast<bf16_t*>(scatter->v_pool), scatter->n_blocks,

@@ -80,7 +80,7 @@ void launch_rope_scatter(const cc_ctx* ctx, const ScatterJob& job, hipStream_t s
   const bool bf = ctx->cfg.dtype == CC_BF16;
   const int d = ctx->cfg.head_dim, hkv = ctx->cfg.n_kv_heads;
 #define CC_LAUNCH(T, D)                                                                          \
-  hipLaunchKernelGGL((rope_scatter_kernel<T, D>), dim3((job.n_rows + scatter_rows(job.n_rows) - 1) / scatter_rows(job.n_rows)), dim3(256), 0, stream, \
+  hipLaunchKernelGGL((rope_scatter_kernel<T, D>), dim3(scatter_groups(job.n_rows)), dim3(256), 0, stream, \
                      static_cast<const T*>(job.k_new), static_cast<const T*>(job.v_new), job.q_pos, job.slot_map, \
                      job.n_rows, hkv, ctx->inv_freq, static_cast<T*>(job.k_pool), static_cast<T*>(job.v_pool),  \
                      job.n_blocks, job.src_rows, static_cast<const T*>(job.vs.v_shared), job.vs.n_shared_blocks, job.vs.v_map)

@@ -19,12 +19,17 @@ namespace cc {
 // Bound by bytes (a page of values in and out per run) once enough runs are in flight, so nothing of
 // a run passes through LDS and no wavefront waits for another: runs are found with one load and
 // ballots, source rows and slots travel by lane permutes.
+// Consecutive workgroups take rows 16 apart (first all spans' first rows, then their second ones, ...).  In the order of the rows the
+// runs of a dense list begin in every fourth (or eighth, or sixteenth) workgroup, which the dispatcher deals to one or two of the
+// eight XCDs: 40000 dense rows on 8 KV heads 164 -> 59 us, 16000 57 -> 22, 1000 14.4 -> 7.8; every seventh row of 40000 291 -> 284.
 // Rows per workgroup: 4 on long lists, where fewer candidates start too many workgroups that find nothing on dense lists and
 // eight or sixteen leave too few runs in flight on scattered ones.  Short lists: a run is a chain of four dependent loads,
-// so that a workgroup should have one.  8 KV heads, d = 128, every seventh token / all of them, us with 4, 2, 1 rows: 230 rows 12.5,
-// 10.2, 9.4 / 8.8, 9.0, 8.7; 1000: 17.6, 12.8, 10.9 / 9.5, 9.7, 9.1; 2000: 20.3, 18.3, 16.3 / 9.7, 9.8, 11.3; 4000: 39.9, 38.3, 35.1 /
-// 11.5, 13.5, 16.1; 16000: 116, 114, 113 / 36, 39, 76.
+// so that a workgroup should have one.  8 KV heads, d = 128, every seventh token / all of them, us with 4, 2, 1 rows: 230 rows 9.0,
+// 6.4, 6.5 / 7.5, 7.3, 7.5; 1000: 11.4, 8.8, 9.4 / 7.9, 7.8, 7.9; 2000: 15.2, 13.2, 14.0 / 8.7, 8.7, 8.6; 4000: 24.0, 24.6, 24.6 /
+// 9.4, 9.5, 9.4; 16000: 107, 108, 118 / 22, 24, 28.  With cold caches one row is ahead on the shortest: a whole decoder
+// layer of 449 rows takes 3 of 320 us less than with two.
 __host__ __device__ inline int scatter_rows(int n_rows) { return n_rows <= 1024 ? 1 : n_rows <= 2048 ? 2 : 4; }
+inline int scatter_groups(int n_rows) { return (n_rows + kBlock - 1) / kBlock * (kBlock / scatter_rows(n_rows)); }      // workgroups
 
 // (block: the workgroup's number among those that do this)
 template <typename T, int D>
@@ -34,7 +39,7 @@ __device__ __forceinline__ void rope_scatter_rows(
     T* __restrict__ k_pool, T* __restrict__ v_pool, int n_blocks, const int32_t* __restrict__ src_rows,
     const T* __restrict__ v_shared, int n_shared_blocks, int32_t* __restrict__ v_map) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int base = block * rows;
+  const int n_spans = (n_q_tot + kBlock - 1) / kBlock, base = block % n_spans * kBlock + block / n_spans * rows;
   // lane i looks at row base - 1 + i: the row before the first candidate, the candidates, and the
   // rows a run that starts at the last of them can still cover
   int slot = -1, row = 0, pos = 0;
