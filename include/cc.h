@@ -128,8 +128,8 @@ const char* cc_last_error(const cc_ctx* ctx);
  * the narrow kernel; CC_IMPL_MFMA_WIDE runs the first of these at
  * every size (narrow kernels for other head groups).  The forms sum in different orders, and P is
  * rounded to bf16 against another softmax reference, so with AUTO the last bits of a request's results
- * depend on the size of the batch it runs in (cc_linear, cc_qkv_project and cc_gated_linear: on n_rows,
- * which decides the tile and the split of the contraction). */
+ * depend on the size of the batch it runs in (cc_linear, cc_qkv_project and cc_gated_linear: on n_rows
+ * and on the workspace, which decide the tile and the split of the contraction). */
 int cc_set_impl(cc_ctx* ctx, int impl);
 
 /* ---- (a) re-position cached keys ----------------------------------------------------------
@@ -221,6 +221,10 @@ int cc_gather_rows(cc_ctx* ctx, const void* src, int32_t n_src_rows, const int32
  * restricted to the rows of the compact list (Sec. 3.4.3). */
 int cc_qkv_project(cc_ctx* ctx, const void* x, const void* w_qkv, int32_t n_rows, int32_t hidden,
                    void* q, void* k, void* v, void* stream);
+/* The same with scratch memory (see cc_linear_ws). */
+size_t cc_qkv_project_workspace_bytes(const cc_ctx* ctx, int32_t n_rows, int32_t hidden);
+int cc_qkv_project_ws(cc_ctx* ctx, const void* x, const void* w_qkv, int32_t n_rows, int32_t hidden,
+                      void* q, void* k, void* v, void* workspace, size_t workspace_bytes, void* stream);
 
 /* ---- (b'') the rest of a decoder layer, for the rows that are recomputed ----------------------
  * The hidden state of a recomputed token passes through the whole layer (Sec. 2.1: the next hidden
@@ -238,11 +242,18 @@ int cc_qkv_project(cc_ctx* ctx, const void* x, const void* w_qkv, int32_t n_rows
  *                    residual may be y itself, x may not).
  *   cc_gated_linear: y [n_rows][n_ffn] = silu(x W_gate^T) * (x W_up^T), silu(t) = t / (1 + exp(-t)).
  * bf16 with n_out (2 n_ffn for the gated form) and n_in multiples of 64: MFMA GEMM; otherwise a plain
- * tiled kernel. */
+ * tiled kernel.
+ *   cc_linear_ws:    cc_linear with scratch memory, in which a product of few rows may keep the sums of
+ *                    parts of its contraction (fp32), so that more of the chip works on it.  workspace:
+ *                    16-byte aligned, cc_linear_workspace_bytes(ctx, n_rows, n_in, n_out) bytes (0: the
+ *                    product stays whole; at most 256 MiB); with less, or NULL, as many parts as fit. */
 int cc_rms_norm(cc_ctx* ctx, const void* x, const void* gain, float eps, int32_t n_rows, int32_t hidden,
                 void* y, void* stream);
 int cc_linear(cc_ctx* ctx, const void* x, const void* w, const void* residual, int32_t n_rows,
               int32_t n_in, int32_t n_out, void* y, void* stream);
+size_t cc_linear_workspace_bytes(const cc_ctx* ctx, int32_t n_rows, int32_t n_in, int32_t n_out);
+int cc_linear_ws(cc_ctx* ctx, const void* x, const void* w, const void* residual, int32_t n_rows,
+                 int32_t n_in, int32_t n_out, void* y, void* workspace, size_t workspace_bytes, void* stream);
 int cc_gated_linear(cc_ctx* ctx, const void* x, const void* w_gate, const void* w_up, int32_t n_rows,
                     int32_t n_in, int32_t n_ffn, void* y, void* stream);
 

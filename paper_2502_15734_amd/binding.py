@@ -74,6 +74,10 @@ def load_library() -> C.CDLL:
     lib.cc_gather_rows.restype = C.c_int
     lib.cc_qkv_project.argtypes = [vp, vp, vp, i32, i32, vp, vp, vp, vp]
     lib.cc_qkv_project.restype = C.c_int
+    lib.cc_qkv_project_workspace_bytes.argtypes = [vp, i32, i32]
+    lib.cc_qkv_project_workspace_bytes.restype = sz
+    lib.cc_qkv_project_ws.argtypes = [vp, vp, vp, i32, i32, vp, vp, vp, vp, sz, vp]
+    lib.cc_qkv_project_ws.restype = C.c_int
     lib.cc_sparse_prefill_workspace_bytes.argtypes = [vp, i32, i32]
     lib.cc_sparse_prefill_workspace_bytes.restype = sz
     lib.cc_sparse_prefill.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, vp, vp, i32, vp, vp, i32,
@@ -86,6 +90,10 @@ def load_library() -> C.CDLL:
     lib.cc_rms_norm.restype = C.c_int
     lib.cc_linear.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp, vp]
     lib.cc_linear.restype = C.c_int
+    lib.cc_linear_workspace_bytes.argtypes = [vp, i32, i32, i32]
+    lib.cc_linear_workspace_bytes.restype = sz
+    lib.cc_linear_ws.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp, vp, sz, vp]
+    lib.cc_linear_ws.restype = C.c_int
     lib.cc_gated_linear.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp, vp]
     lib.cc_gated_linear.restype = C.c_int
     lib.cc_sparse_prefill_mass_workspace_bytes.argtypes = [vp, i32, i32, i32, i32, i32]
@@ -173,6 +181,23 @@ def _stream() -> int:
     return torch.cuda.current_stream().cuda_stream
 
 
+def _nbytes(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
+
+
+def _scratch(nbytes: int, device) -> Optional[torch.Tensor]:
+    """Scratch for one call, from torch's allocator on the stream the call runs on: it goes back when the call has been
+    enqueued, and what takes it next on that stream runs behind the call.  None, which every call that asks for scratch here
+    can do without, when the stream is being captured (the graph would keep using memory that has been given back, unless
+    it is torch that captures) or memory is short."""
+    if nbytes == 0 or device.type != "cuda" or torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 class Context:
     """cc_ctx handle.  Methods mirror the C entry points one to one."""
 
@@ -244,9 +269,15 @@ class Context:
                                              row_idx.shape[0], row_bytes, _ptr(dst), _stream()))
 
     # -- cc_qkv_project ----------------------------------------------------------------------
-    def qkv_project(self, x, w_qkv, q, k, v):
-        self._check(self._lib.cc_qkv_project(self._h, _ptr(x), _ptr(w_qkv), x.shape[0], x.shape[1],
-                                             _ptr(q), _ptr(k), _ptr(v), _stream()))
+    def qkv_project(self, x, w_qkv, q, k, v, workspace=None):
+        """workspace: scratch tensor (qkv_project_workspace_bytes); None: one is taken for the call (see _scratch)."""
+        if workspace is None:
+            workspace = _scratch(self.qkv_project_workspace_bytes(x.shape[0], x.shape[1]), x.device)
+        self._check(self._lib.cc_qkv_project_ws(self._h, _ptr(x), _ptr(w_qkv), x.shape[0], x.shape[1],
+                                                _ptr(q), _ptr(k), _ptr(v), _ptr(workspace), _nbytes(workspace), _stream()))
+
+    def qkv_project_workspace_bytes(self, n_rows: int, hidden: int) -> int:
+        return int(self._lib.cc_qkv_project_workspace_bytes(self._h, n_rows, hidden))
 
     # -- cc_sparse_prefill -------------------------------------------------------------------
     def sparse_prefill_workspace_bytes(self, n_ctx_tokens: int, n_segs: int) -> int:
@@ -280,10 +311,16 @@ class Context:
         self._check(self._lib.cc_rms_norm(self._h, _ptr(x), _ptr(gain), float(eps), x.shape[0], x.shape[1], _ptr(y),
                                           _stream()))
 
-    def linear(self, x, w, y, residual=None):
-        """y = x w^T (+ residual); w [out_features, in_features]."""
-        self._check(self._lib.cc_linear(self._h, _ptr(x), _ptr(w), _ptr(residual), x.shape[0], w.shape[1], w.shape[0],
-                                        _ptr(y), _stream()))
+    def linear(self, x, w, y, residual=None, workspace=None):
+        """y = x w^T (+ residual); w [out_features, in_features].  workspace: scratch tensor (linear_workspace_bytes);
+        None: one is taken for the call (see _scratch)."""
+        if workspace is None:
+            workspace = _scratch(self.linear_workspace_bytes(x.shape[0], w.shape[1], w.shape[0]), x.device)
+        self._check(self._lib.cc_linear_ws(self._h, _ptr(x), _ptr(w), _ptr(residual), x.shape[0], w.shape[1], w.shape[0],
+                                           _ptr(y), _ptr(workspace), _nbytes(workspace), _stream()))
+
+    def linear_workspace_bytes(self, n_rows: int, n_in: int, n_out: int) -> int:
+        return int(self._lib.cc_linear_workspace_bytes(self._h, n_rows, n_in, n_out))
 
     def gated_linear(self, x, w_gate, w_up, y):
         """y = silu(x w_gate^T) * (x w_up^T)."""

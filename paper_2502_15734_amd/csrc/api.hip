@@ -232,17 +232,27 @@ int cc_gather_rows(cc_ctx* ctx, const void* src, int32_t n_src_rows, const int32
   return cc::check_launch(ctx, fn);
 }
 
+size_t cc_qkv_project_workspace_bytes(const cc_ctx* ctx, int32_t n_rows, int32_t hidden) {
+  if (ctx == nullptr) return 0;
+  return cc::gemm_workspace_bytes(ctx, n_rows, hidden, (ctx->cfg.n_q_heads + 2 * ctx->cfg.n_kv_heads) * ctx->cfg.head_dim);
+}
+
 int cc_qkv_project(cc_ctx* ctx, const void* x, const void* w_qkv, int32_t n_rows, int32_t hidden,
                    void* q, void* k, void* v, void* stream) {
+  return cc_qkv_project_ws(ctx, x, w_qkv, n_rows, hidden, q, k, v, nullptr, 0, stream);
+}
+
+int cc_qkv_project_ws(cc_ctx* ctx, const void* x, const void* w_qkv, int32_t n_rows, int32_t hidden,
+                      void* q, void* k, void* v, void* workspace, size_t workspace_bytes, void* stream) {
   static const char* fn = "cc_qkv_project";
   if (ctx == nullptr) return CC_ERR_INVALID_ARG;
   CC_REQUIRE(n_rows >= 0 && hidden > 0, "bad sizes");
   CC_REQUIRE(hidden % 64 == 0, "hidden must be a multiple of 64");
   if (n_rows == 0) return CC_OK;
   CC_REQUIRE(x && w_qkv && q && k && v, "null pointer");
-  CC_REQUIRE(aligned16(x) && aligned16(w_qkv) && aligned16(q) && aligned16(k) && aligned16(v),
+  CC_REQUIRE(aligned16(x) && aligned16(w_qkv) && aligned16(q) && aligned16(k) && aligned16(v) && aligned16(workspace),
              "tensors must be 16-byte aligned");
-  cc::launch_qkv_project(ctx, x, w_qkv, n_rows, hidden, q, k, v, static_cast<hipStream_t>(stream));
+  cc::launch_qkv_project(ctx, x, w_qkv, n_rows, hidden, q, k, v, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
   return cc::check_launch(ctx, fn);
 }
 
@@ -260,16 +270,25 @@ int cc_rms_norm(cc_ctx* ctx, const void* x, const void* gain, float eps, int32_t
   return cc::check_launch(ctx, fn);
 }
 
+size_t cc_linear_workspace_bytes(const cc_ctx* ctx, int32_t n_rows, int32_t n_in, int32_t n_out) {
+  return ctx == nullptr ? 0 : cc::gemm_workspace_bytes(ctx, n_rows, n_in, n_out);
+}
+
 int cc_linear(cc_ctx* ctx, const void* x, const void* w, const void* residual, int32_t n_rows,
               int32_t n_in, int32_t n_out, void* y, void* stream) {
+  return cc_linear_ws(ctx, x, w, residual, n_rows, n_in, n_out, y, nullptr, 0, stream);
+}
+
+int cc_linear_ws(cc_ctx* ctx, const void* x, const void* w, const void* residual, int32_t n_rows,
+                 int32_t n_in, int32_t n_out, void* y, void* workspace, size_t workspace_bytes, void* stream) {
   static const char* fn = "cc_linear";
   if (ctx == nullptr) return CC_ERR_INVALID_ARG;
   CC_REQUIRE(n_rows >= 0 && n_in > 0 && n_out > 0, "bad sizes");
   if (n_rows == 0) return CC_OK;
   CC_REQUIRE(x && w && y, "null pointer");
   CC_REQUIRE(x != y, "x and y must not be the same tensor");
-  CC_REQUIRE(aligned16(x) && aligned16(w) && aligned16(y) && aligned16(residual), "tensors must be 16-byte aligned");
-  cc::launch_linear(ctx, x, w, residual, n_rows, n_in, n_out, y, static_cast<hipStream_t>(stream));
+  CC_REQUIRE(aligned16(x) && aligned16(w) && aligned16(y) && aligned16(residual) && aligned16(workspace), "tensors must be 16-byte aligned");
+  cc::launch_linear(ctx, x, w, residual, n_rows, n_in, n_out, y, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
   return cc::check_launch(ctx, fn);
 }
 

@@ -195,9 +195,12 @@ __device__ __forceinline__ void gemm_store8(const f32x4& lo, const f32x4& hi, co
 // is 0 - 5 % slower, on gated products of 2 x 28672 features 25 %: 9000 rows 7.85 / 6.02 ms; 8 x 4 and 2 x 16 blocks
 // measure the same.)
 constexpr int kBlockN = 4, kBlockM = 8;
-__device__ __forceinline__ bool gemm_tile_of(int tiles_n, int tiles_m, int* tn, int* tm) {
-  const int entry = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  if (entry >= tiles_n * tiles_m) return false;            // (the grid is padded to a multiple of 8)
+// With the contraction in parts the order runs through all tiles of a part before the next one.
+__device__ __forceinline__ bool gemm_tile_of(int tiles_n, int tiles_m, int n_parts, int* tn, int* tm, int* part) {
+  int entry = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (entry >= tiles_n * tiles_m * n_parts) return false;  // (the grid is padded to a multiple of 8)
+  *part = entry / (tiles_n * tiles_m);
+  entry -= *part * (tiles_n * tiles_m);
   const int strip = min(entry / (kBlockN * tiles_m), (tiles_n - 1) / kBlockN);   // strip of up to 4 feature tiles
   const int strip_w = min(kBlockN, tiles_n - strip * kBlockN);
   const int in_strip = entry - strip * kBlockN * tiles_m;
@@ -205,6 +208,21 @@ __device__ __forceinline__ bool gemm_tile_of(int tiles_n, int tiles_m, int* tn, 
   *tn = strip * kBlockN + in_blk % strip_w;
   *tm = blk * kBlockM + in_blk / strip_w;
   return true;
+}
+
+// A contraction in parts (SPLIT): the workgroups of a tile each take a range of its stages and write what their
+// accumulators hold, in fp32 and in the accumulators' own order (a store instruction fills 1 KiB), to the caller's workspace;
+// gemm_sum_kernel adds the parts in their order and does what the epilogue would have done.  Block (token block, feature
+// block) of part p: 2 KiB at ((p n_tb + token block) n_fb + feature block).
+struct GemmParts {
+  f32x4* sums;                 // null: the contraction is not split
+  int n, n_tb, n_fb;           // parts; 16-token blocks (of whole tiles) and 32-feature blocks of the product
+};
+__device__ __forceinline__ void gemm_store_part(const GemmParts& parts, int part, int tb, int fb, int lane, const f32x4& lo, const f32x4& hi) {
+  f32x4* to = parts.sums + ((static_cast<size_t>(part) * parts.n_tb + tb) * parts.n_fb + fb) * 128;        // (wave-uniform)
+  to[lane] = lo;
+  to[64 + lane] = hi;
+  __builtin_amdgcn_sched_barrier(0);                      // (one block's registers at a time)
 }
 
 template <int N>
@@ -229,10 +247,10 @@ __device__ __forceinline__ void gemm_barrier() {
 // lines in flight are bounded, so the rate is that bound over the latency of the level the lines come
 // from), whatever the number of buffers or wavefronts.  A list of 449 rows against the 256 x 256 tile:
 // 4096 x 4096 101 -> 23 us, 4096 x 14336 354 -> 79 us, 6144 x 4096 106 -> 35 us.
-template <int MODE, int FB, int TB, int WF, int WM, int WK, int U, int NBUF>
+template <int MODE, bool SPLIT, int FB, int TB, int WF, int WM, int WK, int U, int NBUF>
 __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NBUF * U * (32 * FB * WF + 16 * TB * WM) * 128 <= 163840) ? 2 : 1) void gemm_tile_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const bf16_t* __restrict__ w2, int n_rows,
-    int hidden, int tiles_n, int tiles_m, GemmOut out) {
+    int hidden, int tiles_n, int tiles_m, GemmOut out, GemmParts parts) {
   constexpr int NW = WF * WM * WK;                    // wavefronts
   constexpr int F = 32 * FB * WF, M = 16 * TB * WM;   // features x tokens of the tile
   constexpr int PW = U * (F + M) / 8 / NW;            // load instructions of a wavefront per stage
@@ -240,16 +258,19 @@ __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NB
   constexpr int S = 2 * U / WK;                       // 32-wide k-steps of a stage a wavefront multiplies
   static_assert((U * (F + M)) % (8 * NW) == 0 && (2 * U) % WK == 0, "stage must divide over the wavefronts");
   static_assert(MODE != kOutGated || FB % 2 == 0, "a wavefront holds gate and up rows of the same outputs");
+  static_assert(!SPLIT || MODE == kOutLinear, "a part's epilogue knows no outputs; gated products are not split");
   __shared__ uint4 lds[NBUF * kStage / 16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nl = lane & 15, g = lane >> 4;
   const int wk = wave % WK, wn = (wave / WK) % WF, wm = wave / (WK * WF);
-  int n0, m0;
-  if (!gemm_tile_of(tiles_n, tiles_m, &n0, &m0)) return;
+  int n0, m0, part;
+  if (!gemm_tile_of(tiles_n, tiles_m, SPLIT ? parts.n : 1, &n0, &m0, &part)) return;
   n0 *= F;
   m0 *= M;
-  const int n_k = hidden / (kTK * U);
+  const int n_k_all = hidden / (kTK * U), k_first = SPLIT ? n_k_all * part / parts.n : 0;      // this part's stages: k_first .. + n_k - 1
+  const int n_k = SPLIT ? n_k_all * (part + 1) / parts.n - k_first : n_k_all;
+  __builtin_assume(!SPLIT || n_k > 0);
 
   // ---- staging: image rows 0..F-1 are W, F..F+M-1 are x; wavefront w brings groups PW w .. of 8 rows: lane L
   // -> row 8 j + L / 8, LDS piece L % 8 of that row
@@ -271,7 +292,7 @@ __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NB
       base[j] = reinterpret_cast<const char*>((in >= FB / 2 ? w2 : w) + static_cast<size_t>(n0 / 2) * hidden);
       off_row = 32 * (grp * (FB / 2) + in % (FB / 2)) + (r & 31);
     }
-    base[j] += sub * (kTK * 2);
+    base[j] += (k_first * U + sub) * (kTK * 2);
     voff[j] = static_cast<uint32_t>(off_row) * static_cast<uint32_t>(hidden * 2) +
               16 * ((lane & 7) ^ (r0 >= F ? gemm_swz_x(r - F) : gemm_swz_w(r)));
   }
@@ -392,7 +413,7 @@ __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NB
 #pragma unroll
     for (int b = 0; b < H; ++b)
 #pragma unroll
-      for (int a = 0; a < FO; ++a) res[b][a] = gemm_residual8<MODE>(out, min(tok0 + 16 * (wk * H + b), n_rows - 1), col0 + 32 * a);
+      for (int a = 0; a < FO; ++a) if (!SPLIT) res[b][a] = gemm_residual8<MODE>(out, min(tok0 + 16 * (wk * H + b), n_rows - 1), col0 + 32 * a);
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < H; ++b) {
@@ -416,6 +437,12 @@ __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NB
           }
           sum[a][i2] = v;
         }
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int a = 0; a < FB; ++a)
+          gemm_store_part(parts, part, m0 / 16 + TB * wm + wk * H + b, n0 / 32 + FB * wn + a, lane, sum[a][0], sum[a][1]);
+        continue;
+      }
       const int row = tok0 + 16 * (wk * H + b);
       if (row < n_rows) {
 #pragma unroll
@@ -423,6 +450,12 @@ __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NB
           gemm_store8<MODE>(sum[a][0], sum[a][1], sum[FB - FO + a][0], sum[FB - FO + a][1], res[b][a], out, row, col0 + 32 * a);
       }
     }
+  } else if constexpr (SPLIT) {
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int a = 0; a < FB; ++a)
+        gemm_store_part(parts, part, m0 / 16 + TB * wm + b, n0 / 32 + FB * wn + a, lane, acc[a][0][b], acc[a][1][b]);
   } else {
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
@@ -446,10 +479,10 @@ __global__ __launch_bounds__(64 * WF * WM * WK, (WF * WM * WK * 2 <= 8 && 2 * NB
 // 1.37 - 1.40 PFLOP/s in full rounds of tiles (the 32x32x16 form with four wavefronts of 128 x 128: 1.15 - 1.24):
 // 13 824 rows x 4096 x 14336 1.58 -> 1.28 ms, gated 4096 -> 2 x 14336 2.60 -> 2.37 ms.  What is left: loads from
 // beyond the L2 cost 12 % (measured with the stages repeated), the loads themselves 10 %, operand reads 9 %.
-template <int MODE>
+template <int MODE, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void gemm_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const bf16_t* __restrict__ w2, int n_rows,
-    int hidden, int tiles_n, int tiles_m, GemmOut out) {
+    int hidden, int tiles_n, int tiles_m, GemmOut out, GemmParts parts) {
   constexpr int F = 256, M = 256, FB = 4, TB = 4, WF = 2;
   constexpr int kHalf = 32768, kSlots = 5;             // bytes and number of the half-stage buffers
   constexpr int kMeet = 2;                             // feature half-blocks of the second step in front of the barrier (1 or 3: the same)
@@ -458,17 +491,20 @@ __global__ __launch_bounds__(512, 2) void gemm_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nl = lane & 15, g = lane >> 4;
   const int wn = wave % WF, wm = wave / WF;
-  int n0, m0;
-  if (!gemm_tile_of(tiles_n, tiles_m, &n0, &m0)) return;
+  int n0, m0, part;
+  if (!gemm_tile_of(tiles_n, tiles_m, SPLIT ? parts.n : 1, &n0, &m0, &part)) return;
   n0 *= F;
   m0 *= M;
-  const int n_k = hidden / kTK;
+  const int n_k_all = hidden / kTK, k_first = SPLIT ? n_k_all * part / parts.n : 0;            // this part's stages: k_first .. + n_k - 1
+  const int n_k = SPLIT ? n_k_all * (part + 1) / parts.n - k_first : n_k_all;
+  __builtin_assume(!SPLIT || n_k > 0);
   // wavefront w brings rows 32 w .. 32 w + 31 of W and of x, 8 rows per instruction
   uint32_t voff_w[4], voff_x[4];
   const char* base_w;
-  const char* base_x = reinterpret_cast<const char*>(x + static_cast<size_t>(m0) * hidden);
+  const char* base_x = reinterpret_cast<const char*>(x + static_cast<size_t>(m0) * hidden) + k_first * (kTK * 2);
   if (MODE != kOutGated) base_w = reinterpret_cast<const char*>(w + static_cast<size_t>(n0) * hidden);
   else base_w = reinterpret_cast<const char*>(((wave % FB) >= FB / 2 ? w2 : w) + static_cast<size_t>(n0 / 2) * hidden);
+  base_w += k_first * (kTK * 2);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int r = 32 * wave + 8 * j + (lane >> 3);
@@ -556,6 +592,14 @@ __global__ __launch_bounds__(512, 2) void gemm_kernel(
   }
   gemm_wait_loads<0>();            // (nothing may still be landing when the LDS is given back)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int a = 0; a < FB; ++a)
+        gemm_store_part(parts, part, m0 / 16 + TB * wm + b, n0 / 32 + FB * wn + a, lane, acc[a][0][b], acc[a][1][b]);
+    return;
+  }
   const int tok0 = m0 + 16 * TB * wm + nl;
   const int col0 = (MODE == kOutGated ? n0 / 2 + 32 * (FB / 2) * wn : n0 + 32 * FB * wn) + 8 * g;
   constexpr int FO = MODE == kOutGated ? FB / 2 : FB;
@@ -570,22 +614,58 @@ __global__ __launch_bounds__(512, 2) void gemm_kernel(
   }
 }
 
+// The sums of a contraction in parts: a wavefront per 32 features x 16 tokens adds the parts in their order and
+// finishes the outputs as the kernels above do.  Bound by the parts' bytes (5 - 11 us at 230 rows x 8192 features x 4 parts to 1000 x
+// 4096 x 4, start included).
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_sum_kernel(int n_rows, GemmOut out, GemmParts parts) {
+  const int lane = threadIdx.x & 63;
+  const int at = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tb = at / parts.n_fb, fb = at - tb * parts.n_fb;
+  if (16 * tb >= n_rows) return;
+  const int row = 16 * tb + (lane & 15), col = 32 * fb + 8 * (lane >> 4);
+  const uint4 residual = gemm_residual8<MODE>(out, min(row, n_rows - 1), col);
+  constexpr int kTogether = 4;                            // parts asked for at a time
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+  for (int p0 = 0; p0 < parts.n; p0 += kTogether) {
+    f32x4 v[kTogether][2];
+#pragma unroll
+    for (int i = 0; i < kTogether; ++i) {
+      const f32x4* from = parts.sums + ((static_cast<size_t>(min(p0 + i, parts.n - 1)) * parts.n_tb + tb) * parts.n_fb + fb) * 128 + lane;
+      v[i][0] = from[0];
+      v[i][1] = from[64];
+    }
+#pragma unroll
+    for (int i = 0; i < kTogether; ++i)
+      if (p0 + i < parts.n) { lo += v[i][0]; hi += v[i][1]; }
+  }
+  if (row < n_rows) gemm_store8<MODE>(lo, hi, lo, hi, residual, out, row, col);
+}
+
 template <int MODE>
 void launch_gemm_256(hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in, int n_features,
-                      const GemmOut& out) {
+                      const GemmOut& out, const GemmParts& parts) {
   const int tiles_n = n_features / 256, tiles_m = (n_rows + 255) / 256;
-  hipLaunchKernelGGL((gemm_kernel<MODE>), dim3((tiles_n * tiles_m + 7) / 8 * 8), dim3(512), 0,
-                     stream, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), static_cast<const bf16_t*>(w2),
-                     n_rows, n_in, tiles_n, tiles_m, out);
+#define CC_GO(M, SPLIT)                                                                                              \
+  hipLaunchKernelGGL((gemm_kernel<M, SPLIT>), dim3((tiles_n * tiles_m * parts.n + 7) / 8 * 8), dim3(512), 0,            \
+                     stream, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), static_cast<const bf16_t*>(w2), \
+                     n_rows, n_in, tiles_n, tiles_m, out, parts)
+  if (parts.sums == nullptr) CC_GO(MODE, false);
+  else if constexpr (MODE != kOutGated) CC_GO(kOutLinear, true);
+#undef CC_GO
 }
 
 template <int MODE, int FB, int TB, int WF, int WM, int WK, int U, int NBUF>
 void launch_gemm_tile(hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in, int n_features,
-                      const GemmOut& out) {
+                      const GemmOut& out, const GemmParts& parts) {
   const int tiles_n = n_features / (32 * FB * WF), tiles_m = (n_rows + 16 * TB * WM - 1) / (16 * TB * WM);
-  hipLaunchKernelGGL((gemm_tile_kernel<MODE, FB, TB, WF, WM, WK, U, NBUF>), dim3((tiles_n * tiles_m + 7) / 8 * 8), dim3(64 * WF * WM * WK), 0,
-                     stream, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), static_cast<const bf16_t*>(w2),
-                     n_rows, n_in, tiles_n, tiles_m, out);
+#define CC_GO(M, SPLIT)                                                                                              \
+  hipLaunchKernelGGL((gemm_tile_kernel<M, SPLIT, FB, TB, WF, WM, WK, U, NBUF>), dim3((tiles_n * tiles_m * parts.n + 7) / 8 * 8), \
+                     dim3(64 * WF * WM * WK), 0, stream, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w),  \
+                     static_cast<const bf16_t*>(w2), n_rows, n_in, tiles_n, tiles_m, out, parts)
+  if (parts.sums == nullptr) CC_GO(MODE, false);
+  else if constexpr (MODE != kOutGated) CC_GO(kOutLinear, true);
+#undef CC_GO
 }
 
 // Tile shapes and what a stage of 64 contraction indices takes on a compute unit that runs one workgroup of
@@ -615,10 +695,10 @@ inline int gemm_best_tile(int n_features, int n_in, int n_rows, bool gated) {
 
 template <int MODE>
 void launch_gemm_shape(int shape, hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in,
-                       int n_features, const GemmOut& out) {
-#define CC_TILE(...) launch_gemm_tile<MODE, __VA_ARGS__>(stream, x, w, w2, n_rows, n_in, n_features, out)
+                       int n_features, const GemmOut& out, const GemmParts& parts) {
+#define CC_TILE(...) launch_gemm_tile<MODE, __VA_ARGS__>(stream, x, w, w2, n_rows, n_in, n_features, out, parts)
   switch (shape) {
-    case 0: launch_gemm_256<MODE>(stream, x, w, w2, n_rows, n_in, n_features, out); break;
+    case 0: launch_gemm_256<MODE>(stream, x, w, w2, n_rows, n_in, n_features, out, parts); break;
     case 1: CC_TILE(2, 4, 2, 4, 1, 1, 3); break;      // (128 x 256: 8 wavefronts of 64 x 64)
     case 2: CC_TILE(2, 4, 2, 2, 2, 1, 4); break;      // (128 x 128: 8 of 64 x 64, half the k-steps each)
     case 3: CC_TILE(2, 4, 1, 2, 2, 1, 5); break;      // (64 x 128: 4 of 64 x 64, half the k-steps each)
@@ -626,52 +706,105 @@ void launch_gemm_shape(int shape, hipStream_t stream, const void* x, const void*
     default: if constexpr (MODE != kOutGated) CC_TILE(1, 4, 1, 1, 4, 2, 5); break;   // (32 x 64: the same)
   }
 #undef CC_TILE
+  if constexpr (MODE != kOutGated)
+    if (parts.sums != nullptr)
+      hipLaunchKernelGGL((gemm_sum_kernel<MODE>), dim3(((n_rows + 15) / 16 * parts.n_fb + 3) / 4), dim3(256), 0, stream, n_rows, out, parts);
+}
+
+// How a range of rows is multiplied: the tile, the parts of the contraction, and what that is expected to take.
+struct GemmChoice { int shape, parts; float us; };
+inline int gemm_padded_rows(int shape, int n_rows) { return (n_rows + kGemmTiles[shape].m - 1) / kGemmTiles[shape].m * kGemmTiles[shape].m; }
+inline size_t gemm_parts_bytes(const GemmChoice& c, int n_features, int n_rows) {
+  return c.parts == 1 ? 0 : static_cast<size_t>(c.parts) * gemm_padded_rows(c.shape, n_rows) * n_features * sizeof(float);
+}
+
+// A short list has too few big tiles for 256 compute units, and small ones pass each weight line through an L1 with few tokens to
+// multiply: parts of the contraction let big tiles fill the chip.  They cost their sums' way through memory
+// (8 bytes per part and output at kPartsRate) and a launch; and nothing is faster than the weights arrive.  Whole / in parts, us:
+// 28672 -> 8192 features, 60 rows 128 / 101, 230 rows 197 / 136, 449 250 / 208, 1000 414 / 372; 14336 -> 4096, 60 rows 50 / 29, 230
+// 60 / 44, 449 78 / 66, 1000 127 / 110; 8192 -> 10240, 230 rows 73 / 55, 449 105 / 84; 4096 -> 6144, 449 rows 35 / 48: stays whole.
+// (Over 204 products of these widths and 20 to 2300 rows the choice takes 1.6 % longer than the best of all tiles and
+// parts, the choice without parts 10 %; none is slower than that.)  Gated products have enough tiles by themselves: 2 x 14336 features,
+// 230 rows 66 / 79, 449 99 / 136.
+constexpr int kMaxParts = 8;
+constexpr size_t kMaxPartsBytes = size_t{256} << 20;
+constexpr float kPartsUs = 6.f, kPartsRate = 5e6f, kWeightRate = 5.5e6f;       // a launch; bytes per us
+inline GemmChoice gemm_choose(int n_features, int n_in, int n_rows, bool gated, size_t room) {
+  GemmChoice c{gemm_best_tile(n_features, n_in, n_rows, gated), 1, 0.f};
+  c.us = gemm_tile_cost(c.shape, n_features, n_rows) * n_in / kTK;
+  if (gated) return c;
+  const float weights_us = 2.f * n_features * n_in / kWeightRate;
+  float whole = c.us > weights_us ? c.us : weights_us;
+  for (int i = 0; i < 6; ++i) {
+    if (!gemm_tile_fits(i, n_features, n_in, gated)) continue;
+    const GemmTile& t = kGemmTiles[i];
+    const int64_t tiles = static_cast<int64_t>(n_features / t.f) * ((n_rows + t.m - 1) / t.m);
+    const int stages = n_in / t.k;
+    for (int p = 2; p <= kMaxParts && p <= stages; ++p) {
+      GemmChoice s{i, p, 0.f};
+      const size_t bytes = gemm_parts_bytes(s, n_features, n_rows);
+      if (bytes > room || bytes > kMaxPartsBytes) break;
+      const float mul = static_cast<float>((tiles * p + kGemmUnits - 1) / kGemmUnits) * t.stage_us * ((stages + p - 1) / p) * (t.k / kTK);
+      s.us = (mul > weights_us ? mul : weights_us) + kPartsUs + 2.f * bytes / kPartsRate;
+      if (s.us < whole) { whole = s.us; c = s; }
+    }
+  }
+  return c;
+}
+
+// A product of a few rounds of 256 x 256 tiles leaves most of the chip idle in its last one: then the first `full` rows (whole
+// rounds) go to that kernel and the rest to what suits it, in a launch of its own (about 6 us more).
+struct GemmPlan { int full; GemmChoice rest; };
+inline GemmPlan gemm_plan(int n_features, int n_in, int n_rows, bool gated, size_t room) {
+  GemmPlan plan{0, gemm_choose(n_features, n_in, n_rows, gated, room)};
+  if (!gemm_tile_fits(0, n_features, n_in, gated)) return plan;
+  const int tiles_n = n_features / 256, rounds = tiles_n * ((n_rows + 255) / 256) / kGemmUnits;
+  const int rows_full = rounds * kGemmUnits / tiles_n * 256, rest = n_rows - rows_full;
+  if (rows_full <= 0 || rest <= 0) return plan;
+  const GemmChoice tail = gemm_choose(n_features, n_in, rest, gated, room);
+  if (gemm_tile_cost(0, n_features, rows_full) * n_in / kTK + tail.us + 6.f < plan.rest.us) plan = GemmPlan{rows_full, tail};
+  return plan;
 }
 
 template <int MODE>
 void launch_gemm(hipStream_t stream, const void* x, const void* w, const void* w2, int n_rows, int n_in, int n_features,
-                 const GemmOut& out) {
-  constexpr bool kGated = MODE == kOutGated;
-  const int best = gemm_best_tile(n_features, n_in, n_rows, kGated);
-  // A product of a few rounds of 256 x 256 tiles leaves most of the chip idle in its last one: then the
-  // rows of the whole rounds go to that kernel and the rest to the shape that suits it, in a launch of its
-  // own (about 6 us more).
-  if (gemm_tile_fits(0, n_features, n_in, kGated)) {
-    const int tiles_n = n_features / 256, rounds = tiles_n * ((n_rows + 255) / 256) / kGemmUnits;
-    const int rows_full = rounds * kGemmUnits / tiles_n * 256, rest = n_rows - rows_full;
-    if (rows_full > 0 && rest > 0) {
-      const int tail = gemm_best_tile(n_features, n_in, rest, kGated);
-      const float split = gemm_tile_cost(0, n_features, rows_full) + gemm_tile_cost(tail, n_features, rest) + 6.f * kTK / n_in;
-      if (split < gemm_tile_cost(best, n_features, n_rows)) {
-        launch_gemm_shape<MODE>(0, stream, x, w, w2, rows_full, n_in, n_features, out);
-        const size_t at = static_cast<size_t>(rows_full);
-        auto shift = [&](const void* p, int width) { return p == nullptr ? nullptr : static_cast<const bf16_t*>(p) + at * width; };
-        GemmOut o = out;
-        if (MODE == kOutQkv) {
-          o.o0 = const_cast<bf16_t*>(shift(out.o0, out.nq)); o.o1 = const_cast<bf16_t*>(shift(out.o1, out.nk)); o.o2 = const_cast<bf16_t*>(shift(out.o2, out.nk));
-        } else {
-          o.o0 = const_cast<bf16_t*>(shift(out.o0, out.width)); o.residual = shift(out.residual, out.width);
-        }
-        launch_gemm_shape<MODE>(tail, stream, shift(x, n_in), w, w2, rest, n_in, n_features, o);
-        return;
-      }
-    }
+                 const GemmOut& out, void* workspace, size_t room) {
+  const GemmPlan plan = gemm_plan(n_features, n_in, n_rows, MODE == kOutGated, workspace != nullptr ? room : 0);
+  auto shift = [&](const void* p, int width) { return p == nullptr ? nullptr : static_cast<const bf16_t*>(p) + static_cast<size_t>(plan.full) * width; };
+  const GemmParts whole{nullptr, 1, 0, 0};
+  if (plan.full > 0) launch_gemm_shape<MODE>(0, stream, x, w, w2, plan.full, n_in, n_features, out, whole);
+  const int rest = n_rows - plan.full;
+  GemmOut o = out;
+  if (MODE == kOutQkv) {
+    o.o0 = const_cast<bf16_t*>(shift(out.o0, out.nq)); o.o1 = const_cast<bf16_t*>(shift(out.o1, out.nk)); o.o2 = const_cast<bf16_t*>(shift(out.o2, out.nk));
+  } else {
+    o.o0 = const_cast<bf16_t*>(shift(out.o0, out.width)); o.residual = shift(out.residual, out.width);
   }
-  launch_gemm_shape<MODE>(best, stream, x, w, w2, n_rows, n_in, n_features, out);
+  const GemmParts parts = plan.rest.parts == 1 ? whole
+      : GemmParts{static_cast<f32x4*>(workspace), plan.rest.parts, gemm_padded_rows(plan.rest.shape, rest) / 16, n_features / 32};
+  launch_gemm_shape<MODE>(plan.rest.shape, stream, shift(x, n_in), w, w2, rest, n_in, n_features, o, parts);
 }
 
 // the MFMA GEMMs take outputs in tiles of at least 64 features and contraction lengths in whole cache lines
-inline bool gemm_fits(int n_features, int n_in) { return n_features % 64 == 0 && n_in % kTK == 0; }
+inline bool gemm_fits(const cc_ctx* ctx, int n_features, int n_in) {
+  return ctx->cfg.dtype == CC_BF16 && ctx->impl != CC_IMPL_SCALAR && n_features % 64 == 0 && n_in % kTK == 0;
+}
 
 }  // namespace
 
+// bytes that let a product of these sizes take the parts it would like to (0: it stays whole)
+size_t gemm_workspace_bytes(const cc_ctx* ctx, int n_rows, int n_in, int n_features) {
+  if (n_rows <= 0 || n_in <= 0 || n_features <= 0 || !gemm_fits(ctx, n_features, n_in)) return 0;
+  const GemmPlan plan = gemm_plan(n_features, n_in, n_rows, false, kMaxPartsBytes);
+  return gemm_parts_bytes(plan.rest, n_features, n_rows - plan.full);
+}
+
 void launch_qkv_project(const cc_ctx* ctx, const void* x, const void* w, int n_rows, int hidden,
-                        void* q, void* k, void* v, hipStream_t stream) {
+                        void* q, void* k, void* v, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const int d = ctx->cfg.head_dim;
   const int nq = ctx->cfg.n_q_heads * d, nk = ctx->cfg.n_kv_heads * d, n_cols = nq + 2 * nk;
-  if (ctx->cfg.dtype == CC_BF16 && ctx->impl != CC_IMPL_SCALAR && gemm_fits(n_cols, hidden) &&
-      nq % 32 == 0 && nk % 32 == 0) {
-    launch_gemm<kOutQkv>(stream, x, w, nullptr, n_rows, hidden, n_cols, GemmOut{q, k, v, nullptr, nq, nk, 0});
+  if (gemm_fits(ctx, n_cols, hidden) && nq % 32 == 0 && nk % 32 == 0) {
+    launch_gemm<kOutQkv>(stream, x, w, nullptr, n_rows, hidden, n_cols, GemmOut{q, k, v, nullptr, nq, nk, 0}, workspace, workspace_bytes);
     return;
   }
   dim3 grid((n_cols + 63) / 64, (n_rows + 63) / 64);
@@ -689,10 +822,10 @@ void launch_qkv_project(const cc_ctx* ctx, const void* x, const void* w, int n_r
 
 // y [n_rows][n_out] = x [n_rows][n_in] W^T (+ residual [n_rows][n_out]); W [n_out][n_in]
 void launch_linear(const cc_ctx* ctx, const void* x, const void* w, const void* residual, int n_rows, int n_in,
-                   int n_out, void* y, hipStream_t stream) {
+                   int n_out, void* y, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const bool bf = ctx->cfg.dtype == CC_BF16;
-  if (bf && ctx->impl != CC_IMPL_SCALAR && gemm_fits(n_out, n_in)) {
-    launch_gemm<kOutLinear>(stream, x, w, nullptr, n_rows, n_in, n_out, GemmOut{y, nullptr, nullptr, residual, 0, 0, n_out});
+  if (gemm_fits(ctx, n_out, n_in)) {
+    launch_gemm<kOutLinear>(stream, x, w, nullptr, n_rows, n_in, n_out, GemmOut{y, nullptr, nullptr, residual, 0, 0, n_out}, workspace, workspace_bytes);
     return;
   }
   dim3 grid((n_out + 63) / 64, (n_rows + 63) / 64);
@@ -710,8 +843,8 @@ void launch_linear(const cc_ctx* ctx, const void* x, const void* w, const void* 
 void launch_gated_linear(const cc_ctx* ctx, const void* x, const void* w_gate, const void* w_up, int n_rows,
                          int n_in, int n_ffn, void* y, hipStream_t stream) {
   const bool bf = ctx->cfg.dtype == CC_BF16;
-  if (bf && ctx->impl != CC_IMPL_SCALAR && gemm_fits(2 * n_ffn, n_in)) {
-    launch_gemm<kOutGated>(stream, x, w_gate, w_up, n_rows, n_in, 2 * n_ffn, GemmOut{y, nullptr, nullptr, nullptr, 0, 0, n_ffn});
+  if (gemm_fits(ctx, 2 * n_ffn, n_in)) {
+    launch_gemm<kOutGated>(stream, x, w_gate, w_up, n_rows, n_in, 2 * n_ffn, GemmOut{y, nullptr, nullptr, nullptr, 0, 0, n_ffn}, nullptr, 0);
     return;
   }
   dim3 grid((n_ffn + 63) / 64, (n_rows + 63) / 64);

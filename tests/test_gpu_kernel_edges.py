@@ -814,3 +814,42 @@ def test_selection_behind_wide_scores_of_eight_heads_per_kv_head(n, frac):
     own = scores[int(sg[W.SEG_TOK]): int(sg[W.SEG_TOK]) + n]
     assert (own == 0).sum() > n // 4 and (own > 0).sum() > n // 4
     assert np.array_equal(H.gpu_selection(w, b.sel_idx.cpu().numpy())[0][1], O.top_n(own, int(sg[W.SEG_NSEL])))
+
+
+@pytest.mark.parametrize("op,n_out,n_in,rows", [
+    ("linear", 64, 8192, 1), ("linear", 128, 5056, 17), ("linear", 256, 14336, 63), ("linear", 1024, 14336, 65),      # 64 x 64 and 64 x 128 tiles
+    ("linear", 4096, 14336, 129), ("linear", 2048, 28672, 257), ("linear", 4096, 8256, 513),     # 128 x 128 up to 256 x 256
+    ("linear", 8192, 14336, 2278),                               # whole rounds of the largest tile, the rest in parts
+    ("qkv", 6144, 8192, 16), ("qkv", 6144, 14336, 300)])
+def test_matrix_products_with_the_contraction_in_parts(op, n_out, n_in, rows):
+    # stages that do and do not divide over the parts, row blocks one row short and one over, tiles whose rows end early
+    import paper_2502_15734_amd as P
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    rnd = lambda *s, sc=1.0: (torch.randn(*s, device="cuda", generator=g) * sc).to(torch.bfloat16)
+    ctx = P.Context(32, 8, 128, 5.0e5, P.CC_BF16)
+    x, w, res = rnd(rows, n_in), rnd(n_out, n_in, sc=n_in ** -0.5), rnd(rows, n_out)
+    nbytes = ctx.qkv_project_workspace_bytes(rows, n_in) if op == "qkv" else ctx.linear_workspace_bytes(rows, n_in, n_out)
+    assert 0 < nbytes <= 256 << 20
+    room = torch.full((nbytes + 64,), 0xff, dtype=torch.uint8, device="cuda")        # (NaN in every place a part could leave out)
+    def product(workspace):
+        if op == "qkv":
+            got = [torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (4096, 1024, 1024)]
+            ctx.qkv_project(x, w, *got, workspace=workspace)
+            return torch.cat(got, dim=1).float()
+        y = res.clone()
+        ctx.linear(x, w, y, residual=y, workspace=workspace)                     # (the residual may be the output)
+        return y.float()
+    want = x.double() @ w.double().t() + (0 if op == "qkv" else res.double())
+    whole = product(torch.empty(0, dtype=torch.uint8, device="cuda"))            # no room: not split
+    # half a unit in the last place of bf16, and fp32 sums of n_in products of size n_in^-1/2
+    off = lambda got: float(((got - want).abs() - 2.0 ** -8 * want.abs()).max())
+    # the room asked for, half of it (fewer parts or none), what the call takes by itself
+    for workspace in (room[:nbytes], room[:nbytes // 32 * 16], None):
+        got = product(workspace)
+        assert off(got) <= 8 * n_in * 2.0 ** -24 * 4
+        # no further from 64 bits than the whole contraction (both are roundings of nearly the same sums)
+        assert float((got - want).norm()) <= 1.01 * float((whole - want).norm())
+    torch.cuda.synchronize()
+    assert bool((room[nbytes:] == 0xff).all())
+    with pytest.raises(P.CacheCraftError):
+        ctx.linear(x, w, res, workspace=room[8:])                                # not 16-byte aligned
