@@ -191,8 +191,10 @@ __device__ __forceinline__ void load_query_rows(uint4 (&raw)[8], const bf16_t* _
     raw[i] = *reinterpret_cast<const uint4*>(q + (static_cast<size_t>(r) * hq + h) * kD + (lane & 15) * 8);
   }
 }
-// ... and regrouped through 8 KiB of LDS of the wavefront's own: afterwards raw[k] holds dims 16k + 8 (lane / 32) .. + 7 of column
-// lane % 32 (pieces of a row are permuted by its number, so that neither side meets a bank conflict)
+// ... and regrouped through 8 KiB of LDS of the wavefront's own into operands of W = 32 or 16 columns: afterwards raw[k] holds dims
+// 16k + 8 (lane / 32) .. + 7 of column lane % 32, or dims 32 (k % 4) + 8 (lane / 16) .. + 7 of column 16 (k / 4) + lane % 16 (pieces
+// of a row are permuted by its number, so that neither side meets a bank conflict)
+template <int W = 32>
 __device__ __forceinline__ void regroup_query_rows(uint4 (&raw)[8], char* own, int lane) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -200,10 +202,11 @@ __device__ __forceinline__ void regroup_query_rows(uint4 (&raw)[8], char* own, i
     *reinterpret_cast<uint4*>(own + r * 256 + (((lane & 15) ^ (r & 15)) << 4)) = raw[i];
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (other lanes' pieces: an order the compiler does not see)
-  const int r = lane & 31;
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
-    raw[k] = *reinterpret_cast<const uint4*>(own + r * 256 + (((2 * k + (lane >> 5)) ^ (r & 15)) << 4));
+  for (int k = 0; k < 8; ++k) {
+    const int r = W == 32 ? lane & 31 : 16 * (k >> 2) + (lane & 15), piece = W == 32 ? 2 * k + (lane >> 5) : 4 * (k & 3) + (lane >> 4);
+    raw[k] = *reinterpret_cast<const uint4*>(own + r * 256 + ((piece ^ (r & 15)) << 4));
+  }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 // two bf16 pairs (x, y) packed in a word each, turned by the two angles of t

@@ -371,6 +371,27 @@ def test_scores_of_tokens_numbered_through_the_chunks_of_a_request(hq, lens, chu
     assert float(got["MFMA_NARROW"].max()) > 0.1
 
 
+@pytest.mark.parametrize("lens", [[7, 15], [16, 17], [33, 16, 15, 1], [64, 49, 80], [70, 130, 3]])
+def test_scores_of_the_wide_form_around_16_tokens_and_16_keys(lens):
+    # the form of large grids multiplies 16 tokens by 16 keys: last tokens, chunk boundaries and causal edges one short of
+    # such a block, on it and one behind it
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("halves", "bf16", 4, 1, 128, 5.0e5, lens, [7] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [0.2] * len(lens), 9)], 1.0, seed=29)
+    for gain in (1.0, 40.0):
+        got = []
+        for impl in (P.CC_IMPL_MFMA_WIDE, P.CC_IMPL_MFMA_NARROW):
+            b = DeviceBatch(w, impl=impl, poison=True)
+            b.q.mul_(gain)
+            b.rope_shift(); b.select(); torch.cuda.synchronize()
+            got.append(b.scores.cpu().double())
+        # (the bound of test_scores_in_two_key_streams)
+        assert torch.isfinite(got[0]).all()
+        assert float((got[0] - got[1]).abs().max()) <= (4 * math.sqrt(sum(lens)) * 2.0 ** -24 + 1e-6) * gain
+        assert float(got[1].max()) > 0.1
+
+
 @pytest.mark.parametrize("n_requests", [65536, 65537])
 def test_scores_behind_many_empty_requests(n_requests):
     # a list entry has 32 bits for request and row tile: 16 for the one and 16 for the other, 17 and 15
