@@ -89,6 +89,8 @@ constexpr int kBufs = 4;
 // 159 (1 of 10k), 160: 94 / 77 (1 of 3k), 65 / 61 (4 of 1.2k), 55.5 / 53.9 (4 of 1.2k, 8 heads); 192: 220 / 173 (1 of 10k), 99 / 82
 // (2 of 3k), 101 / 116 (4 of 3k), 224: 58 / 60 (2 of 1.2k), 61 / 67 (4 of 1.2k), 256: 232 / 197 (1 of 10k), 106 / 125 (4 of 3k).
 constexpr int kTwoStreamGrid = 160;
+// KS = 2: blocks of 32 keys per stream: K in five places, V in four
+constexpr int kHalf = 8192, kRingK = 5, kRingV = 4;
 #ifndef CC_RING_DEPTH
 #define CC_RING_DEPTH 8
 #endif
@@ -168,8 +170,9 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     const int32_t* __restrict__ snap_index, float* __restrict__ cum, int s_max,
     const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
   constexpr int TQ = KS == 1 ? 64 : 32;     // query rows per workgroup
-  // LDS: KS = 1: four images of K | V; KS = 2: per key stream three K images and two V images
-  __shared__ uint4 lds_all[KS == 1 ? kBufs * kImage : 5 * kImage];
+  // LDS: KS = 1: four images of K | V; KS = 2: per key stream a ring of five 32-key blocks of K and one of four of V, and what the streams
+  // tell each other at a segment's end
+  __shared__ uint4 lds_all[KS == 1 ? kBufs * kImage : 2 * (kRingK + kRingV) * (kHalf / 16) + 256];
   auto here = [&]() __attribute__((always_inline)) { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t & 63; };
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int n = lane & 31, hh = lane >> 5;
@@ -228,7 +231,8 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   // w_own: block of the page this wavefront brings in (-1: none); w_vown: where that page's values
   // are - the same block of v_pool, or (<= -2) block -2 - w_vown of v_shared while the value map
   // still points there (copy-on-write pending)
-  int w_kpos0, w_nvalid, w_seg, w_seg_next, w_own, w_vown, w_flags, w_pair = 0, w_seg_far = 0;
+  // (KS = 2: a wavefront brings half a page of every 32-key block: w_own and w_vown for a tile's first block, w_own1 and w_vown1 for its second)
+  int w_kpos0, w_nvalid, w_seg, w_seg_next, w_own, w_vown, w_own1 = 0, w_vown1 = 0, w_flags, w_pair = 0, w_seg_far = 0;
   auto fill_window = [&](int base) __attribute__((always_inline)) {
     const int jl = min(KS * (base + lane) + ks, n_all - 1);
     const TileDesc v = fetch_desc(tiles, j_begin + jl, max_tiles);
@@ -248,23 +252,34 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
         w_seg = tiles[je].seg; w_seg_next = tiles[jo].seg; w_seg_far = tiles[jf].seg;
       }
     }
-    w_own = whead == 0 ? b0 : whead == 1 ? b1 : whead == 2 ? b2 : b3;
-    w_vown = w_own;
-    if (v_map != nullptr && w_own >= 0) {
-      const int m = v_map[w_own];
-      if (m >= 0 && m < n_shared_blocks) w_vown = -2 - m;
+    auto values_of = [&](int own) __attribute__((always_inline)) {
+      int at = own;
+      if (v_map != nullptr && own >= 0) {
+        const int m = v_map[own];
+        if (m >= 0 && m < n_shared_blocks) at = -2 - m;
+      }
+      return at;
+    };
+    if constexpr (KS == 1) {
+      w_own = whead == 0 ? b0 : whead == 1 ? b1 : whead == 2 ? b2 : b3;
+    } else {
+      w_own = whead < 2 ? b0 : b1;
+      w_own1 = whead < 2 ? b2 : b3;
+      w_vown1 = values_of(w_own1);
     }
+    w_vown = values_of(w_own);
     const bool edge = v.nvalid < kTile || (b0 | b1 | b2 | b3) < 0;
     w_flags = (edge ? 3 : 0) | (w_seg_next != w_seg ? 4 : 0) | (KS == 2 && BY && w_seg_far != w_seg_next ? 8 : 0);
   };
   fill_window(0);
   load_query_rows(rows, q, src_row, hq, h, lane);
-  // byte offset of the K / V image of (local) tile t (KS = 1: one image, V behind K)
-  auto k_image = [&](int t) __attribute__((always_inline)) { return KS == 1 ? (t & (kBufs - 1)) * (kImage * 16) : ks * 49152 + (t % 3) * 16384; };
-  auto v_image = [&](int t) __attribute__((always_inline)) { return KS == 1 ? (t & (kBufs - 1)) * (kImage * 16) : 98304 + ks * 32768 + (t & 1) * 16384; };
+  // KS = 1: byte offset of the image of tile t, K in front of V.  KS = 2: offset of the 32-key block b of K or V
+  auto image = [&](int t) __attribute__((always_inline)) { return (t & (kBufs - 1)) * (kImage * 16); };
+  auto k_block = [&](int b) __attribute__((always_inline)) { return ks * (kRingK + kRingV) * kHalf + (b % kRingK) * kHalf; };
+  auto v_block = [&](int b) __attribute__((always_inline)) { return (ks * (kRingK + kRingV) + kRingK) * kHalf + (b % kRingV) * kHalf; };
   constexpr int kVPart = KS == 1 ? 16384 : 0;
-  // Loads of one tile, straight into image `img_off`: wavefront w brings page w % 4 - K and V if
-  // there are four wavefronts, else K (w < 4) or V.
+  // Loads straight into LDS.  KS = 1: wavefront w brings page w % 4 of a tile, K (w < 4) or V.  KS = 2: of a 32-key block of K and of V
+  // wavefront w brings half of page w / 2 % 2: eight rows of K, 64 dims of V.
   //   K: instruction (rg, kq) brings rows 8 rg .. 8 rg + 7 of the page (row r sits in token slot
   //      swap23(r)), 128 bytes each at dim 64 kq: lane L reads row 8 rg + L % 8, piece (L / 8) ^ rg
   //   V: lane (hh, n) reads slots 8hh.. of dim row 32 j + n
@@ -278,44 +293,53 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   const uint32_t v_voff = n * 32 + hh * 16;
   typedef __attribute__((address_space(3))) const uint4 lds_piece;
   const uint32_t lds_base = uniform(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_piece*)lds_all)));   // LDS byte address
-  const int page = whead;
-  const bool brings_k = KS == 2 || wave < 4, brings_v = KS == 2 || wave >= 4;
-  const uint32_t k_img = lds_base + ((page >> 1) * 8 + (page & 1) * 2) * 1024;   // this wavefront's first K group in image 0
-  const uint32_t v_img = lds_base + kVPart + 4 * page * 1024;                   // ... and its V page
+  const int page = KS == 1 ? whead : whead >> 1, part = whead & 1;              // (KS = 2: page of a 32-key block and half of it)
+  const bool brings_k = wave < 4;                                              // (KS = 1)
+  const uint32_t k_img = lds_base + (KS == 1 ? ((page >> 1) * 8 + (page & 1) * 2) * 1024 : (2 * page + part) * 1024);   // this wavefront's first K group in image 0
+  const uint32_t v_img = lds_base + kVPart + 4 * page * 1024 + (KS == 1 ? 0 : 2048 * part);                   // ... and its V page
   const char* k_src = nullptr;                                                // page of the tile being loaded (scalar)
   const char* v_src = nullptr;
   uint32_t k_dst = 0, v_dst = 0;
-  auto dma_begin = [&](int lk, int lv, int k_to, int v_to) __attribute__((always_inline)) {      // the tiles' lanes in the window, their images
-    const int own = __builtin_amdgcn_readlane(w_own, lk), vown = __builtin_amdgcn_readlane(w_vown, lv);
+  auto k_from = [&](int own, int to) __attribute__((always_inline)) {
     k_src = k_head + static_cast<size_t>(max(own, 0)) * blk_bytes;
+    k_dst = k_img + to;
+  };
+  auto v_from = [&](int vown, int to) __attribute__((always_inline)) {
     v_src = vown <= -2 ? v_head_shared + static_cast<size_t>(-2 - vown) * blk_bytes
                        : v_head + static_cast<size_t>(max(vown, 0)) * blk_bytes;
-    k_dst = k_img + k_to;
-    v_dst = v_img + v_to;
+    if (KS == 2) v_src += 2048 * part;
+    v_dst = v_img + to;
+  };
+  // KS = 1: the tile in lane l of the window, into image offset `to`
+  auto dma_begin = [&](int l, int to) __attribute__((always_inline)) {
+    k_from(__builtin_amdgcn_readlane(w_own, l), to);
+    v_from(__builtin_amdgcn_readlane(w_vown, l), to);
   };
   // (the two halves of a row are 4 KiB apart in the image and 128 bytes apart in memory; the two
   // row groups of a page are neighbours in the image)
   auto dma_k = [&](int j) __attribute__((always_inline)) {
-    if (!brings_k) return;
-    if (j == 0) dma_one<0>(k_voff0, k_src, k_dst);
-    else if (j == 1) dma_one<128>(k_voff0, k_src, k_dst + (4096 - 128));
-    else if (j == 2) dma_one<0>(k_voff1, k_src, k_dst + 1024);
-    else dma_one<128>(k_voff1, k_src, k_dst + 1024 + (4096 - 128));
+    if (KS == 1 && !brings_k) return;
+    const uint32_t voff = KS == 2 ? (part ? k_voff1 : k_voff0) : j < 2 ? k_voff0 : k_voff1;
+    if (j == 0) dma_one<0>(voff, k_src, k_dst);
+    else if (j == 1) dma_one<128>(voff, k_src, k_dst + (4096 - 128));
+    else if (j == 2) dma_one<0>(voff, k_src, k_dst + 1024);
+    else dma_one<128>(voff, k_src, k_dst + 1024 + (4096 - 128));
   };
   auto dma_v = [&](int half) __attribute__((always_inline)) {
-    if (!brings_v) return;
+    if (KS == 1 && brings_k) return;
     if (half == 0) dma_two<0, 1024>(v_voff, v_src, v_dst);
     else dma_two<2048, 3072>(v_voff, v_src, v_dst);
   };
-  // blank the padding slots of the V page this wavefront loaded (rare; after its loads have landed)
-  auto blank_padding = [&](int l, int img) __attribute__((always_inline)) {
-    const int nvalid = __builtin_amdgcn_readlane(w_nvalid, l), own = __builtin_amdgcn_readlane(w_own, l);
-    const int nv = own < 0 ? 0 : min(max(nvalid - kBlock * page, 0), kBlock);
-    if (brings_v && nv < kBlock) {
+  // blank the padding slots of the V page this wavefront loaded (rare; after its loads have landed).  l: the tile's lane of the window; KS = 2: second:
+  // its second 32-key block
+  auto blank_padding = [&](int l, int img, bool second) __attribute__((always_inline)) {
+    const int nvalid = __builtin_amdgcn_readlane(w_nvalid, l), own = __builtin_amdgcn_readlane(KS == 2 && second ? w_own1 : w_own, l);
+    const int nv = own < 0 ? 0 : min(max(nvalid - kBlock * (page + (KS == 2 && second ? 2 : 0)), 0), kBlock);
+    if ((KS == 2 || !brings_k) && nv < kBlock) {
       const int ln = here();
-      uint4* vp = reinterpret_cast<uint4*>(const_cast<char*>(lds_bytes) + img + kVPart + 4 * page * 1024 + ln * 16);
+      uint4* vp = reinterpret_cast<uint4*>(const_cast<char*>(lds_bytes) + img + kVPart + 4 * page * 1024 + (KS == 2 ? 2048 * part : 0) + ln * 16);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) vp[j * 64] = zero_pad_slots(vp[j * 64], ln >> 5, nv);
+      for (int j = 0; j < 4 / KS; ++j) vp[j * 64] = zero_pad_slots(vp[j * 64], ln >> 5, nv);
       // (a rare branch leaves nothing pending, so that the code behind the join waits for no more
       // than the straight path does)
       wait_lds<0>();
@@ -334,23 +358,35 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   };
 
   // ---- first tiles: on their way before anything about the rows is known ------------------------------
-  // (KS = 1: images 0, 1, image 2 when the queries are turned; KS = 2: K of the stream's tiles 0 and 1, V of tile 0.  Tiles no row sees are
-  // loaded in vain; past the request's last tile that tile is repeated.)
-  constexpr int kAheadK = KS == 1 ? 3 : 2, kAheadV = KS == 1 ? 3 : 1;
-  constexpr int kFirstV = KS == 1 ? 2 : 1;
+  // (KS = 1: images 0, 1, image 2 when the queries are turned; KS = 2: K blocks 0, 1, 2 and V block 0, the next two of each when the queries are
+  // turned.  Tiles no row sees are loaded in vain; past the request's last tile that tile is repeated.)
   const int n_av = (n_all - ks + KS - 1) / KS;                // tiles of the stream in the whole request
-  auto first_loads = [&](int t) __attribute__((always_inline)) {
-    const int l = max(min(t, n_av - 1), 0);
-    dma_begin(l, l, k_image(t), v_image(t));
+  auto first_lane = [&](int t) __attribute__((always_inline)) { return max(min(t, n_av - 1), 0); };
+  auto first_tile = [&](int t) __attribute__((always_inline)) {         // KS = 1
+    dma_begin(first_lane(t), image(t));
 #pragma unroll
     for (int j = 0; j < 4; ++j) dma_k(j);
-    if (t < kAheadV) {
-      dma_v(0);
-      dma_v(1);
-    }
+    dma_v(0);
+    dma_v(1);
   };
-  first_loads(0);
-  first_loads(1);
+  auto first_k = [&](int b, int l) __attribute__((always_inline)) {     // KS = 2: block b, of the tile in lane l of the window
+    k_from(__builtin_amdgcn_readlane(b & 1 ? w_own1 : w_own, l), k_block(b));
+    dma_k(0);
+    dma_k(1);
+  };
+  auto first_v = [&](int b, int l) __attribute__((always_inline)) {
+    v_from(__builtin_amdgcn_readlane(b & 1 ? w_vown1 : w_vown, l), v_block(b));
+    dma_v(0);
+  };
+  if constexpr (KS == 1) {
+    first_tile(0);
+    first_tile(1);
+  } else {
+    first_k(0, first_lane(0));
+    first_v(0, first_lane(0));
+    first_k(1, first_lane(0));
+    first_k(2, first_lane(1));
+  }
 
   // first and last position over all rows of the workgroup (every wavefront walks the same tiles)
   const int p_mine = uniform(wave_max_i(p));
@@ -390,15 +426,17 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   // The four heads share the angles (KS = 2: so do the two streams): a wavefront computes a quarter (an eighth) of them.
   auto load_queries = [&]() __attribute__((always_inline)) {
     char* lds_w = const_cast<char*>(lds_bytes);
-    // scratch: KS = 1: images 2 and 3; KS = 2: the streams' third K and second V images
-    regroup_query_rows(rows, lds_w + (KS == 1 ? 2 * (kImage * 16) + wave * 8192
-                                              : (whead < 2 ? k_image(2) + whead * 8192 : v_image(1) + (whead - 2) * 8192)), lane);
+    // scratch: KS = 1: images 2 and 3; KS = 2: the places of the streams' K block 4 and V blocks 1 to 3, for the angles those of K block 3 of both
+    regroup_query_rows(rows, lds_w + (KS == 1 ? 2 * (kImage * 16) + wave * 8192 : whead == 0 ? k_block(4) : v_block(whead)), lane);
     barrier();
-    float4* turns = reinterpret_cast<float4*>(lds_w + (KS == 1 ? 2 * (kImage * 16) + wgrp * 16384 : 2 * 16384)) + lane;
+    char* turns_at = lds_w + (KS == 1 ? 2 * (kImage * 16) + wgrp * 16384 : 3 * kHalf) + lane * 16;
+    auto turn_at = [&](int c) __attribute__((always_inline)) {
+      return reinterpret_cast<float4*>(turns_at + c * 1024 + (KS == 2 && c >= 8 ? (kRingK + kRingV - 1) * kHalf : 0));
+    };
 #pragma unroll
     for (int i = 0; i < 4 / KS; ++i) {             // (float4 number c: rotation pairs 16 (c / 4) + 8 hh + 2 (c % 4), + 1)
       const int c = KS == 1 ? 4 * whead + i : 2 * wave + i;
-      turns[c * 64] = query_turn(inv_freq, p, 16 * (c >> 2) + 2 * (c & 3), hh, c2);
+      *turn_at(c) = query_turn(inv_freq, p, 16 * (c >> 2) + 2 * (c & 3), hh, c2);
     }
     wait_lds<0>();
     barrier();
@@ -408,7 +446,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         uint32_t x = xv[i], y = yv[i];
-        turn_words(x, y, turns[(kk * 4 + i) * 64]);
+        turn_words(x, y, *turn_at(kk * 4 + i));
         xv[i] = x;
         yv[i] = y;
       }
@@ -436,28 +474,29 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   }
 
   // ---- operand ring ---------------------------------------------------------------------------
-  // Steps of one iteration (tile t, image img; nimg = image of tile t+1):
-  //    0.. 7  K pieces of block 1 of img        (S of the tile's second block)
-  //    8..15  V pieces of pages 0, 1 of img     (PV of the first block)
-  //   16..23  K pieces of block 0 of nimg       (S of the next tile's first block)
-  //   24..31  V pieces of pages 2, 3 of img     (PV of the second block)
+  // Steps of one iteration (tile t):
+  //    0.. 7  K pieces of the tile's second block      (S of that block)
+  //    8..15  V pieces of the first block              (PV of the first block)
+  //   16..23  K pieces of the next tile's first block  (S of that block)
+  //   24..31  V pieces of the second block             (PV of the second block)
   //   32..39  = steps 0..7 of the next iteration
-  // (behind the last tile the "next image" holds stale keys: that S block is masked as a whole)
+  // (behind the last tile the "next tile" is stale keys: that S block is masked as a whole)
   // Reads are issued two at a time behind every odd step (into the slots of the two pieces just
   // used), and one wait in front of every even step covers that step and the next.
   u32x4 ring[kDepth];
-  auto k_piece = [&](int img, int b, int kk) __attribute__((always_inline)) {
-    return *reinterpret_cast<const u32x4*>(lds_bytes + img + k_rd + b * 8192 + (kk >> 2) * 4096 + (kk & 3) * 256);
+  struct Blocks { int k1, v0, k0_next, v1, k1_next; };      // where these blocks are
+  auto k_piece = [&](int at, int kk) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(lds_bytes + at + k_rd + (kk >> 2) * 4096 + (kk & 3) * 256);
   };
-  auto v_piece = [&](int img, int j) __attribute__((always_inline)) {      // j = page * 4 + dim group
-    return *reinterpret_cast<const u32x4*>(lds_bytes + img + v_rd + j * 1024);
+  auto v_piece = [&](int at, int j) __attribute__((always_inline)) {      // j = page of the block * 4 + dim group
+    return *reinterpret_cast<const u32x4*>(lds_bytes + at + v_rd + j * 1024);
   };
-  auto issue = [&](int kimg, int vimg, int knext, int s) __attribute__((always_inline)) {   // s: compile-time
-    if (s < 8) ring[s % kDepth] = k_piece(kimg, 1, s);
-    else if (s < 16) ring[s % kDepth] = v_piece(vimg, s - 8);
-    else if (s < 24) ring[s % kDepth] = k_piece(knext, 0, s - 16);
-    else if (s < 32) ring[s % kDepth] = v_piece(vimg, s - 16);
-    else ring[s % kDepth] = k_piece(knext, 1, s - 32);
+  auto issue = [&](const Blocks& at, int s) __attribute__((always_inline)) {   // s: compile-time
+    if (s < 8) ring[s % kDepth] = k_piece(at.k1, s);
+    else if (s < 16) ring[s % kDepth] = v_piece(at.v0, s - 8);
+    else if (s < 24) ring[s % kDepth] = k_piece(at.k0_next, s - 16);
+    else if (s < 32) ring[s % kDepth] = v_piece(at.v1, s - 24);
+    else ring[s % kDepth] = k_piece(at.k1_next, s - 32);
   };
 
   // one exponential: element i (0..15) of block parity bp.  An even element first packs the pair
@@ -469,7 +508,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     else exp_behind_pack(pk[bp][(i - 2) >> 3][((i - 2) & 7) >> 1], lsum, ev, vodd, s);
   };
   // S block into parity bp from the ring; side(kk) runs after each MFMA
-  auto s_slot = [&](int kimg, int vimg, int knext, int s0, int bp, auto&& side) __attribute__((always_inline)) {
+  auto s_slot = [&](const Blocks& at, int s0, int bp, auto&& side) __attribute__((always_inline)) {
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       if ((kk & 1) == 0) wait_lds<kDepth - 2>();
@@ -477,8 +516,8 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
         if (kk == 0) mfma_s_first(sacc[bp], ring[(s0 + kk) % kDepth], qreg[kk], cinit);
         else mfma_s_acc(sacc[bp], ring[(s0 + kk) % kDepth], qreg[kk]);
         if ((kk & 1)) {
-          issue(kimg, vimg, knext, s0 + kk - 1 + kDepth);
-          issue(kimg, vimg, knext, s0 + kk + kDepth);
+          issue(at, s0 + kk - 1 + kDepth);
+          issue(at, s0 + kk + kDepth);
         }
         side(kk);
         __builtin_amdgcn_sched_barrier(0);
@@ -486,7 +525,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     }
   };
   // PV of block parity bp: step st = (u, db): 16-key half u (page), 32-dim group db
-  auto pv_slot = [&](int kimg, int vimg, int knext, int s0, int bp, auto&& side) __attribute__((always_inline)) {
+  auto pv_slot = [&](const Blocks& at, int s0, int bp, auto&& side) __attribute__((always_inline)) {
 #pragma unroll
     for (int st = 0; st < 8; ++st) {
       const int u = st >> 2, db = st & 3;
@@ -495,8 +534,8 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
         const u32x4 pw = {pk[bp][u][0], pk[bp][u][1], pk[bp][u][2], pk[bp][u][3]};
         mfma_o_acc(o[db], ring[(s0 + st) % kDepth], pw);
         if ((st & 1)) {
-          issue(kimg, vimg, knext, s0 + st - 1 + kDepth);
-          issue(kimg, vimg, knext, s0 + st + kDepth);
+          issue(at, s0 + st - 1 + kDepth);
+          issue(at, s0 + st + kDepth);
         }
         side(st);
         __builtin_amdgcn_sched_barrier(0);
@@ -527,19 +566,26 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   load_queries();
   wait_loads(std::integral_constant<int, 0>{});
 #pragma unroll
-  for (int t = 0; t < kFirstV; ++t) {
-    const int l = max(min(t, n_av - 1), 0);
-    if (__builtin_amdgcn_readlane(w_flags, l) & 2) blank_padding(l, v_image(t));
+  for (int t = 0; t < (KS == 1 ? 2 : 1); ++t) {
+    const int l = first_lane(t);
+    if (__builtin_amdgcn_readlane(w_flags, l) & 2) blank_padding(l, KS == 1 ? image(t) : v_block(0), false);
   }
   __syncthreads();
-  if (KS == 1) first_loads(2);
+  if constexpr (KS == 1) {
+    first_tile(2);
+  } else {
+    first_k(3, lane_of(1));
+    first_v(1, lane_of(0));
+    first_k(4, lane_of(2));
+    first_v(2, lane_of(1));        // (values that are multiplied are those whose padding is blanked: of the last tile that is seen, not of one behind it)
+  }
   int f_cur = __builtin_amdgcn_readlane(w_flags, lane_of(0));      // flags of tile t, t+1 (carried from tile to tile)
   int f_next = __builtin_amdgcn_readlane(w_flags, lane_of(1));
   {
-    const int kimg = k_image(0);
+    const Blocks at{KS == 1 ? image(0) + kHalf : k_block(1), 0, 0, 0, 0};
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      const u32x4 a = k_piece(kimg, 0, kk);
+      const u32x4 a = k_piece(KS == 1 ? image(0) : k_block(0), kk);
       {
         if (kk == 0) mfma_s_zero(sacc[0], a, qreg[kk]);
         else mfma_s_acc(sacc[0], a, qreg[kk]);
@@ -565,7 +611,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     for (int i = 1; i < 8; ++i)
 exp_step(0, i);
 #pragma unroll
-    for (int s = 0; s < kDepth; ++s) issue(kimg, v_image(0), kimg, s);     // steps 0..kDepth-1 of iteration 0
+    for (int s = 0; s < kDepth; ++s) issue(at, s);     // steps 0..kDepth-1 of iteration 0
     __builtin_amdgcn_sched_barrier(0);
   }
 
@@ -586,7 +632,7 @@ exp_step(0, i);
   // (segments without tokens have no tile: the value also stands for those between this tile's
   // segment and the next tile's; the row sum is taken with the pair that is still to be packed)
   // KS = 2: the even stream writes what a segment that ends with its tile leaves, the odd one likewise; each needs the
-  // other's sum up to there, through the K image of tile t (free behind slot 1; rare as this is, it pays two
+  // other's sum up to there, through LDS (rare as this is, it pays two
   // barriers).  prev: the odd stream's sum one tile ago.
   float prev = 0.f;
   auto running = [&]() __attribute__((always_inline)) {
@@ -600,8 +646,7 @@ exp_step(0, i);
     float m_all = m_ref;
     bool writes = true;
     if constexpr (KS == 2) {
-      float4* meet = reinterpret_cast<float4*>(lds_all) + whead * 32 + (ln & 31);      // (the even stream's K image of tile t)
-      meet = reinterpret_cast<float4*>(reinterpret_cast<char*>(meet) + (t % 3) * 16384);
+      float4* meet = reinterpret_cast<float4*>(lds_all) + 2 * (kRingK + kRingV) * (kHalf / 16) + whead * 32 + (ln & 31);
       barrier();
       if (ln < 32) meet[ks * 128] = make_float4(m_ref, tot, prev, 0.f);
       wait_lds<0>();
@@ -631,43 +676,68 @@ exp_step(0, i);
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));      // vmcnt(0) here, so the hot path never waits for it
     }
   };
-  // what the next iteration reads must be whole: KS = 1: image t+2 (loads started one iteration ago);
-  // KS = 2: K of tile t+2 and V of tile t+1, started in this iteration
+  // KS = 1: what the next iteration reads must be whole, image t+2 (loads started one iteration ago)
   auto end_tile = [&](int t) __attribute__((always_inline)) {
-    wait_loads(std::integral_constant<int, KS == 1 ? 4 : 0>{});
-    if (KS == 1) {
-      if (f_far & 2) blank_padding(lane_of(t + 2), v_image(t + 2));
-    } else {
-      if (f_next & 2) blank_padding(lane_of(t + 1), v_image(t + 1));
-    }
+    wait_loads(std::integral_constant<int, 4>{});
+    if (f_far & 2) blank_padding(lane_of(t + 2), image(t + 2), false);
     barrier();
     f_cur = f_next; f_next = f_far;
+  };
+  // KS = 2: half-step s (S(s + 1), PV(s)) reads V block s and K block s + 2, which must be whole; K block s + 5 and V block s + 3 are
+  // started in it, into the places it found free.  Of the loads of the last two half-steps all eight may be out.
+  auto end_half = [&](int t, bool pads, int b) __attribute__((always_inline)) {
+    wait_loads(std::integral_constant<int, 8>{});
+    if (pads) blank_padding(lane_of(t), v_block(b), b & 1);
+    barrier();
+  };
+  int k_at = 2 * kHalf;          // KS = 2: place of K block 2 t + 2 in its ring
+  auto k_place = [&](int blocks) __attribute__((always_inline)) {         // ... of the block so many behind it
+    const int to = k_at + blocks * kHalf;
+    return to >= kRingK * kHalf ? to - kRingK * kHalf : to;
   };
   int t = 0;
   // (Where the loop lies in the lines of the instruction cache shows: 70B on 8 requests of 10k tokens 1527 us with what is
   // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20.  The form with the by-product is no faster for it.)
   if constexpr (KS == 1 && !BY) asm volatile(".p2align 6");
   for (; t < n_mine; ++t) {
-    const int kimg = k_image(t), vimg = v_image(t), knext = k_image(t + 1);
+    Blocks at;
+    if constexpr (KS == 1) at = Blocks{0, image(t), image(t + 1), image(t) + kHalf, image(t + 1) + kHalf};
+    else at = Blocks{0, v_block(2 * t), k_block(0) + k_at, v_block(2 * t + 1), k_block(0) + k_place(1)};
     move_window(t);
     // slot 1: S of the tile's second block; second half of the first block's exponentials.
     // Underneath: the loads of the tiles ahead (past the last tile they repeat the last tile into an
     // image nobody reads), one instruction group per k-step.
-    s_slot(kimg, vimg, knext, 0, 1, [&](int kk) __attribute__((always_inline)) {
+    s_slot(at, 0, 1, [&](int kk) __attribute__((always_inline)) {
       exp_step(0, 8 + kk);
       if (kk == 0) {
         f_far = __builtin_amdgcn_readlane(w_flags, lane_of(t + 2));
-        dma_begin(lane_of(t + kAheadK), lane_of(t + kAheadV), k_image(t + kAheadK), v_image(t + kAheadV));
+        if constexpr (KS == 1) {
+          dma_begin(lane_of(t + 3), image(t + 3));
+        } else {
+          k_from(__builtin_amdgcn_readlane(w_own1, lane_of(t + 2)), k_block(0) + k_place(3));
+          v_from(__builtin_amdgcn_readlane(w_vown1, lane_of(t + 1)), v_block(2 * t + 3));
+        }
       }
-      if (kk >= 1 && kk <= 4) dma_k(kk - 1);
-      if (kk == 5) dma_v(0);
-      if (kk == 6) dma_v(1);
+      if (kk >= 1 && kk <= 4 / KS) dma_k(kk - 1);
+      if (kk == (KS == 1 ? 5 : 3)) dma_v(0);
+      if (KS == 1 && kk == 6) dma_v(1);
     });
     if ((f_cur & 1) || (KS == 2 && t >= n_loc)) mask_tile(1, 1, t);
     // slot 2: PV of the first block; first half of the second block's exponentials
-    pv_slot(kimg, vimg, knext, 8, 0, [&](int st) __attribute__((always_inline)) { exp_step(1, st); });
+    pv_slot(at, 8, 0, [&](int st) __attribute__((always_inline)) { exp_step(1, st); });
+    if constexpr (KS == 2) end_half(t, f_cur & 2, 2 * t + 1);
     // slot 3: S of the next tile's first block; second half of the second block's exponentials
-    s_slot(kimg, vimg, knext, 16, 0, [&](int kk) __attribute__((always_inline)) { exp_step(1, 8 + kk); });
+    s_slot(at, 16, 0, [&](int kk) __attribute__((always_inline)) {
+      exp_step(1, 8 + kk);
+      if constexpr (KS == 2) {
+        if (kk == 0) {
+          k_from(__builtin_amdgcn_readlane(w_own, lane_of(t + 3)), k_block(0) + k_place(4));
+          v_from(__builtin_amdgcn_readlane(w_vown, lane_of(t + 2)), v_block(2 * t));
+        }
+        if (kk == 1 || kk == 2) dma_k(kk - 1);
+        if (kk == 3) dma_v(0);
+      }
+    });
     if constexpr (BY && KS == 1) {
       if (f_cur & 4) snapshot(t, running(), 0);       // tile t was the last of its segment
     } else if constexpr (BY) {                     // (both streams decide alike: one of the two tiles was)
@@ -678,8 +748,14 @@ exp_step(0, i);
     }
     if ((f_next & 1) || t + 1 >= (KS == 1 ? n_mine : n_loc)) mask_tile(0, 0, t + 1);
     // slot 4: PV of the second block; first half of the next block's exponentials
-    pv_slot(kimg, vimg, knext, 24, 1, [&](int st) __attribute__((always_inline)) { exp_step(0, st); });
-    end_tile(t);
+    pv_slot(at, 24, 1, [&](int st) __attribute__((always_inline)) { exp_step(0, st); });
+    if constexpr (KS == 1) {
+      end_tile(t);
+    } else {
+      end_half(t + 1, f_next & 2, 2 * t + 2);
+      f_cur = f_next; f_next = f_far;
+      k_at = k_place(2);
+    }
   }
   // KS = 1: tiles that only the workgroup's other rows see: this wavefront brings in its share of the tiles ahead and
   // leaves the matrix pipe to the other half
@@ -687,7 +763,7 @@ exp_step(0, i);
     for (; t < n_it; ++t) {
       move_window(t);
       f_far = __builtin_amdgcn_readlane(w_flags, lane_of(t + 2));
-      dma_begin(lane_of(t + kAheadK), lane_of(t + kAheadV), k_image(t + kAheadK), v_image(t + kAheadV));
+      dma_begin(lane_of(t + 3), image(t + 3));
 #pragma unroll
       for (int j = 0; j < 4; ++j) dma_k(j);
       dma_v(0);
