@@ -347,21 +347,58 @@ void launch_self_weight(const cc_ctx* ctx, const void* q, const int32_t* src_row
 #undef CC_LAUNCH
 }
 
+// number of the pair (t, s = 0) in the matrix's list; tl: t's number in request r
+__device__ __forceinline__ int pair_index(const int32_t* req_seg_off, int r, int tl) {
+  int base = 0;
+  for (int r2 = 0; r2 < r; ++r2) {
+    const int n2 = req_seg_off[r2 + 1] - req_seg_off[r2];
+    base += n2 * (n2 + 1) / 2;
+  }
+  return base + tl * (tl + 1) / 2;
+}
+// what pair_mass_from_cum_kernel leaves to be added up: sums [t][n][s]
+struct PairParts {
+  const float* sums = nullptr;
+  int n = 0, s_max = 0, n_pairs = 0;
+  const int32_t* req_seg_off = nullptr;
+  float* mass = nullptr;
+};
 __global__ __launch_bounds__(256) void self_sum_kernel(
     const int32_t* __restrict__ q_pos, const int32_t* __restrict__ cu_q, const cc_segment* __restrict__ segs,
-    int n_requests, int hq, const float* __restrict__ row_self, float* __restrict__ self_mass) {
+    int n_requests, int hq, const float* __restrict__ row_self, float* __restrict__ self_mass, PairParts pairs) {
   const int s = blockIdx.x;
   const cc_segment sg = segs[s];
   float acc = 0.f;
   if (sg.req >= 0 && sg.req < n_requests) {
     const int j0 = cu_q[sg.req], n = cu_q[sg.req + 1] - j0;
-    for (int u = threadIdx.x; u < n; u += 256) {
-      const int pos = q_pos[j0 + u];
-      if (pos >= sg.logical_start && pos < sg.logical_start + sg.n_tokens) acc += row_self[j0 + u];
+    constexpr int kAhead = 8;                               // (rows whose loads are in flight together; one by one 11 us for requests of 5k rows, now 8 with the pairs)
+    for (int u0 = threadIdx.x; u0 < n; u0 += 256 * kAhead) {
+      int pos[kAhead];
+      float v[kAhead];
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e) {
+        const int u = min(u0 + 256 * e, n - 1);
+        pos[e] = q_pos[j0 + u];
+        v[e] = row_self[j0 + u];
+      }
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e)
+        if (u0 + 256 * e < n && pos[e] >= sg.logical_start && pos[e] < sg.logical_start + sg.n_tokens) acc += v[e];
     }
   }
   const float tot = block_sum_256(acc);
   if (threadIdx.x == 0) self_mass[s] = tot / static_cast<float>(hq);
+  if (pairs.sums != nullptr && sg.req >= 0 && sg.req < n_requests) {      // (t = s: the sums of pair_mass_from_cum_kernel's parts, in their order)
+    const int tl = s - pairs.req_seg_off[sg.req];
+    if (tl >= pairs.s_max) return;
+    const int at = pair_index(pairs.req_seg_off, sg.req, tl);
+    for (int sl = threadIdx.x; sl <= tl && at + sl < pairs.n_pairs; sl += 256) {
+      float v = 0.f;
+#pragma unroll 8
+      for (int p = 0; p < pairs.n; ++p) v += pairs.sums[(static_cast<size_t>(s) * pairs.n + p) * pairs.s_max + sl];
+      pairs.mass[at + sl] = v / static_cast<float>(hq);
+    }
+  }
 }
 
 // ---- question rows of the batch, numbered request after request ("snap rows") ------------------------
@@ -430,7 +467,7 @@ __global__ __launch_bounds__(256) void snap_fill_kernel(
 // head, the request's keys in prompt order with a running maximum, lane i owning rotation pair
 // (i, i + d/2).  (Slow, and meant to be: it only ever runs for rows whose logits overflowed.)
 template <typename T, int D>
-__global__ __launch_bounds__(64) void cum_scalar_kernel(
+__global__ __launch_bounds__(256) void cum_scalar_kernel(
     const T* __restrict__ q, const int32_t* __restrict__ src_rows, const int32_t* __restrict__ q_pos,
     const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ snap_base, int n_requests, const int32_t* __restrict__ snap_rows,
@@ -438,7 +475,7 @@ __global__ __launch_bounds__(64) void cum_scalar_kernel(
     const T* __restrict__ k_pool, int n_blocks, const int32_t* __restrict__ block_tab,
     const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     InvFreq inv_freq, float* __restrict__ cum, int s_max) {
-  const int u = blockIdx.x, lane = threadIdx.x;
+  const int u = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;      // (a wavefront per row, no barriers)
   if (u >= snap_base[n_requests]) return;
   // (no maps: every list row is a snap row, snap_base is cu_q itself)
   const int j = snap_rows != nullptr ? snap_rows[u] : u;
@@ -510,50 +547,62 @@ __global__ __launch_bounds__(256) void seg_mass_from_cum_kernel(
   if (threadIdx.x == 0) seg_mass[s] = tot / static_cast<float>(hq);
 }
 
-// pair_mass from the cumulative log-sum-exps of EVERY row (snap row = list row): workgroup t sums,
-// over the rows of segment t (they sit at [sel_off, sel_off + n_select) of the list, as cc_select
-// lays them out) and all heads, the weight on each segment s <= t of the same request:
-// exp(cum_s - lse) - exp(cum_{s-1} - lse) for s < t, and what is left for s = t.
+// pair_mass from the cumulative log-sum-exps of EVERY row (snap row = list row): the weight of the rows of segment t (they
+// sit at [sel_off, sel_off + n_select) of the list, as cc_select lays them out), over all heads, on each segment s <= t of the same
+// request: exp(cum_s - lse) - exp(cum_{s-1} - lse) for s < t, and what is left for s = t.
+// Workgroup (t, part) takes a part of t's rows and all their s: a thread keeps one s and walks the (row, head) pairs, so that neighbours read
+// neighbouring floats and cum goes through once, in wavefronts that fill the chip.  (A workgroup per t and s read every line of cum once per s:
+// 20k rows of 32 heads and 10 segments, 28 MB, 47 us; this 14, most of it the latency of three rounds of loads; 8 parts 34.)  parts: sums [t][part][s], which self_sum_kernel adds up; null: one part, the result.
+constexpr int kPairParts = 32;
 __global__ __launch_bounds__(256) void pair_mass_from_cum_kernel(
     const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int n_requests, int n_q_tot,
     int hq, const float* __restrict__ cum, int s_max, const float* __restrict__ lse,
-    float* __restrict__ pair_mass, int n_pairs) {
-  const int t = blockIdx.x, sl = blockIdx.y;               // (row segment, key segment's index in the request)
+    float* __restrict__ pair_mass, int n_pairs, float* __restrict__ parts) {
+  __shared__ float sums[256];
+  const int t = blockIdx.x, part = blockIdx.y, tid = threadIdx.x;
   const cc_segment sg = segs[t];
   const int r = sg.req;
   if (r < 0 || r >= n_requests) return;
   const int tl = t - req_seg_off[r];
-  if (sl > tl) return;
-  int pair_base = 0;
-  for (int r2 = 0; r2 < r; ++r2) {
-    const int n2 = req_seg_off[r2 + 1] - req_seg_off[r2];
-    pair_base += n2 * (n2 + 1) / 2;
-  }
+  if (tl >= s_max) return;                                 // (its masses stay 0)
   const int row0 = max(sg.sel_off, 0), n_rows = max(min(sg.n_select, n_q_tot - row0), 0);
-  float acc = 0.f;
-  if (tl < s_max) {
-    // (loads of eight terms in flight, summed in the order of the terms: one after the other 81 us for 20k rows of 32 heads, 49 now)
-    constexpr int kAhead = 8;
-    const int n = n_rows * hq;
-    for (int i0 = threadIdx.x; i0 < n; i0 += 256 * kAhead) {
-      float total[kAhead], upto[kAhead], before[kAhead];
+  const int first = static_cast<int>(static_cast<int64_t>(n_rows) * part / gridDim.y) * hq;
+  const int end = static_cast<int>(static_cast<int64_t>(n_rows) * (part + 1) / gridDim.y) * hq;
+  const float* c0 = cum + static_cast<size_t>(row0) * hq * s_max;
+  const float* l0 = lse + static_cast<size_t>(row0) * hq;
+  for (int s0 = 0; s0 <= tl; s0 += 256) {
+    const int w = min(256, tl + 1 - s0), per = 256 / w, sl = s0 + tid % w, mine = tid / w;      // pairs that are walked side by side
+    float acc = 0.f;
+    if (mine < per) {
+      constexpr int kAhead = 8;
+      for (int i0 = first + mine; i0 < end; i0 += per * kAhead) {
+        float total[kAhead], upto[kAhead], before[kAhead];
 #pragma unroll
-      for (int e = 0; e < kAhead; ++e) {
-        const int i = min(i0 + 256 * e, n - 1), u = row0 + i / hq, h = i % hq;
-        const float* c = cum + (static_cast<size_t>(u) * hq + h) * s_max;
-        total[e] = lse[static_cast<size_t>(u) * hq + h];
-        upto[e] = c[sl];
-        before[e] = c[max(sl - 1, 0)];
+        for (int e = 0; e < kAhead; ++e) {
+          const int i = min(i0 + per * e, end - 1);
+          const float* c = c0 + static_cast<size_t>(i) * s_max;
+          total[e] = l0[i];
+          upto[e] = c[sl];
+          before[e] = c[max(sl - 1, 0)];
+        }
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e)
+          if (i0 + per * e < end)
+            acc += (sl < tl ? __expf(upto[e] - total[e]) : 1.f) - (sl > 0 ? __expf(before[e] - total[e]) : 0.f);
       }
-#pragma unroll
-      for (int e = 0; e < kAhead; ++e)
-        if (i0 + 256 * e < n)
-          acc += (sl < tl ? __expf(upto[e] - total[e]) : 1.f) - (sl > 0 ? __expf(before[e] - total[e]) : 0.f);
+    }
+    __syncthreads();                                       // (the sums before have been read)
+    sums[tid] = acc;
+    for (int o = 128; o > 0; o >>= 1) {
+      __syncthreads();
+      if (mine < o && mine + o < per) sums[tid] += sums[tid + o * w];
+    }
+    if (mine == 0) {
+      const int pi = pair_index(req_seg_off, r, tl) + sl;
+      if (parts != nullptr) parts[(static_cast<size_t>(t) * gridDim.y + part) * s_max + sl] = sums[tid];
+      else if (pi < n_pairs) pair_mass[pi] = sums[tid] / static_cast<float>(hq);
     }
   }
-  const float tot = block_sum_256(acc);
-  const int pi = pair_base + tl * (tl + 1) / 2 + sl;
-  if (threadIdx.x == 0 && pi < n_pairs) pair_mass[pi] = tot / static_cast<float>(hq);
 }
 
 // seg_mass[s] = the entry of the pair matrix whose rows are the request's question segment
@@ -610,6 +659,16 @@ struct ListBuffers {
 };
 
 }  // namespace
+
+// -infinity for every entry of cum, 16 bytes per thread (20k rows of 32 heads, 11 segments: 10.8 -> 6.8 us); the array has room for whole pieces
+static __global__ __launch_bounds__(256) void no_key_yet_kernel(float4* __restrict__ p, size_t n) {
+  const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i < n) p[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+}
+static void launch_no_key_yet(float* cum, size_t n, hipStream_t stream) {
+  const size_t pieces = (n + 3) / 4;
+  hipLaunchKernelGGL(no_key_yet_kernel, dim3(static_cast<unsigned>((pieces + 255) / 256)), dim3(256), 0, stream, reinterpret_cast<float4*>(cum), pieces);
+}
 
 void launch_fill_zero(float* p, int n, hipStream_t stream) {
   if (n > 0) hipLaunchKernelGGL(fill_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p, static_cast<size_t>(n), 0.f);
@@ -711,7 +770,7 @@ void launch_chunk_attention(const cc_ctx* ctx, const void* q, const int32_t* src
   if (self_mass != nullptr) {
     launch_self_weight(ctx, q, src_rows, q_pos, slot_map, k_pool, n_blocks, n_q_tot, lse, b.row_self, stream);
     hipLaunchKernelGGL(self_sum_kernel, dim3(n_segs), dim3(256), 0, stream, q_pos, cu_q, segs, n_requests, hq,
-                       b.row_self, self_mass);
+                       b.row_self, self_mass, PairParts{});
   }
 }
 
@@ -765,8 +824,7 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
                        snap_base, snap_index, snap_rows, snap_req);
     // (a segment without tokens, or before the first tile, keeps "no key yet")
     const size_t n_cum = cap * hq * s_max;
-    hipLaunchKernelGGL(fill_kernel, dim3(static_cast<unsigned>((n_cum + 255) / 256)), dim3(256), 0, stream, cum, n_cum,
-                       -INFINITY);
+    launch_no_key_yet(cum, n_cum, stream);
     launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                      n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs, &scatter);
   } else {
@@ -779,7 +837,7 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
     const bool bf = ctx->cfg.dtype == CC_BF16;
     const int d = ctx->cfg.head_dim;
 #define CC_LAUNCH(T, D)                                                                                  \
-  hipLaunchKernelGGL((cum_scalar_kernel<T, D>), dim3(static_cast<unsigned>(cap)), dim3(64), 0, stream, \
+  hipLaunchKernelGGL((cum_scalar_kernel<T, D>), dim3(static_cast<unsigned>((cap + 3) / 4)), dim3(256), 0, stream, \
                      static_cast<const T*>(q), src_rows, q_pos, cu_q, snap_base, n_requests, snap_rows, snap_req,   \
                      by.redo, static_cast<const T*>(k_pool), n_blocks, block_tab, segs, req_seg_off, hq,  \
                      hkv, ctx->inv_freq, cum, s_max)
@@ -829,8 +887,7 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
   const bool mfma = ctx->impl != CC_IMPL_SCALAR && attn_mfma_supported(ctx);
   AttnByProduct by{nullptr, cum, s_max, false, nullptr};          // no index: every row is a snap row
   if (mfma) {
-    hipLaunchKernelGGL(fill_kernel, dim3(static_cast<unsigned>((n_cum + 255) / 256)), dim3(256), 0, stream, cum, n_cum,
-                       -INFINITY);
+    launch_no_key_yet(cum, n_cum, stream);
     launch_attn_mfma(ctx, q, q_pos, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks, block_tab, segs,
                      n_segs, req_seg_off, n_requests, out, lse, plan_ws, max_tiles, src_rows, 0, stream, &by, vs, &scatter);
   } else {
@@ -842,7 +899,7 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
   const int d = ctx->cfg.head_dim;
   if (by.wide) {
 #define CC_LAUNCH(T, D)                                                                                       \
-  hipLaunchKernelGGL((cum_scalar_kernel<T, D>), dim3(static_cast<unsigned>(n_q_tot)), dim3(64), 0, stream,     \
+  hipLaunchKernelGGL((cum_scalar_kernel<T, D>), dim3(static_cast<unsigned>((n_q_tot + 3) / 4)), dim3(256), 0, stream, \
                      static_cast<const T*>(q), src_rows, q_pos, cu_q, cu_q, n_requests, static_cast<const int32_t*>(nullptr), \
                      static_cast<const int32_t*>(nullptr), by.redo, static_cast<const T*>(k_pool), n_blocks,   \
                      block_tab, segs, req_seg_off, hq, hkv, ctx->inv_freq, cum, s_max)
@@ -851,12 +908,16 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
     else if (!bf && d == 128) CC_LAUNCH(float, 128);
     else CC_LAUNCH(float, 64);
 #undef CC_LAUNCH
-    hipLaunchKernelGGL(pair_mass_from_cum_kernel, dim3(n_segs, s_max), dim3(256), 0, stream, segs, req_seg_off, n_requests,
-                       n_q_tot, hq, cum, s_max, lse, pair_mass, n_pairs);
+    // (parts in what the pass of its own would have used)
+    const size_t room = segment_mass_bytes(ctx, n_segs, max_tiles, max_q_per_req, n_q_tot) / (static_cast<size_t>(n_segs) * s_max * sizeof(float));
+    const int n_parts = self_mass == nullptr ? 1 : static_cast<int>(std::min<size_t>(std::max<size_t>(room, 1), kPairParts));
+    float* parts = n_parts > 1 ? static_cast<float*>(fallback_ws) : nullptr;
+    hipLaunchKernelGGL(pair_mass_from_cum_kernel, dim3(n_segs, n_parts), dim3(256), 0, stream, segs, req_seg_off, n_requests,
+                       n_q_tot, hq, cum, s_max, lse, pair_mass, n_pairs, parts);
     if (self_mass != nullptr) {
       launch_self_weight(ctx, q, src_rows, q_pos, slot_map, k_pool, n_blocks, n_q_tot, lse, row_self, stream);
       hipLaunchKernelGGL(self_sum_kernel, dim3(n_segs), dim3(256), 0, stream, q_pos, cu_q, segs, n_requests, hq,
-                         row_self, self_mass);
+                         row_self, self_mass, PairParts{parts, n_parts, s_max, n_pairs, req_seg_off, pair_mass});
     }
   } else {
     launch_chunk_attention(ctx, q, src_rows, q_pos, slot_map, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks,

@@ -874,3 +874,30 @@ def test_matrix_products_with_the_contraction_in_parts(op, n_out, n_in, rows):
     assert bool((room[nbytes:] == 0xff).all())
     with pytest.raises(P.CacheCraftError):
         ctx.linear(x, w, res, workspace=room[8:])                                # not 16-byte aligned
+
+
+@pytest.mark.parametrize("lens,question,n_requests", [([5], 40, 1), ([64, 0, 1, 130], 3, 2), ([2] * 254, 1, 1), ([1] * 255, 2, 1), ([3] * 300, 5, 1),
+                                                      ([700], 90, 3)])
+def test_pair_masses_of_few_and_of_many_segments(lens, question, n_requests):
+    # the masses are summed a segment's rows in parts, threads side by side along the key segments: a segment with one key segment, segments without
+    # tokens, 255 to 301 of them (a workgroup has 256 threads), fewer rows than parts, more
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    k = len(lens)
+    w = W.custom("pairs", "bf16", 8, 2, 128, 5.0e5, lens * n_requests, [0] * (k * n_requests),
+                 [W.RequestSpec(list(range(k * r, k * r + k)), [1.0] * k, question) for r in range(n_requests)], 1.0, seed=59)
+    b = DeviceBatch(w, poison=True)
+    b.rope_shift(); b.select(); b.gather()
+    pair, own, off = b.sparse_prefill_pairs()
+    pair, own = pair.double().cpu(), own.double().cpu()
+    pair2, own2, _ = b.chunk_attention()                     # by passes of its own over the segments
+    torch.cuda.synchronize()
+    # the weights of a row sum to 1: 8 heads' terms of up to (k + 1) segments in fp32
+    for r in range(n_requests):
+        for t in range(k + 1):
+            rows = question if t == k else lens[t]
+            at = int(off[r]) + t * (t + 1) // 2
+            assert abs(float(pair[at:at + t + 1].sum()) - rows) <= 2.0 ** -20 * max(rows, 1) * (t + 2)
+    # (both from products of the same bf16 queries and keys; the log-sum-exps, of up to 10, are fp32 and enter as exp: 2^-20 of a row each)
+    rows_of = torch.tensor([float(question if t == k else lens[t]) for _ in range(n_requests) for t in range(k + 1) for _ in range(t + 1)])
+    assert bool(((pair - pair2.double().cpu()).abs() <= 2.0 ** -9 * pair2.double().cpu() + 2.0 ** -17 * (rows_of + 1)).all())
+    assert torch.equal(own, own2.double().cpu()) or float((own - own2.double().cpu()).abs().max()) <= 2.0 ** -9 * (question + max(lens, default=0))
