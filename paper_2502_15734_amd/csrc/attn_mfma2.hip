@@ -166,7 +166,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     const bf16_t* __restrict__ k_pool, const bf16_t* __restrict__ v_pool,
     const TileDesc* __restrict__ tiles, int max_tiles, const WorkItem* __restrict__ items, const int32_t* __restrict__ order, int tile_bits,
     const int32_t* __restrict__ req_seg_off, int hq, int hkv, int n_sub, int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
-    int32_t* __restrict__ redo, const int32_t* __restrict__ q_map, int map_pos,
+    int32_t* __restrict__ redo, int redo_any, const int32_t* __restrict__ q_map, int map_pos,
     const int32_t* __restrict__ snap_index, float* __restrict__ cum, int s_max,
     const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
   constexpr int TQ = KS == 1 ? 64 : 32;     // query rows per workgroup
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
     req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> tile_bits));
     tile = uniform(e & ((1u << tile_bits) - 1));
   } else {
-    req = uniform(order[blockIdx.y]);
+    req = gridDim.y == 1 ? 0 : uniform(order[blockIdx.y]);      // (one load less on the way to the first tile)
     tile = n_tiles_x - 1 - blockIdx.x / per_tile;
   }
   const WorkItem item = items[req];
@@ -838,7 +838,7 @@ exp_step(0, i);
   }
   // rows whose sums left the safe range are redone by the kernel that can move its reference
   const bool give_up = __any(overflow);
-  if (give_up && ln == 0) redo[redo_index(q_first + (tile * TQ / 64) * 64)] = 1;
+  if (give_up && ln == 0) redo[redo_index(q_first + (tile * TQ / 64) * 64)] = redo[redo_any] = 1;
   // The output tile goes through LDS so that a store instruction writes whole 256-byte rows of a head instead
   // of 8-byte pieces of 32 rows: row en of a head at 256 en, its 16-byte piece c at c ^ (en % 16).
   if (KS == 2) __syncthreads();                              // (both streams have taken what they need)
@@ -934,7 +934,7 @@ void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,
                        static_cast<const bf16_t*>(q), q_pos, static_cast<const bf16_t*>(k_pool),               \
                        static_cast<const bf16_t*>(v_pool), pl.tiles, pl.max_tiles, pl.items, pl.order, list.tile_bits, \
                        req_seg_off, ctx->cfg.n_q_heads, hkv, n_sub, n_tiles, ctx->inv_freq,                    \
-                       static_cast<bf16_t*>(out), lse, redo, q_map, map_pos, snap_index, cum, s_max,           \
+                       static_cast<bf16_t*>(out), lse, redo, pl.redo_any, q_map, map_pos, snap_index, cum, s_max, \
                        static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks,                            \
                        static_cast<const int32_t*>(vs.v_map));                                                 \
   } while (0)

@@ -115,6 +115,7 @@ struct AttnByProduct {
   int s_max;
   mutable bool wide;
   mutable const int32_t* redo;
+  mutable int redo_any = 0;
 };
 void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const int32_t* cu_q,
                       int n_q_tot, int max_q_per_req, const void* k_pool, const void* v_pool,

@@ -471,11 +471,12 @@ __global__ __launch_bounds__(256) void cum_scalar_kernel(
     const T* __restrict__ q, const int32_t* __restrict__ src_rows, const int32_t* __restrict__ q_pos,
     const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ snap_base, int n_requests, const int32_t* __restrict__ snap_rows,
-    const int32_t* __restrict__ snap_req, const int32_t* __restrict__ redo,
+    const int32_t* __restrict__ snap_req, const int32_t* __restrict__ redo, int redo_any,
     const T* __restrict__ k_pool, int n_blocks, const int32_t* __restrict__ block_tab,
     const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     InvFreq inv_freq, float* __restrict__ cum, int s_max) {
   const int u = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;      // (a wavefront per row, no barriers)
+  if (redo != nullptr && redo[redo_any] == 0) return;
   if (u >= snap_base[n_requests]) return;
   // (no maps: every list row is a snap row, snap_base is cu_q itself)
   const int j = snap_rows != nullptr ? snap_rows[u] : u;
@@ -839,7 +840,7 @@ void launch_prefill_mass(const cc_ctx* ctx, const void* q, const int32_t* src_ro
 #define CC_LAUNCH(T, D)                                                                                  \
   hipLaunchKernelGGL((cum_scalar_kernel<T, D>), dim3(static_cast<unsigned>((cap + 3) / 4)), dim3(256), 0, stream, \
                      static_cast<const T*>(q), src_rows, q_pos, cu_q, snap_base, n_requests, snap_rows, snap_req,   \
-                     by.redo, static_cast<const T*>(k_pool), n_blocks, block_tab, segs, req_seg_off, hq,  \
+                     by.redo, by.redo_any, static_cast<const T*>(k_pool), n_blocks, block_tab, segs, req_seg_off, hq,  \
                      hkv, ctx->inv_freq, cum, s_max)
     if (bf && d == 128) CC_LAUNCH(bf16_t, 128);
     else if (bf && d == 64) CC_LAUNCH(bf16_t, 64);
@@ -901,7 +902,7 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
 #define CC_LAUNCH(T, D)                                                                                       \
   hipLaunchKernelGGL((cum_scalar_kernel<T, D>), dim3(static_cast<unsigned>((n_q_tot + 3) / 4)), dim3(256), 0, stream, \
                      static_cast<const T*>(q), src_rows, q_pos, cu_q, cu_q, n_requests, static_cast<const int32_t*>(nullptr), \
-                     static_cast<const int32_t*>(nullptr), by.redo, static_cast<const T*>(k_pool), n_blocks,   \
+                     static_cast<const int32_t*>(nullptr), by.redo, by.redo_any, static_cast<const T*>(k_pool), n_blocks,   \
                      block_tab, segs, req_seg_off, hq, hkv, ctx->inv_freq, cum, s_max)
     if (bf && d == 128) CC_LAUNCH(bf16_t, 128);
     else if (bf && d == 64) CC_LAUNCH(bf16_t, 64);

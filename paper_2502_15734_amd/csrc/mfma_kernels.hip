@@ -90,7 +90,7 @@ __device__ __forceinline__ void sparse_qk(
     const TileDesc* __restrict__ tiles, const int32_t* __restrict__ seg_tile_off, int max_tiles,
     const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
-    float* __restrict__ mass, const int32_t* __restrict__ redo, const int32_t* __restrict__ q_map,
+    float* __restrict__ mass, const int32_t* __restrict__ redo, int redo_any, const int32_t* __restrict__ q_map,
     int map_pos, const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
   constexpr int NT = 64 * G;
   constexpr int TQ = 32 * QB;                       // query tokens per workgroup
@@ -102,6 +102,9 @@ __device__ __forceinline__ void sparse_qk(
   // attention: double-buffered.  score: three images, because the previous tile's image must stay
   // readable (repair path of its deferred block) while the next tile is being stored.
   constexpr int kBufs = SCORE ? 3 : 2;
+  if constexpr (REDO) {
+    if (redo[redo_any] == 0) return;                  // (normally: one load, and nothing that hangs on it)
+  }
   __shared__ uint4 lds_all[kBufs * kImage];
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int n = lane & 31, hh = lane >> 5;
@@ -115,7 +118,7 @@ __device__ __forceinline__ void sparse_qk(
     if constexpr (SCORE) {
       const int t0 = t * TQ;
       if (sg_own.kind != CC_SEG_CHUNK || t0 >= sg_own.n_tokens || sg_own.logical_start == 0) return false;
-      return (redo[(sg_own.tok_off + t0) >> 6] | redo[(sg_own.tok_off + t0 + TQ - 1) >> 6]) != 0;
+      return (redo[(sg_own.tok_off + t0) >> 6] | redo[(sg_own.tok_off + min(t0 + TQ, sg_own.n_tokens) - 1) >> 6]) != 0;
     } else {
       if (q_first + t * TQ >= q_end) return false;
       return redo[redo_index(q_first + (t * TQ / 64) * 64)] != 0;
@@ -540,10 +543,10 @@ __global__ __launch_bounds__(64 * G, 2) void sparse_qk_kernel(
     const TileDesc* __restrict__ tiles, const int32_t* __restrict__ seg_tile_off, int max_tiles,
     const int32_t* __restrict__ order, const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int hq, int hkv,
     int n_tiles_x, InvFreq inv_freq, bf16_t* __restrict__ out, float* __restrict__ lse,
-    float* __restrict__ mass, const int32_t* __restrict__ redo, const int32_t* __restrict__ q_map,
+    float* __restrict__ mass, const int32_t* __restrict__ redo, int redo_any, const int32_t* __restrict__ q_map,
     int map_pos, const bf16_t* __restrict__ v_shared, int n_shared_blocks, const int32_t* __restrict__ v_map) {
-  // segment (score; heaviest first) or request (attention; longest context first)
-  sparse_qk<G, SCORE, QB, REDO>(order[blockIdx.y], q, q_pos, cu_q, k_pool, v_pool, n_blocks, tiles, seg_tile_off, max_tiles, segs, req_seg_off, hq, hkv, n_tiles_x, inv_freq, out, lse, mass, redo, q_map, map_pos, v_shared, n_shared_blocks, v_map);
+  // segment (score; heaviest first) or request (attention; longest context first; second pass: any order)
+  sparse_qk<G, SCORE, QB, REDO>(REDO ? static_cast<int>(blockIdx.y) : order[blockIdx.y], q, q_pos, cu_q, k_pool, v_pool, n_blocks, tiles, seg_tile_off, max_tiles, segs, req_seg_off, hq, hkv, n_tiles_x, inv_freq, out, lse, mass, redo, redo_any, q_map, map_pos, v_shared, n_shared_blocks, v_map);
 }
 
 // Behind the wide score kernel: a segment's workgroup redoes its flagged tokens (normally none) and then selects.  (As
@@ -553,11 +556,11 @@ __global__ __launch_bounds__(64 * G, 2) void redo_topn_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_pool, int n_blocks, const TileDesc* __restrict__ tiles,
     const int32_t* __restrict__ seg_tile_off, int max_tiles, const cc_segment* __restrict__ segs,
     const int32_t* __restrict__ req_seg_off, int hq, int hkv, int n_tiles_x, InvFreq inv_freq, float* mass,
-    const int32_t* __restrict__ redo, const int32_t* __restrict__ block_tab, int32_t* __restrict__ sel_idx,
+    const int32_t* __restrict__ redo, int redo_any, const int32_t* __restrict__ block_tab, int32_t* __restrict__ sel_idx,
     int32_t* __restrict__ q_row, int32_t* __restrict__ q_pos, int32_t* __restrict__ slot_map, float* __restrict__ scores,
     uint32_t* key_buf) {
   sparse_qk<G, true, QB, true>(blockIdx.x, q, nullptr, nullptr, k_pool, nullptr, n_blocks, tiles, seg_tile_off, max_tiles, segs,
-                               req_seg_off, hq, hkv, n_tiles_x, inv_freq, nullptr, nullptr, mass, redo, nullptr, 0, nullptr, 0,
+                               req_seg_off, hq, hkv, n_tiles_x, inv_freq, nullptr, nullptr, mass, redo, redo_any, nullptr, 0, nullptr, 0,
                                nullptr);
   __syncthreads();                                    // (what it wrote is read by the other wavefronts)
   topn_block<G>(blockIdx.x, mass, hq, false, block_tab, segs, sel_idx, q_row, q_pos, slot_map, scores, key_buf);
@@ -948,7 +951,7 @@ void launch_attn_g(const cc_ctx* ctx, const void* q, const int32_t* q_pos, const
 #define CC_KARGS static_cast<const bf16_t*>(q), q_pos, cu_q, static_cast<const bf16_t*>(k_pool),                 \
                  static_cast<const bf16_t*>(v_pool), n_blocks, pl.tiles, pl.seg_tile_off, pl.max_tiles,         \
                  pl.order, segs, req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq,                  \
-                 static_cast<bf16_t*>(out), lse, static_cast<float*>(nullptr), redo, q_map, map_pos,            \
+                 static_cast<bf16_t*>(out), lse, static_cast<float*>(nullptr), redo, pl.redo_any, q_map, map_pos, \
                  static_cast<const bf16_t*>(vs.v_shared), vs.n_shared_blocks, static_cast<const int32_t*>(vs.v_map)
   if (redo != nullptr)
     hipLaunchKernelGGL((sparse_qk_kernel<G, false, kAttnQB, true>), dim3(1, n_requests), dim3(64 * G), 0, stream, CC_KARGS);
@@ -968,7 +971,7 @@ void launch_select_g(const cc_ctx* ctx, const void* q, const void* k_pool, int n
     if (redo != nullptr) {
       hipLaunchKernelGGL((redo_topn_kernel<G, kScoreQB>), dim3(topn.n_segs), dim3(64 * G), 0, stream, static_cast<const bf16_t*>(q),
                          static_cast<const bf16_t*>(k_pool), n_blocks, pl.tiles, pl.seg_tile_off, pl.max_tiles, topn.segs,
-                         req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq, mass, redo, topn.block_tab, topn.sel_idx,
+                         req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq, mass, redo, pl.redo_any, topn.block_tab, topn.sel_idx,
                          topn.q_row, topn.q_pos, topn.slot_map, topn.scores, topn.key_buf);
       return;
     }
@@ -978,7 +981,7 @@ void launch_select_g(const cc_ctx* ctx, const void* q, const void* k_pool, int n
                      static_cast<const int32_t*>(nullptr), static_cast<const bf16_t*>(k_pool),
                      static_cast<const bf16_t*>(nullptr), n_blocks, pl.tiles, pl.seg_tile_off, pl.max_tiles,
                      pl.order, topn.segs, req_seg_off, ctx->cfg.n_q_heads, hkv, n_tiles, ctx->inv_freq,
-                     static_cast<bf16_t*>(nullptr), static_cast<float*>(nullptr), mass, redo,
+                     static_cast<bf16_t*>(nullptr), static_cast<float*>(nullptr), mass, redo, pl.redo_any,
                      static_cast<const int32_t*>(nullptr), 0, static_cast<const bf16_t*>(nullptr), 0,
                      static_cast<const int32_t*>(nullptr));
   launch_topn(ctx, mass, topn, false, stream);
@@ -1014,6 +1017,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
   pl.items = reinterpret_cast<WorkItem*>(static_cast<char*>(ws) + plan_ints_bytes(n_segs));
   pl.tiles = reinterpret_cast<TileDesc*>(static_cast<char*>(ws) + plan_head_bytes(n_segs));
   pl.max_tiles = max_tiles;
+  pl.redo_any = n_redo - 1;
   pl.redo = n_redo > 0 ? reinterpret_cast<int32_t*>(pl.tiles + max_tiles) : nullptr;
   const bool listed = list.kind != WorkList::kNone;
   const int n_items = by_request ? n_requests : n_segs, n_fill = (max_tiles + 255) / 256;
@@ -1112,6 +1116,7 @@ void launch_attn_mfma(const cc_ctx* ctx, const void* q, const int32_t* q_pos, co
   if (by != nullptr) {
     by->wide = wide;
     by->redo = pl.redo;
+    by->redo_any = pl.redo_any;
   }
   const int32_t* redo = pl.redo;
 #define CC_ARGS ctx, q, q_pos, cu_q, max_q_per_req, k_pool, v_pool, n_blocks, pl, segs, req_seg_off, n_requests, out, lse, redo, q_map, map_pos, stream, vs

@@ -266,7 +266,7 @@ inline int list_tile_bits(int n_requests) {
   return bits;
 }
 inline bool list_can_name(int n_requests, int row_tiles) { return row_tiles <= static_cast<int64_t>(1) << list_tile_bits(n_requests); }
-struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; };
+struct Plan { int32_t* seg_tile_off; int32_t* order; WorkItem* items; tile::TileDesc* tiles; int max_tiles; int32_t* redo; int redo_any; };      // redo[redo_any]: whether any flag is set
 size_t plan_head_bytes(int n_segs);
 // by_request: dispatch order over requests (attention; cu_q delimits their rows), else over segments (score; none where a list is made).
 // list: the list of workgroups to build beside it.  scatter: a scatter to run beside it (attention), or null.
@@ -280,6 +280,7 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
 // move its reference.  q0 is the first row of the 64-row tile (the request's first row + 64 k);
 // two tiles of different requests may share an entry, which only costs a spurious redo.
 __host__ __device__ inline int redo_index(int q0) { return q0 >> 5; }
+// (the last entry is no row's: it says whether any flag is set, so that a second pass with nothing to do reads one word and leaves)
 inline size_t redo_entries(int n_q_tot) { return static_cast<size_t>(n_q_tot) / 32 + 2; }
 
 void launch_attn_v2(const cc_ctx* ctx, const void* q, const int32_t* q_pos,

@@ -150,8 +150,8 @@ template <int kQB, int KS>
 __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_pool,
     const TileDesc* __restrict__ tiles, int max_tiles, int tile_bits, const cc_segment* __restrict__ segs,
-    const int32_t* __restrict__ req_seg_off, const int32_t* __restrict__ seg_tile_off, int hq, int hkv, int n_sub,
-    InvFreq inv_freq, float* __restrict__ mass, int32_t* __restrict__ redo) {
+    int n_requests, const int32_t* __restrict__ req_seg_off, const int32_t* __restrict__ seg_tile_off, int hq, int hkv, int n_sub,
+    InvFreq inv_freq, float* __restrict__ mass, int32_t* __restrict__ redo, int redo_any) {
   constexpr int kTQ = 32 * kQB;               // tokens per workgroup
   // 16 columns where the chip is held by its power budget, 32 where a workgroup waits for its own instructions (half as many MFMAs to
   // issue: the loop of an 8B request of 2.6 k tokens 23.0 us, 24.0 with 16 columns)
@@ -169,9 +169,20 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
 
   // ---- which tokens ---------------------------------------------------------------------------
   const int e = tiles[entry].work, n_list = tiles[max_tiles - 1].work;
+  int seg_begin, seg_end;
+  if (n_requests == 1) {                      // (a load that need not wait for the list's)
+    seg_begin = req_seg_off[0];
+    seg_end = req_seg_off[1];
+  } else {
+    if (entry >= uniform(n_list)) return;     // (what is behind the list names no request)
+    const int req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> tile_bits));
+    seg_begin = req_seg_off[req];
+    seg_end = req_seg_off[req + 1];
+  }
+  seg_begin = uniform(seg_begin);
+  seg_end = uniform(seg_end);
   if (entry >= uniform(n_list)) return;
-  const int req = uniform(static_cast<int>(static_cast<uint32_t>(e) >> tile_bits)), u0 = uniform(e & ((1u << tile_bits) - 1)) * kTQ;
-  const int seg_begin = uniform(req_seg_off[req]), seg_end = uniform(req_seg_off[req + 1]);
+  const int u0 = uniform(e & ((1u << tile_bits) - 1)) * kTQ;
   const int j_begin = uniform(seg_tile_off[seg_begin]);
   // The scored tokens of the request are numbered through; this workgroup has u0 .. u0 + kTQ - 1.  A lane looks at one
   // segment; those that hold tokens of the workgroup (mostly one or two) are then walked.  Columns past the last
@@ -498,7 +509,7 @@ __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
     if (u0 + u >= u_end || g != 0) continue;
     const int at = tokens[u].y;
     const float t = lt[i / kTG][i % kTG], p = lp[i / kTG][i % kTG];
-    if (give_up) redo[at >> 6] = 1;
+    if (give_up) redo[at >> 6] = redo[redo_any] = 1;
     else mass[static_cast<size_t>(at) * hq + h] = p / (p + t);
   }
 }
@@ -519,8 +530,8 @@ void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const
   const int entries = std::min(n_tok / rows + n_requests, pl.max_tiles - 1);
 #define CC_LAUNCH(...)                                                                                        \
   hipLaunchKernelGGL((score_v2_kernel<__VA_ARGS__>), dim3(per_tile * entries), dim3(small ? 512 : 256), 0, stream, static_cast<const bf16_t*>(q), \
-                     static_cast<const bf16_t*>(k_pool), pl.tiles, pl.max_tiles, list.tile_bits, segs, req_seg_off, pl.seg_tile_off,  \
-                     ctx->cfg.n_q_heads, hkv, n_sub, ctx->inv_freq, mass, redo)
+                     static_cast<const bf16_t*>(k_pool), pl.tiles, pl.max_tiles, list.tile_bits, segs, n_requests, req_seg_off, pl.seg_tile_off,  \
+                     ctx->cfg.n_q_heads, hkv, n_sub, ctx->inv_freq, mass, redo, pl.redo_any)
   if (small) CC_LAUNCH(kSmallQB, 2);
   else CC_LAUNCH(kBigQB, 1);
 #undef CC_LAUNCH

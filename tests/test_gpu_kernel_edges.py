@@ -901,3 +901,35 @@ def test_pair_masses_of_few_and_of_many_segments(lens, question, n_requests):
     rows_of = torch.tensor([float(question if t == k else lens[t]) for _ in range(n_requests) for t in range(k + 1) for _ in range(t + 1)])
     assert bool(((pair - pair2.double().cpu()).abs() <= 2.0 ** -9 * pair2.double().cpu() + 2.0 ** -17 * (rows_of + 1)).all())
     assert torch.equal(own, own2.double().cpu()) or float((own - own2.double().cpu()).abs().max()) <= 2.0 ** -9 * (question + max(lens, default=0))
+
+
+@pytest.mark.parametrize("impl", ["AUTO", "MFMA_WIDE"])
+@pytest.mark.parametrize("which,question", [(0, 32), (2, 32), (2, 31), (2, 1)])
+def test_one_request_of_a_batch_leaves_the_safe_range(impl, which, question):
+    # the second passes leave at once unless some row or token was flagged: only the first or only the last request's are, and the
+    # list's last row is the last of a flag's 32, the first, in between
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("one", "bf16", 8, 2, 128, 5.0e5, [64, 96] * 3, [0] * 6, [W.RequestSpec([2 * r, 2 * r + 1], [1.0, 1.0], question) for r in range(3)],
+                 1.0 / math.sqrt(128), seed=29)
+    w.q[:, :, 60:64] = 2.0
+    w.q[:, :, 124:128] = 0.0
+    blocks = w.store_tab[w.store_tab_off[2 * which]: w.store_tab_off[2 * which + 1]]
+    first = which * (64 + 96 + question)
+    for t in range(64):                                      # (logits around -100, as above)
+        for keys, at in ((w.k_store, (blocks[t // 16], slice(None), t % 16)), (w.k_new, (first + t, slice(None)))):
+            keys[at + (slice(60, 64),)] = -141.0
+            keys[at + (slice(124, 128),)] = 0.0
+    got = []
+    for form in ("MFMA_NARROW", impl):
+        b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + form), poison=True)
+        b.step(); torch.cuda.synchronize()
+        n = w.n_q_tot
+        got.append((b.out[:n].double(), b.lse[:n].double(), b.scores.double(), b.q_pos[:n].cpu()))
+    assert torch.equal(got[0][3], got[1][3])                 # (everything is recomputed: the same rows)
+    assert bool(torch.isfinite(got[1][0]).all()) and bool(torch.isfinite(got[1][1]).all())
+    assert float((got[1][0] - got[0][0]).norm() / got[0][0].norm()) <= H.TOL["bf16"]
+    rows = torch.arange(w.n_q_tot) // (64 + 96 + question)
+    alone = (rows == which) & (got[0][3] < 64)               # rows that see such keys only: half a unit in the last place of four of them
+    assert bool(((got[1][1] - got[0][1]).abs().cpu() <= torch.where(alone[:, None], 0.8, 2e-3)).all())
+    assert float((got[1][2] - got[0][2]).abs().max()) <= 5e-5
