@@ -32,11 +32,11 @@
 // sum leaves the safe range are flagged and redone by the kernel that can move its reference
 // (see the launcher).
 //
-// Staging: tile images in LDS (KS = 1: four of K and V; KS = 2: three of K and two of V per key stream), filled by
+// Staging: tile images in LDS (KS = 1: four of K and V; KS = 2: per key stream rings of five 32-key blocks of K and four of V), filled by
 // loads that write LDS directly (global_load_lds, 16
 // bytes per lane: lane L of an instruction fills piece base + L, so the image layout is chosen by
 // the global address each lane is given).  KS = 1: wavefronts 0-3 bring the four K pages (16 tokens) of a tile,
-// 4-7 the four V pages; KS = 2: the four wavefronts of a key stream bring a K and a V page each of their own
+// 4-7 the four V pages; KS = 2: the four wavefronts of a key stream bring half a page of K and of V each of every block of their own
 // tiles.  A page is four instructions whose addresses are one scalar base + one per-lane constant + an
 // immediate: no vector arithmetic per tile.  Image of a tile (16-byte pieces):
 //   K piece (MFMA row m of 32-key block b, k-step kk, half hh):
@@ -47,9 +47,11 @@
 // An MFMA operand read takes contiguous runs of 128 bytes that alternate between the two halves
 // of the 256-byte bank sweep (K) or one contiguous KiB (V): no bank conflicts.  In iteration t the wavefronts
 // read image t and (for S of the next tile's first block) image t+1.  KS = 1: they start the loads of image t+3
-// and, before the iteration's barrier, wait for their loads of image t+2; KS = 2: they
-// start the loads of K of tile t+2 and of V of tile t+1, into the images they left in the last iteration, and wait for
-// them at the iteration's end.  One s_barrier per tile.
+// and, before the iteration's barrier, wait for their loads of image t+2, one s_barrier per tile.  KS = 2: in half an iteration (one block) they
+// start the loads of K five blocks and of V three blocks ahead, into the places the half before left, and at its end wait for what
+// they started two halves ago; a barrier per half.  (Whole tiles, three images of K and two of V, had their loads half a tile ahead
+// and waited for them: one request of 449 rows in a decoder layer 317 -> 306 us, 70B with 230 rows 592 -> 570.  With all its keys in the
+// L2 a pair of tiles takes as long, 1.55 us on 120 workgroups, 1.2 of it the two wavefronts' MFMAs and exponentials.)
 // Block padding: K padding never reaches a product (its S entries are masked by selection); V
 // padding would, as 0 x garbage, so the wavefront that loaded a V page blanks the page's padding
 // slots in LDS before the barrier, in a branch only a segment's last tile takes.
@@ -697,8 +699,10 @@ exp_step(0, i);
   };
   int t = 0;
   // (Where the loop lies in the lines of the instruction cache shows: 70B on 8 requests of 10k tokens 1527 us with what is
-  // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20.  The form with the by-product is no faster for it.)
+  // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20; the layer of the 8B batch of 32 with the by-product 2040 at the line's beginning,
+  // 2053 28 bytes behind it, 2058 with 44 and no better with 20 or 52.  There 20 bytes of moves lie between this and the loop.)
   if constexpr (KS == 1 && !BY) asm volatile(".p2align 6");
+  if constexpr (KS == 1 && BY) asm volatile(".p2align 6\n\t.fill 11, 4, 0xbf800000");      // (11 s_nop)
   for (; t < n_mine; ++t) {
     Blocks at;
     if constexpr (KS == 1) at = Blocks{0, image(t), image(t + 1), image(t) + kHalf, image(t + 1) + kHalf};

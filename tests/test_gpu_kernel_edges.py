@@ -933,3 +933,28 @@ def test_one_request_of_a_batch_leaves_the_safe_range(impl, which, question):
     alone = (rows == which) & (got[0][3] < 64)               # rows that see such keys only: half a unit in the last place of four of them
     assert bool(((got[1][1] - got[0][1]).abs().cpu() <= torch.where(alone[:, None], 0.8, 2e-3)).all())
     assert float((got[1][2] - got[0][2]).abs().max()) <= 5e-5
+
+
+@pytest.mark.parametrize("n", [1, 32, 33, 64, 97, 129, 192, 257, 320, 385, 449, 512, 609, 641, 705, 833])
+def test_two_key_streams_of_few_blocks(n):
+    # the streams' rings hold five 32-key blocks of K and four of V: less than that, as much, more, an odd tile, a last tile of one block or a part
+    # of one; the by-product has its segments' ends in either stream
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    lens = [n // 3, n - n // 3]
+    w = W.custom("rings", "bf16", 4, 1, 128, 5.0e5, lens, [0, 0], [W.RequestSpec([0, 1], [0.1, 0.05], 2)], 1.0, seed=n)
+    b = DeviceBatch(w, poison=True)
+    b.rope_shift(); b.select(); b.gather(); b.sparse_prefill(); torch.cuda.synchronize()
+    sel = tuple(t.cpu().numpy()[: w.n_q_tot] for t in (b.sel_idx, b.q_row, b.q_pos, b.slot_map))
+    s = DeviceBatch(w, impl=P.CC_IMPL_SCALAR, poison=True)
+    s.rope_shift(); s.set_selection(*sel); s.gather(); s.sparse_prefill(); torch.cuda.synchronize()
+    k = w.n_q_tot
+    out, ref = b.out[:k].double(), s.out[:k].double()
+    assert float((out - ref).norm() / ref.norm()) <= H.TOL["bf16"]
+    # (bounds as above: six roundings of the query in a row that sees a single key)
+    assert float((b.lse[:k] - s.lse[:k]).abs().max()) <= 6 * 2.0 ** -9 / 3.0 ** 0.5
+    out1, lse1 = b.out[:k].clone(), b.lse[:k].clone()
+    mass, want = b.sparse_prefill_mass(), s.sparse_prefill_mass()
+    torch.cuda.synchronize()
+    assert torch.equal(out1, b.out[:k]) and torch.equal(lse1, b.lse[:k])
+    assert float((mass - want).abs().max()) <= 2.0 ** -7          # (two question rows; their logits within 6.8e-3, see above)
