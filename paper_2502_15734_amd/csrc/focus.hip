@@ -553,7 +553,7 @@ __global__ __launch_bounds__(256) void seg_mass_from_cum_kernel(
 // request: exp(cum_s - lse) - exp(cum_{s-1} - lse) for s < t, and what is left for s = t.
 // Workgroup (t, part) takes a part of t's rows and all their s: a thread keeps one s and walks the (row, head) pairs, so that neighbours read
 // neighbouring floats and cum goes through once, in wavefronts that fill the chip.  (A workgroup per t and s read every line of cum once per s:
-// 20k rows of 32 heads and 10 segments, 28 MB, 47 us; this 14, most of it the latency of three rounds of loads; 8 parts 34.)  parts: sums [t][part][s], which self_sum_kernel adds up; null: one part, the result.
+// 20k rows of 32 heads and 10 segments, 28 MB, 47 us; this 14, most of it the latency of two rounds of loads; 8 parts 34.)  parts: sums [t][part][s], which self_sum_kernel adds up; null: one part, the result.
 constexpr int kPairParts = 32;
 __global__ __launch_bounds__(256) void pair_mass_from_cum_kernel(
     const cc_segment* __restrict__ segs, const int32_t* __restrict__ req_seg_off, int n_requests, int n_q_tot,
@@ -575,7 +575,7 @@ __global__ __launch_bounds__(256) void pair_mass_from_cum_kernel(
     const int w = min(256, tl + 1 - s0), per = 256 / w, sl = s0 + tid % w, mine = tid / w;      // pairs that are walked side by side
     float acc = 0.f;
     if (mine < per) {
-      constexpr int kAhead = 8;
+      constexpr int kAhead = 16;
       for (int i0 = first + mine; i0 < end; i0 += per * kAhead) {
         float total[kAhead], upto[kAhead], before[kAhead];
 #pragma unroll
@@ -594,7 +594,9 @@ __global__ __launch_bounds__(256) void pair_mass_from_cum_kernel(
     }
     __syncthreads();                                       // (the sums before have been read)
     sums[tid] = acc;
-    for (int o = 128; o > 0; o >>= 1) {
+    int top = 1;
+    while (2 * top < per) top *= 2;
+    for (int o = per > 1 ? top : 0; o > 0; o >>= 1) {
       __syncthreads();
       if (mine < o && mine + o < per) sums[tid] += sums[tid + o * w];
     }
