@@ -615,6 +615,8 @@ exp_step(0, i);
 #pragma unroll
     for (int s = 0; s < kDepth; ++s) issue(at, s);     // steps 0..kDepth-1 of iteration 0
     __builtin_amdgcn_sched_barrier(0);
+    // (KS = 2: the first half-step brings K block 5 into block 0's place, which every wavefront of the stream has read by here)
+    if constexpr (KS == 2) barrier();
   }
 
   // ---- the tile loop --------------------------------------------------------------------------------
@@ -686,7 +688,8 @@ exp_step(0, i);
     f_cur = f_next; f_next = f_far;
   };
   // KS = 2: half-step s (S(s + 1), PV(s)) reads V block s and K block s + 2, which must be whole; K block s + 5 and V block s + 3 are
-  // started in it, into the places it found free.  Of the loads of the last two half-steps all eight may be out.
+  // started in it, into the places of K block s and V block s - 1, whose last operands left LDS in front of the barrier that opens it.  Of
+  // the loads of the last two half-steps all eight may be out.
   auto end_half = [&](int t, bool pads, int b) __attribute__((always_inline)) {
     wait_loads(std::integral_constant<int, 8>{});
     if (pads) blank_padding(lane_of(t), v_block(b), b & 1);

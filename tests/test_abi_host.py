@@ -296,3 +296,52 @@ def test_bench_refuses_more_than_one_gpu():
     res = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                          timeout=120)
     assert res.returncode != 0 and "one GPU" in res.stderr + res.stdout
+
+
+def _device_code(lib_path, kernel, tmp_path):
+    """{mangled name: [(address, mnemonic, first encoded word)]} of the kernels in the built library whose name holds `kernel`."""
+    import shutil
+    import subprocess
+    tool = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(tool):
+        pytest.skip("no llvm-objdump")
+    run = lambda *args: subprocess.run([tool, *args], capture_output=True, text=True, cwd=tmp_path, check=True).stdout
+    shutil.copy(lib_path, tmp_path / "lib.so")
+    run("--offloading", "lib.so")
+    code = {}
+    for image in sorted(f for f in os.listdir(tmp_path) if f.endswith("gfx950")):
+        for line in run("-t", image).splitlines():
+            name = line.split()[-1] if line.split() else ""
+            if kernel in name and " F " in line:
+                text = run("-d", "--disassemble-symbols=" + name, image)
+                code[name] = [(int(m[2], 16), m[1], int(m[3], 16)) for m in re.finditer(r"^\s+(\w+).*// ([0-9A-F]+): ([0-9A-F]{8})", text, re.M)]
+    return code
+
+
+def _most_loads_between_barriers(ops):
+    """The largest number of loads into LDS on any way through the kernel that meets no barrier (16: that many or more)."""
+    at = {a: i for i, (a, _, _) in enumerate(ops)}
+    most, todo = [-1] * len(ops), [(0, 0)]
+    while todo:
+        i, n = todo.pop()
+        if n <= most[i]:
+            continue
+        most[i] = n
+        a, op, word = ops[i]
+        n = 0 if op == "s_barrier" else min(n + op.startswith("global_load_lds"), 16)
+        if op.startswith(("s_branch", "s_cbranch")):
+            todo.append((at[a + 4 + 4 * ((word & 0xffff) - ((word & 0x8000) << 1))], n))
+        if op not in ("s_branch", "s_endpgm"):
+            todo.append((i + 1, n))
+    return max(most)
+
+
+def test_no_load_into_a_place_of_keys_that_may_still_be_read(lib, tmp_path):
+    # The attention in two key streams keeps five 32-key blocks of K per stream and four of V in LDS.  The prologue asks for blocks 0 to 2 of K and
+    # 0 of V and, behind its last barrier, for the next two of each; it reads block 0 and goes on to the loop, which brings block 5 into block
+    # 0's place: not before all wavefronts have read that, hence a barrier in between.  Two blocks of K and of V are 2 x 2 + 2 x 2 instructions.
+    import paper_2502_15734_amd as P
+    code = {n: ops for n, ops in _device_code(P.library_path(), "attn_v2_kernel", tmp_path).items() if "ILi2E" in n}
+    assert len(code) == 2, "with and without the by-product"
+    for name, ops in code.items():
+        assert _most_loads_between_barriers(ops) == 8, name
