@@ -185,17 +185,33 @@ def _nbytes(t: Optional[torch.Tensor]) -> int:
     return 0 if t is None else t.numel() * t.element_size()
 
 
-def _scratch(nbytes: int, device) -> Optional[torch.Tensor]:
-    """Scratch for one call, from torch's allocator on the stream the call runs on: it goes back when the call has been
-    enqueued, and what takes it next on that stream runs behind the call.  None, which every call that asks for scratch here
-    can do without, when the stream is being captured (the graph would keep using memory that has been given back, unless
-    it is torch that captures) or memory is short."""
-    if nbytes == 0 or device.type != "cuda" or torch.cuda.is_current_stream_capturing():
+def _kept_by_a_graph(t: torch.Tensor) -> bool:
+    """Whether t's memory lies in a pool of its own, as what torch hands out while it captures a graph does: nobody else gets it
+    as long as the graph lives."""
+    at = t.data_ptr()
+    return any(s["address"] <= at < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
+               for s in torch.cuda.memory_snapshot())
+
+
+def _scratch(nbytes: int, x: torch.Tensor) -> Optional[torch.Tensor]:
+    """Scratch for one call over x, from torch's allocator for the device and the stream the call runs on: it goes back when the call has
+    been enqueued, and what takes it next on that stream runs behind the call.  While torch captures a graph it comes from the graph's own pool, so
+    that a captured product is the eager one.  None, and the product stays whole (other last bits), where there is no such memory: when the
+    allocator has none left, and in a capture that is not torch's, whose graph would go on using memory that has been given back.  A program
+    that must not depend on that passes a workspace."""
+    if nbytes == 0 or not x.is_cuda:
         return None
+    # (new device memory is asked for in the relaxed mode: in the default one that would break a capture that another thread has under way)
+    mode = C.c_int(2)                                  # hipStreamCaptureModeRelaxed
+    exchange = load_library().hipThreadExchangeStreamCaptureMode
+    exchange(C.byref(mode))
     try:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     except torch.cuda.OutOfMemoryError:
         return None
+    finally:
+        exchange(C.byref(mode))
+    return None if torch.cuda.is_current_stream_capturing() and not _kept_by_a_graph(t) else t
 
 
 class Context:
@@ -272,7 +288,7 @@ class Context:
     def qkv_project(self, x, w_qkv, q, k, v, workspace=None):
         """workspace: scratch tensor (qkv_project_workspace_bytes); None: one is taken for the call (see _scratch)."""
         if workspace is None:
-            workspace = _scratch(self.qkv_project_workspace_bytes(x.shape[0], x.shape[1]), x.device)
+            workspace = _scratch(self.qkv_project_workspace_bytes(x.shape[0], x.shape[1]), x)
         self._check(self._lib.cc_qkv_project_ws(self._h, _ptr(x), _ptr(w_qkv), x.shape[0], x.shape[1],
                                                 _ptr(q), _ptr(k), _ptr(v), _ptr(workspace), _nbytes(workspace), _stream()))
 
@@ -315,7 +331,7 @@ class Context:
         """y = x w^T (+ residual); w [out_features, in_features].  workspace: scratch tensor (linear_workspace_bytes);
         None: one is taken for the call (see _scratch)."""
         if workspace is None:
-            workspace = _scratch(self.linear_workspace_bytes(x.shape[0], w.shape[1], w.shape[0]), x.device)
+            workspace = _scratch(self.linear_workspace_bytes(x.shape[0], w.shape[1], w.shape[0]), x)
         self._check(self._lib.cc_linear_ws(self._h, _ptr(x), _ptr(w), _ptr(residual), x.shape[0], w.shape[1], w.shape[0],
                                            _ptr(y), _ptr(workspace), _nbytes(workspace), _stream()))
 

@@ -145,3 +145,100 @@ def test_layer_tail_at_the_8b_model_shape_on_sampled_rows():
     assert H.rel_l2(h1[which], w1) <= 1e-2 and H.rel_l2(h2[which], w2) <= 1e-2
     assert np.isfinite(h2).all()
     ctx.close()
+
+
+def _products_in_parts():
+    """Context, tensors and a call of a QKV projection and a linear product whose contractions run in parts."""
+    import paper_2502_15734_amd as P
+    g = torch.Generator(device="cuda").manual_seed(7)
+    rnd = lambda *shape, sc=1.0: (torch.randn(*shape, device="cuda", generator=g) * sc).to(torch.bfloat16)
+    ctx = P.Context(8, 2, 128, 5.0e5, P.CC_BF16)
+    x, w_qkv, a, w_down = rnd(100, 4096), rnd(1536, 4096, sc=4096 ** -0.5), rnd(100, 14336), rnd(4096, 14336, sc=14336 ** -0.5)
+    assert ctx.qkv_project_workspace_bytes(100, 4096) > 0 and ctx.linear_workspace_bytes(100, 14336, 4096) > 0
+    outs = [torch.empty((100, n), dtype=torch.bfloat16, device="cuda") for n in (1024, 256, 256, 4096)]
+
+    def call(**kw):
+        for o in outs:
+            o.fill_(float("nan"))
+        ctx.qkv_project(x, w_qkv, *outs[:3], **kw)
+        ctx.linear(a, w_down, outs[3], residual=x, **kw)
+        return outs
+    return call
+
+
+def _same(a, b):
+    return all(torch.equal(s.view(torch.uint8), t.view(torch.uint8)) for s, t in zip(a, b))
+
+
+def test_products_in_parts_replay_in_a_hip_graph():
+    # (the scratch of a captured call is the graph's own: eager calls and other tensors in between do not get it)
+    call = _products_in_parts()
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    whole = [t.clone() for t in call(workspace=none)]
+    want = [t.clone() for t in call()]
+    assert not _same(want, whole), "the two sums round alike: nothing to tell them apart by"
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        outs = call()
+    for rep in range(3):
+        other = [torch.full((n << 20,), rep + 1, dtype=torch.uint8, device="cuda") for n in (1, 3, 8, 24)]
+        assert _same(call(), want)
+        torch.cuda.synchronize()
+        graph.replay(); torch.cuda.synchronize()
+        assert _same(outs, want), f"replay {rep}"
+        assert all(bool((t == rep + 1).all()) for t in other)
+
+
+def test_products_without_memory_for_their_parts_stay_whole(monkeypatch):
+    call = _products_in_parts()
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    whole = [t.clone() for t in call(workspace=none)]
+    torch.cuda.synchronize()
+    # a capture that torch does not know of
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    assert _same(call(), whole)
+    monkeypatch.undo()
+    # no memory
+    def refuse(*args, **kw):
+        raise torch.cuda.OutOfMemoryError("no memory")
+    monkeypatch.setattr(torch, "empty", refuse)
+    got = [t.clone() for t in call()]
+    monkeypatch.undo()
+    assert _same(got, whole)
+    assert not _same(call(), whole)
+
+
+def test_products_while_another_thread_captures():
+    # a size that the allocator has no memory for yet, on another stream: neither the call nor the capture may fail
+    import threading
+    call = _products_in_parts()
+    want = [t.clone() for t in call()]
+    a = torch.ones(1 << 20, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    got, failed = [], []
+
+    def other():
+        try:
+            with torch.cuda.stream(stream):
+                got.extend(call())
+        except Exception as e:                           # (reported by the assertion below)
+            failed.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        a.mul_(2.0)
+        t = threading.Thread(target=other)
+        t.start(); t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    assert _same(got, want)
+    graph.replay(); torch.cuda.synchronize()
+    assert bool((a == 2.0).all())
