@@ -20,7 +20,7 @@ import numpy as np
 import torch
 
 from .binding import CC_IMPL_AUTO, FocusTracker, Preloader, preload_depth
-from .pipeline import DeviceBatch
+from .pipeline import DeviceBatch, product_workspace
 
 
 class DecoderLoop:
@@ -49,6 +49,10 @@ class DecoderLoop:
         n, hidden, ffn = max(1, b.n_q_tot), w.hidden.shape[1], weights[0].w_gate.shape[0]
         mk = lambda cols: torch.empty((n, cols), dtype=b.dt, device=device)
         self.h, self.h1, self.x, self.act, self.h_alt = mk(hidden), mk(hidden), mk(hidden), mk(ffn), mk(hidden)
+        n_attn = w.spec.n_q_heads * w.spec.head_dim
+        self.ws_products = product_workspace(b.n_q_tot, device, lambda r: b.ctx.qkv_project_workspace_bytes(r, hidden),
+                                             lambda r: b.ctx.linear_workspace_bytes(r, n_attn, hidden),
+                                             lambda r: b.ctx.linear_workspace_bytes(r, ffn, hidden))
         seg = w.segments
         self.chunk_segs = [[s for s in range(int(w.req_seg_off[r]), int(w.req_seg_off[r + 1])) if seg[s][1] == 0]
                            for r in range(w.n_requests)]
@@ -118,17 +122,17 @@ class DecoderLoop:
                 rec["h_in"] = h.float().cpu().numpy()
                 rec["cu_q"] = np.array(getattr(b, "cu_q_host", self.w.cu_q), copy=True)
             b.ctx.rms_norm(h, lw["gain_attn"], self.eps[l], x)
-            b.ctx.qkv_project(x, lw["w_qkv"], b.q_c[:n], b.k_c[:n], b.v_c[:n])
+            b.ctx.qkv_project(x, lw["w_qkv"], b.q_c[:n], b.k_c[:n], b.v_c[:n], workspace=self.ws_products)
             if self.window:
                 mass = b.sparse_prefill_mass()
             else:
                 b.sparse_prefill()
             if self.pre is not None and b.cow:
                 self.pre[1].release(l)
-            b.ctx.linear(o2, lw["w_o"], h1, residual=h)
+            b.ctx.linear(o2, lw["w_o"], h1, residual=h, workspace=self.ws_products)
             b.ctx.rms_norm(h1, lw["gain_ffn"], self.eps[l], x)
             b.ctx.gated_linear(x, lw["w_gate"], lw["w_up"], act)
-            b.ctx.linear(act, lw["w_down"], h, residual=h1)
+            b.ctx.linear(act, lw["w_down"], h, residual=h1, workspace=self.ws_products)
             t1.record()
             rec["_events"] = (t0, t1)
             if keep:

@@ -20,6 +20,13 @@ def _dev(a: np.ndarray, dtype=None, device="cuda") -> torch.Tensor:
     return t if dtype is None else t.to(dtype)
 
 
+def product_workspace(n_rows: int, device, *needs) -> torch.Tensor:
+    """One workspace for products of up to n_rows rows; needs: bytes that each of them wants, as functions of the rows (more rows may
+    want fewer).  Kept by who makes the calls, so that none of them allocates and all run alike: eager, captured, short of memory."""
+    most = max((need(n) for need in needs for n in range(1, n_rows + 1)), default=0)
+    return torch.empty(max(256, most), dtype=torch.uint8, device=device)
+
+
 class DeviceBatch:
     def __init__(self, w, device: str = "cuda", impl: int = CC_IMPL_AUTO, poison: bool = False,
                  miss_segments=(), fused_gather: bool = True, cow: bool = True):
@@ -81,6 +88,7 @@ class DeviceBatch:
             self.hidden = _dev(w.hidden, dt, device)
             self.w_qkv = _dev(w.w_qkv, dt, device)
             self.x_c = torch.empty((max(1, self.n_q_tot), w.hidden.shape[1]), dtype=dt, device=device)
+            self.ws_project = product_workspace(self.n_q_tot, device, lambda n: self.ctx.qkv_project_workspace_bytes(n, w.hidden.shape[1]))
         else:
             self.k_new = _dev(w.k_new, dt, device)
             self.v_new = _dev(w.v_new, dt, device)
@@ -177,7 +185,7 @@ class DeviceBatch:
         r = self._rows
         if self.projected:
             self.ctx.gather_rows(self.hidden, r(self.q_row), r(self.x_c))
-            self.ctx.qkv_project(r(self.x_c), self.w_qkv, r(self.q_c), r(self.k_c), r(self.v_c))
+            self.ctx.qkv_project(r(self.x_c), self.w_qkv, r(self.q_c), r(self.k_c), r(self.v_c), workspace=self.ws_project)
         else:
             self.ctx.gather_rows(self.q, r(self.q_row), r(self.q_c))
             self.ctx.gather_rows(self.k_new, r(self.q_row), r(self.k_c))

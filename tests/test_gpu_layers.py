@@ -135,3 +135,54 @@ def test_decoder_loop_with_early_termination(dtype, preload):
             np.testing.assert_allclose(rec["mass"][s0:s1], o["mass"], rtol=1e-2 if dtype == "bf16" else 1e-4, atol=1e-3)
     assert recs[-1]["rows"] < recs[0]["rows"]
     loop.close()
+
+
+def _no_scratch(monkeypatch):
+    from paper_2502_15734_amd import binding
+
+    def refuse(nbytes, x):
+        raise AssertionError("a call takes scratch of its own")
+    monkeypatch.setattr(binding, "_scratch", refuse)
+
+
+def test_decoder_loop_owns_the_workspace_of_its_products(monkeypatch):
+    """Products whose contraction runs in parts, with rows that leave the list on the way: no call allocates, and a second loop over
+    the same state gives the same bits."""
+    from paper_2502_15734_amd.layers import DecoderLoop
+    w = _decoder_workload("bf16")
+    weights = [W.layer_weights(w.spec, 256, 4096, layer=l, qkv_scale=1.0 / 16) for l in range(4)]
+    _no_scratch(monkeypatch)
+    runs = []
+    for _ in range(2):
+        loop = DecoderLoop(w, weights, window=2)
+        rows = [n for n in range(1, loop.batch.n_q_tot + 1) if loop.batch.ctx.linear_workspace_bytes(n, 4096, 256) > 0]
+        runs.append(loop.run(keep=True))
+        assert all(rec["rows"] in rows for rec in runs[-1])
+        assert loop.ws_products.numel() >= max(loop.batch.ctx.linear_workspace_bytes(n, 4096, 256) for n in rows)
+        loop.close()
+    assert runs[0][-1]["rows"] < runs[0][0]["rows"]
+    for a, b in zip(*runs):
+        assert np.array_equal(a["h2"].view(np.uint32), b["h2"].view(np.uint32)) and np.array_equal(a["out"].view(np.uint32), b["out"].view(np.uint32))
+
+
+def test_projected_step_replays_in_a_hip_graph(monkeypatch):
+    """As test_step_replays_in_a_hip_graph, of a batch whose projection runs in parts: it keeps the workspace."""
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("projected", "bf16", 8, 2, 128, 5.0e5, [100, 77, 130], [0, 5, 0], [W.RequestSpec([0, 1, 2], [0.1, 0.2, 0.15], 40)],
+                 1.0 / math.sqrt(128), seed=47, hidden=4096)
+    b = DeviceBatch(w)
+    assert b.ctx.qkv_project_workspace_bytes(b.n_q_tot, 4096) > 0
+    _no_scratch(monkeypatch)
+    b.step(); torch.cuda.synchronize()
+    want = [t.clone() for t in (b.out, b.lse, b.q_c, b.k_c, b.v_c, b.k_req, b.v_req)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.step()
+    for rep in range(3):
+        for t in (b.out, b.lse, b.q_c, b.k_c, b.v_c):
+            t.fill_(float("nan"))
+        b.k_req.zero_(); b.v_req.zero_()
+        torch.cuda.synchronize()
+        graph.replay(); torch.cuda.synchronize()
+        for i, (g, e) in enumerate(zip((b.out, b.lse, b.q_c, b.k_c, b.v_c, b.k_req, b.v_req), want)):
+            assert torch.equal(g.view(torch.uint8), e.view(torch.uint8)), f"replay {rep}, tensor {i}"
