@@ -914,15 +914,14 @@ void launch_prefill_pairs(const cc_ctx* ctx, const void* q, const int32_t* src_r
     // (parts in what the pass of its own would have used, none of fewer than 512 pairs of a row and a head, on the average: two rounds of loads or more)
     const int wanted = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(n_q_tot) * hq / (512 * static_cast<int64_t>(n_segs)), kPairParts));
     const size_t room = segment_mass_bytes(ctx, n_segs, max_tiles, max_q_per_req, n_q_tot) / (static_cast<size_t>(n_segs) * s_max * sizeof(float));
-    const int n_parts = self_mass == nullptr ? 1 : static_cast<int>(std::min<size_t>(std::max<size_t>(room, 1), std::max(wanted, 1)));
+    const int n_parts = static_cast<int>(std::min<size_t>(std::max<size_t>(room, 1), std::max(wanted, 1)));
     float* parts = n_parts > 1 ? static_cast<float*>(fallback_ws) : nullptr;
     hipLaunchKernelGGL(pair_mass_from_cum_kernel, dim3(n_segs, n_parts), dim3(256), 0, stream, segs, req_seg_off, n_requests,
                        n_q_tot, hq, cum, s_max, lse, pair_mass, n_pairs, parts);
-    if (self_mass != nullptr) {
-      launch_self_weight(ctx, q, src_rows, q_pos, slot_map, k_pool, n_blocks, n_q_tot, lse, row_self, stream);
-      hipLaunchKernelGGL(self_sum_kernel, dim3(n_segs), dim3(256), 0, stream, q_pos, cu_q, segs, n_requests, hq,
-                         row_self, self_mass, PairParts{parts, n_parts, s_max, n_pairs, req_seg_off, pair_mass});
-    }
+    launch_self_weight(ctx, q, src_rows, q_pos, slot_map, k_pool, n_blocks, n_q_tot, lse, row_self, stream);
+    // (with parts it is this kernel that writes pair_mass)
+    hipLaunchKernelGGL(self_sum_kernel, dim3(n_segs), dim3(256), 0, stream, q_pos, cu_q, segs, n_requests, hq,
+                       row_self, self_mass, PairParts{parts, n_parts, s_max, n_pairs, req_seg_off, pair_mass});
   } else {
     launch_chunk_attention(ctx, q, src_rows, q_pos, slot_map, cu_q, n_q_tot, max_q_per_req, k_pool, v_pool, n_blocks,
                            block_tab, segs, n_segs, req_seg_off, n_requests, lse, pair_mass, n_pairs, self_mass,
