@@ -702,8 +702,9 @@ exp_step(0, i);
   };
   int t = 0;
   // (Where the loop lies in the lines of the instruction cache shows: 70B on 8 requests of 10k tokens 1527 us with what is
-  // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20; the layer of the 8B batch of 32 with the by-product 2040 at the line's beginning,
-  // 2053 28 bytes behind it, 2058 with 44 and no better with 20 or 52.  There 20 bytes of moves lie between this and the loop.)
+  // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20; with the by-product the layer of the 8B batch of 32 and a cache build are 0.4 - 0.9 %
+  // slower 44 bytes behind a line than at its beginning, in five runs of five.  There 20 bytes of moves lie between this and the loop (an
+  // alignment asked of the compiler for the loop itself has no effect); a test looks where the two loops begin.)
   if constexpr (KS == 1 && !BY) asm volatile(".p2align 6");
   if constexpr (KS == 1 && BY) asm volatile(".p2align 6\n\t.fill 11, 4, 0xbf800000");      // (11 s_nop)
   for (; t < n_mine; ++t) {

@@ -318,6 +318,10 @@ def _device_code(lib_path, kernel, tmp_path):
     return code
 
 
+def _branch_target(address, word):
+    return address + 4 + 4 * ((word & 0xffff) - ((word & 0x8000) << 1))
+
+
 def _most_loads_between_barriers(ops):
     """The largest number of loads into LDS on any way through the kernel that meets no barrier (16: that many or more)."""
     at = {a: i for i, (a, _, _) in enumerate(ops)}
@@ -330,7 +334,7 @@ def _most_loads_between_barriers(ops):
         a, op, word = ops[i]
         n = 0 if op == "s_barrier" else min(n + op.startswith("global_load_lds"), 16)
         if op.startswith(("s_branch", "s_cbranch")):
-            todo.append((at[a + 4 + 4 * ((word & 0xffff) - ((word & 0x8000) << 1))], n))
+            todo.append((at[_branch_target(a, word)], n))
         if op not in ("s_branch", "s_endpgm"):
             todo.append((i + 1, n))
     return max(most)
@@ -345,3 +349,17 @@ def test_no_load_into_a_place_of_keys_that_may_still_be_read(lib, tmp_path):
     assert len(code) == 2, "with and without the by-product"
     for name, ops in code.items():
         assert _most_loads_between_barriers(ops) == 8, name
+
+
+def test_key_loop_of_long_prompts_begins_a_line_of_the_instruction_cache(lib, tmp_path):
+    # (asked for in front of the loop, by the count of what the compiler puts in between: see there for what another place costs)
+    import paper_2502_15734_amd as P
+    code = {n: ops for n, ops in _device_code(P.library_path(), "attn_v2_kernel", tmp_path).items() if "ILi1E" in n}
+    assert len(code) == 2, "with and without the by-product"
+    for name, ops in code.items():
+        at = {a: i for i, (a, _, _) in enumerate(ops)}
+        back = [(at[_branch_target(a, word)], i) for i, (a, op, word) in enumerate(ops)
+                if op.startswith(("s_branch", "s_cbranch")) and _branch_target(a, word) < a]
+        heads = {h for h, i in back if sum(op.startswith("v_mfma") for _, op, _ in ops[h:i]) == 32}      # (a tile: 2 x 8 products for S, 2 x 8 for PV)
+        assert len(heads) == 1, name
+        assert ops[heads.pop()][0] % 64 == 0, name
