@@ -123,9 +123,10 @@ const char* cc_last_error(const cc_ctx* ctx);
  * CC_IMPL_SCALAR forces the plain ones, CC_IMPL_MFMA_NARROW the MFMA kernels that give a
  * workgroup one head group and 32 query rows (64 tokens in the score stage; the only MFMA form for
  * head groups of 1 or 2).  For head groups that are a multiple of 4 AUTO runs the wide kernels (four
- * heads and 64 rows, 128 tokens in the score stage, per workgroup), or, on grids that leave compute units
+ * heads and 64 rows, 128 tokens in the score stage, per workgroup; long score calls in products of 16
+ * columns, others of 32), or, on grids that leave compute units
  * idle, a form with half of that whose key tiles are walked in two streams, or (scores of grids in between)
- * the narrow kernel; CC_IMPL_MFMA_WIDE runs the first of these at
+ * the narrow kernel; CC_IMPL_MFMA_WIDE runs the first of these (scores: with 16 columns) at
  * every size (narrow kernels for other head groups).  The forms sum in different orders, and P is
  * rounded to bf16 against another softmax reference, so with AUTO the last bits of a request's results
  * depend on the size of the batch it runs in (cc_linear, cc_qkv_project and cc_gated_linear: on n_rows

@@ -1049,14 +1049,15 @@ Plan run_plan(const cc_ctx* ctx, void* ws, const cc_segment* segs, int n_segs, c
 // tiles decides: it halves that chain.  In between the narrow kernel, of which two workgroups share a unit (later where a
 // KV head has 8 query heads: a narrow workgroup takes all of them, so there are half as many, and the wide one's line is lower).  Whole
 // cc_select call, narrow / wide, us, by the 128-token workgroups that the rule estimates and the chunks of the requests.  32 / 8
-// heads: 288 (3 of 40 x 17-60) 133 / 151, 288 (12 of 3 x 160) 49 / 56, 320 (8 of 6 x 100) 53 / 72, 384 (6 of 3 x 440) 82 / 87,
-// 448 (2 of 6 x 700) 185 / 204, 488 (12 x 700) 347 / 314, 560 (12 x 800) 412 / 372, 576 (12 of 20 x 17-60) 135 / 105.  8 heads per KV head: 280 (16 / 2, 12 x 800)
-// 293 / 282, 288 (16 / 2, 6 of 40 x 17-60) 138 / 155, 368 (64 / 8, 30 x 100) 169 / 167, 448 (64 / 8, 4 of 10 x 100) 101 / 86, 560 (16 / 2, 2 of 12 x 800) 433 / 374.
+// heads: 288 (3 of 40 x 17-60) 135 / 154, 288 (12 of 3 x 160) 48 / 56, 320 (8 of 6 x 100) 53 / 57, 384 (6 of 3 x 440) 76 / 84,
+// 448 (2 of 6 x 700) 182 / 201, 488 (12 x 700) 330 / 309, 552 (12 x 800) 419 / 377, 576 (12 of 20 x 17-60) 136 / 103.  8 heads per KV head: 276 (16 / 2, 12 x 800)
+// 294 / 283, 312 (16 / 2, 6 of 40 x 17-60) 133 / 171, 368 (64 / 8, 30 x 100) 150 / 167, 368 (16 / 2, 4 of 5 x 700) 141 / 168, 512 (64 / 8, 4 of 10 x 100) 99 / 95,
+// 552 (16 / 2, 2 of 12 x 800) 440 / 379.
 // Narrow / small, by the 64-token workgroups that the rule estimates.  32 / 8
-// heads: 130 (3 x 512) 49.9 / 38.7, 258 (5 x 512) 72.2 / 52.3, 304 (2 of 5 x 300) 56.8 / 52.5, 389 (3 of 3 x 512) 58.0 / 59.1,
-// 413 (8 of 3 x 200) 40.6 / 52.2, 519 (4 of 3 x 512) 63.4 / 66.8, 602 (9 x 600) 163 / 158, 758 (4 of 6 x 300) 96.8 / 100.  64 / 8:
-// 416 (4 of 5 x 100) 41.2 / 52.6, 608 (2 of 5 x 300) 77.1 / 83.3.  16 / 2: 301 (9 x 600) 178 / 95.0, 608 (8 of 5 x 300) 76.6 / 82.1,
-// 704 (4 of 5 x 700) 144 / 137.
+// heads: 130 (3 x 512) 49.5 / 37.2, 259 (5 x 512) 72.9 / 50.5, 306 (2 of 5 x 300) 55.4 / 49.6, 392 (3 of 3 x 512) 57.5 / 56.9,
+// 421 (8 of 3 x 200) 37.4 / 48.6, 522 (4 of 3 x 512) 60.7 / 62.9, 603 (9 x 600) 164 / 156, 763 (4 of 6 x 300) 92.2 / 95.7.  64 / 8:
+// 425 (4 of 5 x 100) 39.9 / 49.3, 612 (2 of 5 x 300) 75.3 / 80.3.  16 / 2: 301 (9 x 600) 177 / 91.3, 612 (8 of 5 x 300) 79.2 / 80.3,
+// 706 (4 of 5 x 700) 141 / 131.
 // The wide ATTENTION kernel is faster at every size measured, down to 64 workgroups (7-25 %), so it has no such limit.
 constexpr int kMinWideGrid = 512, kMinWideGrid8 = 360;
 constexpr int kOneRoundScore = 288, kTwoRoundScore = 540;
@@ -1067,9 +1068,25 @@ static int64_t scored_tokens(int n_tok, int n_segs, int n_requests) {
   const int64_t per_req = std::max(n_segs / n_requests, 2), scored = per_req > 2 ? per_req - 2 : 1, chunks = scored + 1;
   return n_tok * scored / chunks;
 }
-static bool wide_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
+static int64_t wide_score_groups(int n_q_heads, int n_tok, int n_segs, int n_requests) {
   const int64_t requests = std::min(n_requests, n_segs), per_request = scored_tokens(n_tok, n_segs, n_requests) / requests;
-  return n_q_heads / 4 * requests * ((per_request + 127) / 128) >= (n_q_heads / n_kv_heads > 4 ? kMinWideGrid8 : kMinWideGrid);
+  return n_q_heads / 4 * requests * ((per_request + 127) / 128);
+}
+static bool wide_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
+  return wide_score_groups(n_q_heads, n_tok, n_segs, n_requests) >= (n_q_heads / n_kv_heads > 4 ? kMinWideGrid8 : kMinWideGrid);
+}
+// Products of 16 columns where the call is long enough for the chip's power budget to hold its clock down: from about 0.1 TFLOP on (128-token workgroups x a
+// request's tokens are 2^-16 of the flops), unless little more than one round of workgroups (512) leaves the chip half idle behind it, or chunks of a key tile or less
+// put masks and their beginnings between the products; else 32 columns.  32 columns / 16, us, by
+// workgroups and that product.  32 / 8 heads: 552 (1 of 12 x 800, 5.3 M) 377 / 382, 576 (12 of 20 x 17-60, 0.2 M) 103 / 111, 864 (9 of 3 x 743, 1.7 M)
+// 171 / 161, 1280 (5 of 23 x 184, 4.7 M) 356 / 341, 3320 (5 of 23 x 477, 30 M) 1676 / 1610.  64 / 8: 512 (4 of 10 x 100, 0.5 M) 95 / 102, 5760 (5 of 23 x 414, 46 M) 2620 /
+// 2558.  16 / 2: 480 (5 of 13 x 247, 1.3 M) 139 / 150, 896 (8 of 6 x 692, 3.2 M) 251 / 232, 1008 (36 of 3 x 413, 1.2 M) 134 / 135.  8 / 2: 646 (19 of 4 x 681, 1.5 M) 140 / 140,
+// 1140 (57 of 5 x 247, 1.5 M) 131 / 128.  By tokens of a segment in the mean: 45 (64 / 8, 35 of 18 x 37-56, 3.9 M) 467 / 492, 66 (32 / 8, 22 of 20 x 49-74, 3.1 M) 282 / 289, 76 (33 of
+// 27 x 58-87, 10.7 M) 1003 / 989.  (Over 150 calls of 1 to 64 requests this takes 0.03 % longer than the better of the two for each, 16 columns throughout 1 - 2 %.)
+constexpr int64_t kPowerLine = 1400000, kPowerGrid = 680, kPowerSegment = 72;
+static bool score_held_by_power(int n_q_heads, int n_tok, int n_segs, int n_requests) {
+  const int64_t groups = wide_score_groups(n_q_heads, n_tok, n_segs, n_requests);
+  return groups >= kPowerGrid && n_tok >= kPowerSegment * n_segs && groups * (n_tok / std::min(n_requests, n_segs)) >= kPowerLine;
 }
 static bool small_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_segs, int n_requests) {
   const int64_t groups = n_q_heads / 4 * scored_tokens(n_tok, n_segs, n_requests) / 64;
@@ -1079,10 +1096,10 @@ static bool small_score_grid(int n_q_heads, int n_kv_heads, int n_tok, int n_seg
 
 // Where there is a workgroup for every compute unit, but a request has one scored chunk (with the question three segments) and that
 // fits a workgroup of the narrow kernel, a wide workgroup is as good as half empty and its longer prologue decides.  Whole call, wide /
-// narrow, us, two chunks and a question.  64 / 8 heads: 100 requests, chunks of 20-30 tokens 91.9 / 72.5, 60-64 94.7 / 81.1, but
-// 60-80 (two narrow workgroups a chunk) 112 / 131, and three chunks of 17-33 115 / 123.  32 / 8: 100 of 40-50 62.1 / 44.6.
-// 16 / 2: 300 of 40-50 94.4 / 81.7.  The narrow kernel needs a dispatch order of the segments, which takes some 20 us beyond kPlanFused and only many heads
-// outweigh: 1000 of 40-50 on 8 / 1 146 / 170, 16 / 2 223 / 233, 32 / 8 362 / 311, 64 / 8 673 / 627.  Nothing is scored of a chunk and a question
+// narrow, us, two chunks and a question.  64 / 8 heads: 100 requests, chunks of 20-30 tokens 91 / 72, 60-64 94 / 82, but
+// 60-80 (two narrow workgroups a chunk) 109 / 134, and three chunks of 17-33 115 / 124.  32 / 8: 100 of 40-50 62 / 46.
+// 16 / 2: 300 of 40-50 97 / 84.  The narrow kernel needs a dispatch order of the segments, which takes some 20 us beyond kPlanFused and only many heads
+// outweigh: 1000 of 40-50 on 8 / 1 147 / 172, 16 / 2 225 / 233, 32 / 8 364 / 312, 64 / 8 680 / 630.  Nothing is scored of a chunk and a question
 // (1000 on 32 / 8: 34 / 83).
 static bool one_score_tile(int n_q_heads, int max_seg_tokens, int n_segs, int n_requests) {
   return static_cast<int64_t>(n_q_heads / 4) * n_requests >= 256 && max_seg_tokens <= 32 * kScoreQB && n_segs > 2 * static_cast<int64_t>(n_requests) &&
@@ -1154,7 +1171,9 @@ void launch_select_mfma(const cc_ctx* ctx, const void* q, const void* k_pool, in
     list.places = std::max((small ? 256 : 512) / (ctx->cfg.n_q_heads / 4), 1);
   }
   const Plan pl = run_plan(ctx, plan_ws, segs, n_segs, req_seg_off, n_requests, false, nullptr, block_tab, n_blocks, max_tiles, n_redo, list, nullptr, stream);
-  if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, small, list, stream);
+  // (CC_IMPL_MFMA_WIDE: the same sums at every size)
+  const ScoreForm form = small ? ScoreForm::kSmall : forced || score_held_by_power(hq, n_tok, n_segs, n_requests) ? ScoreForm::kBig16 : ScoreForm::kBig;
+  if (wide) launch_score_v2(ctx, q, k_pool, pl, segs, req_seg_off, n_requests, n_tok, mass, pl.redo, form, list, stream);
   const int32_t* redo = pl.redo;
 #define CC_ARGS ctx, q, k_pool, n_blocks, pl, req_seg_off, max_seg_tokens, mass, redo, topn, stream
   switch (ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads) {

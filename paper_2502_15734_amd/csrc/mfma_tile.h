@@ -294,8 +294,10 @@ WorkList attn_v2_list(const cc_ctx* ctx, const int32_t* q_pos, int n_q_tot, int 
 // The wide score kernel (128 tokens per wavefront, no softmax reference) flags 64-row granules of
 // the per-token tensors whose sums left the safe range; the narrow kernel redoes them.
 inline size_t score_redo_entries(int n_tok) { return static_cast<size_t>(n_tok) / 64 + 2; }
+// 64 tokens and two key streams; 128 tokens in products of 32 columns; of 16
+enum class ScoreForm { kSmall, kBig, kBig16 };
 void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const Plan& pl, const cc_segment* segs,
-                     const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, bool small,
+                     const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, ScoreForm form,
                      const WorkList& list, hipStream_t stream);
 
 }  // namespace cc

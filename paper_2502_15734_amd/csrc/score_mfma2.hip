@@ -8,13 +8,13 @@
 // four rotated query blocks sit in accumulation registers (128), two S blocks (32) and the key block's eight K
 // operands (32) in vector registers: 256 in all, so two workgroups share a compute unit.
 //
-// Schedule.  A 32-key block is walked column block by column block: 16 MFMAs of 16 x 16 x 32 into one S block, and under each of
-// them an exponential and an add of the S block before.  (With all MFMAs of a block first and its 64
+// Schedule.  A 32-key block is walked column block by column block, in 16 MFMAs of 16 x 16 x 32 or eight of 32 x 32 x 16 into one S block, and
+// underneath the exponentials and adds of the S block before.  (With all MFMAs of a block first and its 64
 // exponentials behind them a wavefront's own chain was 2900 clocks a block, more than the two wavefronts
-// of a SIMD need of the matrix pipe; now 2450 - 2600.)  What is left is the clock that the chip's power budget leaves, 1.65 -
-// 1.7 GHz: hence the 16-column MFMAs, which move a quarter of the accumulator bytes per flop of the 32-column ones (this
-// loop alone 1.44 -> 1.51 PFLOP/s; 4 x 32 k tokens 5 - 6 % faster on four boxes, 12.70 -> 11.97 ms, the 8B batch of 32
-// 2 - 3 %, 2.97 -> 2.87).
+// of a SIMD need of the matrix pipe; now 2450 - 2600.)  A long call is then held by the clock that the chip's power budget leaves, 1.65 -
+// 1.7 GHz: hence 16 columns there, which move half the accumulator bytes per flop (this loop alone 1.44 -> 1.51 PFLOP/s; 4 x 32 k tokens 3 - 6 %
+// faster, by the box, 12.70 -> 11.97 ms on one; the 8B batch of 32 2 - 3 %, 2.97 -> 2.87).  A call that is over before the clock falls waits for its
+// own instructions, of which 32 columns need half as many: see score_held_by_power for the line between them.
 //
 // The tokens of a workgroup are numbered through the request's scored chunks: a workgroup per chunk and 128 tokens
 // leaves columns empty in every chunk's last one.  Each column takes its prior chunks' mass where its own chunk
@@ -35,7 +35,7 @@
 // Small grids take a second form: 64 tokens per workgroup and eight wavefronts, two key streams (KS = 2: wavefronts 0-3 walk
 // the even key tiles, 4-7 the odd ones, each stream with images of its own; the sums are just added at the end).
 // With one workgroup per compute unit the four-wavefront form has nothing to put beside its exponentials;
-// the second stream is that, and halves the chain of tiles.  It takes 32-column MFMAs.
+// the second stream is that, and halves the chain of tiles.  It takes 32-column MFMAs (the loop of an 8B request of 2.6 k tokens 23.0 us, 24.0 with 16).
 //
 // Staging: four K-tile images in LDS (16 KiB each), filled by loads that write LDS directly
 // (global_load_lds, lane L of an instruction fills piece base + L), whole 128-byte lines each:
@@ -146,16 +146,15 @@ __device__ __forceinline__ float4 two_turns(const double (&freq)[2], int pos, fl
 }
 
 // One workgroup = 128 (kQB = 4) or 64 (kQB = 2) consecutive scored tokens of a request, whatever chunks they lie in.
-template <int kQB, int KS>
+// Products of W columns.
+template <int kQB, int KS, int W>
 __global__ __launch_bounds__(256 * KS, 2) void score_v2_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_pool,
     const TileDesc* __restrict__ tiles, int max_tiles, int tile_bits, const cc_segment* __restrict__ segs,
     int n_requests, const int32_t* __restrict__ req_seg_off, const int32_t* __restrict__ seg_tile_off, int hq, int hkv, int n_sub,
     InvFreq inv_freq, float* __restrict__ mass, int32_t* __restrict__ redo, int redo_any) {
   constexpr int kTQ = 32 * kQB;               // tokens per workgroup
-  // 16 columns where the chip is held by its power budget, 32 where a workgroup waits for its own instructions (half as many MFMAs to
-  // issue: the loop of an 8B request of 2.6 k tokens 23.0 us, 24.0 with 16 columns)
-  constexpr int W = KS == 1 ? 16 : 32, kTG = 32 / W, kKS = 8 / kTG;      // columns of an MFMA; token halves of a block; k-steps
+  constexpr int kTG = 32 / W, kKS = 8 / kTG;  // token halves of a block; k-steps
   static_assert(kQB % 2 == 0, "two S blocks in turn");
   __shared__ uint4 lds_all[KS * kBufs * kImageK];
   __shared__ int4 tokens[kTQ];                // what is rarely asked of a token: position, row, first key tile of its chunk
@@ -522,18 +521,20 @@ bool score_v2_supported(const cc_ctx* ctx) {
 }
 
 void launch_score_v2(const cc_ctx* ctx, const void* q, const void* k_pool, const Plan& pl, const cc_segment* segs,
-                     const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, bool small,
+                     const int32_t* req_seg_off, int n_requests, int n_tok, float* mass, int32_t* redo, ScoreForm form,
                      const WorkList& list, hipStream_t stream) {
   const int hkv = ctx->cfg.n_kv_heads, n_sub = ctx->cfg.n_q_heads / hkv / 4, per_tile = hkv * n_sub;
   // (the chunks' lengths are on the device: the grid is an upper bound, what is too much leaves at once)
+  const bool small = form == ScoreForm::kSmall;
   const int rows = small ? 32 * kSmallQB : 32 * kBigQB;
   const int entries = std::min(n_tok / rows + n_requests, pl.max_tiles - 1);
 #define CC_LAUNCH(...)                                                                                        \
   hipLaunchKernelGGL((score_v2_kernel<__VA_ARGS__>), dim3(per_tile * entries), dim3(small ? 512 : 256), 0, stream, static_cast<const bf16_t*>(q), \
                      static_cast<const bf16_t*>(k_pool), pl.tiles, pl.max_tiles, list.tile_bits, segs, n_requests, req_seg_off, pl.seg_tile_off,  \
                      ctx->cfg.n_q_heads, hkv, n_sub, ctx->inv_freq, mass, redo, pl.redo_any)
-  if (small) CC_LAUNCH(kSmallQB, 2);
-  else CC_LAUNCH(kBigQB, 1);
+  if (small) CC_LAUNCH(kSmallQB, 2, 32);
+  else if (form == ScoreForm::kBig) CC_LAUNCH(kBigQB, 1, 32);
+  else CC_LAUNCH(kBigQB, 1, 16);
 #undef CC_LAUNCH
 }
 

@@ -392,6 +392,30 @@ def test_scores_of_the_wide_form_around_16_tokens_and_16_keys(lens):
         assert float(got[1].max()) > 0.1
 
 
+@pytest.mark.parametrize("lens,n_requests,columns", [([16, 17, 1], 24, 32), ([33, 16, 15, 1], 24, 32), ([64, 49, 80], 24, 32), ([70, 130, 3], 24, 32), ([5, 31, 33], 24, 32),
+                                                     ([590, 589, 590, 600, 590, 577, 590, 590], 1, 32), ([700, 689, 702, 700, 711], 2, 16)])
+def test_scores_of_short_and_of_long_calls_on_large_grids(lens, n_requests, columns):
+    # short calls multiply 32 columns, long ones 16 (as the forced wide kernel always does): last tokens, chunk boundaries and causal edges around 16 and 32
+    import paper_2502_15734_amd as P
+    from paper_2502_15734_amd.pipeline import DeviceBatch
+    w = W.custom("columns", "bf16", 64, 8, 128, 5.0e5, lens, [7] * len(lens),
+                 [W.RequestSpec(list(range(len(lens))), [0.2] * len(lens), 9) for _ in range(n_requests)], 1.0, seed=31)
+    for gain in (1.0, 40.0):
+        got = {}
+        for impl in ("AUTO", "MFMA_WIDE", "MFMA_NARROW"):
+            b = DeviceBatch(w, impl=getattr(P, "CC_IMPL_" + impl), poison=True)
+            b.q.mul_(gain)
+            b.rope_shift(); b.select(); torch.cuda.synchronize()
+            got[impl] = b.scores.cpu().double()
+        # (the bound of test_scores_in_two_key_streams; the forms add in different orders, so their bits tell which one ran, unless the second
+        # pass has redone what left the safe range)
+        assert torch.isfinite(got["AUTO"]).all()
+        assert float((got["AUTO"] - got["MFMA_NARROW"]).abs().max()) <= (4 * math.sqrt(sum(lens)) * 2.0 ** -24 + 1e-6) * gain
+        if gain == 1.0:
+            assert torch.equal(got["AUTO"], got["MFMA_WIDE"]) == (columns == 16) and not torch.equal(got["AUTO"], got["MFMA_NARROW"])
+        assert float(got["MFMA_NARROW"].max()) > 0.1
+
+
 @pytest.mark.parametrize("n_requests", [65536, 65537])
 def test_scores_behind_many_empty_requests(n_requests):
     # a list entry has 32 bits for request and row tile: 16 for the one and 16 for the other, 17 and 15
