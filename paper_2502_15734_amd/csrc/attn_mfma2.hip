@@ -209,9 +209,10 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
   // ---- rows and positions: asked for first, whole rows each (see load_query_rows) ---------------------
   // (with a row map, list row j takes its query from row q_map[j] of q - and, if map_pos, its
   // position from q_pos[q_map[j]]; results are always indexed by the list row)
-  int src_row, p, p_other = 0;
+  int src_row, p, p_other = 0, snap_row = -1;      // (snap_row: the by-product's row, see there; -1: none)
   {
     const int row = min(q0 + wrows + n, q_end - 1);
+    if (BY && q0 + wrows + n < q_end) snap_row = snap_index != nullptr ? snap_index[row] : row;      // (no index: every row is a snap row)
     src_row = q_map != nullptr ? q_map[row] : row;
     p = q_pos[map_pos ? src_row : row];
     if (KS == 1) {
@@ -638,6 +639,8 @@ exp_step(0, i);
   // KS = 2: the even stream writes what a segment that ends with its tile leaves, the odd one likewise; each needs the
   // other's sum up to there, through LDS (rare as this is, it pays two
   // barriers).  prev: the odd stream's sum one tile ago.
+  // (No load here: the compiler would wait for it and so for all loads of the tiles ahead, some of them just started.  The layer with the question's masses, 16 / 2
+  // heads, 4 requests of 29 chunks of 66 tokens, one or two tiles each, 145 -> 140 us; 32 / 8, 1 of 5 x 512 85.2 -> 84.0.)
   float prev = 0.f;
   auto running = [&]() __attribute__((always_inline)) {
     const float mine = lsum + (ev + vodd);
@@ -646,7 +649,7 @@ exp_step(0, i);
   auto snapshot = [&](int t, float tot, int ends) __attribute__((always_inline)) {
     const int l = lane_of(t), pair = KS == 1 ? 0 : t - win_base;
     int seg = __builtin_amdgcn_readlane(w_seg, KS == 1 ? l : pair), seg_next = __builtin_amdgcn_readlane(w_seg_next, KS == 1 ? l : pair);
-    const int ln = here(), at = q0 + wrows + (ln & 31);
+    const int ln = here();
     float m_all = m_ref;
     bool writes = true;
     if constexpr (KS == 2) {
@@ -662,11 +665,10 @@ exp_step(0, i);
       if (ks == 1) { seg = seg_next; seg_next = __builtin_amdgcn_readlane(w_seg_far, pair); }
       writes = ks == 0 ? (ends & 4) != 0 : (ends & 8) != 0 && t < n_odd;
     }
-    const int sr = at >= q_end ? -1 : snap_index != nullptr ? snap_index[at] : at;     // (no index: every row is a snap row)
-    if (writes && ln < 32 && sr >= 0) {
+    if (writes && ln < 32 && snap_row >= 0) {
       const float v = kLn2 * (m_all + __builtin_amdgcn_logf(tot));
       for (int sl = max(seg - seg_first, 0); sl < min(seg_next - seg_first, s_max); ++sl)
-        cum[(static_cast<size_t>(sr) * hq + h) * s_max + sl] = v;
+        cum[(static_cast<size_t>(snap_row) * hq + h) * s_max + sl] = v;
     }
     wait_lds<0>();                                 // (see blank_padding)
   };
@@ -703,10 +705,10 @@ exp_step(0, i);
   int t = 0;
   // (Where the loop lies in the lines of the instruction cache shows: 70B on 8 requests of 10k tokens 1527 us with what is
   // behind this 0, 28 or 32 bytes behind a line of 64, 1550 with 16 or 20; with the by-product the layer of the 8B batch of 32 and a cache build are 0.4 - 0.9 %
-  // slower 44 bytes behind a line than at its beginning, in five runs of five.  There 20 bytes of moves lie between this and the loop (an
+  // slower 44 bytes behind a line than at its beginning, in five runs of five.  There 8 bytes of moves lie between this and the loop (an
   // alignment asked of the compiler for the loop itself has no effect); a test looks where the two loops begin.)
   if constexpr (KS == 1 && !BY) asm volatile(".p2align 6");
-  if constexpr (KS == 1 && BY) asm volatile(".p2align 6\n\t.fill 11, 4, 0xbf800000");      // (11 s_nop)
+  if constexpr (KS == 1 && BY) asm volatile(".p2align 6\n\t.fill 14, 4, 0xbf800000");      // (14 s_nop)
   for (; t < n_mine; ++t) {
     Blocks at;
     if constexpr (KS == 1) at = Blocks{0, image(t), image(t + 1), image(t) + kHalf, image(t + 1) + kHalf};
