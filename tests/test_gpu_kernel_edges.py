@@ -901,16 +901,16 @@ def test_matrix_products_with_the_contraction_in_parts(op, n_out, n_in, rows):
 
 
 @pytest.mark.parametrize("hq,hkv,lens,question,n_requests,parts", [
-    (8, 2, [5], 40, 1, 1), (8, 2, [64, 0, 1, 130], 3, 2, 1), (8, 2, [2] * 254, 1, 1, 1), (8, 2, [1] * 255, 2, 1, 1), (8, 2, [3] * 300, 5, 1, 1),
-    (8, 2, [700], 90, 3, 6), (8, 2, [2100, 0, 1, 300, 5], 33, 2, 6), (8, 2, [4000, 0, 1, 3], 2, 1, 12), (64, 8, [9000] + [0, 1] * 130, 3, 1, 4), (32, 8, [1500, 0, 30], 1, 1, 23),
-    (64, 8, [1100], 2, 1, 32)])
+    (8, 2, [5], 40, 1, 1), (8, 2, [64, 0, 1, 130], 3, 2, 2), (8, 2, [2] * 254, 1, 1, 1), (8, 2, [1] * 255, 2, 1, 1), (8, 2, [3] * 300, 5, 1, 1),
+    (8, 2, [700], 90, 3, 24), (8, 2, [210, 0, 1, 300, 5], 33, 2, 5), (8, 2, [1000, 0, 1, 3], 2, 1, 12), (64, 8, [2000] + [0, 1] * 130, 3, 1, 4),
+    (32, 8, [300, 0, 30], 1, 1, 20), (64, 8, [1100], 2, 1, 32)])
 def test_pair_masses_of_few_and_of_many_segments(hq, hkv, lens, question, n_requests, parts):
-    # the masses are summed a segment's rows in parts (one part for every 512 pairs of a row and a head that a segment has on the average, up to 32), threads
+    # the masses are summed a segment's rows in parts (one part for every 128 pairs of a row and a head that a segment has on the average, up to 32), threads
     # side by side along the key segments: a segment with one key segment, segments without tokens, 255 to 301 of them (a workgroup has 256 threads); in one part,
     # and in several with fewer rows than parts, none at all, more
     from paper_2502_15734_amd.pipeline import DeviceBatch
     k = len(lens)
-    assert parts == min(max((sum(lens) + question) * hq // (512 * (k + 1)), 1), 32)
+    assert parts == min(max((sum(lens) + question) * hq // (128 * (k + 1)), 1), 32)
     w = W.custom("pairs", "bf16", hq, hkv, 128, 5.0e5, lens * n_requests, [0] * (k * n_requests),
                  [W.RequestSpec(list(range(k * r, k * r + k)), [1.0] * k, question) for r in range(n_requests)], 1.0, seed=59)
     b = DeviceBatch(w, poison=True)
