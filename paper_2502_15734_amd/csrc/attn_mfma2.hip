@@ -87,9 +87,9 @@ constexpr int kBufs = 4;
 // Two key streams up to this many 64-row workgroups.  A compute unit holds one workgroup; twice as many with half
 // the tiles fill units that would idle and still run in one round, or nearly.  Up to 160 they are ahead whatever the
 // batch; behind that it hangs on how unevenly its requests fill their last tiles, and what one or two requests would gain
-// four lose.  cc_sparse_prefill, one stream / two, us: 112 workgroups 52 / 45 (1 request of 1.2k), 128: 62 / 53 (4 of 1.2k), 214 /
-// 159 (1 of 10k), 160: 94 / 77 (1 of 3k), 65 / 61 (4 of 1.2k), 55.5 / 53.9 (4 of 1.2k, 8 heads); 192: 220 / 173 (1 of 10k), 99 / 82
-// (2 of 3k), 101 / 116 (4 of 3k), 224: 58 / 60 (2 of 1.2k), 61 / 67 (4 of 1.2k), 256: 232 / 197 (1 of 10k), 106 / 125 (4 of 3k).
+// four lose.  cc_sparse_prefill, one stream / two, us: 40 workgroups 47 / 39 (4 requests of 1.2k, 8 / 2 heads), 64: 91 / 65 (1 of 3.6k, 64 / 8), 112: 50 / 44 (1 of 1.2k), 128: 54 / 46
+// (4 of 1.2k), 96 / 72 (2 of 3.6k, 64 / 8), 136: 224 / 155 (1 of 10k), 160: 86 / 66 (1 of 3k), 54 / 54 (4 of 1.2k); 192: 225 / 167 (1 of 10k), 88 / 73
+// (2 of 3k), 91 / 94 (4 of 3k), 224: 54 / 53 (2 of 1.2k), 54 / 61 (4 of 1.2k), 256: 95 / 109 (4 of 3k), 264: 237 / 207 (1 of 10k).
 constexpr int kTwoStreamGrid = 160;
 // KS = 2: blocks of 32 keys per stream: K in five places, V in four
 constexpr int kHalf = 8192, kRingK = 5, kRingV = 4;
@@ -224,8 +224,8 @@ __global__ __launch_bounds__(512, 1) void attn_v2_kernel(
 
   // ---- descriptors and staging --------------------------------------------------------------------
   // What the loop needs of 64 consecutive tiles sits in vector registers, one tile per lane, and is
-  // handed out with v_readlane: no memory access per tile.  The straight path reads two values per
-  // tile (the flags of tile t+2, the page of tile t+3 this wavefront brings in); positions, key
+  // handed out with v_readlane: no memory access per tile.  The straight path reads the flags of tile t+2 and where this wavefront's pages of the tiles
+  // ahead are (KS = 1: of tile t+3; KS = 2: keys of t+2 and t+3, values of t+1 and t+2, a block each); positions, key
   // counts and segments are read only inside the branches that need them.
   //   flag 1: the tile needs masking for some row (padding, or its last key lies behind p_min)
   //   flag 2: the tile has padding slots or missing pages

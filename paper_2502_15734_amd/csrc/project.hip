@@ -132,7 +132,7 @@ __device__ __forceinline__ void gemm_mfma(f32x4& d, const u32x4& a, const u32x4&
 // Both GEMM kernels below share the following.
 //
 // v_mfma_f32_16x16x32_bf16, not 32x32x16: under matrix load the chip is held by its power budget, and this
-// shape moves a quarter of the accumulator bytes per flop (MFMAs and barriers alone, everything else taken
+// shape moves half the accumulator bytes per flop (MFMAs and barriers alone, everything else taken
 // out of the loop: 1.9 PFLOP/s against 1.48; the whole product 1.30 against 1.17 at 4096 x 4096 x 14336).
 //
 // Operands go straight from global memory into LDS (global_load_lds: lane L of an instruction fills
@@ -669,7 +669,9 @@ void launch_gemm_tile(hipStream_t stream, const void* x, const void* w, const vo
 }
 
 // Tile shapes and what a stage of 64 contraction indices takes on a compute unit that runs one workgroup of
-// that shape (measured, us): big tiles do more flops per byte that passes a compute unit's L1, small
+// that shape (us; measured over and over with the same weights, which the memory-side cache then holds.  In a decoder layer they come from HBM, and whole products of few rows take 10 to
+// 30 % longer than these times say: 449 rows 4096 -> 6144 35 / 38, 4096 -> 4096 23 / 29, 230 rows 8192 -> 8192 46 / 58; products in parts, whose cost has a term for the
+// weights, hardly: 230 rows 28672 -> 8192 118 / 123): big tiles do more flops per byte that passes a compute unit's L1, small
 // ones give short lists enough workgroups.  A product takes the shape with the smallest
 // (rounds of 256 workgroups) x (stage time).
 struct GemmTile { int f, m, k; float stage_us; };
