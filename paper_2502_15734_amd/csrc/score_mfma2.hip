@@ -13,7 +13,7 @@
 // exponentials behind them a wavefront's own chain was 2900 clocks a block, more than the two wavefronts
 // of a SIMD need of the matrix pipe; now 2450 - 2600.)  A long call is then held by the clock that the chip's power budget leaves, 1.7 GHz
 // with the pipe 77 % busy: hence 16 columns there, which move half the accumulator bytes per flop: 1.9 GHz, the pipe 70 % busy (this loop alone 1.44 -> 1.51 PFLOP/s; 4 x 32 k tokens 3 - 6 %
-// faster, by the box, 12.70 -> 11.97 ms on one; the 8B batch of 32 2 - 3 %, 2.97 -> 2.87).  A call that is over before the clock falls waits for its
+// faster, by the card, 12.70 -> 11.97 ms on one; the 8B batch of 32 2 - 3 %, 2.97 -> 2.87).  A call that is over before the clock falls waits for its
 // own instructions, of which 32 columns need half as many: see score_held_by_power for the line between them.
 //
 // The tokens of a workgroup are numbered through the request's scored chunks: a workgroup per chunk and 128 tokens
