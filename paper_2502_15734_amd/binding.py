@@ -187,10 +187,13 @@ def _nbytes(t: Optional[torch.Tensor]) -> int:
 
 def _kept_by_a_graph(t: torch.Tensor) -> bool:
     """Whether t's memory lies in a pool of its own, as what torch hands out while it captures a graph does: nobody else gets it
-    as long as the graph lives."""
+    as long as the graph lives.  (Not every allocator can tell.)"""
     at = t.data_ptr()
-    return any(s["address"] <= at < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
-               for s in torch.cuda.memory_snapshot())
+    try:
+        segments = torch.cuda.memory_snapshot()
+    except RuntimeError:
+        return False
+    return any(s["address"] <= at < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0) for s in segments)
 
 
 def _scratch(nbytes: int, x: torch.Tensor) -> Optional[torch.Tensor]:

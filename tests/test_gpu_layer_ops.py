@@ -203,6 +203,11 @@ def test_products_without_memory_for_their_parts_stay_whole(monkeypatch):
     # a capture that torch does not know of
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
     assert _same(call(), whole)
+    # an allocator that does not say where its memory lies
+    def silent():
+        raise RuntimeError("no snapshot")
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", silent)
+    assert _same(call(), whole)
     monkeypatch.undo()
     # no memory
     def refuse(*args, **kw):
